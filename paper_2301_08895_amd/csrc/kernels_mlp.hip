@@ -37,6 +37,7 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int TM = 128;   // rows of C per workgroup
 constexpr int BK = 64;    // contraction elements per main-loop step
@@ -68,7 +69,6 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
 #define ABS_STREAM_MIN_BYTES (64u << 20)
 #endif
 __device__ __forceinline__ void store16_stream(uint16_t* p, const uint4& v, bool stream) {
-  typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
   // (written out by hand: when both forms of the store sit in the two arms of a branch the optimiser
   // merges them into one plain store)
   if (stream) asm volatile("global_store_dwordx4 %0, %1, off nt" : : "v"(p), "v"(u32x4_t{v.x, v.y, v.z, v.w}) : "memory");
@@ -368,52 +368,72 @@ __device__ __forceinline__ void lds_dma16(const uint16_t* gsrc, uint16_t* lds_bl
                                    (__attribute__((address_space(3))) void*)lds_block, 16, 0, 0);
 }
 
-// 256 threads = 2 x 2 wavefronts; a wavefront owns a 64 x (TN/2) sub-tile made of
-// 32x32x16 MFMA blocks (TN = 256: 2 x 4 blocks, 128 accumulator registers).  A and B
-// tiles of BK = 64 are staged in LDS (one stage; the next tile's global loads are in
-// flight in registers while the current one is multiplied, and two workgroups per CU
-// cover each other's barriers).  A tile row is 128 bytes; its 16-byte chunk c is stored at
-// position c ^ ((row >> 1) & 7): the 16 lanes that one cycle of a 128-bit LDS read serves
-// (16 consecutive rows of a fragment) then cover all 64 banks.
-#ifndef ABS_RING64
-#define ABS_RING64 3
-#endif
-#ifndef ABS_RING128
-#define ABS_RING128 2
-#endif
-template <int TN>
-struct GemmCfg {
-  static constexpr int WN = TN / 2;            // columns per wavefront
-  static constexpr int NI = WN / 32;           // MFMA blocks along n per wavefront
-  static constexpr int BCH = TN / 32;          // 16-byte chunks of the B tile per thread
-  static constexpr int kMainElems = (TM + TN) * BK;
-  static constexpr int kEpiPitch = 64 + 8;     // transposed staging: [WN][64 + 8] per wavefront
-  static constexpr int kEpiElems = 4 * WN * kEpiPitch;
+// The same request written out by hand.  The compiler makes every LDS read that it cannot tell
+// apart from a pending global->LDS request wait for all of them, and it cannot for the
+// transposing read: a k-step would then start by waiting for the tile it has just requested.
+// Requests issued this way are invisible to that bookkeeping; the loop's own vmcnt(0) and
+// barrier order them against the reads.  The LDS base travels in m0, which the register
+// allocator hands over through the "{m0}" constraint (it knows the register is written).
+__device__ __forceinline__ void lds_dma16_raw(const uint16_t* gsrc, uint16_t* lds_block) {
+  const uint32_t lds = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_block);
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               :
+               : "v"(gsrc), "{m0}"(lds)
+               : "memory");
+}
+
+// A ring's hand-over: at most N of this wavefront's requests are still on their way (the later stages'),
+// its own LDS reads are done, and everybody has got here.
+template <int N>
+__device__ __forceinline__ void ring_wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
+}
+
+// ------------------------------------------------------------------ the GEMM on tiles of 64 and 128
+// What a round of few or narrow rows waits for is not arithmetic but the trip of a k-step's tiles from
+// memory into LDS and, behind it, the fixed cost of a step (barrier, first fragment reads).  So
+//  * tiles travel global -> LDS by DMA through a ring of RING k-steps, RING - 1 of them on
+//    their way at any time (one wait, one barrier and one batch of requests per stage);
+//  * a wavefront owns a 64 x 64 sub-tile (2 x 2 blocks of MFMA 32x32x16, the fewest fragment bytes per
+//    flop that 64 accumulator registers allow), and the KG wavefront groups of a workgroup share the
+//    CONTRACTION of a step, not its columns: two wavefronts per SIMD cover each other's fragment reads
+//    without staging a byte more.  At the end the groups exchange blocks through LDS, every group adds
+//    and finishes OWN of its sub-tile's four blocks (always in group order);
+//  * both orientations of a bf16 result leave through LDS as 16-byte pieces.
+// Measured against the same products with one wavefront group, a ring that every barrier drained
+// (__syncthreads waits for all of a wavefront's requests when the compiler knows of them) and 2-byte
+// row-major stores: first-layer forward 1024 x 512 x 3072 32.0 -> 18.3 us, 4096 x 1024 x 3072 55 -> 39,
+// hidden forward / input gradient 4096 x 1024 x 1024 22 -> 18.5.  What bounds it now: a CU draws 23-32 bytes
+// per clock from beyond its L1 whatever the ring's depth, about 30 KB in flight over the latency of a miss.
+// A tile row is 128 bytes; its 16-byte chunk c is stored at position c ^ ((row >> 1) & 7): the 16 lanes
+// that one cycle of a 128-bit LDS read serves (16 consecutive rows of a fragment) then cover all 64 banks.
+template <int T>
+struct TileCfg {
+  static constexpr int WS = T / 64;                      // 64 x 64 sub-tiles along each side
+  static constexpr int KG = T == 128 ? 2 : 4;            // wavefront groups along the contraction
+  static constexpr int NW = WS * WS * KG, NT = NW * 64;  // wavefronts (8; 4 for the 64 x 64 tile), threads
+  static constexpr int OWN = 4 / KG;                     // blocks a wavefront finishes
+  static constexpr int kStage = 2 * T * BK;              // elements of a k-step's tiles
+  static constexpr int kRed = WS * WS * 4 * (KG - 1) * 1024 * 2;   // exchanged blocks (in elements of 2 bytes)
+  static constexpr int kPitch = T + 8;                   // of the staged results
+  static constexpr int kOut = 2 * T * kPitch + (T / 32) * T * 2;   // both orientations, column sums per 32 rows
 };
 
-// TAG only separates kernel symbols (first layer / other layers) for profilers.
-//
-// RING > 0: the tiles travel global -> LDS by DMA through a ring of RING stages with RING - 1
-// tiles in flight and one barrier per k-step (as in the 256 x 256 kernel, swizzle on the global
-// side).  For products with few tiles per CU, where one tile in flight per workgroup leaves the
-// k-steps waiting for memory latency one after the other.  Needs whole 64-wide k-steps of A
-// (a_kvalid a multiple of BK covering the contraction).  KPS > 1: a stage holds KPS consecutive
-// k-steps, requested, awaited and released together (one barrier per KPS k-steps).
-template <int TN, int EPI, bool GATHER, bool PER_UPLOAD, int TAG, int RING = 0, int KPS = 1>
-__global__ __launch_bounds__(256, (RING * KPS * GemmCfg<TN>::kMainElems * 2 > 80 * 1024) ? 1 : 2)
-void mlp_gemm_kernel(GemmArgs g, RoundDesc rd) {
-  using Cfg = GemmCfg<TN>;
-  constexpr int WN = Cfg::WN, NI = Cfg::NI, BCH = Cfg::BCH;
+template <int T, int EPI, bool GATHER, bool PER_UPLOAD, int TAG, int RING>
+__global__ __launch_bounds__(TileCfg<T>::NT, 2) void mlp_tile_kernel(GemmArgs g, RoundDesc rd) {
+  using Cfg = TileCfg<T>;
+  constexpr int NW = Cfg::NW, NT = Cfg::NT, KG = Cfg::KG, OWN = Cfg::OWN;
   constexpr bool kStageT = (EPI == EPI_RELU || EPI == EPI_DGRAD);
-  static_assert(KPS == 1 || RING > 0, "several k-steps per stage: ring only");
-  constexpr int kStageElems = KPS * Cfg::kMainElems;       // a ring stage holds KPS consecutive k-steps
-  constexpr int kMain = (RING ? RING : 1) * kStageElems;
-  constexpr int kSmem = kStageT && Cfg::kEpiElems > kMain ? Cfg::kEpiElems : kMain;
-  static_assert(kSmem * 2 <= 160 * 1024, "LDS budget");
+  constexpr int kEpi = Cfg::kRed + (kStageT ? Cfg::kOut : 0);
+  constexpr int kSmem = RING * Cfg::kStage > kEpi ? RING * Cfg::kStage : kEpi;
+  static_assert(kSmem * 2 <= 160 * 1024 - 1024, "LDS budget");
   __shared__ __attribute__((aligned(16))) uint16_t smem[kSmem];
+  __shared__ uint32_t s_row[GATHER ? T : 1];
 
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int kg = wave / (Cfg::WS * Cfg::WS), wsub = wave % (Cfg::WS * Cfg::WS);
+  const int wm = wsub / Cfg::WS, wn = wsub % Cfg::WS;
   const int bx = blockIdx.x;
   if (EPI == EPI_WGRAD && (g.pig_blocks | g.bias_blocks)) {
     // The update's blocks come last in the grid: they take the CUs that the product's last wave of
@@ -424,7 +444,7 @@ void mlp_gemm_kernel(GemmArgs g, RoundDesc rd) {
       bias_block(g.bias_upd, bx - own - g.pig_blocks, [](int) { return 0; }, g.bias_upd.w_cur, g.bias_upd.w_next, (float*)smem);
       return;
     }
-    if (bx >= own) { piggy_update<256, false>(g, bx - own, smem); return; }
+    if (bx >= own) { piggy_update<NT, false>(g, bx - own, smem); return; }
   }
   // Block -> tile mapping.  Workgroups are handed to the 8 XCDs round-robin and every XCD has
   // its own L2, so block b works for XCD b % 8.  The (split, row-tile) pairs are cut into 8
@@ -435,7 +455,7 @@ void mlp_gemm_kernel(GemmArgs g, RoundDesc rd) {
   const int trow = xcd * g.rows_per_xcd + jx / g.nt;
   if (trow >= g.mt * g.nsplit) return;
   const int zsplit = trow / g.mt;
-  const int m0 = (trow - zsplit * g.mt) * TM, n0 = (jx % g.nt) * TN;
+  const int m0 = (trow - zsplit * g.mt) * T, n0 = (jx % g.nt) * T;
   const int ks0 = zsplit * g.ksteps_per_split;
   const int ks1 = min(g.ksteps_total, ks0 + g.ksteps_per_split);
 
@@ -449,254 +469,204 @@ void mlp_gemm_kernel(GemmArgs g, RoundDesc rd) {
     Bt += (size_t)slot * g.bt_slot_stride;
   }
 
-  // staging.  Register path: thread t moves chunk (row r0 + 32 i, 16-byte column c) of each tile.
-  // DMA path: instruction i of wavefront w fills 8 rows of 128 bytes, lane l row (l >> 3) of them at
-  // chunk position l & 7, fetching logical chunk (l & 7) ^ ((row >> 1) & 7): A rows 32 w + 8 i
-  // (i < 4), B rows (TN / 4) w + 8 i (i < TN / 32); (row >> 1) & 7 is (l >> 4) + 4 (i & 1) for both.
-  constexpr int kRowStep = RING ? 8 : 32;
-  const int r0 = RING ? wave * 32 + (lane >> 3) : t >> 3;
-  const int c8 = (t & 7) * 8;
-  const int c_even = ((t & 7) ^ ((lane >> 4) & 7)) * 8, c_odd = ((t & 7) ^ ((4 + (lane >> 4)) & 7)) * 8;
-  const int st_off = r0 * BK + (((t & 7) ^ ((r0 >> 1) & 7)) << 3);   // swizzled LDS offset of chunk i = 0
-  const uint16_t* pa0; const uint16_t* pa1; const uint16_t* pa2; const uint16_t* pa3;
+  // Requests: one fills 8 rows of 128 bytes; wavefront w takes rows 8 (w + NW i) .. of A and of B, lane l
+  // row (l >> 3) of them at chunk position l & 7, fetching logical chunk (l & 7) ^ ((row >> 1) & 7), and
+  // (row >> 1) & 7 is (l >> 4) + 4 (w & 1).
+  constexpr int NI = T / (8 * NW);
+  const int c8 = ((lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7)) * 8;
+  const int rq = 8 * wave + (lane >> 3);
+  const uint16_t* pa[NI]; const uint16_t* pb[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) pb[i] = Bt + (size_t)(n0 + rq + 8 * NW * i) * g.ldb + c8;
   if (GATHER) {
-    uint32_t ri[4];
-    if (g.gen_rows) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
+    // one draw per row of the tile, shared through LDS
+    if (t < T) {
+      uint32_t row;
+      if (g.gen_rows) {
         bool real;
-        ri[i] = gen_row_of(g, rd, m0 + r0 + kRowStep * i, &real);
-        if (n0 == 0 && (t & 7) == 0) gen_row_store(g, m0 + r0 + kRowStep * i, ri[i], real);
+        row = gen_row_of(g, rd, m0 + t, &real);
+        if (n0 == 0) gen_row_store(g, m0 + t, row, real);
+      } else {
+        row = g.a_rowidx[m0 + t];
       }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) ri[i] = g.a_rowidx[m0 + r0 + kRowStep * i];
+      s_row[t] = row;
     }
-    pa0 = g.A + (size_t)ri[0] * g.lda + (RING ? c_even : c8);
-    pa1 = g.A + (size_t)ri[1] * g.lda + (RING ? c_odd : c8);
-    pa2 = g.A + (size_t)ri[2] * g.lda + (RING ? c_even : c8);
-    pa3 = g.A + (size_t)ri[3] * g.lda + (RING ? c_odd : c8);
-  } else if (RING) {
-    const uint16_t* base = g.A + (size_t)(m0 + r0) * g.lda;
-    pa0 = base + c_even; pa1 = base + 8 * g.lda + c_odd;
-    pa2 = base + 16 * g.lda + c_even; pa3 = base + 24 * g.lda + c_odd;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NI; ++i) pa[i] = g.A + (size_t)s_row[rq + 8 * NW * i] * g.lda + c8;
   } else {
-    pa0 = g.A + (size_t)(m0 + r0) * g.lda + c8;
-    pa1 = pa0 + 32 * g.lda; pa2 = pa0 + 64 * g.lda; pa3 = pa0 + 96 * g.lda;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) pa[i] = g.A + (size_t)(m0 + rq + 8 * NW * i) * g.lda + c8;
   }
-  const uint16_t* pb0 = RING ? Bt + (size_t)(n0 + wave * (TN / 4) + (lane >> 3)) * g.ldb
-                             : Bt + (size_t)(n0 + r0) * g.ldb + c8;
-  const size_t b_step = (RING ? 8 : 32) * g.ldb;
-  const bool a_ok = !GATHER || c8 < g.a_kvalid;       // refined per k-step below
+  // GATHER: elements beyond a_kvalid (the padding of the contraction) must read as zero.  The lanes that
+  // would fetch them are pointed at the zero pad behind the first row of B (see kPitchPad).
+  const int kpad = GATHER ? g.a_kvalid - c8 : 0;
+  const uint16_t* const zpad = Bt + (size_t)g.ksteps_total * BK + (lane & 7) * 8;
 
-  f32x16_t acc[2][NI];
-#pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+#define ABS_TILE_DMA(ks_, st_)                                                            \
+  {                                                                                       \
+    const int k0_ = (ks_) * BK;                                                           \
+    uint16_t* a_ = smem + (st_) * Cfg::kStage + wave * 512;                               \
+    _Pragma("unroll") for (int i = 0; i < NI; ++i)                                        \
+      lds_dma16_raw(GATHER && k0_ >= kpad ? zpad : pa[i] + k0_, a_ + i * NW * 512);       \
+    _Pragma("unroll") for (int i = 0; i < NI; ++i)                                        \
+      lds_dma16_raw(pb[i] + k0_, a_ + T * BK + i * NW * 512);                             \
+  }
 
-  uint4 ra0, ra1, ra2, ra3, rb0, rb1, rb2, rb3, rb4, rb5, rb6, rb7;
-  const uint4 zero4 = make_uint4(0, 0, 0, 0);
-  rb2 = rb3 = rb4 = rb5 = rb6 = rb7 = zero4;
-#define ABS_FETCH(ks)                                                                     \
-  {                                                                                       \
-    const int k0_ = (ks) * BK;                                                            \
-    if (GATHER && (!a_ok || k0_ + c8 >= g.a_kvalid)) {                                    \
-      ra0 = zero4; ra1 = zero4; ra2 = zero4; ra3 = zero4;                                 \
-    } else {                                                                              \
-      ra0 = *(const uint4*)(pa0 + k0_); ra1 = *(const uint4*)(pa1 + k0_);                 \
-      ra2 = *(const uint4*)(pa2 + k0_); ra3 = *(const uint4*)(pa3 + k0_);                 \
-    }                                                                                     \
-    const uint16_t* pb_ = pb0 + k0_;                                                      \
-    rb0 = *(const uint4*)(pb_); rb1 = *(const uint4*)(pb_ + b_step);                      \
-    if (BCH > 2) { rb2 = *(const uint4*)(pb_ + 2 * b_step); rb3 = *(const uint4*)(pb_ + 3 * b_step); } \
-    if (BCH > 4) { rb4 = *(const uint4*)(pb_ + 4 * b_step); rb5 = *(const uint4*)(pb_ + 5 * b_step);   \
-                   rb6 = *(const uint4*)(pb_ + 6 * b_step); rb7 = *(const uint4*)(pb_ + 7 * b_step); } \
-  }
-#define ABS_STAGE()                                                                       \
-  {                                                                                       \
-    *(uint4*)&smem[st_off] = ra0;            *(uint4*)&smem[st_off + 32 * BK] = ra1;          \
-    *(uint4*)&smem[st_off + 64 * BK] = ra2;  *(uint4*)&smem[st_off + 96 * BK] = ra3;          \
-    *(uint4*)&smem[TM * BK + st_off] = rb0;            *(uint4*)&smem[TM * BK + st_off + 32 * BK] = rb1;          \
-    if (BCH > 2) { *(uint4*)&smem[TM * BK + st_off + 64 * BK] = rb2; *(uint4*)&smem[TM * BK + st_off + 96 * BK] = rb3; }   \
-    if (BCH > 4) { *(uint4*)&smem[TM * BK + st_off + 128 * BK] = rb4; *(uint4*)&smem[TM * BK + st_off + 160 * BK] = rb5;   \
-                   *(uint4*)&smem[TM * BK + st_off + 192 * BK] = rb6; *(uint4*)&smem[TM * BK + st_off + 224 * BK] = rb7; } \
-  }
+  f32x16_t acc[4];                       // block 2 mi + ni of the 64 x 64 sub-tile
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
 
   const int lr = lane & 31, lk = lane >> 5;
-  const int fa_row = (wm * 64 + lr) * BK, fb_row = (wn * WN + lr) * BK;
+  const int fa = (wm * 64 + lr) * BK, fb = T * BK + (wn * 64 + lr) * BK;
   const int sw = (lr >> 1) & 7;
-  // one request per 8 rows: stage `st_` receives tile `ks_`
-#define ABS_RING_DMA(ks_, st_)                                                            \
-  _Pragma("unroll") for (int p_ = 0; p_ < KPS; ++p_) {                                    \
-    const int k0_ = ((ks_) + p_) * BK;                                                    \
-    uint16_t* a_ = smem + (st_) * kStageElems + p_ * Cfg::kMainElems + wave * 32 * BK;    \
-    uint16_t* b_ = smem + (st_) * kStageElems + p_ * Cfg::kMainElems + TM * BK + wave * (TN / 4) * BK; \
-    lds_dma16(pa0 + k0_, a_);            lds_dma16(pa1 + k0_, a_ + 8 * BK);               \
-    lds_dma16(pa2 + k0_, a_ + 16 * BK);  lds_dma16(pa3 + k0_, a_ + 24 * BK);              \
-    _Pragma("unroll") for (int i = 0; i < TN / 32; ++i)                                   \
-      lds_dma16(pb0 + i * b_step + ((i & 1) ? c_odd : c_even) + k0_, b_ + i * 8 * BK);    \
-  }
-  constexpr int kDmaPerWave = KPS * (4 + TN / 32);        // requests per wavefront and stage
-  if (ks0 < ks1) {
-    if (RING) {
+  constexpr int SUB = 4 / KG;            // 16-wide sub-steps of a k-step per wavefront group
 #pragma unroll
-      for (int j = 0; j < RING - 1; ++j)
-        if (ks0 + j * KPS < ks1) ABS_RING_DMA(ks0 + j * KPS, j);
-    } else {
-      ABS_FETCH(ks0);
-    }
-    int stage = 0;
-    for (int ks = ks0; ks < ks1; ++ks) {
-      const uint16_t* sA = smem;
-      if (RING) {
-        // (KPS > 1: the launcher hands over whole stages, ks1 - ks0 a multiple of KPS; wait, barrier and
-        // requests happen once per stage, at its first k-step)
-        const int pnl = KPS > 1 ? (ks - ks0) % KPS : 0;
-        if (pnl == 0) {
-          // stage ks has landed when at most the RING - 2 stages behind it are outstanding
-          constexpr int kOut = RING > 2 ? (RING - 2) * kDmaPerWave : 0;
-          if (ks + (RING - 2) * KPS < ks1) __builtin_amdgcn_s_waitcnt(0x0F70 | (kOut & 15) | ((kOut >> 4) << 14));
-          else                             __builtin_amdgcn_s_waitcnt(0x0F70);
-          __syncthreads();      // ... for every wavefront; and everybody is done with stage ks - KPS
-          if (ks + (RING - 1) * KPS < ks1) ABS_RING_DMA(ks + (RING - 1) * KPS, stage == 0 ? RING - 1 : stage - 1);
-        }
-        sA = smem + stage * kStageElems + pnl * Cfg::kMainElems;
-        if (pnl == KPS - 1) stage = stage + 1 == RING ? 0 : stage + 1;
-      } else {
-        ABS_STAGE();
-        __syncthreads();
-        if (ks + 1 < ks1) ABS_FETCH(ks + 1);
+  for (int j = 0; j < RING - 1; ++j)
+    if (ks0 + j < ks1) ABS_TILE_DMA(ks0 + j, j);
+  int stage = 0;
+  for (int ks = ks0; ks < ks1; ++ks) {
+    // step ks has landed when at most the RING - 2 steps behind it are outstanding
+    if (ks + RING - 1 <= ks1) ring_wait_barrier<(RING - 2) * 2 * NI>();   // ... for every wavefront; and everybody
+    else                      ring_wait_barrier<0>();                     // is done with step ks - 1
+    if (ks + RING - 1 < ks1) ABS_TILE_DMA(ks + RING - 1, stage == 0 ? RING - 1 : stage - 1);
+    const uint16_t* sS = smem + stage * Cfg::kStage;
+    stage = stage + 1 == RING ? 0 : stage + 1;
+    bf16x8_t va[SUB][2], vb[SUB][2];
+#pragma unroll
+    for (int s = 0; s < SUB; ++s) {
+      const int ch = ((((kg * SUB + s) << 1) | lk) ^ sw) << 3;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        va[s][i] = *(const bf16x8_t*)&sS[fa + i * 32 * BK + ch];
+        vb[s][i] = *(const bf16x8_t*)&sS[fb + i * 32 * BK + ch];
       }
-      const uint16_t* sB = sA + TM * BK;
-      // fragments of sub-step s+1 are read while the MFMAs of sub-step s run
-      bf16x8_t fa[2][2], fb[2][NI];
-#define ABS_FRAGS(set, s_)                                                                        \
-  {                                                                                               \
-    const int ch_ = ((((s_) << 1) | lk) ^ sw) << 3;                                               \
-    _Pragma("unroll") for (int mi = 0; mi < 2; ++mi)                                              \
-      fa[set][mi] = *(const bf16x8_t*)&sA[fa_row + mi * 32 * BK + ch_];                           \
-    _Pragma("unroll") for (int ni = 0; ni < NI; ++ni)                                             \
-      fb[set][ni] = *(const bf16x8_t*)&sB[fb_row + ni * 32 * BK + ch_];                           \
-  }
-      ABS_FRAGS(0, 0);
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        if (s < 3) ABS_FRAGS((s + 1) & 1, s + 1);
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-          for (int ni = 0; ni < NI; ++ni)
-            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s & 1][mi], fb[s & 1][ni], acc[mi][ni], 0, 0, 0);
-      }
-#undef ABS_FRAGS
-      // pin the interleaving: first fragment set, then one LDS read behind each MFMA
-      __builtin_amdgcn_sched_group_barrier(0x100, 2 + NI, 0);
-#pragma unroll
-      for (int s = 0; s < 3; ++s) {
-#pragma unroll
-        for (int i = 0; i < 2 + NI; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        if (2 * NI > 2 + NI) __builtin_amdgcn_sched_group_barrier(0x008, 2 * NI - (2 + NI), 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 2 * NI, 0);
-      if (!RING) __syncthreads();
+        for (int j = 0; j < 2; ++j)
+          acc[2 * i + j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[s][i], vb[s][j], acc[2 * i + j], 0, 0, 0);
     }
   }
-  if (RING) __syncthreads();      // all fragment reads done before the staging area is reused
+#undef ABS_TILE_DMA
 
-#undef ABS_RING_DMA
-#undef ABS_FETCH
-#undef ABS_STAGE
-
-  // ---- epilogue.  Accumulator register r of lane l holds C[8 (r/4) + 4 (l/32) + r%4][l%32]
-  // of its 32 x 32 block.
-  const int lcol = lane & 31, lrow4 = (lane >> 5) * 4;
+  // ---- epilogue.  Accumulator register r of lane l holds C[8 (r/4) + 4 (l/32) + r%4][l%32] of its block.
+  float* const red = (float*)smem;
+  uint16_t* const sT = smem + Cfg::kRed;                 // results [n][kPitch]
+  uint16_t* const sN = sT + T * Cfg::kPitch;              // results [m][kPitch]
+  float* const sC = (float*)(sN + T * Cfg::kPitch);       // column sums per 32 rows
+  u32x4_t mk[EPI == EPI_DGRAD ? T * T / 8 / NT : 1];
+  if (EPI == EPI_DGRAD) {
+    // the ReLU mask, H_l^T [n][m], as whole rows of the tile
+#pragma unroll
+    for (int i = 0; i < T * T / 8 / NT; ++i) {
+      const int q = t + NT * i, nl = q / (T / 8), ch = (q % (T / 8)) * 8;
+      mk[i] = *(const u32x4_t*)(g.maskT + (size_t)(n0 + nl) * g.ldmaskT + m0 + ch);
+    }
+  }
+  __syncthreads();                                       // all fragment reads done before LDS is reused
+  // blocks of other groups to their owners: [sub-tile][block][source group][quarter][lane]
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int owner = b / OWN;
+    if (owner != kg) {
+      float4* q = (float4*)(red + ((wsub * 4 + b) * (KG - 1) + (kg < owner ? kg : kg - 1)) * 1024) + lane;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) q[r * 64] = make_float4(acc[b][4 * r], acc[b][4 * r + 1], acc[b][4 * r + 2], acc[b][4 * r + 3]);
+    }
+  }
+  if (EPI == EPI_DGRAD) {
+#pragma unroll
+    for (int i = 0; i < T * T / 8 / NT; ++i) {
+      const int q = t + NT * i, nl = q / (T / 8), ch = (q % (T / 8)) * 8;
+      *(u32x4_t*)&sT[nl * Cfg::kPitch + ch] = mk[i];
+    }
+  }
+  f32x16_t fin[OWN];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+    if (b / OWN == kg) fin[b % OWN] = acc[b];
+  __syncthreads();
+  const int lcol = lane & 31, lrow4 = lk * 4;
   const float* bias = nullptr;
   if (EPI == EPI_RELU || EPI == EPI_LOGITS) bias = g.bias + (size_t)slot * g.bias_slot_stride;
   float* outf = g.outf;
   if (EPI == EPI_WGRAD) outf += (size_t)zsplit * g.split_stride;
-  uint16_t* const sE = smem + wave * (WN * Cfg::kEpiPitch);     // this wavefront's [WN][72] staging
-  float cs[NI];                           // EPI_DGRAD: column sums over this wavefront's 64 rows
 #pragma unroll
-  for (int ni = 0; ni < NI; ++ni) cs[ni] = 0.f;
-  if (EPI == EPI_DGRAD) {
-    // the ReLU mask of this wavefront's tile, H_l^T [n][m], fetched as whole 128-byte rows into
-    // the staging area; every lane later replaces the 4 entries it read by its 4 results
-    const int mrow = m0 + wm * 64;
+  for (int j = 0; j < OWN; ++j) {
+    const int b = kg * OWN + j;
+    const float4* q = (const float4*)(red + (wsub * 4 + b) * (KG - 1) * 1024) + lane;
 #pragma unroll
-    for (int i = 0; i < WN / 8; ++i) {
-      const int q = lane + 64 * i, nl = q >> 3, ch = (q & 7) * 8;
-      *(uint4*)&sE[nl * Cfg::kEpiPitch + ch] =
-          *(const uint4*)(g.maskT + (size_t)(n0 + wn * WN + nl) * g.ldmaskT + mrow + ch);
-    }
-  }
+    for (int o = 0; o < KG - 1; ++o)
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi) {
+      for (int r = 0; r < 4; ++r) {
+        const float4 v = q[o * 256 + r * 64];
+        fin[j][4 * r] += v.x; fin[j][4 * r + 1] += v.y; fin[j][4 * r + 2] += v.z; fin[j][4 * r + 3] += v.w;
+      }
+    const int bm = wm * 64 + (b >> 1) * 32, nl = wn * 64 + (b & 1) * 32 + lcol;
+    const int n = n0 + nl;
+    float bv = 0.f, cs = 0.f;
+    if (EPI == EPI_RELU || EPI == EPI_LOGITS) bv = n < g.n_valid ? bias[n] : 0.f;
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
-      const int nl = ni * 32 + lcol;
-      const int n = n0 + wn * WN + nl;
-      float bv = 0.f;
-      if (EPI == EPI_RELU || EPI == EPI_LOGITS) bv = n < g.n_valid ? bias[n] : 0.f;
+    for (int rg = 0; rg < 4; ++rg) {
+      const int ml = bm + rg * 8 + lrow4;
+      uint16_t h[4];
+      uint2 hm = make_uint2(0, 0);     // H_l of the 4 consecutive rows this lane holds
+      if (EPI == EPI_DGRAD) hm = *(const uint2*)&sT[nl * Cfg::kPitch + ml];
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        const int ml = mi * 32 + rg * 8 + lrow4;
-        const int mbase = m0 + wm * 64 + ml;
-        uint16_t h[4];
-        uint2 hm = make_uint2(0, 0);     // H_l of the 4 consecutive rows this lane holds
-        if (EPI == EPI_DGRAD) hm = *(const uint2*)&sE[nl * Cfg::kEpiPitch + ml];
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          const int m = mbase + rr;
-          float v = acc[mi][ni][rg * 4 + rr];
-          if (EPI == EPI_RELU) {
-            v = fmaxf(v + bv, 0.f);
-          } else if (EPI == EPI_LOGITS) {
-            v += bv;
-            outf[(size_t)m * g.ldof + n] = v;
-          } else if (EPI == EPI_DGRAD) {
-            const uint32_t pair = rr < 2 ? hm.x : hm.y;
-            v = ((pair >> ((rr & 1) * 16)) & 0x7FFFu) ? v : 0.f;
-          } else {
-            outf[(size_t)m * g.ldof + n] = v;
-          }
-          if (kStageT) {
-            h[rr] = f32_to_bf16(v);
-            if (EPI == EPI_DGRAD) cs[ni] += __uint_as_float((uint32_t)h[rr] << 16);
-            if (g.out) g.out[(size_t)m * g.ldo + n] = h[rr];
-          }
+      for (int rr = 0; rr < 4; ++rr) {
+        float v = fin[j][rg * 4 + rr];
+        if (EPI == EPI_RELU) {
+          v = fmaxf(v + bv, 0.f);
+        } else if (EPI == EPI_LOGITS) {
+          outf[(size_t)(m0 + ml + rr) * g.ldof + n] = v + bv;
+        } else if (EPI == EPI_DGRAD) {
+          const uint32_t pair = rr < 2 ? hm.x : hm.y;
+          v = ((pair >> ((rr & 1) * 16)) & 0x7FFFu) ? v : 0.f;
+        } else {
+          outf[(size_t)(m0 + ml + rr) * g.ldof + n] = v;
         }
         if (kStageT) {
-          uint2 o;
-          o.x = h[0] | ((uint32_t)h[1] << 16);
-          o.y = h[2] | ((uint32_t)h[3] << 16);
-          *(uint2*)&sE[nl * Cfg::kEpiPitch + ml] = o;
+          h[rr] = f32_to_bf16(v);
+          if (EPI == EPI_DGRAD) cs += __uint_as_float((uint32_t)h[rr] << 16);
+          if (g.out) sN[(ml + rr) * Cfg::kPitch + nl] = h[rr];
         }
       }
+      if (kStageT) {
+        uint2 o;
+        o.x = h[0] | ((uint32_t)h[1] << 16);
+        o.y = h[2] | ((uint32_t)h[3] << 16);
+        *(uint2*)&sT[nl * Cfg::kPitch + ml] = o;
+      }
     }
-  }
-  if (EPI == EPI_DGRAD) {
-    // the bias gradient's share of these 64 rows (the two half-wavefronts hold alternate rows)
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
-      const float c = cs[ni] + __shfl_xor(cs[ni], 32, 64);
-      if (lane < 32) g.colsum[(size_t)((m0 + wm * 64) >> 6) * g.ldcs + n0 + wn * WN + ni * 32 + lcol] = c;
+    if (EPI == EPI_DGRAD) {
+      // (the two half-wavefronts hold alternate groups of 4 rows)
+      cs += __shfl_xor(cs, 32, 64);
+      if (lane < 32) sC[(bm >> 5) * T + nl] = cs;
     }
   }
   if (kStageT) {
-    // transposed copy: each staged row is 64 consecutive m of one n -> 16-byte stores
     __syncthreads();
-    const int mrow = m0 + wm * 64;
 #pragma unroll
-    for (int i = 0; i < WN / 8; ++i) {
-      const int q = lane + 64 * i, nl = q >> 3, ch = (q & 7) * 8;
-      const uint4 v = *(const uint4*)&sE[nl * Cfg::kEpiPitch + ch];
-      *(uint4*)(g.outT + (size_t)(n0 + wn * WN + nl) * g.ldoT + mrow + ch) = v;
+    for (int i = 0; i < T * T / 8 / NT; ++i) {
+      const int q = t + NT * i, nl = q / (T / 8), ch = (q % (T / 8)) * 8;
+      *(uint4*)(g.outT + (size_t)(n0 + nl) * g.ldoT + m0 + ch) = *(const uint4*)&sT[nl * Cfg::kPitch + ch];
+    }
+    if (g.out) {
+#pragma unroll
+      for (int i = 0; i < T * T / 8 / NT; ++i) {
+        const int q = t + NT * i, ml = q / (T / 8), ch = (q % (T / 8)) * 8;
+        *(uint4*)(g.out + (size_t)(m0 + ml) * g.ldo + n0 + ch) = *(const uint4*)&sN[ml * Cfg::kPitch + ch];
+      }
+    }
+    if (EPI == EPI_DGRAD) {
+      // the bias gradient's share of every 64 rows
+      for (int q = t; q < (T / 64) * T; q += NT) {
+        const int rb = q / T, nl = q % T;
+        g.colsum[(size_t)((m0 >> 6) + rb) * g.ldcs + n0 + nl] = sC[2 * rb * T + nl] + sC[(2 * rb + 1) * T + nl];
+      }
     }
   }
 }
@@ -720,21 +690,6 @@ constexpr int kEpiPitch3 = 64 + 8;                   // per wavefront: staging [
 constexpr int kEpiElems3 = 8 * 2 * 64 * kEpiPitch3;   // 147456 B
 constexpr int kSmem3 = 2 * kStage3 > kEpiElems3 ? 2 * kStage3 : kEpiElems3;
 static_assert(kSmem3 * 2 <= 160 * 1024, "LDS budget");
-
-// The same request written out by hand.  The compiler makes every LDS read that it cannot tell
-// apart from a pending global->LDS request wait for all of them, and it cannot for the
-// transposing read: a k-step would then start by waiting for the tile it has just requested.
-// Requests issued this way are invisible to that bookkeeping; the loop's own vmcnt(0) and
-// barrier order them against the reads.  The LDS base travels in m0, which the register
-// allocator hands over through the "{m0}" constraint (it knows the register is written).
-__device__ __forceinline__ void lds_dma16_raw(const uint16_t* gsrc, uint16_t* lds_block) {
-  const uint32_t lds = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_block);
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(gsrc), "{m0}"(lds)
-               : "memory");
-}
 
 template <int EPI, bool GATHER, bool PER_UPLOAD, int TAG>
 __global__ __launch_bounds__(512, 1) void mlp_gemm256_kernel(GemmArgs g, RoundDesc rd) {
@@ -1147,8 +1102,6 @@ struct LogitsCeArgs {
   float* colsum; size_t ldcs;            // [rows / 128][ldcs]
 };
 
-__device__ __forceinline__ void lds_dma16_raw(const uint16_t* gsrc, uint16_t* lds_block);
-
 template <int NB>                        // dp_L = 32 NB: 2, 4 or 8
 __global__ __launch_bounds__(256, 1) void mlp_logits_ce_kernel(LogitsCeArgs a, RoundDesc rd) {
   constexpr int NP = 32 * NB;            // padded class count
@@ -1500,31 +1453,37 @@ template <typename T>
 T* at(const MlpArgs& a, size_t off) { return (T*)(a.ws + off); }
 
 // Number of row-range splits of a weight-gradient contraction.  `slots` workgroups run at
-// once; a split costs one k-step time per step of its range and every extra split adds a
-// partial tile to write and read back.  Picks the cheapest under that model.
-int pick_split(int tiles, int ksteps, int slots, double tile_bytes) {
-  const double step_us = 2.0, bytes_per_us = 3.0e6;
+// once; a split costs `step_us` per k-step of its range and `fixed_us` per wave of workgroups, and every
+// extra split adds a partial tile to write and read back.  Picks the cheapest under that model.
+int pick_split(int tiles, int ksteps, int slots, double tile_bytes, double step_us, double fixed_us) {
+  const double bytes_per_us = 3.0e6;
   int best = 1;
   double best_cost = 1e300;
   for (int z = 1; z <= std::min(ksteps, kMaxSplit); ++z) {
     const int rounds = (tiles * z + slots - 1) / slots;
     const int steps = (ksteps + z - 1) / z;
-    const double cost = rounds * steps * step_us * (tile_bytes / (256.0 * 256 * 4)) +
-                        (double)z * tiles * tile_bytes * 2.0 / bytes_per_us;
+    const double cost = rounds * (steps * step_us + fixed_us) + (double)z * tiles * tile_bytes * 2.0 / bytes_per_us;
     if (cost < best_cost) { best_cost = cost; best = z; }
   }
   return best;
 }
 
+// Whether a weight gradient off the large-tile kernel takes 128-wide tiles: a long contraction that can
+// still be cut into a workgroup per CU (cfg 5's output layer, 2048 x 128 over 8192 / 32768 rows: 33 / 62 us
+// against 39 / 71 with 64-wide tiles, which read the activations twice; short ones are faster with 64).
+bool wgrad_wide_tiles(int Mdim, int Ndim, int ksteps) {
+  return Ndim % 128 == 0 && (Mdim / 128) * (Ndim / 128) * std::min(ksteps / 8, kMaxSplit) >= 256;
+}
 // Row-range splits of layer l's weight-gradient contraction over `rows` stacked rows
 // (per_upload > 0: local SGD, one split per upload).
 int wgrad_split(const MlpPlan& p, int l, int rows, int per_upload) {
   if (per_upload > 0) return per_upload;
   const int ksteps = rows / BK;
-  const int tn = p.dp[l + 1] % 256 == 0 ? 256 : p.dp[l + 1] % 128 == 0 ? 128 : 64;
-  const bool big = p.dp[l] % TM3 == 0 && p.dp[l + 1] % TN3 == 0;
-  const int tiles = big ? (p.dp[l] / TM3) * (p.dp[l + 1] / TN3) : (p.dp[l] / TM) * (p.dp[l + 1] / tn);
-  return big ? pick_split(tiles, ksteps, 256, 256.0 * 256 * 4) : pick_split(tiles, ksteps, 512, 128.0 * tn * 4);
+  if (p.dp[l] % TM3 == 0 && p.dp[l + 1] % TN3 == 0)
+    return pick_split((p.dp[l] / TM3) * (p.dp[l + 1] / TN3), ksteps, 256, 256.0 * 256 * 4, 2.0, 0.0);
+  if (wgrad_wide_tiles(p.dp[l], p.dp[l + 1], ksteps))
+    return pick_split((p.dp[l] / 128) * (p.dp[l + 1] / 128), ksteps, 512, 128.0 * 128 * 4, 0.5, 0.0);
+  return pick_split((p.dp[l] / 64) * (p.dp[l + 1] / 64), ksteps, 512, 64.0 * 64 * 4, 0.25, 0.0);
 }
 
 }  // namespace
@@ -1770,47 +1729,26 @@ bool launch_gemm(GemmArgs g, const RoundDesc& rd, int Mdim, int Ndim, int nsplit
     ABS_LAUNCH_K((mlp_gemm256_kernel<EPI, GATHER, PER_UPLOAD, TAG>), dim3(8 * g.rows_per_xcd * g.nt + g.pig_blocks + g.bias_blocks), dim3(512), s, g, rd);
     return true;
   }
-  // widest column tile that still fills the GPU: 256-wide tiles only with two workgroups per CU
-  // (the kernel is built for two: one's loads cover the other's barriers), 128-wide with one
-  int tn = 64;
-  for (int cand : {256, 128}) {
-    if (Ndim % cand) continue;
-    const int need = cand == 256 ? 512 : 256;
-    if ((Mdim / TM) * (Ndim / cand) * nsplit >= need || Ndim % (cand / 2)) { tn = cand; break; }
-  }
-  g.mt = Mdim / TM;
-  g.nt = Ndim / tn;
+  // 128-wide tiles once 64-wide ones would be more than the two workgroups a CU holds (a 64-wide workgroup
+  // stages twice the bytes per flop, but a CU draws at most 23-32 bytes per clock from beyond the L1, so
+  // a product spread over twice the CUs or in two workgroups per CU is the faster one; 3072 x 1024, us with
+  // 64 / 128 wide tiles at 2048 rows: 31.5 / 35.1, 2560: 44.8 / 36.5, 3072: 46.3 / 37.0, 4608: 70.1 / 69.3).
+  const bool wide = EPI == EPI_WGRAD ? wgrad_wide_tiles(Mdim, Ndim, g.ksteps_total)
+                                     : Ndim % 128 == 0 && (Mdim / 128) * (Ndim / 128) * nsplit > 128;
+  const int tile = wide ? 128 : 64;
+  g.mt = Mdim / tile;
+  g.nt = Ndim / tile;
   g.rows_per_xcd = (g.mt * nsplit + 7) / 8;
-  const dim3 block(256);
-  const dim3 grid1(8 * g.rows_per_xcd * g.nt + g.pig_blocks + g.bias_blocks, 1, 1);
-  // DMA ring: whole k-steps only
-  const bool ring_ok = EPI != EPI_LOGITS && (!GATHER || (g.a_kvalid % BK == 0 && g.a_kvalid >= g.ksteps_total * BK));
-  // 64-wide forward tiles: two k-steps per ring stage (one barrier, one wait, one batch of requests for
-  // 128 of the contraction): these tiles do 8 MFMAs per wavefront and k-step, and what a k-step costs is
-  // mostly its fixed part (cfg 3's first-layer forward 43-46 -> 35-38 us; three k-steps in a ring of two
-  // stages 32-35 us.  The 128-wide tiles lose with it: two k-steps per stage leave room for one workgroup
-  // per CU instead of two, cfg 4's first-layer forward 65 -> 91 us).  Widths are padded to 128, so a
-  // forward product always has an even number of k-steps.
-  // Where the k-step count allows, three k-steps per stage in a ring of two (the same 144 KB).
-  if (ring_ok && tn == 64 && ABS_RING64 && EPI == EPI_RELU && g.ksteps_per_split % 3 == 0 && g.ksteps_total % 3 == 0) {
-    plan_note("fwd_ring3", TM, tn, nsplit);
-    ABS_LAUNCH_K((mlp_gemm_kernel<64, EPI, GATHER, PER_UPLOAD, TAG, 2, 3>), grid1, block, s, g, rd);
-    return false;
-  }
-  if (ring_ok && tn == 64 && ABS_RING64 && EPI == EPI_RELU && g.ksteps_per_split % 2 == 0 && g.ksteps_total % 2 == 0) {
-    plan_note("fwd_ring2", TM, tn, nsplit);
-    ABS_LAUNCH_K((mlp_gemm_kernel<64, EPI, GATHER, PER_UPLOAD, TAG, ABS_RING64, 2>), grid1, block, s, g, rd);
-    return false;
-  }
-  if (ring_ok && tn == 128 && ABS_RING128) {
-    plan_note(EPI == EPI_RELU ? "fwd_ring" : EPI == EPI_DGRAD ? "dgrad_ring" : "wgrad_ring", TM, tn, nsplit);
-    ABS_LAUNCH_K((mlp_gemm_kernel<128, EPI, GATHER, PER_UPLOAD, TAG, ABS_RING128>), grid1, block, s, g, rd);
-    return false;
-  }
-  plan_note(EPI == EPI_RELU ? "fwd" : EPI == EPI_LOGITS ? "logits" : EPI == EPI_DGRAD ? "dgrad" : "wgrad", TM, tn, nsplit);
-  if (tn == 256)      ABS_LAUNCH_K((mlp_gemm_kernel<256, EPI, GATHER, PER_UPLOAD, TAG>), grid1, block, s, g, rd);
-  else if (tn == 128) ABS_LAUNCH_K((mlp_gemm_kernel<128, EPI, GATHER, PER_UPLOAD, TAG>), grid1, block, s, g, rd);
-  else                ABS_LAUNCH_K((mlp_gemm_kernel<64, EPI, GATHER, PER_UPLOAD, TAG>), grid1, block, s, g, rd);
+  const dim3 grid(8 * g.rows_per_xcd * g.nt + g.pig_blocks + g.bias_blocks);
+  plan_note(EPI == EPI_RELU ? "fwd_tile" : EPI == EPI_LOGITS ? "logits_tile" : EPI == EPI_DGRAD ? "dgrad_tile" : "wgrad_tile", tile, tile, nsplit);
+  // Ring depths: forward and input-gradient products keep three steps on their way (64-wide: 64 KB, two
+  // workgroups per CU; 8 steps and one workgroup: the evaluation's logits 22.5 instead of 16.8 us; 3 steps: cfg 3's
+  // first layer 22.4 instead of 18.4).  A weight gradient carries the previous layer's update as extra
+  // workgroups and leaves LDS for several of them per CU (128-wide, ring of 4 and one workgroup:
+  // cfg 5's output layer 39 instead of 33 us).
+  constexpr int kRing128 = EPI == EPI_WGRAD ? 2 : 4, kRing64 = EPI == EPI_WGRAD ? 3 : 4;
+  if (wide) ABS_LAUNCH_K((mlp_tile_kernel<128, EPI, GATHER, PER_UPLOAD, TAG, kRing128>), grid, dim3(TileCfg<128>::NT), s, g, rd);
+  else      ABS_LAUNCH_K((mlp_tile_kernel<64, EPI, GATHER, PER_UPLOAD, TAG, kRing64>), grid, dim3(TileCfg<64>::NT), s, g, rd);
   return false;
 }
 

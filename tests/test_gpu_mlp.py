@@ -91,3 +91,21 @@ def test_sampled_kernel_timing_changes_nothing():
         assert s1["timed_launches"] == s1["launches"] and s1["timed_flops"] == s1["flops"] and s1["total_ms"] > 0
         per_round = s4["launches"] // 21
         assert s4["timed_launches"] == 6 * per_round and s4["total_ms"] > 0      # rounds 0, 4, ..., 20
+
+
+@pytest.mark.parametrize("over,T", [
+    # contractions shorter than a ring, one valid chunk of 8 features in a k-step of 64
+    (dict(M=512, dims=[8, 40, 2], n_classes=2, N=4, B=1, n_slow=0, lr=1e-3), 10),
+    (dict(M=1024, dims=[72, 64, 10], N=4, B=130, n_slow=0, lr=1e-3), 10),
+    # nothing a multiple of a tile, three hidden widths, a ragged last k-step in the gathered product
+    (dict(M=2400, dims=[1000, 520, 300, 26], n_classes=26, N=4, B=90, n_slow=0, lr=2e-4), 6),
+    # more than 128 tiles of 128 x 128 in every forward and input-gradient product; one fewer row tile: 64-wide
+    (dict(M=4800, dims=[136, 1024, 1024, 10], N=17, K0=17, B=128, n_slow=0, lr=1e-4), 2),
+    (dict(M=4800, dims=[136, 1024, 1024, 10], N=16, K0=16, B=128, n_slow=0, lr=1e-4), 2),
+    # a weight gradient long enough for 128-wide tiles (128 k-steps, 128 padded classes)
+    (dict(M=12800, dims=[64, 2048, 100], n_classes=100, N=64, K0=64, B=128, n_slow=0, lr=1e-4), 2),
+])
+def test_tile_kernel_edges(over, T):
+    """The tile kernel where its remainders are: short rings, zero-filled columns of gathered rows, both tile sizes."""
+    p = workloads.scaled_preset(3, **over)
+    _check(run_pair(p, T, checkpoints=(1,)))
