@@ -9,20 +9,18 @@
 // [C_in k k][C_out] with row (ci k + u) k + v, a dense layer's [d_in][d_out].
 //
 // Shape of the work: B = 32 images per upload and N <= 128 uploads per round - a few hundred images
-// of 62 K parameters.  Nothing here is bound by arithmetic or bandwidth; the kernels are laid out so
-// that every stage has one workgroup per image (or per upload, or per weight row) and the round is
-// seven short launches:
-//   conv_pool_fwd x 2   a workgroup per stacked row: image (or pooled map) and the upload's stale
-//                       filters in LDS; a thread computes the four convolution outputs of one pooling
-//                       window, keeps max(., 0) and which of the four it was (255: window dead)
-//   dense_fwd_bwd       a workgroup per upload: its B rows through the three dense layers at the
-//                       upload's model version, loss, and back down to the gradient of the pooled map
-//                       (every dZ already carries the upload's coefficient of Eq. 3)
-//   dense_wgrad_update  a thread per dense weight: Eq. 3's sum over all K B stacked rows in row order,
-//                       w^{t+1} = w^t - sum; its first workgroup publishes the uploads' losses
-//   conv2_bwd           a workgroup per row: gradient of the first pooled map
-//   conv_wgrad_update x 2   a workgroup per filter row (ci, u, v): sum over rows and pooling windows,
-//                       fixed-order reduction, w^{t+1} = w^t - sum
+// of 62 K parameters.  Nothing here is bound by arithmetic or bandwidth but by how long a chain of
+// fetches and LDS reads a workgroup walks, and by the launches; a round is four of them:
+//   cnn_fwd      a workgroup per stacked row: image and the upload's stale filters in LDS, both convolutions
+//                with ReLU and pooling; per window max(., 0) and which of the four it was (255: window dead)
+//   cnn_dense    a workgroup per 1 to 8 rows of an upload: the three dense layers forward at the
+//                upload's model version, loss, and back down to the gradient of the pooled map
+//                (every dZ already carries the upload's coefficient of Eq. 3)
+//   cnn_bwd      a workgroup per row: gradient of the first pooled map and the row's share of both filter
+//                gradients; behind them a workgroup per tile of an upload's dense gradient; the first
+//                one publishes the uploads' losses
+//   cnn_combine  Eq. 3: rows' and uploads' shares added in order, w^{t+1} = w^t - sum
+// (20 workers, 32 images each, 5 uploads: 71 us of kernels; nine launches of smaller workgroups took 187.)
 // Pooling is applied to the pre-activations and the ReLU after it (the maximum of the four ReLUs is
 // the ReLU of the maximum, and a window whose maximum is not positive passes no gradient either way).
 // All sums have a fixed order: two runs are bitwise identical.
@@ -137,125 +135,264 @@ __global__ __launch_bounds__(256) void cnn_conv_pool_fwd_kernel(CnnDev d, RoundD
   }
 }
 
-constexpr int kGroup = 8;       // stacked rows per workgroup of the dense stage
-
-// out[b][j] = bias[j] + sum_i in[b][i] W[i][j] for the workgroup's nb <= 8 rows in LDS: a thread
-// takes one column, so a weight is fetched once for all rows and neighbouring threads read
-// neighbouring weights; eight weights of a column are in flight at a time.
-__device__ __forceinline__ void dense_rows(const float* s_in, int Fin, const float* W, const float* bias, int Fout,
-                                           int nb, bool relu, float* s_out, float* g_out) {
-  for (int j = threadIdx.x; j < Fout; j += blockDim.x) {
-    float acc[kGroup];
-    const float bv = bias[j];
+// Both convolutions of a stacked row in one workgroup: the first pooled map stays in LDS for the second.
+// A thread takes a pooling window and two output channels (a filter tap of both is one 8-byte read, the
+// inputs under the window serve 8 sums); every sum runs over (ci, u, v) in the order of
+// cnn_conv_pool_fwd_kernel, so the results are bitwise the same.  Bound by the vector ALU and the LDS reads that feed
+// it, behind the latency of fetching image and filters; 160 rows of the 5 x 5 workload: 32 us in two launches of 256
+// threads, 15 us this way.
+constexpr int kFwdThreads = 1024;
+template <int KS>
+__device__ __forceinline__ void conv_pool_stage(const float* sx, int Cin, int Sin, const float* sw, const float* sb,
+                                                int Cout, int Sp, int k, float* s_out, float* g_out, uint8_t* g_arg) {
+  const int win = Sp * Sp, Cop = (Cout + 1) & ~1, items = Cop / 2 * win;
+  for (int o = threadIdx.x; o < items; o += kFwdThreads) {
+    const int co = o / win * 2, wi = o - o / win * win, pi = wi / Sp, pj = wi - pi * Sp;
+    float a[2][4];
 #pragma unroll
-    for (int q = 0; q < kGroup; ++q) acc[q] = bv;
-    int i = 0;
-    for (; i + 8 <= Fin; i += 8) {
-      float wv[8];
+    for (int c = 0; c < 2; ++c) a[c][0] = a[c][1] = a[c][2] = a[c][3] = sb[min(co + c, Cout - 1)];
+    for (int ci = 0; ci < Cin; ++ci)
+      for (int u = 0; u < (KS ? KS : k); ++u) {
+        const float* x0 = sx + (ci * Sin + 2 * pi + u) * Sin + 2 * pj;
+        const float* wr = sw + ((ci * k + u) * k) * Cop + co;
+        if (KS) {
+          // (an odd filter has an even input side: S - k + 1 is even)
+          float xa[KS + 1], xb[KS + 1];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) wv[e] = W[(size_t)(i + e) * Fout + j];
+          for (int v = 0; v <= KS; v += 2) {
+            const float2 p = *(const float2*)(x0 + v), q = *(const float2*)(x0 + v + Sin);
+            xa[v] = p.x; xa[v + 1] = p.y; xb[v] = q.x; xb[v + 1] = q.y;
+          }
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
+          for (int v = 0; v < KS; ++v) {
+            const float2 wv = *(const float2*)(wr + v * Cop);
+            a[0][0] = fmaf(xa[v], wv.x, a[0][0]); a[0][1] = fmaf(xa[v + 1], wv.x, a[0][1]);
+            a[0][2] = fmaf(xb[v], wv.x, a[0][2]); a[0][3] = fmaf(xb[v + 1], wv.x, a[0][3]);
+            a[1][0] = fmaf(xa[v], wv.y, a[1][0]); a[1][1] = fmaf(xa[v + 1], wv.y, a[1][1]);
+            a[1][2] = fmaf(xb[v], wv.y, a[1][2]); a[1][3] = fmaf(xb[v + 1], wv.y, a[1][3]);
+          }
+        } else {
+          for (int v = 0; v < k; ++v) {
+            const float2 wv = *(const float2*)(wr + v * Cop);
+            const float x00 = x0[v], x01 = x0[v + 1], x10 = x0[v + Sin], x11 = x0[v + Sin + 1];
+            a[0][0] = fmaf(x00, wv.x, a[0][0]); a[0][1] = fmaf(x01, wv.x, a[0][1]);
+            a[0][2] = fmaf(x10, wv.x, a[0][2]); a[0][3] = fmaf(x11, wv.x, a[0][3]);
+            a[1][0] = fmaf(x00, wv.y, a[1][0]); a[1][1] = fmaf(x01, wv.y, a[1][1]);
+            a[1][2] = fmaf(x10, wv.y, a[1][2]); a[1][3] = fmaf(x11, wv.y, a[1][3]);
+          }
+        }
+      }
 #pragma unroll
-        for (int q = 0; q < kGroup; ++q) acc[q] = fmaf(s_in[q * Fin + i + e], wv[e], acc[q]);
-    }
-    for (; i < Fin; ++i) {
-      const float wv = W[(size_t)i * Fout + j];
-#pragma unroll
-      for (int q = 0; q < kGroup; ++q) acc[q] = fmaf(s_in[q * Fin + i], wv, acc[q]);
-    }
-#pragma unroll
-    for (int q = 0; q < kGroup; ++q)
-      if (q < nb) {
-        const float v = relu ? fmaxf(acc[q], 0.f) : acc[q];
-        s_out[q * Fout + j] = v;
-        if (g_out) g_out[(size_t)q * Fout + j] = v;
+    for (int c = 0; c < 2; ++c)
+      if (co + c < Cout) {
+        float m = a[c][0]; int q = 0;
+        if (a[c][1] > m) { m = a[c][1]; q = 1; }
+        if (a[c][2] > m) { m = a[c][2]; q = 2; }
+        if (a[c][3] > m) { m = a[c][3]; q = 3; }
+        const int at = (co + c) * win + wi;
+        const float v = fmaxf(m, 0.f);
+        if (s_out) s_out[at] = v;
+        g_out[at] = v;
+        g_arg[at] = (uint8_t)(m > 0.f ? q : kDead);
       }
   }
 }
 
-// dIn[b][i] = gate(b, i) ? sum_j dOut[b][j] W[i][j] : 0 for the group's rows: a thread takes input
-// feature i for all rows, so a weight row is fetched once.
-template <typename Gate>
+// LDS (floats): image | first filters [tap][C1, even] | second filters [tap][C2, even] | biases | first pooled map
+struct FwdLds { int w0, w1, b, p1, total; };
+__host__ __device__ __forceinline__ FwdLds fwd_lds(const CnnPlan& p) {
+  const int kk = p.k * p.k;
+  FwdLds o;
+  o.w0 = (p.C0 * p.S * p.S + 1) & ~1;
+  o.w1 = o.w0 + p.C0 * kk * ((p.C1 + 1) & ~1);
+  o.b = o.w1 + p.C1 * kk * ((p.C2 + 1) & ~1);
+  o.p1 = (o.b + p.C1 + p.C2 + 1) & ~1;
+  o.total = o.p1 + p.C1 * p.S1 * p.S1;
+  return o;
+}
+template <int KS>
+__global__ __launch_bounds__(kFwdThreads) void cnn_fwd_kernel(CnnDev d, RoundDesc rd) {
+  extern __shared__ __attribute__((aligned(16))) float sm[];
+  const CnnPlan& p = d.p;
+  const int r = blockIdx.x, a = r / p.B, t = threadIdx.x, k = KS ? KS : p.k, kk = k * k;
+  const FwdLds at = fwd_lds(p);
+  const float* w = slot_of(d, rd, a);
+  const uint64_t row = d.fixed_slot >= 0 ? (uint64_t)(d.row0 + r)
+                                         : cnn_batch_row(rd.w[a], d.batch_key, d.shard_rows,
+                                                         (uint32_t)(max(d.step, 0) * p.B + r - a * p.B));
+  if (t == 0) {
+    wsp<uint32_t>(d, p.off_rowidx)[r] = (uint32_t)(d.fixed_slot >= 0 ? r : row);
+    wsp<int32_t>(d, p.off_label)[r] = d.y[row];
+  }
+  const int n_in = p.C0 * p.S * p.S;
+  const float* src = d.X + row * (uint64_t)n_in;
+  for (int i = t; i < n_in; i += kFwdThreads) sm[i] = src[i];
+  const int c1p = (p.C1 + 1) & ~1, c2p = (p.C2 + 1) & ~1;
+  for (int i = t; i < p.C0 * kk * c1p; i += kFwdThreads) {
+    const int q = i / c1p, co = i - q * c1p;
+    sm[at.w0 + i] = co < p.C1 ? w[p.w_off[0] + (size_t)q * p.C1 + co] : 0.f;
+  }
+  for (int i = t; i < p.C1 * kk * c2p; i += kFwdThreads) {
+    const int q = i / c2p, co = i - q * c2p;
+    sm[at.w1 + i] = co < p.C2 ? w[p.w_off[1] + (size_t)q * p.C2 + co] : 0.f;
+  }
+  for (int i = t; i < p.C1 + p.C2; i += kFwdThreads) sm[at.b + i] = i < p.C1 ? w[p.b_off[0] + i] : w[p.b_off[1] + i - p.C1];
+  __syncthreads();
+  const int n1 = p.C1 * p.S1 * p.S1;
+  conv_pool_stage<KS>(sm, p.C0, p.S, sm + at.w0, sm + at.b, p.C1, p.S1, k, sm + at.p1,
+                      wsp<float>(d, p.off_p1) + (size_t)r * n1, wsp<uint8_t>(d, p.off_a1) + (size_t)r * n1);
+  __syncthreads();
+  conv_pool_stage<KS>(sm + at.p1, p.C1, p.S1, sm + at.w1, sm + at.b + p.C1, p.C2, p.S2, k, nullptr,
+                      wsp<float>(d, p.off_p2) + (size_t)r * p.F0, wsp<uint8_t>(d, p.off_a2) + (size_t)r * p.F0);
+}
+
+// The dense stack.  A workgroup takes G stacked rows of one upload; the rows' values of a feature sit next
+// to each other in LDS ([feature][row]), so one read feeds a weight's G sums.
+constexpr int kDenseThreads = 1024;
+
+// out[j][b] = bias[j] + sum_i in[i][b] W[i][j].  The workgroup is cut into slices of the input features,
+// each with a thread per column (neighbouring threads read neighbouring weights, sixteen of a column in
+// flight); the slices' sums are added in slice order.
+template <int G>
+__device__ __forceinline__ void dense_rows(const float* s_in, int Fin, const float* W, const float* bias, int Fout,
+                                           int nb, bool relu, float* s_part, float* s_out, float* g_out) {
+  const int fr = min((Fout + 31) & ~31, kDenseThreads), nz = kDenseThreads / fr, len = (Fin + nz - 1) / nz;
+  const int t = threadIdx.x, z = t / fr, j = t - z * fr;
+  const float b0 = bias[min(t / G, Fout - 1)];             // (on its way under the sums)
+  float acc[G];
+#pragma unroll
+  for (int q = 0; q < G; ++q) acc[q] = 0.f;
+  if (z < nz && j < Fout) {
+    int i = z * len;
+    const int i1 = min(Fin, i + len);
+    for (; i < i1; i += 16) {
+      float wv[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) wv[e] = W[(size_t)min(i + e, i1 - 1) * Fout + j];
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        if (i + e < i1) {
+#pragma unroll
+          for (int q = 0; q < G; ++q) acc[q] = fmaf(s_in[(i + e) * G + q], wv[e], acc[q]);
+        }
+    }
+  }
+  if (z < nz) {
+#pragma unroll
+    for (int q = 0; q < G; ++q) s_part[(z * fr + j) * G + q] = acc[q];
+  }
+  __syncthreads();
+  for (int o = t; o < Fout * G; o += kDenseThreads) {
+    const int jo = o / G, q = o - jo * G;
+    float v = o == t ? b0 : bias[jo];
+    for (int zz = 0; zz < nz; ++zz) v += s_part[(zz * fr + jo) * G + q];
+    if (relu) v = fmaxf(v, 0.f);
+    s_out[o] = v;
+    if (g_out && q < nb) g_out[(size_t)q * Fout + jo] = v;
+  }
+  __syncthreads();
+}
+
+// dIn[i][b] = gate(b, i) ? sum_j dOut[j][b] W[i][j] : 0: sixteen neighbouring lanes take input feature i and
+// read its row of weights in pieces of 64 bytes.
+template <int G, typename Gate>
 __device__ __forceinline__ void dense_rows_back(const float* s_dout, int Fout, const float* W, int Fin, int nb,
                                                 Gate gate, float* s_din, float* g_din) {
-  for (int i = threadIdx.x; i < Fin; i += blockDim.x) {
-    float acc[kGroup];
+  const int l = threadIdx.x & 15;
+  constexpr int kStep = kDenseThreads / 16;
+  for (int i0 = threadIdx.x >> 4; i0 < Fin; i0 += 2 * kStep) {        // features i0 and i0 + kStep together
+    float acc[2][G];
 #pragma unroll
-    for (int q = 0; q < kGroup; ++q) acc[q] = 0.f;
-    const float* wr = W + (size_t)i * Fout;
-    int j = 0;
-    for (; j + 4 <= Fout; j += 4) {
-      const float w0 = wr[j], w1 = wr[j + 1], w2 = wr[j + 2], w3 = wr[j + 3];
+    for (int q = 0; q < G; ++q) acc[0][q] = acc[1][q] = 0.f;
+    const float* wr[2] = {W + (size_t)i0 * Fout, W + (size_t)min(i0 + kStep, Fin - 1) * Fout};
+    for (int j = l; j < Fout; j += 128) {
+      float wv[2][8];
 #pragma unroll
-      for (int q = 0; q < kGroup; ++q) {
-        const float* dz = s_dout + q * Fout + j;
-        acc[q] = fmaf(dz[0], w0, acc[q]); acc[q] = fmaf(dz[1], w1, acc[q]);
-        acc[q] = fmaf(dz[2], w2, acc[q]); acc[q] = fmaf(dz[3], w3, acc[q]);
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) wv[h][e] = wr[h][min(j + 16 * e, Fout - 1)];
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (j + 16 * e < Fout) {
+#pragma unroll
+          for (int q = 0; q < G; ++q) {
+            const float dz = s_dout[(j + 16 * e) * G + q];
+            acc[0][q] = fmaf(dz, wv[0][e], acc[0][q]);
+            acc[1][q] = fmaf(dz, wv[1][e], acc[1][q]);
+          }
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int i = i0 + h * kStep;
+#pragma unroll
+      for (int q = 0; q < G; ++q) {
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) acc[h][q] += __shfl_xor(acc[h][q], o, 16);
+        if (l == q && i < Fin) {
+          const float v = q < nb && gate(q, i) ? acc[h][q] : 0.f;
+          if (s_din) s_din[i * G + q] = v;
+          if (q < nb) g_din[(size_t)q * Fin + i] = v;
+        }
       }
     }
-    for (; j < Fout; ++j) {
-      const float wv = wr[j];
-#pragma unroll
-      for (int q = 0; q < kGroup; ++q) acc[q] = fmaf(s_dout[q * Fout + j], wv, acc[q]);
-    }
-#pragma unroll
-    for (int q = 0; q < kGroup; ++q)
-      if (q < nb) {
-        const float v = gate(q, i) ? acc[q] : 0.f;
-        if (s_din) s_din[q * Fin + i] = v;
-        g_din[(size_t)q * Fin + i] = v;
-      }
   }
+  __syncthreads();
 }
 
-// The dense stack for a group of up to 8 rows of one upload (training) or of the evaluation pass:
+// The dense stack for a group of up to G rows of one upload (training) or of the evaluation pass:
 // forward at the rows' model version, per-row loss, and (training) back down to the gradient of the
 // second pooled map; every dZ carries the upload's coefficient of Eq. 3.
-__global__ __launch_bounds__(256) void cnn_dense_kernel(CnnDev d, RoundDesc rd, float* eval_loss, float* eval_hit) {
+// Every stage is a chain of weight fetches from the L2: what bounds it is how many are in flight, so a
+// round of few rows takes small groups (a workgroup per CU) and slices within them.  5 uploads of 32 rows, 400-120-84-10:
+// 59 us with 20 workgroups of 256 threads (8 rows each, a thread per column); of 1024 threads, 80 for 2 rows
+// each 27 us, 160 for a row each 23.
+template <int G>
+__global__ __launch_bounds__(kDenseThreads) void cnn_dense_kernel(CnnDev d, RoundDesc rd, float* eval_loss, float* eval_hit) {
   extern __shared__ __attribute__((aligned(16))) float sm[];
   const CnnPlan& p = d.p;
   const int t = threadIdx.x;
-  const int gpu_ = (p.B + kGroup - 1) / kGroup;            // groups per upload
+  const int gpu_ = (p.B + G - 1) / G;                      // groups per upload
   const int a = blockIdx.x / gpu_, g = blockIdx.x - a * gpu_;
-  const int r0 = a * p.B + g * kGroup;
-  const int nb = min(kGroup, min(p.B - g * kGroup, d.n_rows - r0));
+  const int r0 = a * p.B + g * G;
+  const int nb = min(G, min(p.B - g * G, d.n_rows - r0));
   if (nb <= 0) return;
-  float* sH0 = sm;
-  float* sH1 = sH0 + kGroup * p.F0;
-  float* sH2 = sH1 + kGroup * p.F1;
-  float* sZ = sH2 + kGroup * p.F2;
-  float* sD2 = sZ + kGroup * p.C;       // dZ of the second dense layer
-  float* sD1 = sD2 + kGroup * p.F2;     // dZ of the first dense layer
+  float* sPart = sm;
+  float* sH0 = sPart + kDenseThreads * G;
+  float* sH1 = sH0 + G * p.F0;
+  float* sH2 = sH1 + G * p.F1;
+  float* sZ = sH2 + G * p.F2;
+  float* sD2 = sZ + G * p.C;            // dZ of the second dense layer
+  float* sD1 = sD2 + G * p.F2;          // dZ of the first dense layer
   const float* w = slot_of(d, rd, a);
   const float* p2 = wsp<const float>(d, p.off_p2) + (size_t)r0 * p.F0;
-  for (int i = t; i < kGroup * p.F0; i += 256) sH0[i] = i < nb * p.F0 ? p2[i] : 0.f;
+  for (int i = t; i < G * p.F0; i += kDenseThreads) {
+    const int q = i / p.F0, f = i - q * p.F0;
+    sH0[f * G + q] = q < nb ? p2[i] : 0.f;
+  }
   __syncthreads();
   const bool train = eval_loss == nullptr;
-  dense_rows(sH0, p.F0, w + p.w_off[2], w + p.b_off[2], p.F1, nb, true, sH1,
-             train ? wsp<float>(d, p.off_h1) + (size_t)r0 * p.F1 : nullptr);
-  __syncthreads();
-  dense_rows(sH1, p.F1, w + p.w_off[3], w + p.b_off[3], p.F2, nb, true, sH2,
-             train ? wsp<float>(d, p.off_h2) + (size_t)r0 * p.F2 : nullptr);
-  __syncthreads();
-  dense_rows(sH2, p.F2, w + p.w_off[4], w + p.b_off[4], p.C, nb, false, sZ, nullptr);
-  __syncthreads();
-  const int32_t* label = wsp<const int32_t>(d, p.off_label) + r0;
+  const int y = t < nb ? wsp<const int32_t>(d, p.off_label)[r0 + t] : 0;
+  dense_rows<G>(sH0, p.F0, w + p.w_off[2], w + p.b_off[2], p.F1, nb, true, sPart, sH1,
+                train ? wsp<float>(d, p.off_h1) + (size_t)r0 * p.F1 : nullptr);
+  dense_rows<G>(sH1, p.F1, w + p.w_off[3], w + p.b_off[3], p.F2, nb, true, sPart, sH2,
+                train ? wsp<float>(d, p.off_h2) + (size_t)r0 * p.F2 : nullptr);
+  dense_rows<G>(sH2, p.F2, w + p.w_off[4], w + p.b_off[4], p.C, nb, false, sPart, sZ, nullptr);
   if (t < nb) {
     // softmax cross-entropy of row t; dZ = c (p - onehot) with the upload's coefficient of Eq. 3
-    float* z = sZ + t * p.C;
-    const int y = label[t];
+    float* z = sZ + t;
     float zmax = z[0]; int best = 0;
-    for (int c = 1; c < p.C; ++c) if (z[c] > zmax) { zmax = z[c]; best = c; }
+    for (int c = 1; c < p.C; ++c) if (z[c * G] > zmax) { zmax = z[c * G]; best = c; }
+    const float zy = z[y * G];
     float ssum = 0.f;
-    for (int c = 0; c < p.C; ++c) ssum += expf(z[c] - zmax);
-    const float loss = logf(ssum) - (z[y] - zmax);
+    for (int c = 0; c < p.C; ++c) { const float e = expf(z[c * G] - zmax); z[c * G] = e; ssum += e; }
+    const float loss = logf(ssum) - (zy - zmax);
     if (train) {
       const float coef = rd.w[a].c, inv = 1.f / ssum;
       float* dz3 = wsp<float>(d, p.off_dz3) + (size_t)(r0 + t) * p.C;
       for (int c = 0; c < p.C; ++c) {
-        const float v = coef * (expf(z[c] - zmax) * inv - (c == y ? 1.f : 0.f));
-        z[c] = v;
+        const float v = coef * (z[c * G] * inv - (c == y ? 1.f : 0.f));
+        z[c * G] = v;
         dz3[c] = v;
       }
       wsp<float>(d, p.off_rowloss)[r0 + t] = loss;
@@ -266,50 +403,261 @@ __global__ __launch_bounds__(256) void cnn_dense_kernel(CnnDev d, RoundDesc rd, 
   }
   if (!train) return;
   __syncthreads();
-  dense_rows_back(sZ, p.C, w + p.w_off[4], p.F2, nb, [&](int b, int i) { return sH2[b * p.F2 + i] > 0.f; }, sD2,
-                  wsp<float>(d, p.off_dz2) + (size_t)r0 * p.F2);
-  __syncthreads();
-  dense_rows_back(sD2, p.F2, w + p.w_off[3], p.F1, nb, [&](int b, int i) { return sH1[b * p.F1 + i] > 0.f; }, sD1,
-                  wsp<float>(d, p.off_dz1) + (size_t)r0 * p.F1);
-  __syncthreads();
-  const uint8_t* a2 = wsp<const uint8_t>(d, p.off_a2) + (size_t)r0 * p.F0;
-  dense_rows_back(sD1, p.F1, w + p.w_off[2], p.F0, nb, [&](int b, int i) { return a2[b * p.F0 + i] != kDead; }, nullptr,
-                  wsp<float>(d, p.off_dp2) + (size_t)r0 * p.F0);
+  dense_rows_back<G>(sZ, p.C, w + p.w_off[4], p.F2, nb, [&](int b, int i) { return sH2[i * G + b] > 0.f; }, sD2,
+                     wsp<float>(d, p.off_dz2) + (size_t)r0 * p.F2);
+  dense_rows_back<G>(sD2, p.F2, w + p.w_off[3], p.F1, nb, [&](int b, int i) { return sH1[i * G + b] > 0.f; }, sD1,
+                     wsp<float>(d, p.off_dz1) + (size_t)r0 * p.F1);
+  // (a window is dead exactly where its pooled value is zero)
+  dense_rows_back<G>(sD1, p.F1, w + p.w_off[2], p.F0, nb, [&](int b, int i) { return sH0[i * G + b] > 0.f; }, nullptr,
+                     wsp<float>(d, p.off_dp2) + (size_t)r0 * p.F0);
 }
 
-// The dense layers' share of an upload's gradient (blockIdx.y = upload): element e of the three
-// weight matrices and biases summed over the upload's B rows in row order.  U = 1: the sum goes to
-// the upload's slot of G (Eq. 3 adds the slots in arrival order, cnn_combine_kernel); local steps:
-// the upload's private model takes the step at once (Eq. 2).
-__global__ __launch_bounds__(256) void cnn_dense_wgrad_kernel(CnnDev d, RoundDesc rd) {
+constexpr int kBwdThreads = 1024;
+
+// A kernel argument's value, opaque: a choice among several members of an argument struct otherwise becomes an
+// indexed load from a copy of the whole struct in scratch memory.
+template <typename T>
+__device__ __forceinline__ T member(T v) { asm("" : "+s"(v)); return v; }
+
+// The dense layers' share of upload a's gradient: a 64 x 64 tile of one of the three weight matrices (its
+// bias is one more input row of ones), summed over the upload's B rows in row order, 32 rows through
+// LDS at a time.  U = 1: the sum goes to the upload's slot of G (Eq. 3 adds the slots in arrival order,
+// cnn_combine_kernel); local steps: the upload's private model takes the step at once (Eq. 2).
+// (A thread per element and two loads from the L2 per row took 15 us for 5 uploads of 62 K weights.)
+__host__ __device__ __forceinline__ int dense_wgrad_tiles(const CnnPlan& p, int l) {
+  const int fi = (l == 0 ? p.F0 : l == 1 ? p.F1 : p.F2) + 1, fo = l == 0 ? p.F1 : l == 1 ? p.F2 : p.C;
+  return ((fi + 63) / 64) * ((fo + 63) / 64);
+}
+__host__ __device__ __forceinline__ int dense_wgrad_blocks(const CnnPlan& p) {
+  return dense_wgrad_tiles(p, 0) + dense_wgrad_tiles(p, 1) + dense_wgrad_tiles(p, 2);
+}
+__device__ __forceinline__ void dense_wgrad_block(const CnnDev& d, const RoundDesc& rd, int blk, float* lds) {
   const CnnPlan& p = d.p;
-  const int a = blockIdx.y;
-  const int Fin[3] = {p.F0, p.F1, p.F2}, Fout[3] = {p.F1, p.F2, p.C};
-  const size_t in_off[3] = {p.off_p2, p.off_h1, p.off_h2}, dz_off[3] = {p.off_dz1, p.off_dz2, p.off_dz3};
-  long e = (long)blockIdx.x * 256 + threadIdx.x;
-  const int ra = a * p.B, rb = ra + p.B;
-  for (int l = 0; l < 3; ++l) {
-    const long nw = (long)Fin[l] * Fout[l], n = nw + Fout[l];
-    if (e < n) {
-      const float* dz = wsp<const float>(d, dz_off[l]);
-      float g = 0.f;
-      size_t at;
-      if (e < nw) {
-        const int i = (int)(e / Fout[l]), j = (int)(e - (long)i * Fout[l]);
-        const float* in = wsp<const float>(d, in_off[l]);
-        for (int r = ra; r < rb; ++r) g = fmaf(in[(size_t)r * Fin[l] + i], dz[(size_t)r * Fout[l] + j], g);
-        at = p.w_off[2 + l] + (size_t)e;
-      } else {
-        const int j = (int)(e - nw);
-        for (int r = ra; r < rb; ++r) g += dz[(size_t)r * Fout[l] + j];
-        at = p.b_off[2 + l] + (size_t)j;
-      }
-      float* priv = wsp<float>(d, p.off_priv) + (size_t)a * p.slot_stride;
-      priv[at] = d.step < 0 ? g : slot_of(d, rd, a)[at] - g;
-      return;
+  const int per = dense_wgrad_blocks(p);
+  const int a = blk / per;
+  int tile = blk - a * per, l = 0;
+  const int n0 = dense_wgrad_tiles(p, 0), n1 = dense_wgrad_tiles(p, 1);
+  if (tile >= n0 + n1) { tile -= n0 + n1; l = 2; }
+  else if (tile >= n0) { tile -= n0; l = 1; }
+  const int F0 = member(p.F0), F1 = member(p.F1), F2 = member(p.F2), C = member(p.C);
+  const int Fin = l == 0 ? F0 : l == 1 ? F1 : F2, Fout = l == 0 ? F1 : l == 1 ? F2 : C;
+  const size_t i_0 = member(p.off_p2), i_1 = member(p.off_h1), i_2 = member(p.off_h2);
+  const size_t z_0 = member(p.off_dz1), z_1 = member(p.off_dz2), z_2 = member(p.off_dz3);
+  const size_t w_0 = member(p.w_off[2]), w_1 = member(p.w_off[3]), w_2 = member(p.w_off[4]);
+  const size_t b_0 = member(p.b_off[2]), b_1 = member(p.b_off[3]), b_2 = member(p.b_off[4]);
+  const float* in = wsp<const float>(d, l == 0 ? i_0 : l == 1 ? i_1 : i_2);
+  const float* dz = wsp<const float>(d, l == 0 ? z_0 : l == 1 ? z_1 : z_2);
+  const size_t w_at = l == 0 ? w_0 : l == 1 ? w_1 : w_2, b_at = l == 0 ? b_0 : l == 1 ? b_1 : b_2;
+  const int nj = (Fout + 63) / 64, i0 = tile / nj * 64, j0 = (tile % nj) * 64;
+  float* s_in = lds;               // [32 rows][64]
+  float* s_dz = lds + 32 * 64;     // [32 rows][64]
+  const int t = threadIdx.x, il = t >> 4, jl = (t & 15) * 4;
+  float g[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int b0 = 0; b0 < p.B; b0 += 32) {
+    const int nr = min(32, p.B - b0);
+    const size_t r0 = (size_t)a * p.B + b0;
+    for (int e = t; e < 32 * 64; e += kBwdThreads) {
+      const int r = e >> 6, i = i0 + (e & 63), j = j0 + (e & 63);
+      s_in[e] = r < nr ? (i < Fin ? in[(r0 + r) * Fin + i] : 1.f) : 0.f;
+      s_dz[e] = r < nr && j < Fout ? dz[(r0 + r) * Fout + j] : 0.f;
     }
-    e -= n;
+    __syncthreads();
+    for (int r = 0; r < nr; ++r) {
+      const float x = s_in[r * 64 + il];
+      const float4 v = *(const float4*)(s_dz + r * 64 + jl);
+      g[0] = fmaf(x, v.x, g[0]); g[1] = fmaf(x, v.y, g[1]); g[2] = fmaf(x, v.z, g[2]); g[3] = fmaf(x, v.w, g[3]);
+    }
+    __syncthreads();
   }
+  const int i = i0 + il;
+  if (i > Fin) return;
+  float* priv = wsp<float>(d, p.off_priv) + (size_t)a * p.slot_stride;
+  const float* cur = slot_of(d, rd, a);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int j = j0 + jl + e;
+    if (j < Fout) {
+      const size_t at = i < Fin ? w_at + (size_t)i * Fout + j : b_at + (size_t)j;
+      priv[at] = d.step < 0 ? g[e] : cur[at] - g[e];
+    }
+  }
+}
+
+// The uploads' mean minibatch losses; U = 1: published at once (the host selects and enqueues the next round
+// while this one's backward half runs), local steps: added to the job's mean.  Whole workgroup, uniform.
+__device__ __forceinline__ void cnn_losses(const CnnDev& d, const RoundDesc& rd, LossMailbox* mailbox) {
+  const CnnPlan& p = d.p;
+  const bool local = d.step >= 0;
+  const int a = threadIdx.x;
+  if (a < rd.K) {
+    const float* rl = wsp<const float>(d, p.off_rowloss) + (size_t)a * p.B;
+    float sum = 0.f;
+    int b = 0;
+    for (; b + 8 <= p.B; b += 8) {
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = rl[b + e];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sum += v[e];
+    }
+    for (; b < p.B; ++b) sum += rl[b];
+    const float mean = sum / (float)p.B;
+    float* lb = wsp<float>(d, p.off_lossbuf) + a;
+    if (!local) *lb = mean;
+    else *lb = (d.step == 0 ? 0.f : *lb) + mean / (float)d.U;       // mean over the job's U steps
+    if (mailbox) mailbox->loss[a] = mean;
+  }
+  if (mailbox) {
+    if (threadIdx.x < ABS_MAX_WORKERS) __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) mailbox->stamp = rd.stamp;
+  }
+}
+
+// A convolution's share of one row's gradient from LDS: sum over the pooling windows of the gradient
+// times the input under the window's maximum (gw: gradient and offset of the maximum in an input plane,
+// per output channel and window); `sp` neighbouring threads share an entry's windows.
+__device__ __forceinline__ void conv_wgrad_stage(const float* sx, int Cin, int Sin, const float2* gw, int Cout, int win,
+                                                 int k, float* out) {
+  const int nW = Cin * k * k * Cout, n = nW + Cout;
+  int sp = 1;
+  while (sp < 8 && n * sp * 2 <= 2 * kBwdThreads) sp *= 2;
+  const int rounds = (n * sp + kBwdThreads - 1) / kBwdThreads;
+  for (int it = 0; it < rounds; ++it) {
+    const int idx = it * kBwdThreads + (int)threadIdx.x, e = idx / sp, h = idx - e * sp;
+    float acc = 0.f;
+    if (e < nW) {
+      const int co = e % Cout, q = e / Cout, ci = q / (k * k), u = (q / k) % k, v = q % k;
+      const float* x0 = sx + (ci * Sin + u) * Sin + v;
+      const float2* gg = gw + co * win;
+#pragma unroll 4
+      for (int w_ = h; w_ < win; w_ += sp) {
+        const float2 a = gg[w_];
+        acc = fmaf(x0[__float_as_int(a.y)], a.x, acc);
+      }
+    } else if (e < n) {
+      const float2* gg = gw + (e - nW) * win;
+      for (int w_ = h; w_ < win; w_ += sp) acc += gg[w_].x;
+    }
+    for (int o = 1; o < sp; o <<= 1) acc += __shfl_xor(acc, o, 64);
+    if (h == 0 && e < n) out[e] = acc;
+  }
+}
+
+// The backward half below the dense stack, one launch.  Workgroup r < rows: everything of stacked row r -
+// the gradient of the first pooled map and the row's share of both filter gradients; the workgroups
+// behind them: the dense layers' share of the uploads' gradients (dense_wgrad_block).  The first workgroup
+// turns the row losses into the uploads' and, at U = 1, publishes them.
+// The gradient of the first pooled map is a product with few columns, [positions][taps x C2] times
+// [taps x C2][C1], on fp32 matrix instructions (16 x 16 x 4): A is the second convolution's output
+// gradient, scattered into a zero-framed map (k - 1 positions on every side, so no tap needs a bounds
+// check; channels innermost at a pitch that puts the 16 positions x 4 channels of a read in different
+// banks), B the upload's filters.  One read of each per 1024 multiply-adds; on the vector ALU the
+// filters alone were an LDS read per 4 (40 us for 160 rows; with the two filter-gradient launches, 25 us, and the
+// dense one, 15 us, now 29 us together: 35 with half the wavefronts, of which the products 12, the filter
+// gradients 6 and 10).
+struct BwdLds { int w, x, p1, g1, g0, total, pc, pw; };
+__host__ __device__ __forceinline__ BwdLds bwd_lds(const CnnPlan& p) {
+  BwdLds o;
+  const int side = 2 * p.S2 + 2 * (p.k - 1), Cp = (p.C2 + 3) & ~3, n1 = p.C1 * p.S1 * p.S1;
+  o.pc = Cp % 8 == 0 ? Cp + 4 : Cp;                  // map pitch: 4 (mod 8) words
+  o.pw = p.C1 | 1;                                   // filters [tap][channel][C1]
+  o.w = side * side * o.pc;
+  o.x = (o.w + p.k * p.k * Cp * o.pw + 32 + 1) & ~1; // (the columns beyond C1 of the last rows are read, and ignored)
+  o.p1 = o.x + p.C0 * p.S * p.S;
+  o.g1 = (o.p1 + n1 + 1) & ~1;                       // second convolution: (gradient, offset) per channel and window
+  o.g0 = o.g1 + 2 * p.F0;                            // first convolution
+  o.total = o.g0 + 2 * n1;
+  if (o.total < 4 * 1024) o.total = 4 * 1024;        // (dense_wgrad_block)
+  return o;
+}
+template <int KS>
+__global__ __launch_bounds__(kBwdThreads) void cnn_bwd_kernel(CnnDev d, RoundDesc rd, int rows, LossMailbox* mailbox) {
+  extern __shared__ __attribute__((aligned(16))) float sm[];
+  const CnnPlan& p = d.p;
+  if ((int)blockIdx.x >= rows) { dense_wgrad_block(d, rd, (int)blockIdx.x - rows, sm); return; }
+  if (blockIdx.x == 0) cnn_losses(d, rd, mailbox);
+  const int r = blockIdx.x, a = r / p.B, t = threadIdx.x, k = KS ? KS : p.k, kk = k * k;
+  const BwdLds at = bwd_lds(p);
+  const int side = 2 * p.S2 + 2 * (k - 1), Cp = (p.C2 + 3) & ~3, n1 = p.C1 * p.S1 * p.S1;
+  const float* w = slot_of(d, rd, a);
+  float* sdc = sm; float* sw = sm + at.w; float* sx = sm + at.x; float* sp1 = sm + at.p1;
+  float2* g1 = (float2*)(sm + at.g1); float2* g0 = (float2*)(sm + at.g0);
+  const int n_in = p.C0 * p.S * p.S;
+  const float* src = d.X + (size_t)wsp<const uint32_t>(d, p.off_rowidx)[r] * n_in;
+  for (int i = t; i < side * side * at.pc; i += kBwdThreads) sdc[i] = 0.f;
+  for (int i = t; i < p.C1 * kk * p.C2; i += kBwdThreads) {
+    const int q = i / p.C2, co = i - q * p.C2, ci = q / kk, tap = q - ci * kk;
+    sw[(tap * Cp + co) * at.pw + ci] = w[p.w_off[1] + i];
+  }
+  const int npad = Cp - p.C2;            // channels of the padding: a zero gradient times any number but these
+  for (int i = t; i < kk * npad * at.pw; i += kBwdThreads) {
+    const int q = i / at.pw, tap = q / npad;
+    sw[(tap * Cp + p.C2 + q - tap * npad) * at.pw + i - q * at.pw] = 0.f;
+  }
+  for (int i = t; i < n_in; i += kBwdThreads) sx[i] = src[i];
+  for (int i = t; i < n1; i += kBwdThreads) sp1[i] = wsp<const float>(d, p.off_p1)[(size_t)r * n1 + i];
+  __syncthreads();
+  const float* dp2 = wsp<const float>(d, p.off_dp2) + (size_t)r * p.F0;
+  const uint8_t* a2 = wsp<const uint8_t>(d, p.off_a2) + (size_t)r * p.F0;
+  const int win2 = p.S2 * p.S2;
+  for (int o = t; o < p.F0; o += kBwdThreads) {
+    const int m = a2[o], co = o / win2, wi = o - co * win2, pi = wi / p.S2, pj = wi - pi * p.S2;
+    // (a dead window contributes 0 x the corner of its inputs)
+    const bool live = m != kDead;
+    const int i = 2 * pi + (live ? m >> 1 : 0), j = 2 * pj + (live ? m & 1 : 0);
+    const float v = live ? dp2[o] : 0.f;
+    g1[o] = make_float2(v, __int_as_float(i * p.S1 + j));
+    if (live) sdc[((i + k - 1) * side + j + k - 1) * at.pc + co] = v;
+  }
+  __syncthreads();
+  // positions (y, x) of the first pooled map x input channels: sum over taps (u, v) and channels of
+  // gradient(y - u, x - v) W(ci, u, v)
+  typedef float f32x4_t __attribute__((ext_vector_type(4)));
+  const int pos = p.S1 * p.S1, mt = (pos + 15) / 16, nt = (p.C1 + 15) / 16;
+  const int lane = t & 63, wave = t >> 6, l15 = lane & 15, l4 = lane >> 4;
+  const uint8_t* a1 = wsp<const uint8_t>(d, p.off_a1) + (size_t)r * n1;
+  for (int item = wave; item < mt * nt; item += kBwdThreads / 64) {
+    const int m0 = item % mt * 16, c0 = item / mt * 16;
+    const int pm = min(m0 + l15, pos - 1);
+    const float* pa = sdc + ((pm / p.S1 + k - 1) * side + pm % p.S1 + k - 1) * at.pc + l4;
+    const float* pb = sw + l4 * at.pw + c0 + l15;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    for (int u = 0; u < k; ++u)
+      for (int c = 0; c < Cp; c += 4) {
+        const float* qa = pa - u * side * at.pc + c;
+        const float* qb = pb + (u * k * Cp + c) * at.pw;
+        if (KS) {
+          // (all reads of a filter row in flight before the first product)
+          float fa[KS ? KS : 1], fb[KS ? KS : 1];
+#pragma unroll
+          for (int v = 0; v < KS; ++v) { fa[v] = qa[-v * at.pc]; fb[v] = qb[v * Cp * at.pw]; }
+#pragma unroll
+          for (int v = 0; v < KS; ++v) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[v], fb[v], acc, 0, 0, 0);
+        } else {
+          for (int v = 0; v < k; ++v) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[-v * at.pc], qb[v * Cp * at.pw], acc, 0, 0, 0);
+        }
+      }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int po = m0 + 4 * l4 + e, ci = c0 + l15;
+      if (po < pos && ci < p.C1) {
+        const int o = ci * pos + po, m = a1[o], pi = po / p.S1, pj = po - pi * p.S1;
+        const bool live = m != kDead;
+        g0[o] = make_float2(live ? acc[e] : 0.f,
+                            __int_as_float((2 * pi + (live ? m >> 1 : 0)) * p.S + 2 * pj + (live ? m & 1 : 0)));
+      }
+    }
+  }
+  conv_wgrad_stage(sp1, p.C1, p.S1, g1, p.C2, win2, k, wsp<float>(d, p.off_grow2) + (size_t)r * (p.C1 * kk * p.C2 + p.C2));
+  __syncthreads();
+  conv_wgrad_stage(sx, p.C0, p.S, g0, p.C1, pos, k, wsp<float>(d, p.off_grow1) + (size_t)r * (p.C0 * kk * p.C1 + p.C1));
+}
+// The same for shapes whose stages do not fit the LDS together: dense shares and losses only.
+__global__ __launch_bounds__(kBwdThreads) void cnn_dense_wgrad_kernel(CnnDev d, RoundDesc rd, LossMailbox* mailbox) {
+  __shared__ __attribute__((aligned(16))) float lds[4 * 1024];
+  if (blockIdx.x == 0) cnn_losses(d, rd, mailbox);
+  dense_wgrad_block(d, rd, blockIdx.x, lds);
 }
 
 // Gradient of the first pooled map of row r: the second convolution's output gradient is non-zero
@@ -413,54 +761,67 @@ __global__ __launch_bounds__(256) void cnn_conv_wgrad_rows_kernel(CnnDev d, int 
   }
 }
 
-// From the rows' and uploads' shares to the stepped model, parameter e per thread:
-//   kPerUpload (blockIdx.y = upload): a convolution parameter's shares of the upload's own rows, added in
-//     row order; with local steps the upload's private model takes the step (Eq. 2; the dense
-//     parameters took theirs in cnn_dense_wgrad_kernel), at U = 1 the sum joins the dense shares in the
-//     upload's slot of G;
-//   kAcrossUploads (U = 1): Eq. 3, w^{t+1} = w^t - the uploads' shares added in arrival order.
-// The first workgroup of kPerUpload / local and of kAcrossUploads turns the row losses into the uploads'
-// mean minibatch losses and, at U = 1, publishes them.
-enum { kPerUpload = 0, kAcrossUploads = 1 };
-__global__ __launch_bounds__(256) void cnn_combine_kernel(CnnDev d, RoundDesc rd, int mode, LossMailbox* mailbox) {
+// Local steps: a convolution parameter's shares of the upload's own rows (blockIdx.y = upload), added in row
+// order; the upload's private model takes the step (Eq. 2; the dense parameters took theirs already).
+__device__ __forceinline__ float conv_rows_sum(const CnnDev& d, size_t e, int a) {
   const CnnPlan& p = d.p;
-  const bool local = d.step >= 0;
-  if (blockIdx.x == 0 && blockIdx.y == 0 && (local || mode == kAcrossUploads)) {
-    const int a = threadIdx.x;
-    if (a < rd.K) {
-      const float* rl = wsp<const float>(d, p.off_rowloss) + (size_t)a * p.B;
-      float sum = 0.f;
-      for (int b = 0; b < p.B; ++b) sum += rl[b];
-      const float mean = sum / (float)p.B;
-      float* lb = wsp<float>(d, p.off_lossbuf) + a;
-      if (!local) *lb = mean;
-      else *lb = (d.step == 0 ? 0.f : *lb) + mean / (float)d.U;       // mean over the job's U steps
-      if (mailbox) mailbox->loss[a] = mean;
-    }
-    if (mailbox) {
-      if (threadIdx.x < ABS_MAX_WORKERS) __threadfence_system();
-      __syncthreads();
-      if (threadIdx.x == 0) mailbox->stamp = rd.stamp;
-    }
-  }
-  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= p.P) return;
-  const int a = blockIdx.y;
+  const int layer = e >= p.w_off[1] ? 1 : 0;
+  const size_t n = (layer ? p.w_off[2] : p.w_off[1]) - p.w_off[layer];
+  const float* G = wsp<const float>(d, layer ? p.off_grow2 : p.off_grow1) + (size_t)a * p.B * n + (e - p.w_off[layer]);
   float sum = 0.f;
-  if (mode == kPerUpload) {
-    if (e >= p.w_off[2]) return;                       // convolution parameters only
-    const int layer = e >= p.w_off[1] ? 1 : 0;
-    const size_t n = (layer ? p.w_off[2] : p.w_off[1]) - p.w_off[layer], idx = e - p.w_off[layer];
-    const float* G = wsp<const float>(d, layer ? p.off_grow2 : p.off_grow1);
-    for (int r = a * p.B; r < (a + 1) * p.B; ++r) sum += G[(size_t)r * n + idx];
-    float* priv = wsp<float>(d, p.off_priv) + (size_t)a * p.slot_stride;
-    priv[e] = local ? slot_of(d, rd, a)[e] - sum : sum;
-  } else {
-    const float* G = wsp<const float>(d, p.off_priv);
-    for (int k = 0; k < rd.K; ++k) sum += G[(size_t)k * p.slot_stride + e];
-    const float* ring = wsp<const float>(d, p.off_ring);
-    wsp<float>(d, p.off_ring)[(size_t)rd.slot_next * p.slot_stride + e] = ring[(size_t)rd.slot_cur * p.slot_stride + e] - sum;
+  int r = 0;
+  for (; r + 8 <= p.B; r += 8) {
+    float v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = G[(size_t)(r + q) * n];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) sum += v[q];
   }
+  for (; r < p.B; ++r) sum += G[(size_t)r * n];
+  return sum;
+}
+__global__ __launch_bounds__(256) void cnn_conv_step_kernel(CnnDev d, RoundDesc rd) {
+  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+  const int a = blockIdx.y;
+  if (e >= d.p.w_off[2]) return;
+  wsp<float>(d, d.p.off_priv)[(size_t)a * d.p.slot_stride + e] = slot_of(d, rd, a)[e] - conv_rows_sum(d, e, a);
+}
+
+// U = 1: Eq. 3, w^{t+1} = w^t - the uploads' shares added in arrival order.  The first conv_blocks workgroups
+// take 32 convolution parameters each, eight groups of 32 threads adding the rows' shares of an upload
+// in row order; the others a dense parameter per thread, its shares in the uploads' slots of G.
+__global__ __launch_bounds__(256) void cnn_combine_kernel(CnnDev d, RoundDesc rd, int conv_blocks) {
+  __shared__ float s_up[ABS_MAX_WORKERS * 32];
+  const CnnPlan& p = d.p;
+  const float* cur = wsp<const float>(d, p.off_ring) + (size_t)rd.slot_cur * p.slot_stride;
+  float* nxt = wsp<float>(d, p.off_ring) + (size_t)rd.slot_next * p.slot_stride;
+  const int t = threadIdx.x;
+  if ((int)blockIdx.x < conv_blocks) {
+    const size_t e = (size_t)blockIdx.x * 32 + (t & 31);
+    const bool ok = e < p.w_off[2];
+    for (int a = t >> 5; a < rd.K; a += 8) s_up[a * 32 + (t & 31)] = ok ? conv_rows_sum(d, e, a) : 0.f;
+    __syncthreads();
+    if (t < 32 && ok) {
+      float sum = 0.f;
+      for (int a = 0; a < rd.K; ++a) sum += s_up[a * 32 + t];
+      nxt[e] = cur[e] - sum;
+    }
+    return;
+  }
+  const size_t e = p.w_off[2] + (size_t)((int)blockIdx.x - conv_blocks) * 256 + t;
+  if (e >= p.P) return;
+  const float* G = wsp<const float>(d, p.off_priv) + e;
+  float sum = 0.f;
+  int a = 0;
+  for (; a + 4 <= rd.K; a += 4) {
+    float v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = G[(size_t)(a + q) * p.slot_stride];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum += v[q];
+  }
+  for (; a < rd.K; ++a) sum += G[(size_t)a * p.slot_stride];
+  nxt[e] = cur[e] - sum;
 }
 
 // Eq. 3 after U local steps: w^{t+1} = w^t - (1/K) sum_a (w^{t - tau_a} - w_a^U), uploads in arrival
@@ -489,9 +850,10 @@ size_t conv_fwd_lds(const CnnPlan& p, int layer) {
   const int Cin = layer ? p.C1 : p.C0, Cout = layer ? p.C2 : p.C1, Sin = layer ? p.S1 : p.S;
   return ((size_t)Cin * Sin * Sin + (size_t)Cin * p.k * p.k * Cout + Cout) * 4;
 }
-size_t dense_lds(const CnnPlan& p) {
-  return (size_t)kGroup * (p.F0 + 2 * p.F1 + 2 * p.F2 + p.C) * 4;
-}
+// (what decides whether a shape is accepted: 8 rows' values of the dense stack)
+size_t dense_lds(const CnnPlan& p) { return (size_t)8 * (p.F0 + 2 * p.F1 + 2 * p.F2 + p.C) * 4; }
+size_t dense_group_lds(const CnnPlan& p, int G) { return ((size_t)G * (p.F0 + 2 * p.F1 + 2 * p.F2 + p.C) + (size_t)kDenseThreads * G) * 4; }
+constexpr size_t kMaxLds = 150 * 1024;
 size_t conv_wgrad_lds(const CnnPlan& p, int layer) {
   const int Cin = layer ? p.C1 : p.C0, Cout = layer ? p.C2 : p.C1, Sin = layer ? p.S1 : p.S, Sp = layer ? p.S2 : p.S1;
   return ((size_t)Cin * Sin * Sin + 2 * (size_t)Cout * Sp * Sp) * 4;
@@ -503,6 +865,16 @@ size_t conv2_bwd_lds(const CnnPlan& p) {
 
 void launch_conv_fwd(const CnnDev& d, const RoundDesc& rd, int rows, hipStream_t s) {
   const CnnPlan& p = d.p;
+  const size_t fused = (size_t)fwd_lds(p).total * 4;
+  if (fused <= kMaxLds) {
+    switch (p.k) {
+      case 3: cnn_fwd_kernel<3><<<dim3(rows), dim3(kFwdThreads), fused, s>>>(d, rd); break;
+      case 5: cnn_fwd_kernel<5><<<dim3(rows), dim3(kFwdThreads), fused, s>>>(d, rd); break;
+      default: cnn_fwd_kernel<0><<<dim3(rows), dim3(kFwdThreads), fused, s>>>(d, rd);
+    }
+    return;
+  }
+  // (both convolutions' filters and maps do not fit the LDS together)
   for (int layer = 0; layer < 2; ++layer) {
     const size_t lds = conv_fwd_lds(p, layer);
     switch (p.k) {
@@ -511,6 +883,22 @@ void launch_conv_fwd(const CnnDev& d, const RoundDesc& rd, int rows, hipStream_t
       default: cnn_conv_pool_fwd_kernel<0><<<dim3(rows), dim3(256), lds, s>>>(d, rd, layer);
     }
   }
+}
+
+// Rows per workgroup of the dense stack: few while there are CUs without a workgroup (160 rows: 23 us one by one,
+// 27 in twos, 34 in fours), more for long launches (every group fetches all dense weights from the L2).
+void launch_dense(const CnnDev& d, const RoundDesc& rd, int uploads, hipStream_t s, float* eval_loss, float* eval_hit) {
+  const CnnPlan& p = d.p;
+  auto groups = [&](int G) { return uploads * ((p.B + G - 1) / G); };
+  const dim3 block(kDenseThreads);
+  if (groups(1) <= 256)
+    cnn_dense_kernel<1><<<dim3(groups(1)), block, dense_group_lds(p, 1), s>>>(d, rd, eval_loss, eval_hit);
+  else if (groups(2) <= 256)
+    cnn_dense_kernel<2><<<dim3(groups(2)), block, dense_group_lds(p, 2), s>>>(d, rd, eval_loss, eval_hit);
+  else if (groups(4) <= 512 || dense_group_lds(p, 8) > kMaxLds)
+    cnn_dense_kernel<4><<<dim3(groups(4)), block, dense_group_lds(p, 4), s>>>(d, rd, eval_loss, eval_hit);
+  else
+    cnn_dense_kernel<8><<<dim3(groups(8)), block, dense_group_lds(p, 8), s>>>(d, rd, eval_loss, eval_hit);
 }
 
 CnnDev dev_of(const CnnArgs& a) {
@@ -598,34 +986,46 @@ hipError_t launch_cnn_round(const CnnArgs& a, const RoundDesc& rd, hipStream_t s
   const double fd = 2.0 * ar * ((double)p.F0 * p.F1 + (double)p.F1 * p.F2 + (double)p.F2 * p.C);
   const double n1 = (double)p.C1 * p.S1 * p.S1;
   const long n_dense = (long)p.F0 * p.F1 + p.F1 + (long)p.F1 * p.F2 + p.F2 + (long)p.F2 * p.C + p.C;
-  const unsigned groups = (unsigned)(rd.K * ((p.B + kGroup - 1) / kGroup));
   for (int step = 0; step < p.U; ++step) {
     d.step = local ? step : -1;
     hook->begin(KK_CNN_CONV_FWD, f1 + f2, ar * 4.0 * (p.C0 * (double)p.S * p.S + 2.0 * n1 + p.F0));
     launch_conv_fwd(d, rd, rows, s);
     hook->end(KK_CNN_CONV_FWD);
     hook->begin(KK_CNN_DENSE, 2.0 * fd, ar * 4.0 * (2.0 * p.F0 + 2.0 * p.F1 + 2.0 * p.F2 + p.C));
-    cnn_dense_kernel<<<dim3(groups), dim3(256), dense_lds(p), s>>>(d, rd, nullptr, nullptr);
+    launch_dense(d, rd, rd.K, s, nullptr, nullptr);
     hook->end(KK_CNN_DENSE);
-    // everything that reads a model comes before the kernels that step a private model in place
-    hook->begin(KK_CNN_CONV_BWD, 2.0 * ar * n1 * kk * p.C2, ar * 4.0 * (p.F0 + n1));
-    switch (p.k) {
-      case 3: cnn_conv2_bwd_kernel<3><<<dim3(rows), dim3(256), conv2_bwd_lds(p), s>>>(d, rd); break;
-      case 5: cnn_conv2_bwd_kernel<5><<<dim3(rows), dim3(256), conv2_bwd_lds(p), s>>>(d, rd); break;
-      default: cnn_conv2_bwd_kernel<0><<<dim3(rows), dim3(256), conv2_bwd_lds(p), s>>>(d, rd);
+    // (a private model is stepped in place only where nothing reads it any more: the dense layers here, which the
+    // convolutions' backward pass does not read, the filters in the launch behind it)
+    const size_t fused = (size_t)bwd_lds(p).total * 4;
+    const unsigned dense_blocks = (unsigned)(rd.K * dense_wgrad_blocks(p));
+    LossMailbox* box = local ? nullptr : a.mailbox;
+    hook->begin(KK_CNN_CONV_BWD, 2.0 * ar * n1 * kk * p.C2 + fd + (f1 + f2) / 4.0,
+                ar * 4.0 * (p.C0 * (double)p.S * p.S + 3.0 * n1 + 3.0 * p.F0 + 2.0 * p.F1 + 2.0 * p.F2 + p.C) + (double)n_dense * 8.0);
+    if (fused <= kMaxLds) {
+      const dim3 grid(rows + dense_blocks), block(kBwdThreads);
+      switch (p.k) {
+        case 3: cnn_bwd_kernel<3><<<grid, block, fused, s>>>(d, rd, rows, box); break;
+        case 5: cnn_bwd_kernel<5><<<grid, block, fused, s>>>(d, rd, rows, box); break;
+        default: cnn_bwd_kernel<0><<<grid, block, fused, s>>>(d, rd, rows, box);
+      }
+    } else {
+      switch (p.k) {
+        case 3: cnn_conv2_bwd_kernel<3><<<dim3(rows), dim3(256), conv2_bwd_lds(p), s>>>(d, rd); break;
+        case 5: cnn_conv2_bwd_kernel<5><<<dim3(rows), dim3(256), conv2_bwd_lds(p), s>>>(d, rd); break;
+        default: cnn_conv2_bwd_kernel<0><<<dim3(rows), dim3(256), conv2_bwd_lds(p), s>>>(d, rd);
+      }
+      cnn_conv_wgrad_rows_kernel<<<dim3(rows), dim3(256), conv_wgrad_lds(p, 1), s>>>(d, 1);
+      cnn_conv_wgrad_rows_kernel<<<dim3(rows), dim3(256), conv_wgrad_lds(p, 0), s>>>(d, 0);
+      cnn_dense_wgrad_kernel<<<dim3(dense_blocks), dim3(kBwdThreads), 0, s>>>(d, rd, box);
     }
     hook->end(KK_CNN_CONV_BWD);
-    hook->begin(KK_CNN_DENSE_WGRAD, fd, (double)n_dense * 8.0 + ar * 4.0 * (p.F0 + 2.0 * p.F1 + 2.0 * p.F2 + p.C));
-    cnn_dense_wgrad_kernel<<<dim3((unsigned)((n_dense + 255) / 256), (unsigned)rd.K), dim3(256), 0, s>>>(d, rd);
-    hook->end(KK_CNN_DENSE_WGRAD);
-    hook->begin(KK_CNN_CONV_WGRAD, (f1 + f2) / 4.0, ar * 4.0 * (p.C0 * (double)p.S * p.S + 2.0 * n1 + p.F0));
-    cnn_conv_wgrad_rows_kernel<<<dim3(rows), dim3(256), conv_wgrad_lds(p, 1), s>>>(d, 1);
-    cnn_conv_wgrad_rows_kernel<<<dim3(rows), dim3(256), conv_wgrad_lds(p, 0), s>>>(d, 0);
-    hook->end(KK_CNN_CONV_WGRAD);
     hook->begin(KK_CNN_COMBINE, (double)p.P * rd.K, 4.0 * (ar * (double)p.w_off[2] + (double)rd.K * n_dense + 2.0 * p.P));
-    cnn_combine_kernel<<<dim3((unsigned)((p.w_off[2] + 255) / 256), (unsigned)rd.K), dim3(256), 0, s>>>(d, rd, kPerUpload, nullptr);
-    if (!local)
-      cnn_combine_kernel<<<dim3((unsigned)((p.P + 255) / 256)), dim3(256), 0, s>>>(d, rd, kAcrossUploads, a.mailbox);
+    if (local) {
+      cnn_conv_step_kernel<<<dim3((unsigned)((p.w_off[2] + 255) / 256), (unsigned)rd.K), dim3(256), 0, s>>>(d, rd);
+    } else {
+      const int conv_blocks = (int)((p.w_off[2] + 31) / 32);
+      cnn_combine_kernel<<<dim3((unsigned)(conv_blocks + (p.P - p.w_off[2] + 255) / 256)), dim3(256), 0, s>>>(d, rd, conv_blocks);
+    }
     hook->end(KK_CNN_COMBINE);
   }
   if (local) {
@@ -648,8 +1048,7 @@ hipError_t launch_cnn_eval(const CnnArgs& a, uint32_t slot, const EvalArgs& e, h
     d.fixed_slot = (int)slot; d.row0 = row0; d.n_rows = n;
     hook->begin(KK_EVAL, 0.0, 4.0 * n * p.C0 * p.S * p.S);
     launch_conv_fwd(d, rd, n, s);
-    cnn_dense_kernel<<<dim3((unsigned)(((n + p.B - 1) / p.B) * ((p.B + kGroup - 1) / kGroup))), dim3(256), dense_lds(p), s>>>(
-        d, rd, e.rowloss, e.correct);
+    launch_dense(d, rd, (n + p.B - 1) / p.B, s, e.rowloss, e.correct);
     hook->end(KK_EVAL);
     err = hipGetLastError();
     if (err == hipSuccess) err = launch_eval_reduce(e, n, s, hook);
@@ -660,14 +1059,15 @@ hipError_t launch_cnn_eval(const CnnArgs& a, uint32_t slot, const EvalArgs& e, h
 hipError_t cnn_prepare() {
   // stages whose LDS need exceeds the default limit must opt in once per process
   static hipError_t done = [] {
-    const void* fns[] = {(const void*)cnn_conv_pool_fwd_kernel<0>, (const void*)cnn_conv_pool_fwd_kernel<3>,
-                         (const void*)cnn_conv_pool_fwd_kernel<5>, (const void*)cnn_dense_kernel,
-                         (const void*)cnn_conv2_bwd_kernel<0>, (const void*)cnn_conv2_bwd_kernel<3>,
-                         (const void*)cnn_conv2_bwd_kernel<5>};
+    const void* fns[] = {(const void*)cnn_fwd_kernel<0>, (const void*)cnn_fwd_kernel<3>, (const void*)cnn_fwd_kernel<5>,
+                         (const void*)cnn_conv_pool_fwd_kernel<0>, (const void*)cnn_conv_pool_fwd_kernel<3>,
+                         (const void*)cnn_conv_pool_fwd_kernel<5>, (const void*)cnn_dense_kernel<1>, (const void*)cnn_dense_kernel<2>, (const void*)cnn_dense_kernel<4>,
+                         (const void*)cnn_dense_kernel<8>, (const void*)cnn_bwd_kernel<0>, (const void*)cnn_bwd_kernel<3>,
+                         (const void*)cnn_bwd_kernel<5>, (const void*)cnn_conv2_bwd_kernel<0>, (const void*)cnn_conv2_bwd_kernel<3>, (const void*)cnn_conv2_bwd_kernel<5>,
+                         (const void*)cnn_conv_wgrad_rows_kernel};
     hipError_t e = hipSuccess;
     for (const void* f : fns)
-      if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)cnn_conv_wgrad_rows_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
+      if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
     return e;
   }();
   return done;

@@ -132,3 +132,21 @@ def test_unsupported_settings_are_refused():
     p = _small(S=15)           # 15 - 3 + 1 = 13 is odd: no 2 x 2 pooling
     with pytest.raises(lib.AbsError):
         lib.abs_workspace_size(lib.make_config(p))
+
+
+@pytest.mark.parametrize("over,T", [
+    (dict(S=12, k=1, C1=18, C2=7, C=3), 8),                        # one tap, two column tiles, channels not a multiple of 4
+    (dict(S=11, k=2, C1=3, C2=6, F1=70, F2=33), 8),                # odd image side
+    (dict(N=6, K0=6, k_mode=1, B=70), 3),                          # 2 rows per workgroup of the dense stack, more than 32 per upload
+    (dict(N=8, K0=8, k_mode=1, B=130), 2),                         # 4 rows
+    (dict(N=16, K0=16, k_mode=1, B=135, M=4000), 2),               # 8 rows
+    (dict(C0=4, S=62, C1=10, C2=8, N=2, K0=1, B=3, M=60, lr=1e-4), 3),            # the backward half does not fit the LDS at once
+    (dict(C0=4, S=62, k=7, C1=14, C2=32, N=2, K0=1, B=3, M=60, lr=1e-4), 3),      # nor do both convolutions
+    (dict(C0=4, S=62, k=7, C1=14, C2=32, N=2, K0=1, B=3, M=60, lr=1e-4, U=2), 2),
+])
+def test_kernel_forms(over, T):
+    """Each form the launches choose by shape: filter sizes, column tiles, rows per workgroup, stages together or apart."""
+    p = _small(**over)
+    res = run_pair(p, T, checkpoints=(1,))
+    assert_trace_equal(res, 1e-4)
+    check_models(res, FP32_TOL, label=p["name"], guard=GUARD)
