@@ -257,6 +257,21 @@ __device__ __forceinline__ void bias_block(const BiasCore& a, int blk, FirstRow 
   }
 }
 
+// Local SGD (Eq. 2): the weight gradient of one step of upload z, W_l of its private model and the two
+// bf16 copies.  The contraction is not split (range z = the rows of upload z), so the accumulators hold
+// the whole gradient and the epilogue takes the step itself: no partial is written and read back, and
+// the update needs no launch (the bias update and the losses ride in this and in the input gradient's launch).
+// Bound by the model's own bytes: 10 (12 with a row-major copy) per weight and upload instead of 22.
+// 3072-512-10, 8 uploads of 10 steps x 128 rows: update kernels 56 us, losses and biases 9 us of a step gone,
+// first layer's product 15.5 -> 28.4 us; a round 1229 -> 711 us.
+// `own`: the model is private copy z of `cur`, else ring slot rd.w[z].slot.
+struct LocalUpdate {
+  int own;
+  const float* cur; float* next; size_t stride;      // fp32 [d_in][d_out] at the layer's place in a model; models `stride` apart
+  uint16_t* wn; size_t ldwn; uint16_t* wt; size_t ldwt; size_t shadow_stride;   // bf16 copies of the private models (wn may be null)
+  int d_in, d_out;
+};
+
 struct GemmArgs {
   const uint16_t* A;  size_t lda;     // [Mdim][lda], k contiguous
   const uint32_t* a_rowidx;           // GATHER: row m of A is A + a_rowidx[m] * lda
@@ -311,9 +326,15 @@ struct GemmArgs {
   // sums are complete before the first weight-gradient launch).
   int bias_blocks;
   BiasCore bias_upd;
-  // EPI_DGRAD with pub_mailbox set: the first workgroup publishes the uploads' mean minibatch losses
-  // (sums of pub_nb row blocks each, left by the output-layer kernel) before it starts on its tile.
+  // (local SGD, TAG 4 / 5: bias_per blocks for each upload, on the upload's own model as local_upd says)
+  int bias_per;
+  LocalUpdate local_upd;
+  // EPI_DGRAD with pub_rowloss set: the first workgroup forms the uploads' mean minibatch losses
+  // (sums of pub_nb row blocks each, left by the output-layer kernel) before it starts on its tile and
+  // publishes them if pub_mailbox is set.  Local SGD: pub_lossacc carries the sum over the job's pub_U
+  // steps, and what the last step publishes is the job's average local loss.
   LossMailbox* pub_mailbox; const float* pub_rowloss; int pub_nb; int pub_B;
+  float* pub_lossacc; int pub_first, pub_U;
 };
 
 // Dataset row of stacked row m (and whether it carries a sample).
@@ -334,17 +355,35 @@ __device__ __forceinline__ void gen_row_store(const GemmArgs& g, int m, uint32_t
 // mailbox, then the stamp: thread a < K adds the loss sums of upload a's row blocks in order.  Every
 // wavefront that wrote fences at system scope before the barrier, so the host that sees the stamp
 // sees the losses.  Whole workgroup, uniform call.
-__device__ __forceinline__ void publish_upload_losses(LossMailbox* box, const float* rowloss, int nb, int B,
-                                                      int K, uint32_t stamp) {
+__device__ __forceinline__ void publish_upload_losses(const GemmArgs& g, int K, uint32_t stamp) {
   const int up = threadIdx.x;
   if (up < K) {
     float sum = 0.f;
-    for (int q = 0; q < nb; ++q) sum += rowloss[(size_t)up * nb + q];
-    box->loss[up] = sum / (float)B;
+    for (int q = 0; q < g.pub_nb; ++q) sum += g.pub_rowloss[(size_t)up * g.pub_nb + q];
+    float mean = sum / (float)g.pub_B;
+    if (g.pub_lossacc) {
+      if (!g.pub_first) mean += g.pub_lossacc[up];
+      g.pub_lossacc[up] = mean;
+      mean /= (float)g.pub_U;
+    }
+    if (g.pub_mailbox) g.pub_mailbox->loss[up] = mean;
   }
+  if (!g.pub_mailbox) return;
   if (threadIdx.x < ABS_MAX_WORKERS) __threadfence_system();
   __syncthreads();
-  if (threadIdx.x == 0) box->stamp = stamp;
+  if (threadIdx.x == 0) g.pub_mailbox->stamp = stamp;
+}
+
+// Block b of the bias blocks at the end of a weight-gradient launch: 16 bias entries, of the global model
+// or (LOCAL) of upload b / bias_per's private one, over the row blocks of that upload.
+template <bool LOCAL>
+__device__ __forceinline__ void rider_bias(const GemmArgs& g, const RoundDesc& rd, int b, float* lds) {
+  const BiasCore& u = g.bias_upd;
+  if (!LOCAL) { bias_block(u, b, [](int) { return 0; }, u.w_cur, u.w_next, lds); return; }
+  const int up = b / g.bias_per;
+  const size_t from = g.local_upd.own ? (size_t)up : (size_t)rd.w[up].slot;
+  bias_block(u, b - up * g.bias_per, [&](int l) { return up * u.prow[l]; }, u.w_cur + from * g.local_upd.stride,
+             u.w_next + (size_t)up * g.local_upd.stride, lds);
 }
 
 // A piggybacked update block (see GemmArgs::pig_blocks): block b of the other layer's matrix, 64 rows
@@ -424,7 +463,8 @@ template <int T, int EPI, bool GATHER, bool PER_UPLOAD, int TAG, int RING>
 __global__ __launch_bounds__(TileCfg<T>::NT, 2) void mlp_tile_kernel(GemmArgs g, RoundDesc rd) {
   using Cfg = TileCfg<T>;
   constexpr int NW = Cfg::NW, NT = Cfg::NT, KG = Cfg::KG, OWN = Cfg::OWN;
-  constexpr bool kStageT = (EPI == EPI_RELU || EPI == EPI_DGRAD);
+  constexpr bool kLocal = EPI == EPI_WGRAD && TAG >= 4;  // local SGD: the epilogue takes the step (LocalUpdate)
+  constexpr bool kStageT = (EPI == EPI_RELU || EPI == EPI_DGRAD || kLocal);
   constexpr int kEpi = Cfg::kRed + (kStageT ? Cfg::kOut : 0);
   constexpr int kSmem = RING * Cfg::kStage > kEpi ? RING * Cfg::kStage : kEpi;
   static_assert(kSmem * 2 <= 160 * 1024 - 1024, "LDS budget");
@@ -441,7 +481,7 @@ __global__ __launch_bounds__(TileCfg<T>::NT, 2) void mlp_tile_kernel(GemmArgs g,
     // down: 260 -> 400 us for the hidden layer's product at K = 128.)  Behind them the bias blocks.
     const int own = (int)gridDim.x - g.pig_blocks - g.bias_blocks;
     if (bx >= own + g.pig_blocks) {
-      bias_block(g.bias_upd, bx - own - g.pig_blocks, [](int) { return 0; }, g.bias_upd.w_cur, g.bias_upd.w_next, (float*)smem);
+      rider_bias<kLocal>(g, rd, bx - own - g.pig_blocks, (float*)smem);
       return;
     }
     if (bx >= own) { piggy_update<NT, false>(g, bx - own, smem); return; }
@@ -459,8 +499,7 @@ __global__ __launch_bounds__(TileCfg<T>::NT, 2) void mlp_tile_kernel(GemmArgs g,
   const int ks0 = zsplit * g.ksteps_per_split;
   const int ks1 = min(g.ksteps_total, ks0 + g.ksteps_per_split);
 
-  if (EPI == EPI_DGRAD && g.pub_mailbox && blockIdx.x == 0)
-    publish_upload_losses(g.pub_mailbox, g.pub_rowloss, g.pub_nb, g.pub_B, rd.K, rd.stamp);
+  if (EPI == EPI_DGRAD && g.pub_rowloss && blockIdx.x == 0) publish_upload_losses(g, rd.K, rd.stamp);
 
   const uint16_t* Bt = g.Bt;
   uint32_t slot = 0;
@@ -593,10 +632,26 @@ __global__ __launch_bounds__(TileCfg<T>::NT, 2) void mlp_tile_kernel(GemmArgs g,
   const float* bias = nullptr;
   if (EPI == EPI_RELU || EPI == EPI_LOGITS) bias = g.bias + (size_t)slot * g.bias_slot_stride;
   float* outf = g.outf;
-  if (EPI == EPI_WGRAD) outf += (size_t)zsplit * g.split_stride;
+  if (EPI == EPI_WGRAD && !kLocal) outf += (size_t)zsplit * g.split_stride;
+  const LocalUpdate& lu = g.local_upd;
+  const float* lcur = nullptr; float* lnext = nullptr;
+  if (kLocal) {
+    lcur = lu.cur + (size_t)(lu.own ? (uint32_t)zsplit : rd.w[zsplit].slot) * lu.stride;
+    lnext = lu.next + (size_t)zsplit * lu.stride;
+  }
+  const bool row_major = kLocal ? lu.wn != nullptr : g.out != nullptr;
 #pragma unroll
   for (int j = 0; j < OWN; ++j) {
     const int b = kg * OWN + j;
+    float wv[kLocal ? 16 : 1];             // the block's 16 model elements of this lane, asked for together
+    if (kLocal) {
+      const int i0 = m0 + wm * 64 + (b >> 1) * 32 + lrow4, jn = n0 + wn * 64 + (b & 1) * 32 + lcol;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int i = i0 + (r >> 2) * 8 + (r & 3);
+        wv[r] = i < lu.d_in && jn < lu.d_out ? lcur[(size_t)i * lu.d_out + jn] : 0.f;
+      }
+    }
     const float4* q = (const float4*)(red + (wsub * 4 + b) * (KG - 1) * 1024) + lane;
 #pragma unroll
     for (int o = 0; o < KG - 1; ++o)
@@ -625,13 +680,18 @@ __global__ __launch_bounds__(TileCfg<T>::NT, 2) void mlp_tile_kernel(GemmArgs g,
         } else if (EPI == EPI_DGRAD) {
           const uint32_t pair = rr < 2 ? hm.x : hm.y;
           v = ((pair >> ((rr & 1) * 16)) & 0x7FFFu) ? v : 0.f;
+        } else if (kLocal) {
+          const int i = m0 + ml + rr;
+          const bool ok = i < lu.d_in && n < lu.d_out;      // padding stays zero in both copies
+          v = ok ? wv[rg * 4 + rr] - v : 0.f;
+          if (ok) lnext[(size_t)i * lu.d_out + n] = v;
         } else {
           outf[(size_t)(m0 + ml + rr) * g.ldof + n] = v;
         }
         if (kStageT) {
           h[rr] = f32_to_bf16(v);
           if (EPI == EPI_DGRAD) cs += __uint_as_float((uint32_t)h[rr] << 16);
-          if (g.out) sN[(ml + rr) * Cfg::kPitch + nl] = h[rr];
+          if (row_major) sN[(ml + rr) * Cfg::kPitch + nl] = h[rr];
         }
       }
       if (kStageT) {
@@ -647,7 +707,23 @@ __global__ __launch_bounds__(TileCfg<T>::NT, 2) void mlp_tile_kernel(GemmArgs g,
       if (lane < 32) sC[(bm >> 5) * T + nl] = cs;
     }
   }
-  if (kStageT) {
+  if (kLocal) {
+    __syncthreads();
+    uint16_t* const wt = lu.wt + (size_t)zsplit * lu.shadow_stride;
+#pragma unroll
+    for (int i = 0; i < T * T / 8 / NT; ++i) {
+      const int q = t + NT * i, nl = q / (T / 8), ch = (q % (T / 8)) * 8;
+      if (n0 + nl < lu.d_out) *(uint4*)(wt + (size_t)(n0 + nl) * lu.ldwt + m0 + ch) = *(const uint4*)&sT[nl * Cfg::kPitch + ch];
+    }
+    if (row_major) {
+      uint16_t* const wr = lu.wn + (size_t)zsplit * lu.shadow_stride;
+#pragma unroll
+      for (int i = 0; i < T * T / 8 / NT; ++i) {
+        const int q = t + NT * i, ml = q / (T / 8), ch = (q % (T / 8)) * 8;
+        if (m0 + ml < lu.d_in) *(uint4*)(wr + (size_t)(m0 + ml) * lu.ldwn + n0 + ch) = *(const uint4*)&sN[ml * Cfg::kPitch + ch];
+      }
+    }
+  } else if (kStageT) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < T * T / 8 / NT; ++i) {
@@ -700,7 +776,9 @@ __global__ __launch_bounds__(512, 1) void mlp_gemm256_kernel(GemmArgs g, RoundDe
   // TAG 3 (forward / input gradient of a hidden layer): the A operand is the TRANSPOSED copy of the
   // activations / output gradients, [k = features][m = stacked rows], read the same way - the layer
   // that produced it then writes no row-major copy at all.
-  constexpr bool kATR = (EPI == EPI_WGRAD && TAG == 2) || ((EPI == EPI_RELU || EPI == EPI_DGRAD) && TAG == 3);
+  // TAG 4 / 5 (weight gradients of local SGD): TAG 2 / 0 whose epilogue takes the step (LocalUpdate).
+  constexpr bool kLocal = EPI == EPI_WGRAD && TAG >= 4;
+  constexpr bool kATR = (EPI == EPI_WGRAD && (TAG == 2 || TAG == 4)) || ((EPI == EPI_RELU || EPI == EPI_DGRAD) && TAG == 3);
   constexpr bool kARows = kATR && EPI == EPI_WGRAD;      // the k rows of A are gathered through a_rowidx
   __shared__ __attribute__((aligned(16))) uint16_t smem[kSmem3];
 
@@ -713,7 +791,7 @@ __global__ __launch_bounds__(512, 1) void mlp_gemm256_kernel(GemmArgs g, RoundDe
     // down: 260 -> 400 us for the hidden layer's product at K = 128.)  Behind them the bias blocks.
     const int own = (int)gridDim.x - g.pig_blocks - g.bias_blocks;
     if (bx >= own + g.pig_blocks) {
-      bias_block(g.bias_upd, bx - own - g.pig_blocks, [](int) { return 0; }, g.bias_upd.w_cur, g.bias_upd.w_next, (float*)smem);
+      rider_bias<kLocal>(g, rd, bx - own - g.pig_blocks, (float*)smem);
       return;
     }
     if (bx >= own) { piggy_update<512, true>(g, bx - own, smem); return; }
@@ -743,8 +821,7 @@ __global__ __launch_bounds__(512, 1) void mlp_gemm256_kernel(GemmArgs g, RoundDe
     ks1 = min(g.ksteps_total, ks0 + g.ksteps_per_split);
   }
 
-  if (EPI == EPI_DGRAD && g.pub_mailbox && blockIdx.x == 0)
-    publish_upload_losses(g.pub_mailbox, g.pub_rowloss, g.pub_nb, g.pub_B, rd.K, rd.stamp);
+  if (EPI == EPI_DGRAD && g.pub_rowloss && blockIdx.x == 0) publish_upload_losses(g, rd.K, rd.stamp);
 
   for (;;) {       // one pass per piece of the run (a single pass without runs)
   if (kRuns) {
@@ -944,6 +1021,61 @@ __global__ __launch_bounds__(512, 1) void mlp_gemm256_kernel(GemmArgs g, RoundDe
   // bytes per row.  The ReLU mask of the tile is one bit per element in accumulator order:
   // word a / 2 of a lane, bit (a & 1) 16 + 4 b + r for block (a, b), register r.
   const int lcol = lane & 15, lrow4 = (lane >> 4) * 4;
+  if constexpr (kLocal) {
+    // half of the wavefront's tile at a time: the 64 model elements of a lane are asked for together
+    // (they may be where the results go, so the compiler cannot move them ahead of a store)
+    const LocalUpdate& lu = g.local_upd;
+    const float* const cur = lu.cur + (size_t)(lu.own ? (uint32_t)zsplit : rd.w[zsplit].slot) * lu.stride;
+    float* const next = lu.next + (size_t)zsplit * lu.stride;
+    uint16_t* const wt = lu.wt + (size_t)zsplit * lu.shadow_stride;
+    uint16_t* const wr = lu.wn ? lu.wn + (size_t)zsplit * lu.shadow_stride : nullptr;
+    uint16_t* const sT = smem + wave * (2 * 64 * kEpiPitch3);     // [64 n][72]
+    uint16_t* const sN = sT + 64 * kEpiPitch3;                    // [64 m][72]
+    const int ncol = n0 + wn * 64;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int mrow = m0 + wm * 128 + half * 64;
+      float wv[4][4][4];
+#pragma unroll
+      for (int ah = 0; ah < 4; ++ah)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const int i = mrow + ah * 16 + lrow4 + rr, n = ncol + b * 16 + lcol;
+            wv[ah][b][rr] = i < lu.d_in && n < lu.d_out ? cur[(size_t)i * lu.d_out + n] : 0.f;
+          }
+#pragma unroll
+      for (int ah = 0; ah < 4; ++ah) {
+        const int ml = ah * 16 + lrow4;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const int nl = b * 16 + lcol, n = ncol + nl;
+          uint16_t h[4];
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr) {
+            const int i = mrow + ml + rr;
+            const bool ok = i < lu.d_in && n < lu.d_out;         // padding stays zero in both copies
+            const float v = ok ? wv[ah][b][rr] - acc[half * 4 + ah][b][rr] : 0.f;
+            if (ok) next[(size_t)i * lu.d_out + n] = v;
+            h[rr] = f32_to_bf16(v);
+            if (wr) sN[(ml + rr) * kEpiPitch3 + nl] = h[rr];
+          }
+          uint2 o;
+          o.x = h[0] | ((uint32_t)h[1] << 16);
+          o.y = h[2] | ((uint32_t)h[3] << 16);
+          *(uint2*)&sT[nl * kEpiPitch3 + ml] = o;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int q = lane + 64 * i, r = q >> 3, ch = (q & 7) * 8;
+        if (ncol + r < lu.d_out) *(uint4*)(wt + (size_t)(ncol + r) * lu.ldwt + mrow + ch) = *(const uint4*)&sT[r * kEpiPitch3 + ch];
+        if (wr && mrow + r < lu.d_in) *(uint4*)(wr + (size_t)(mrow + r) * lu.ldwn + ncol + ch) = *(const uint4*)&sN[r * kEpiPitch3 + ch];
+      }
+    }
+    break;
+  }
   if constexpr (EPI == EPI_WGRAD || EPI == EPI_LOGITS) {
     // fp32 results straight from the accumulators (64 contiguous bytes per row and quarter-wavefront):
     // this piece's partial of the tile, or the logits with their bias
@@ -1285,35 +1417,19 @@ __global__ __launch_bounds__(256, 1) void mlp_logits_ce_kernel(LogitsCeArgs a, R
 }
 
 // ------------------------------------------------------------------ update + snapshot
-// The update as a kernel of its own (a TileUpdate for a whole matrix): local SGD, the averaged change of
-// the uploads, matrices whose rows are not 16-byte aligned, a round's last layer, the bf16 copies of w^0.
-struct UpdateArgs : TileUpdate {
-  // batched form (local SGD): blockIdx.z = upload a; partial a, nsplit = 1, the model read from
-  // slot cur_index[a] of w_cur's ring and written to slot a of w_next's ring / shadow ring
-  int batched;
-  size_t cur_stride, next_stride, shadow_stride;
-  uint16_t cur_index[ABS_MAX_WORKERS];
-};
-__device__ __forceinline__ void update_select_upload(UpdateArgs& u) {
-  if (!u.batched) return;
-  const int a = blockIdx.z;
-  u.partial += (size_t)a * u.split_stride;
-  u.w_cur += (size_t)u.cur_index[a] * u.cur_stride;
-  u.w_next += (size_t)a * u.next_stride;
-  if (u.wn) u.wn += (size_t)a * u.shadow_stride;
-  u.wt += (size_t)a * u.shadow_stride;
-}
+// The update as a kernel of its own (a TileUpdate for a whole matrix): the averaged change of the uploads
+// of local SGD, matrices whose rows are not 16-byte aligned, a round's last layer, the bf16 copies of w^0.
+// (With a per-upload form that moved its argument's pointers the whole argument lived in scratch memory: a
+// 512 x 10 layer 7.5 us instead of 3.3.)
 template <int TJ>
-__global__ __launch_bounds__(256) void mlp_update_kernel(UpdateArgs u) {
+__global__ __launch_bounds__(256) void mlp_update_kernel(TileUpdate u) {
   __shared__ __attribute__((aligned(16))) uint16_t tile[64 * (TJ + 2)];
-  update_select_upload(u);
   update_block64<256, TJ>(u, blockIdx.y * 64, blockIdx.x * TJ, tile);
 }
 
 // Element-wise version for narrow or odd output widths (e.g. the 10-class output layer):
 // one thread per weight, four partial loads in flight.
-__global__ __launch_bounds__(256) void mlp_update_small_kernel(UpdateArgs u) {
-  update_select_upload(u);
+__global__ __launch_bounds__(256) void mlp_update_small_kernel(TileUpdate u) {
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= u.d_in * u.d_out) return;
   const int i = e / u.d_out, j = e - i * u.d_out;
@@ -1333,43 +1449,6 @@ __global__ __launch_bounds__(256) void mlp_update_small_kernel(UpdateArgs u) {
   const uint16_t h = f32_to_bf16(wnew);
   if (u.wn) u.wn[(size_t)i * u.ldwn + j] = h;
   u.wt[(size_t)j * u.ldwt + i] = h;
-}
-
-// The bias update as a launch of its own.  Global form: all `prow[l]` blocks, model w_cur -> w_next.
-// Per-upload form (local SGD, blockIdx.y = upload a): the blocks of a's own rows, model slot
-// cur_index[a] of w_cur -> slot a of w_next.
-struct BiasArgs : BiasCore {
-  int batched;
-  size_t cur_stride, next_stride;
-  uint16_t cur_index[ABS_MAX_WORKERS];
-};
-__global__ __launch_bounds__(256) void mlp_bias_kernel(BiasArgs a) {
-  __shared__ float s_part[16 * 17];
-  const int up = blockIdx.y;
-  const float* cur = a.w_cur + (a.batched ? (size_t)a.cur_index[up] * a.cur_stride : 0);
-  float* nxt = a.w_next + (a.batched ? (size_t)up * a.next_stride : 0);
-  bias_block(a, blockIdx.x, [&](int l) { return a.batched ? up * a.prow[l] : 0; }, cur, nxt, s_part);
-}
-
-// Local SGD: the uploads' mean minibatch losses of one local step, one thread per upload over the
-// loss sums of its `nb` row blocks; lossacc carries the sum over the job's steps and the last step
-// publishes the job's average local loss (worker part of Algorithm 1).  (With U = 1 the first
-// workgroup of the input-gradient kernel publishes: publish_upload_losses.)
-__global__ __launch_bounds__(128) void mlp_loss_kernel(const float* rowloss, int B, int nb, int K, uint32_t stamp,
-                                                       LossMailbox* mailbox, float* lossacc, int first, int last,
-                                                       int U) {
-  __shared__ float s_loss[ABS_MAX_WORKERS];
-  const int up = threadIdx.x;
-  if (up < K) {
-    float s = 0.f;
-    for (int q = 0; q < nb; ++q) s += rowloss[(size_t)up * nb + q];
-    s /= (float)B;
-    s += first ? 0.f : lossacc[up];
-    lossacc[up] = s;
-    s_loss[up] = s / (float)U;
-  }
-  __syncthreads();
-  if (last) publish_losses(mailbox, s_loss, K, stamp);
 }
 
 // ------------------------------------------------------------------ local SGD helpers
@@ -1585,10 +1664,9 @@ struct NullHook : LaunchHook {
 
 // The three uses of the update kernels:
 //   UPD_GLOBAL  w^{t+1} = w^t - sum of the split partials                    (U = 1, Eq. 3)
-//   UPD_LOCAL   private model of upload a <- its model - its own partial     (Eq. 2, step u)
 //   UPD_DELTA   w^{t+1} = w^t - D, D = the averaged change of the uploads    (U > 1, Eq. 3)
 // each also writes the bf16 copies of what it produced.
-enum { UPD_GLOBAL = 0, UPD_LOCAL = 1, UPD_DELTA = 2 };
+enum { UPD_GLOBAL = 0, UPD_DELTA = 1 };
 // Weight gradient of layer l over `rows` stacked rows on the 256 x 256 tile kernel: k-steps per run if
 // the contraction should be cut into equal runs across the tiles (GemmArgs::sk_q), else 0.  Runs pay
 // when equal row ranges per tile leave a good part of the CUs idle in the launch's last wave and a
@@ -1631,34 +1709,16 @@ TileUpdate global_update_args(const MlpArgs& a, int l, const RoundDesc& rd, int 
 // Whether the rows of layer l's fp32 weight matrix can be moved 16 bytes at a time.
 bool update_rows_aligned(const MlpPlan& p, int l) { return p.d[l + 1] % 4 == 0 && p.w_off[l] % 4 == 0; }
 
-void launch_update(const MlpArgs& a, int l, const RoundDesc& rd, int mode, int step, int nsplit,
+void launch_update(const MlpArgs& a, int l, const RoundDesc& rd, int mode, int nsplit,
                    hipStream_t s, LaunchHook* hook, int run_q = 0, int run_ksteps = 0) {
   const MlpPlan& p = a.plan;
   float* ring = at<float>(a, p.off_ring);
-  UpdateArgs u{};
+  TileUpdate u{};
   u.d_in = p.d[l];
   u.d_out = p.d[l + 1];
   u.ldwn = (size_t)p.ld[l + 1];
   u.ldwt = (size_t)p.ld[l];
-  int batch = 1;
-  if (mode == UPD_LOCAL) {
-    float* priv = at<float>(a, p.off_priv);
-    uint16_t* pshadow = at<uint16_t>(a, p.off_priv_shadow);
-    u.batched = 1;
-    batch = rd.K;
-    u.partial = at<float>(a, p.off_partial[l]);
-    u.split_stride = (size_t)p.dp[l] * (p.dp[l + 1] + kPartialPad);
-    u.ldp = (size_t)p.dp[l + 1] + kPartialPad;
-    u.nsplit = 1;
-    u.w_cur = (step == 0 ? ring : priv) + p.w_off[l];
-    u.cur_stride = p.slot_stride;
-    for (int k = 0; k < rd.K; ++k) u.cur_index[k] = (uint16_t)(step == 0 ? rd.w[k].slot : (uint32_t)k);
-    u.w_next = priv + p.w_off[l];
-    u.next_stride = p.slot_stride;
-    u.wn = l >= 1 ? pshadow + p.wn_off[l] : nullptr;
-    u.wt = pshadow + p.wt_off[l];
-    u.shadow_stride = p.shadow_stride;
-  } else {
+  {
     uint16_t* shadow = at<uint16_t>(a, p.off_shadow) + (size_t)rd.slot_next * p.shadow_stride;
     if (mode == UPD_GLOBAL) {
       u.partial = at<float>(a, p.off_partial[l]);
@@ -1677,16 +1737,16 @@ void launch_update(const MlpArgs& a, int l, const RoundDesc& rd, int mode, int s
     u.wt = shadow + p.wt_off[l];
   }
   if (run_q) { u.sk_q = run_q; u.sk_ksteps = run_ksteps; u.sk_nt = p.dp[l + 1] / TN3; }
-  const double n = (double)p.d[l] * p.d[l + 1] * batch;
+  const double n = (double)p.d[l] * p.d[l + 1];
   kbegin(hook, KK_MLP_UPDATE, n * (u.nsplit + 1), n * (4.0 * (u.nsplit + 2) + (l >= 1 ? 4.0 : 2.0)));
   const dim3 block(256);
   const bool vec = update_rows_aligned(p, l);
   // wide tiles (fewer, longer stores) only where they still give every CU a workgroup
-  const bool wide = p.d[l + 1] >= 256 && ((p.d[l + 1] + 255) / 256) * ((p.d[l] + 63) / 64) * batch >= 256;
+  const bool wide = p.d[l + 1] >= 256 && ((p.d[l + 1] + 255) / 256) * ((p.d[l] + 63) / 64) >= 256;
   plan_note("update", 64, vec && wide ? 256 : vec ? 64 : 1, u.nsplit);
-  if (vec && wide) ABS_LAUNCH_K((mlp_update_kernel<256>), dim3((p.d[l + 1] + 255) / 256, (p.d[l] + 63) / 64, batch), block, s, u);
-  else if (vec) ABS_LAUNCH_K((mlp_update_kernel<64>), dim3((p.d[l + 1] + 63) / 64, (p.d[l] + 63) / 64, batch), block, s, u);
-  else     ABS_LAUNCH_K(mlp_update_small_kernel, dim3((p.d[l] * p.d[l + 1] + 255) / 256, 1, batch), block, s, u);
+  if (vec && wide) ABS_LAUNCH_K((mlp_update_kernel<256>), dim3((p.d[l + 1] + 255) / 256, (p.d[l] + 63) / 64), block, s, u);
+  else if (vec) ABS_LAUNCH_K((mlp_update_kernel<64>), dim3((p.d[l + 1] + 63) / 64, (p.d[l] + 63) / 64), block, s, u);
+  else     ABS_LAUNCH_K(mlp_update_small_kernel, dim3((p.d[l] * p.d[l + 1] + 255) / 256), block, s, u);
   kend(hook, KK_MLP_UPDATE);
 }
 
@@ -1725,7 +1785,7 @@ bool launch_gemm(GemmArgs g, const RoundDesc& rd, int Mdim, int Ndim, int nsplit
     g.stream_out = (EPI == EPI_RELU || EPI == EPI_DGRAD) && !GATHER && g.ksteps_total >= 16 &&
                    (size_t)Mdim * (size_t)Ndim * 2 >= ABS_STREAM_MIN_BYTES;
     plan_note(EPI == EPI_RELU ? (TAG == 3 ? "fwd_t" : "fwd") : EPI == EPI_LOGITS ? "logits" : EPI == EPI_DGRAD ? (TAG == 3 ? "dgrad_t" : "dgrad")
-              : TAG == 2 ? "wgrad_x" : "wgrad", TM3, TN3, nsplit);
+              : TAG == 4 ? "wgrad_x_step" : TAG == 5 ? "wgrad_step" : TAG == 2 ? "wgrad_x" : "wgrad", TM3, TN3, nsplit);
     ABS_LAUNCH_K((mlp_gemm256_kernel<EPI, GATHER, PER_UPLOAD, TAG>), dim3(8 * g.rows_per_xcd * g.nt + g.pig_blocks + g.bias_blocks), dim3(512), s, g, rd);
     return true;
   }
@@ -1740,7 +1800,7 @@ bool launch_gemm(GemmArgs g, const RoundDesc& rd, int Mdim, int Ndim, int nsplit
   g.nt = Ndim / tile;
   g.rows_per_xcd = (g.mt * nsplit + 7) / 8;
   const dim3 grid(8 * g.rows_per_xcd * g.nt + g.pig_blocks + g.bias_blocks);
-  plan_note(EPI == EPI_RELU ? "fwd_tile" : EPI == EPI_LOGITS ? "logits_tile" : EPI == EPI_DGRAD ? "dgrad_tile" : "wgrad_tile", tile, tile, nsplit);
+  plan_note(EPI == EPI_RELU ? "fwd_tile" : EPI == EPI_LOGITS ? "logits_tile" : EPI == EPI_DGRAD ? "dgrad_tile" : TAG >= 4 ? "wgrad_step_tile" : "wgrad_tile", tile, tile, nsplit);
   // Ring depths: forward and input-gradient products keep three steps on their way (64-wide: 64 KB, two
   // workgroups per CU; 8 steps and one workgroup: the evaluation's logits 22.5 instead of 16.8 us; 3 steps: cfg 3's
   // first layer 22.4 instead of 18.4).  A weight gradient carries the previous layer's update as extra
@@ -1868,7 +1928,7 @@ hipError_t mlp_prepare(const MlpArgs& a, hipStream_t s) {
                                                           (size_t)p.N * p.shadow_stride * 2 / 16);
   NullHook nh;
   RoundDesc rd0{};                       // slot_cur = slot_next = 0, no partials: w^0 onto itself
-  for (int l = 0; l < p.L; ++l) launch_update(a, l, rd0, UPD_GLOBAL, 0, 0, s, &nh);   // bf16 copies of w^0
+  for (int l = 0; l < p.L; ++l) launch_update(a, l, rd0, UPD_GLOBAL, 0, s, &nh);   // bf16 copies of w^0
   return hipGetLastError();
 }
 
@@ -1907,12 +1967,6 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
     // ---- output layer: loss and output gradient, already scaled by the uploads' coefficients
     launch_logits_ce(a, rd, rows, arows, wbase, sbase, own, s, hook);
     const int loss_blocks = p.Bp / kCeRows;          // row blocks of the loss sums per upload
-    if (local) {
-      kbegin(hook, KK_MLP_LOSS, arows, arows * 4.0);
-      ABS_LAUNCH_K(mlp_loss_kernel, dim3(1), dim3(128), s, at<float>(a, p.off_rowloss), p.B, loss_blocks, K, rd.stamp,
-                   a.mailbox, at<float>(a, p.off_lossacc), (int)(step == 0), (int)(step == U - 1), U);
-      kend(hook, KK_MLP_LOSS);
-    }
 
     // ---- input gradients back through W_{L-1} .. W_1 (none is needed for the first layer)
     // (dZ_l likewise: read row-major only by the next product down; when writer and reader both run on
@@ -1932,11 +1986,13 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
       g.out = l >= 2 ? at<uint16_t>(a, p.off_dz[l]) : nullptr; g.ldo = (size_t)p.ld[l];
       g.outT = at<uint16_t>(a, p.off_dzt[l]); g.ldoT = p.ldm;
       g.colsum = at<float>(a, p.off_colsum[l]); g.ldcs = (size_t)p.dp[l];
-      if (!local && l == L - 1) {
+      if (l == L - 1) {
         // the losses reach the host as the backward pass starts: it selects and enqueues the next
         // round while the device is still in this one
-        g.pub_mailbox = a.mailbox; g.pub_rowloss = at<float>(a, p.off_rowloss);
+        // (local SGD: every step adds its losses, the job's last one publishes)
+        g.pub_mailbox = step == U - 1 ? a.mailbox : nullptr; g.pub_rowloss = at<float>(a, p.off_rowloss);
         g.pub_nb = loss_blocks; g.pub_B = p.B;
+        if (local) { g.pub_lossacc = at<float>(a, p.off_lossacc); g.pub_first = step == 0; g.pub_U = U; }
       }
       // the product through the output layer contracts over the classes only: bandwidth-bound
       const int kind = l == L - 1 ? KK_MLP_DGRAD_OUT : KK_MLP_DGRAD;
@@ -1983,14 +2039,15 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
       bias.prow[l] = (local ? p.Bp : rows) / (l == L - 1 ? kCeRows : 64);
     }
     bias.col_begin[L] = bias_cols;
-    bias.w_cur = ring + (size_t)rd.slot_cur * p.slot_stride;
-    bias.w_next = ring + (size_t)rd.slot_next * p.slot_stride;
+    bias.w_cur = local ? wbase : ring + (size_t)rd.slot_cur * p.slot_stride;
+    bias.w_next = local ? priv : ring + (size_t)rd.slot_next * p.slot_stride;
     int pend = -1, pend_split = 0, pend_q = 0;   // layer whose partials are complete and whose update is still due (its splits or run length)
     for (int li = 0; li < L; ++li) {
       const int l = local ? L - 1 - li : li;
       GemmArgs g{};
-      if (!local && li == L - 1) {
-        g.bias_blocks = (bias_cols + 15) / 16;
+      if (li == L - 1) {
+        g.bias_per = (bias_cols + 15) / 16;
+        g.bias_blocks = g.bias_per * (local ? K : 1);
         g.bias_upd = bias;
         plan_note("with_biases", 16, 1, 1);
       }
@@ -2019,9 +2076,19 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
       }
       const int kind = l == 0 ? KK_MLP_WGRAD_L1 : l == L - 1 ? KK_MLP_WGRAD_OUT : KK_MLP_WGRAD;
       kbegin(hook, kind, 2.0 * arows * p.d[l] * p.d[l + 1],
-             arows * (p.d[l] + p.d[l + 1]) * 2.0 + (double)nsplit * p.d[l] * p.d[l + 1] * 4.0 + upd_bytes);
-      if (l == 0 && wg0_direct) {
-        g.A = a.X; g.lda = (size_t)p.d[0]; g.a_rowidx = rowidx;
+             arows * (p.d[l] + p.d[l + 1]) * 2.0 +
+                 (double)nsplit * p.d[l] * p.d[l + 1] * (local ? l >= 1 ? 12.0 : 10.0 : 4.0) + upd_bytes);
+      if (l == 0 && wg0_direct) { g.A = a.X; g.lda = (size_t)p.d[0]; g.a_rowidx = rowidx; }
+      if (local) {
+        LocalUpdate& lu = g.local_upd;
+        uint16_t* pw = at<uint16_t>(a, p.off_priv_shadow);
+        lu.own = own; lu.cur = wbase + p.w_off[l]; lu.next = priv + p.w_off[l]; lu.stride = p.slot_stride;
+        lu.wn = l >= 1 ? pw + p.wn_off[l] : nullptr; lu.ldwn = (size_t)p.ld[l + 1];
+        lu.wt = pw + p.wt_off[l]; lu.ldwt = (size_t)p.ld[l]; lu.shadow_stride = p.shadow_stride;
+        lu.d_in = p.d[l]; lu.d_out = p.d[l + 1];
+        if (l == 0 && wg0_direct) launch_gemm<EPI_WGRAD, false, false, 4>(g, rd, p.dp[l], p.dp[l + 1], nsplit, s);
+        else                      launch_gemm<EPI_WGRAD, false, false, 5>(g, rd, p.dp[l], p.dp[l + 1], nsplit, s);
+      } else if (l == 0 && wg0_direct) {
         launch_gemm<EPI_WGRAD, false, false, 2>(g, rd, p.dp[l], p.dp[l + 1], nsplit, s);
       } else if (l == 0) {
         launch_gemm<EPI_WGRAD, false, false, 1>(g, rd, p.dp[l], p.dp[l + 1], nsplit, s);
@@ -2031,23 +2098,7 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
       kend(hook, kind);
       const int parts = run_q ? run_parts : nsplit;          // partials per tile (at most, with runs)
       if (!local && update_rows_aligned(p, l) && li + 1 < L) { pend = l; pend_split = parts; pend_q = run_q; }
-      else launch_update(a, l, rd, local ? UPD_LOCAL : UPD_GLOBAL, step, parts, s, hook, run_q, ksteps);
-    }
-
-    // ---- biases (local steps: a launch of its own, per upload; else they rode on the last
-    // weight-gradient launch)
-    if (local) {
-      BiasArgs b{};
-      (BiasCore&)b = bias;
-      {
-        b.batched = 1;
-        b.w_cur = wbase; b.cur_stride = p.slot_stride;
-        b.w_next = priv; b.next_stride = p.slot_stride;
-        for (int k = 0; k < K; ++k) b.cur_index[k] = (uint16_t)(own ? (uint32_t)k : rd.w[k].slot);
-      }
-      kbegin(hook, KK_MLP_BIAS_LOSS, (double)bias_cols * rows / 64, (double)bias_cols * rows / 64 * 4.0);
-      ABS_LAUNCH_K(mlp_bias_kernel, dim3((bias_cols + 15) / 16, K), dim3(256), s, b);
-      kend(hook, KK_MLP_BIAS_LOSS);
+      else if (!local) launch_update(a, l, rd, UPD_GLOBAL, parts, s, hook, run_q, ksteps);
     }
   }
 
@@ -2065,7 +2116,7 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
     kbegin(hook, KK_DELTA_UPDATE, 2.0 * K * p.P, (2.0 * K + 1.0) * p.P * 4.0);
     ABS_LAUNCH_K(mlp_delta_kernel, dim3((unsigned)((p.P + 255) / 256)), dim3(256), s, d, rd);
     kend(hook, KK_DELTA_UPDATE);
-    for (int l = L - 1; l >= 0; --l) launch_update(a, l, rd, UPD_DELTA, 0, 1, s, hook);
+    for (int l = L - 1; l >= 0; --l) launch_update(a, l, rd, UPD_DELTA, 1, s, hook);
   }
   return t_plan ? hipSuccess : hipGetLastError();
 }

@@ -56,6 +56,24 @@ def test_mlp_local_steps(over, T):
     _check(run_pair(p, T, checkpoints=(1, 5)), 2e-2, 2e-3)       # the bf16 workloads' tolerance
 
 
+@pytest.mark.parametrize("over,T", [
+    # one row per upload, 8 features: tiles that are nearly all padding
+    (dict(U=2, M=512, dims=[8, 40, 2], n_classes=2, N=4, B=1, n_slow=0, lr=1e-3), 10),
+    # no width a multiple of a tile or of 4, a hidden layer with a row-major copy
+    (dict(U=3, M=2400, dims=[1000, 521, 299, 26], n_classes=26, N=4, B=90, n_slow=0, lr=2e-4), 5),
+    # ragged widths on the 256 x 256 tile kernel (64 uploads): dataset rows read directly, then a hidden layer
+    (dict(U=2, M=6400, dims=[512, 200, 500, 10], N=64, K0=64, B=3, n_slow=0, lr=1e-3), 3),
+    # the same with a first layer that needs the transposed copy of the minibatch
+    (dict(U=2, M=6400, dims=[328, 200, 10], N=64, K0=64, B=3, n_slow=0, lr=1e-3), 3),
+    # 128-wide tiles (a long contraction over many uploads)
+    (dict(U=2, M=12800, dims=[64, 2040, 100], n_classes=100, N=64, K0=64, B=128, n_slow=0, lr=1e-4), 2),
+])
+def test_local_step_in_the_weight_gradient(over, T):
+    """The step taken in the weight gradient's epilogue at the edges of its tiles, in both copies of the weights."""
+    p = workloads.scaled_preset(3, **over)
+    _check(run_pair(p, T, checkpoints=(1,)), 2e-2, 2e-3)
+
+
 def test_cfg3_shape_local_steps():
     """The 3072-512-10 workload at its real layer and batch shapes (shorter dataset) with U = 2."""
     p = workloads.scaled_preset(3, M=6400, U=2)
