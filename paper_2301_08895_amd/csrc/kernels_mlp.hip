@@ -113,6 +113,51 @@ __global__ __launch_bounds__(256) void mlp_gather_t_kernel(const uint16_t* X, in
   }
 }
 
+// The same by the last workgroups of the output-layer kernel's launch: it needs nothing but the drawn rows,
+// and that launch's own workgroups (one per 128 rows) leave most CUs idle.  Blocks of 64 rows x 256 columns,
+// all of a thread's loads in flight together.  The kernel's LDS lets a CU hold one workgroup, so beyond
+// kGatherRide blocks (two waves) the launch of its own above is the faster one (microseconds per round, own
+// launch / riding: 1024 x 3072, 192 blocks 60.1 / 55.9; 8192 x 1024, 512 blocks 227 / 220; 8192 x 2048,
+// 1024 blocks 86 / 91; 32768 x 3072, 6144 blocks 1234 / 1326; blocks of this form in a launch of
+// their own 1250).
+constexpr int kGatherRide = 512;
+constexpr int kGatherPitch = 256 + 2;      // the 8 blocks of 8 rows a wavefront reads start 8 banks apart
+struct GatherT {
+  int blocks;                              // row blocks x column blocks that ride; 0: none
+  const uint16_t* X; int d0, dp0;
+  const uint32_t* rowidx;
+  uint16_t* XgT; size_t ldt;
+};
+__device__ __forceinline__ void gather_t_block(const GatherT& a, int b, uint16_t* tile) {
+  const int nk = (a.dp0 + 255) / 256;
+  const int m0 = (b / nk) * 64, k0 = (b % nk) * 256;
+  const int t = threadIdx.x;
+  uint4 v[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = (t >> 5) + 8 * i, k = k0 + (t & 31) * 8;
+    v[i] = make_uint4(0, 0, 0, 0);
+    if (k < a.d0) v[i] = *(const uint4*)(a.X + (size_t)a.rowidx[m0 + r] * a.d0 + k);     // d0 % 8 == 0
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    uint32_t* q = (uint32_t*)&tile[((t >> 5) + 8 * i) * kGatherPitch + (t & 31) * 8];
+    q[0] = v[i].x; q[1] = v[i].y; q[2] = v[i].z; q[3] = v[i].w;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int kk = (t >> 3) + 32 * i, c = t & 7;      // output row kk, 8 consecutive m
+    uint16_t h[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) h[j] = tile[(c * 8 + j) * kGatherPitch + kk];
+    uint4 o;
+    o.x = h[0] | ((uint32_t)h[1] << 16); o.y = h[2] | ((uint32_t)h[3] << 16);
+    o.z = h[4] | ((uint32_t)h[5] << 16); o.w = h[6] | ((uint32_t)h[7] << 16);
+    if (k0 + kk < a.dp0) *(uint4*)(a.XgT + (size_t)(k0 + kk) * a.ldt + m0 + c * 8) = o;
+  }
+}
+
 // ------------------------------------------------------------------ Eq. 3 on a block of a weight matrix
 // w^{t+1} = w^t - sum_z partial[z] (fixed order) for one weight matrix, written as fp32 into the next
 // ring slot and as bf16 in both orientations into the next shadow slot.
@@ -1232,6 +1277,7 @@ struct LogitsCeArgs {
   uint16_t* dZT; size_t lddzt;           // [dp_L][lddzt]
   float* rowloss;                        // [rows / 128]
   float* colsum; size_t ldcs;            // [rows / 128][ldcs]
+  GatherT gt;                            // its blocks are the launch's last workgroups
 };
 
 template <int NB>                        // dp_L = 32 NB: 2, 4 or 8
@@ -1247,6 +1293,11 @@ __global__ __launch_bounds__(256, 1) void mlp_logits_ce_kernel(LogitsCeArgs a, R
   __shared__ __attribute__((aligned(16))) uint16_t smem[kStages * kStageElems];
   __shared__ float s_l[4];
   __shared__ __attribute__((aligned(16))) float s_bias[NP];
+  static_assert(kStages * kStageElems >= 64 * kGatherPitch, "a gather block fits the ring");
+  if (const int own = (int)gridDim.x - a.gt.blocks; (int)blockIdx.x >= own) {
+    gather_t_block(a.gt, (int)blockIdx.x - own, smem);
+    return;
+  }
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int m0 = blockIdx.x * kCeRows;
   const int up = m0 / a.rows_per_upload;
@@ -1888,10 +1939,26 @@ unsigned mlp_forward(const MlpArgs& a, const uint16_t* Xsrc, const RoundDesc& rd
 // Output layer of a training pass: logits, loss sums per 32 rows, dZ_L in both orientations and its
 // column sums, in one kernel (mlp_logits_ce_kernel).
 void launch_logits_ce(const MlpArgs& a, const RoundDesc& rd, int rows, double arows, const float* wbase,
-                      const uint16_t* sbase, bool own, hipStream_t s, LaunchHook* hook) {
+                      const uint16_t* sbase, bool own, bool gather_t, hipStream_t s, LaunchHook* hook) {
   const MlpPlan& p = a.plan;
   const int L = p.L;
   LogitsCeArgs c{};
+  if (gather_t) {
+    GatherT gt{};
+    gt.X = a.X; gt.d0 = p.d[0]; gt.dp0 = p.dp[0];
+    gt.rowidx = at<uint32_t>(a, p.off_rowidx);
+    gt.XgT = at<uint16_t>(a, p.off_xgt); gt.ldt = p.ldm;
+    gt.blocks = (rows / 64) * ((p.dp[0] + 255) / 256);
+    if (gt.blocks <= kGatherRide) {
+      plan_note("with_gather_t", 64, 256, 1);
+      c.gt = gt;
+    } else {
+      kbegin(hook, KK_MLP_GATHER_T, 0, arows * p.d[0] * 4.0);
+      plan_note("gather_t", 64, 64, 1);
+      ABS_LAUNCH_K(mlp_gather_t_kernel, dim3(rows / 64, p.dp[0] / 64), dim3(256), s, gt.X, gt.d0, gt.rowidx, gt.XgT, gt.ldt);
+      kend(hook, KK_MLP_GATHER_T);
+    }
+  }
   c.H = at<uint16_t>(a, p.off_h[L - 1]); c.ldh = (size_t)p.ld[L - 1];
   c.ksteps = p.dp[L - 1] / BK;
   c.Wt = sbase + p.wt_off[L - 1]; c.ldw = (size_t)p.ld[L - 1];
@@ -1905,9 +1972,9 @@ void launch_logits_ce(const MlpArgs& a, const RoundDesc& rd, int rows, double ar
   c.rowloss = at<float>(a, p.off_rowloss);
   c.colsum = at<float>(a, p.off_colsum[L]); c.ldcs = (size_t)p.dp[L];
   kbegin(hook, KK_MLP_LOGITS_CE, 2.0 * arows * p.d[L - 1] * p.d[L] + arows * p.d[L] * 8.0,
-              arows * (p.d[L - 1] * 2.0 + p.d[L] * 4.0));
+              arows * (p.d[L - 1] * 2.0 + p.d[L] * 4.0 + (c.gt.blocks ? p.d[0] * 4.0 : 0.0)));
   plan_note("logits_ce", kCeRows, p.dp[L], 1);
-  const dim3 grid(rows / kCeRows), block(256);
+  const dim3 grid(rows / kCeRows + c.gt.blocks), block(256);
   switch (p.dp[L] / 64) {
     case 1: ABS_LAUNCH_K((mlp_logits_ce_kernel<2>), grid, block, s, c, rd); break;
     case 2: ABS_LAUNCH_K((mlp_logits_ce_kernel<4>), grid, block, s, c, rd); break;
@@ -1965,7 +2032,7 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
                                            (long)step * (long)p.B, s, hook);
 
     // ---- output layer: loss and output gradient, already scaled by the uploads' coefficients
-    launch_logits_ce(a, rd, rows, arows, wbase, sbase, own, s, hook);
+    launch_logits_ce(a, rd, rows, arows, wbase, sbase, own, !wg0_direct, s, hook);
     const int loss_blocks = p.Bp / kCeRows;          // row blocks of the loss sums per upload
 
     // ---- input gradients back through W_{L-1} .. W_1 (none is needed for the first layer)
@@ -2011,13 +2078,6 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
     // ---- weight gradients.  U = 1: one contraction over all stacked rows = the K-of-N
     //      reduction, split over row ranges for occupancy, then update + snapshot per layer.
     //      U > 1: split a = the rows of upload a, applied to that upload's private model.
-    if (!wg0_direct) {
-      kbegin(hook, KK_MLP_GATHER_T, 0, arows * p.d[0] * 4.0);
-      plan_note("gather_t", 64, 64, 1);
-      ABS_LAUNCH_K(mlp_gather_t_kernel, dim3(rows / 64, p.dp[0] / 64), dim3(256), s, a.X, p.d[0], (const uint32_t*)rowidx,
-                   at<uint16_t>(a, p.off_xgt), p.ldm);
-      kend(hook, KK_MLP_GATHER_T);
-    }
     // U = 1: first layer first.  The update of a layer (Eq. 3: bound by memory) does not get a launch of
     // its own but rides along in the NEXT layer's weight-gradient launch (bound by the matrix cores) as
     // that launch's last workgroups: they take the CUs its last wave of tiles leaves idle and its tail,

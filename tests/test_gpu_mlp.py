@@ -102,6 +102,10 @@ def test_sampled_kernel_timing_changes_nothing():
     # more than 128 tiles of 128 x 128 in every forward and input-gradient product; one fewer row tile: 64-wide
     (dict(M=4800, dims=[136, 1024, 1024, 10], N=17, K0=17, B=128, n_slow=0, lr=1e-4), 2),
     (dict(M=4800, dims=[136, 1024, 1024, 10], N=16, K0=16, B=128, n_slow=0, lr=1e-4), 2),
+    # the transposed minibatch: the most blocks that ride with the output layer's kernel, and a launch of its own;
+    # half a block of 256 columns of padding
+    (dict(M=6400, dims=[1096, 64, 10], N=50, K0=50, B=100, n_slow=0, lr=2e-4), 2),
+    (dict(M=6400, dims=[1096, 64, 10], N=64, K0=64, B=100, n_slow=0, lr=2e-4), 2),
     # a weight gradient long enough for 128-wide tiles (128 k-steps, 128 padded classes)
     (dict(M=12800, dims=[64, 2048, 100], n_classes=100, N=64, K0=64, B=128, n_slow=0, lr=1e-4), 2),
 ])
