@@ -6,12 +6,15 @@
 #include <atomic>
 #include <chrono>
 #include <cmath>
+#include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <memory>
 #include <mutex>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -494,6 +497,59 @@ int abs_round(abs_ctx* ctx, int32_t n_rounds) {
 }
 
 // ---- batched simulations: S handles of one shape advance together, one set of launches per round
+// The host threads of a batch beside the caller's: created with it and joined when it is destroyed, asleep
+// between calls (started and joined by every call they cost 10-20 us each, so a call had one per 32
+// simulations, and the host's part bounded the round: figures at abs_batch_create).
+namespace {
+class HostPool {
+ public:
+  explicit HostPool(int n) {
+    try {
+      for (int k = 1; k <= n; ++k) threads_.emplace_back([this, k] { loop(k); });
+    } catch (const std::system_error&) {}          // fewer threads than asked for (perhaps none) also do
+  }
+  ~HostPool() {
+    { std::lock_guard<std::mutex> g(m_); stop_ = true; }
+    wake_.notify_all();
+    for (std::thread& t : threads_) t.join();
+  }
+  int size() const { return (int)threads_.size(); }
+  // thread k = 1 .. size() runs job(k); returns at once, `job` must live until wait() has returned
+  void start(const std::function<void(int)>& job) {
+    { std::lock_guard<std::mutex> g(m_); job_ = &job; running_ = size(); ++calls_; }
+    wake_.notify_all();
+  }
+  void wait() {
+    std::unique_lock<std::mutex> g(m_);
+    idle_.wait(g, [this] { return running_ == 0; });
+    job_ = nullptr;
+  }
+
+ private:
+  void loop(int k) {
+    uint64_t seen = 0;
+    std::unique_lock<std::mutex> g(m_);
+    for (;;) {
+      wake_.wait(g, [&] { return stop_ || calls_ != seen; });
+      if (stop_) return;
+      seen = calls_;
+      const std::function<void(int)>* job = job_;
+      g.unlock();
+      (*job)(k);
+      g.lock();
+      if (--running_ == 0) idle_.notify_one();
+    }
+  }
+  std::mutex m_;
+  std::condition_variable wake_, idle_;
+  const std::function<void(int)>* job_ = nullptr;
+  uint64_t calls_ = 0;
+  int running_ = 0;
+  bool stop_ = false;
+  std::vector<std::thread> threads_;
+};
+}  // namespace
+
 constexpr int kBatchGroups = 4;            // a large batch advances as up to this many groups
 struct abs_batch {
   std::vector<abs_ctx*> ctx;
@@ -507,6 +563,7 @@ struct abs_batch {
   LossMailbox* h_box = nullptr;            // pinned, device-visible [S]
   LossMailbox* d_box = nullptr;
   char* d_slots = nullptr;                 // softmax: per-upload gradient slots and losses of all simulations
+  std::unique_ptr<HostPool> pool;          // regression models: the further host threads of a round
   uint64_t rounds = 0;
   std::string err;
 };
@@ -618,13 +675,19 @@ int abs_batch_create(abs_ctx** ctxs, int32_t n, void* d_workspace, size_t worksp
   }
   if (!hip(hipMemcpyAsync(b->d_args, args.data(), (size_t)n * sizeof(RegressionArgs), hipMemcpyHostToDevice, b->stream), "hipMemcpyAsync")) return ABS_E_HIP;
   if (!hip(hipStreamSynchronize(b->stream), "hipStreamSynchronize")) return ABS_E_HIP;
+  // A simulation's selection, descriptor and Eq. 4-6 take the host about a microsecond per round (16 workers),
+  // and the threads' phase changes as long as a few simulations: eight threads from 64 simulations on.
+  // (microseconds per round, one thread per 32 simulations started by every call / these: linear, 64
+  // simulations 30-36 / 30, 128 38-44 / 35, 256 57 / 52; softmax 64 64-71 / 60, 128 90 / 80; a thread per
+  // eight simulations below 64: linear 16 23.1 / 25.0, 32 26.4 / 29.3, softmax 16 40.8 / 42.8.)
+  const int helpers = n >= 64 ? std::min(8, (int)std::thread::hardware_concurrency() / 2) - 1 : 0;
+  if (helpers > 0) b->pool.reset(new HostPool(helpers));
   *out = b.release();
   return ABS_OK;
 }
 
 // The host part of a batched round (select, descriptor, mailbox, Eq. 4-6 per simulation) is
-// independent per simulation, so large batches spread it over a few threads that live for the
-// duration of the call: thread k owns simulations lo + k, lo + k + T, ... of the group [lo, hi) in
+// independent per simulation, so large batches spread it over the batch's threads: thread k owns simulations lo + k, lo + k + T, ... of the group [lo, hi) in
 // hand.  A round of a group has two parallel phases around the launch; workers spin on a phase
 // counter (a round lasts tens of microseconds).
 namespace {
@@ -777,7 +840,7 @@ int abs_batch_round(abs_batch* b, int32_t n_rounds) {
   BatchRoundState st;
   st.b = b;
   st.S = S;
-  st.T = std::max(1, std::min({8, S / 32, (int)std::thread::hardware_concurrency() / 2}));
+  st.T = 1 + (b->pool ? b->pool->size() : 0);
   st.sel.resize((size_t)S);
   st.stamp.resize((size_t)S);
   st.kmax.assign((size_t)st.T, 0);
@@ -807,8 +870,8 @@ int abs_batch_round(abs_batch* b, int32_t n_rounds) {
     for (int g = 1; g < G && e == hipSuccess; ++g) e = hipStreamWaitEvent(gstream[g], b->ev_in, 0);
     if (e != hipSuccess) { b->err = std::string("hipStreamWaitEvent: ") + hipGetErrorString(e); return ABS_E_HIP; }
   }
-  std::vector<std::thread> pool;            // from here on every path joins them
-  for (int k = 1; k < st.T; ++k) pool.emplace_back([&st, k] { st.worker(k); });
+  const std::function<void(int)> work = [&st](int k) { st.worker(k); };
+  if (st.T > 1) b->pool->start(work);       // from here on every path waits for them
   bool inflight[kBatchGroups] = {};
   auto finish = [&](int g) {
     inflight[g] = false;
@@ -850,7 +913,7 @@ int abs_batch_round(abs_batch* b, int32_t n_rounds) {
   }
   st.kind = -1;
   st.phase.fetch_add(1, std::memory_order_release);
-  for (std::thread& t : pool) t.join();
+  if (st.T > 1) b->pool->wait();
   if (G > 1 && n_rounds > 0) {
     hipError_t e = hipSuccess;
     for (int g = 1; g < G && e == hipSuccess; ++g) {

@@ -344,3 +344,22 @@ def test_softmax_batch_random_shapes():
             one.close()
             assert_matches_oracle(ps[k], d, got[k][0], got[k][1], 8, 1e-5, _rerun_as_batch_of_one(d),
                                   where=f"case {case} simulation {k}")
+
+
+@pytest.mark.parametrize("S", [1, 63, 64, 67])
+def test_many_short_calls_equal_one_long_call(S):
+    """The batch's host threads sleep between calls and take up the next one (none below 64 simulations)."""
+    base = workloads.scaled_preset(1, M=1000, dims=[12, 1], N=5, B=4, K0=2)
+    d = workloads.make_inputs(base)
+    out = []
+    for calls in ([1] * 12, [0, 12]):
+        sims = [lib.Simulation(p, d) for p in _variants(base, S)]
+        batch = lib.Batch(sims)
+        for n in calls:
+            batch.round(n)
+        batch.close()
+        out.append([(s.model().copy(), s.trace().copy()) for s in sims])
+        for s in sims:
+            s.close()
+    for (m0, t0), (m1, t1) in zip(*out):
+        assert np.array_equal(m0, m1) and np.array_equal(t0, t1)
