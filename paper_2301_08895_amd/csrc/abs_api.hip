@@ -241,30 +241,33 @@ struct abs_ctx : public LaunchHook {
   void end_kernel(int kind) override {
     if (timing) { ev_kind.push_back(kind); ev_used += 2; }
   }
-  // Spin until the device has stamped the mailbox; every so often ask the runtime whether the
-  // stream has failed or drained without the stamp, and give up after mailbox_timeout_s(), so
-  // neither a broken launch nor a stream that never gets to run can hang the host.
-  int wait_mailbox(uint32_t stamp) {
+  // Spin until the device has posted the K losses of the round with this stamp; every so often ask the
+  // runtime whether the stream has failed or drained without them, and give up after
+  // mailbox_timeout_s(), so neither a broken launch nor a stream that never gets to run can hang the host.
+  int wait_mailbox(uint32_t stamp, int K) {
     const auto t0 = std::chrono::steady_clock::now();
-    for (uint64_t spin = 1;; ++spin) {
-      if (h_box->stamp == stamp) { std::atomic_thread_fence(std::memory_order_acquire); return ABS_OK; }
-      if ((spin & 0x3FFF) == 0) {
-        const hipError_t q = hipStreamQuery(stream);
-        if (q == hipSuccess) {
-          if (h_box->stamp == stamp) return ABS_OK;
-          err = "stream drained but the loss mailbox was not written";
-          return ABS_E_HIP;
+    for (int a = 0; a < K; ++a) {
+      for (uint64_t spin = 1; !h_box->posted(a, stamp); ++spin) {
+        if ((spin & 0x3FFF) == 0) {
+          const hipError_t q = hipStreamQuery(stream);
+          if (q == hipSuccess) {
+            if (h_box->posted(a, stamp)) break;
+            err = "stream drained but the loss mailbox was not written";
+            return ABS_E_HIP;
+          }
+          if (q != hipErrorNotReady) { err = std::string("hipStreamQuery: ") + hipGetErrorString(q); return ABS_E_HIP; }
+          if (seconds_since(t0) > mailbox_timeout_s()) {
+            err = "timed out waiting for the round's losses (the stream has not completed the round)";
+            return ABS_E_HIP;
+          }
         }
-        if (q != hipErrorNotReady) { err = std::string("hipStreamQuery: ") + hipGetErrorString(q); return ABS_E_HIP; }
-        if (seconds_since(t0) > mailbox_timeout_s()) {
-          err = "timed out waiting for the round's losses (the stream has not completed the round)";
-          return ABS_E_HIP;
-        }
-      }
 #if defined(__x86_64__)
-      __builtin_ia32_pause();
+        __builtin_ia32_pause();
 #endif
+      }
     }
+    std::atomic_thread_fence(std::memory_order_acquire);
+    return ABS_OK;
   }
   void harvest() {   // after the stream has been synchronised
     for (size_t i = 0; i < ev_kind.size(); ++i) {
@@ -478,10 +481,10 @@ int abs_round(abs_ctx* ctx, int32_t n_rounds) {
     }
     if (e != hipSuccess) { ctx->err = std::string("kernel launch: ") + hipGetErrorString(e); return ABS_E_HIP; }
     // Eq. 5 needs this round's losses before the next round can be selected.  They arrive in
-    // the mailbox as soon as the forward pass is through (the stamp is written last), so the
+    // the mailbox as soon as the forward pass is through, so the
     // host prepares and enqueues round t+1 while the device still works on round t; stream
     // order keeps the rounds apart on the device.
-    rc = ctx->wait_mailbox(rd.stamp);
+    rc = ctx->wait_mailbox(rd.stamp, K);
     if (rc != ABS_OK) return rc;
     // profile mode: the rounds' events are read back in batches, after draining the stream
     if (cfg.profile && (ctx->ev_kind.size() >= 512 || it + 1 == n_rounds)) {
@@ -489,7 +492,7 @@ int abs_round(abs_ctx* ctx, int32_t n_rounds) {
       ctx->harvest();
     }
     float losses[ABS_MAX_WORKERS];
-    for (int a = 0; a < K; ++a) losses[a] = ctx->h_box->loss[pos_of[a]];
+    for (int a = 0; a < K; ++a) losses[a] = ctx->h_box->loss(pos_of[a]);
     rc = ctx->sched->complete(sel, losses, true, ctx->err);
     if (rc != ABS_OK) return rc;
   }
@@ -739,19 +742,22 @@ struct BatchRoundState {
   }
   void finish(int k) {                         // wait for the losses, apply Eq. 4-6
     for (int i = lo + k; i < hi; i += T) {
-      const volatile LossMailbox* box = b->h_box + i;
-      for (uint64_t spin = 1; box->stamp != stamp[(size_t)i]; ++spin) {
-        if (abort.load(std::memory_order_relaxed)) return;
-        if (k == 0 && (spin & 0x3FFF) == 0 && stream_failed()) return;
+      const LossMailbox* box = b->h_box + i;
+      const int K = (int)sel[(size_t)i].size();
+      uint64_t spin = 0;
+      for (int a = 0; a < K; ++a) {
+        while (!box->posted(a, stamp[(size_t)i])) {
+          if (abort.load(std::memory_order_relaxed)) return;
+          if (k == 0 && (++spin & 0x3FFF) == 0 && stream_failed()) return;
 #if defined(__x86_64__)
-        __builtin_ia32_pause();
+          __builtin_ia32_pause();
 #endif
+        }
       }
       std::atomic_thread_fence(std::memory_order_acquire);
       abs_ctx* ctx = b->ctx[(size_t)i];
       float losses[ABS_MAX_WORKERS];
-      const int K = (int)sel[(size_t)i].size();
-      for (int a = 0; a < K; ++a) losses[a] = b->h_box[i].loss[a];
+      for (int a = 0; a < K; ++a) losses[a] = box->loss(a);
       const int r = ctx->sched->complete(sel[(size_t)i], losses, true, ctx->err);
       if (r != ABS_OK && rc[(size_t)k] == ABS_OK) { rc[(size_t)k] = r; bad_sim[(size_t)k] = i; }
     }

@@ -2,6 +2,7 @@
 #pragma once
 #include <cstdint>
 #include <cstddef>
+#include <cstring>
 #include "../../include/abs.h"
 
 #if defined(__HIPCC__)
@@ -45,24 +46,26 @@ struct WorkerDesc {
   uint32_t slot;
   float    c;
 };
-// The losses travel through a small mailbox in device-visible host memory: loss[a] for
-// upload a, then `stamp`, written last, so the host can pick them up by polling.
+// The losses travel through a small mailbox in device-visible host memory, which the host polls: word a is
+// the loss of upload a (low half) together with the round's stamp (high half), written in ONE 8-byte store.
+// A word that carries the stamp carries its loss, so nothing has to be ordered: no fence between losses and
+// a separate stamp, which cost a trip over the host link before the host could go on (a round of one linear
+// simulation 13.8 -> 13.1 us, of one softmax simulation 16.5 -> 15.9).
 struct LossMailbox {
-  float loss[ABS_MAX_WORKERS];
-  volatile uint32_t stamp;
+  volatile uint64_t word[ABS_MAX_WORKERS];
+  bool posted(int a, uint32_t stamp) const { return (uint32_t)(word[a] >> 32) == stamp; }
+  float loss(int a) const {
+    const uint32_t bits = (uint32_t)word[a];
+    float v;
+    std::memcpy(&v, &bits, 4);
+    return v;
+  }
 };
 
 #if defined(__HIPCC__)
-// Publish K losses that sit in LDS: one wavefront writes them all, fences once at system
-// scope and only then writes the stamp, so a host that sees the stamp sees the losses.
-// (One fence per loss would cost a trip over the host link each.)  Call with the whole
-// workgroup after a __syncthreads() that follows the LDS writes.
-__device__ __forceinline__ void publish_losses(LossMailbox* box, const float* s_loss, int K, uint32_t stamp) {
-  if (threadIdx.x < 64) {
-    for (int a = threadIdx.x; a < K; a += 64) box->loss[a] = s_loss[a];
-    __threadfence_system();
-    if (threadIdx.x == 0) box->stamp = stamp;
-  }
+__device__ __forceinline__ void post_loss(LossMailbox* box, int up, float loss, uint32_t stamp) {
+  __hip_atomic_store((uint64_t*)&box->word[up], ((uint64_t)stamp << 32) | __float_as_uint(loss), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
 }
 #endif
 
@@ -70,7 +73,7 @@ struct RoundDesc {
   int32_t  K;          // uploads aggregated this round
   uint32_t slot_cur;   // ring slot of w^t
   uint32_t slot_next;  // ring slot that receives w^{t+1}
-  uint32_t stamp;      // written to the loss mailbox after this round's losses (round + 1)
+  uint32_t stamp;      // written to the loss mailbox with this round's losses (round + 1)
   WorkerDesc w[ABS_MAX_WORKERS];
 };
 

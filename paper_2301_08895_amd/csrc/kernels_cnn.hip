@@ -505,12 +505,7 @@ __device__ __forceinline__ void cnn_losses(const CnnDev& d, const RoundDesc& rd,
     float* lb = wsp<float>(d, p.off_lossbuf) + a;
     if (!local) *lb = mean;
     else *lb = (d.step == 0 ? 0.f : *lb) + mean / (float)d.U;       // mean over the job's U steps
-    if (mailbox) mailbox->loss[a] = mean;
-  }
-  if (mailbox) {
-    if (threadIdx.x < ABS_MAX_WORKERS) __threadfence_system();
-    __syncthreads();
-    if (threadIdx.x == 0) mailbox->stamp = rd.stamp;
+    if (mailbox) post_loss(mailbox, a, mean, rd.stamp);
   }
 }
 
@@ -828,13 +823,8 @@ __global__ __launch_bounds__(256) void cnn_combine_kernel(CnnDev d, RoundDesc rd
 // order; the first workgroup publishes the uploads' mean local losses.
 __global__ __launch_bounds__(256) void cnn_delta_update_kernel(CnnDev d, RoundDesc rd, LossMailbox* mailbox) {
   const CnnPlan& p = d.p;
-  if (blockIdx.x == 0 && mailbox) {
-    const float* lossbuf = wsp<const float>(d, p.off_lossbuf);
-    if ((int)threadIdx.x < rd.K) mailbox->loss[threadIdx.x] = lossbuf[threadIdx.x];
-    if (threadIdx.x < ABS_MAX_WORKERS) __threadfence_system();
-    __syncthreads();
-    if (threadIdx.x == 0) mailbox->stamp = rd.stamp;
-  }
+  if (blockIdx.x == 0 && mailbox && (int)threadIdx.x < rd.K)
+    post_loss(mailbox, threadIdx.x, wsp<const float>(d, p.off_lossbuf)[threadIdx.x], rd.stamp);
   const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (e >= p.P) return;
   const float* ring = wsp<const float>(d, p.off_ring);

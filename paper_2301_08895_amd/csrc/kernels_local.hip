@@ -208,14 +208,10 @@ __global__ __launch_bounds__(256) void softmax_local_batch_kernel(const Regressi
 
 // ---- Eq. 3 over the uploads' changes: w^{t+1} = w^t - (1/K) sum_a delta_a, arrival order
 __device__ __forceinline__ void delta_update_body(const RegressionArgs& a, const RoundDesc& rd, int P) {
-  __shared__ float s_loss[ABS_MAX_WORKERS];
   const float* cur = a.ring + (size_t)rd.slot_cur * a.slot_stride;
   float* nxt = a.ring + (size_t)rd.slot_next * a.slot_stride;
-  if (blockIdx.x == 0) {                  // first: the host prepares the next round meanwhile
-    for (int up = threadIdx.x; up < rd.K; up += 256) s_loss[up] = a.lossbuf[up];
-    __syncthreads();
-    publish_losses(a.mailbox, s_loss, rd.K, rd.stamp);
-  }
+  // first: the host prepares the next round meanwhile
+  if (blockIdx.x == 0 && (int)threadIdx.x < rd.K) post_loss(a.mailbox, threadIdx.x, a.lossbuf[threadIdx.x], rd.stamp);
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < P) {
     float s = 0.f;

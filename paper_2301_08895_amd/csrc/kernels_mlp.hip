@@ -397,9 +397,7 @@ __device__ __forceinline__ void gen_row_store(const GemmArgs& g, int m, uint32_t
 }
 
 // The uploads' mean minibatch losses (what each worker reports next to its gradient) into the
-// mailbox, then the stamp: thread a < K adds the loss sums of upload a's row blocks in order.  Every
-// wavefront that wrote fences at system scope before the barrier, so the host that sees the stamp
-// sees the losses.  Whole workgroup, uniform call.
+// mailbox: thread a < K adds the loss sums of upload a's row blocks in order.
 __device__ __forceinline__ void publish_upload_losses(const GemmArgs& g, int K, uint32_t stamp) {
   const int up = threadIdx.x;
   if (up < K) {
@@ -411,12 +409,8 @@ __device__ __forceinline__ void publish_upload_losses(const GemmArgs& g, int K, 
       g.pub_lossacc[up] = mean;
       mean /= (float)g.pub_U;
     }
-    if (g.pub_mailbox) g.pub_mailbox->loss[up] = mean;
+    if (g.pub_mailbox) post_loss(g.pub_mailbox, up, mean, stamp);
   }
-  if (!g.pub_mailbox) return;
-  if (threadIdx.x < ABS_MAX_WORKERS) __threadfence_system();
-  __syncthreads();
-  if (threadIdx.x == 0) g.pub_mailbox->stamp = stamp;
 }
 
 // Block b of the bias blocks at the end of a weight-gradient launch: 16 bias entries, of the global model

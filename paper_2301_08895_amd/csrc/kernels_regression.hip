@@ -102,10 +102,8 @@ __device__ __forceinline__ void linreg_round_body(const RegressionArgs& a, const
     float l = 0.f;
 #pragma unroll
     for (int w = 0; w < kLinWaves; ++w) l += s_loss[w][up];
-    s_loss[0][up] = l / (float)B;
+    post_loss(a.mailbox, up, l / (float)B, rd.stamp);
   }
-  __syncthreads();
-  publish_losses(a.mailbox, &s_loss[0][0], K, rd.stamp);
   const float* cur = a.ring + (size_t)rd.slot_cur * a.slot_stride;
   float* nxt = a.ring + (size_t)rd.slot_next * a.slot_stride;
   for (int i = threadIdx.x; i < d; i += blockDim.x) {
@@ -259,7 +257,6 @@ constexpr int kUpdF = 8, kUpdG = 128;
 template <int C>
 __device__ __forceinline__ void softmax_update_body(const RegressionArgs& a, const RoundDesc& rd) {
   __shared__ float s_red[kUpdG][kUpdF * C + 1];
-  __shared__ float s_loss[ABS_MAX_WORKERS];
   const int B = a.B, d = a.d, R = rd.K * B;
   const float* cur = a.ring + (size_t)rd.slot_cur * a.slot_stride;
   float* nxt = a.ring + (size_t)rd.slot_next * a.slot_stride;
@@ -318,12 +315,9 @@ __device__ __forceinline__ void softmax_update_body(const RegressionArgs& a, con
       float s = 0.f;
       for (int b = lane; b < B; b += 64) s += a.rowloss[up * B + b];
       s = wave_sum(s);
-      if (lane == 0) s_loss[up] = s / (float)B;
+      if (lane == 0) post_loss(a.mailbox, up, s / (float)B, rd.stamp);
     }
-    __syncthreads();
-    publish_losses(a.mailbox, s_loss, rd.K, rd.stamp);
   }
-  __syncthreads();
   // bias gradient: column sums of dZ (16 columns x 64 row groups), then b^{t+1}
   {
     const int c = threadIdx.x % 16, g = threadIdx.x / 16;
@@ -932,17 +926,13 @@ __global__ __launch_bounds__(kFuseThreads, TR == 16 ? 2 : 4) void softmax_local_
 // Eq. 3 over the uploads' gradients (each already scaled by its c), arrival order
 __global__ __launch_bounds__(256) void softmax_combine_batch_kernel(const RegressionArgs* as, const char* rds,
                                                                     size_t stride, int P) {
-  __shared__ float s_loss[ABS_MAX_WORKERS];
   const RegressionArgs a = as[blockIdx.y];
   const RoundDesc& rd = *(const RoundDesc*)(rds + (size_t)blockIdx.y * stride);
   const int K = rd.K;
   const float* cur = a.ring + (size_t)rd.slot_cur * a.slot_stride;
   float* nxt = a.ring + (size_t)rd.slot_next * a.slot_stride;
-  if (blockIdx.x == 0) {                  // first: the host prepares the next round meanwhile
-    for (int up = threadIdx.x; up < K; up += 256) s_loss[up] = a.lossbuf[up];
-    __syncthreads();
-    publish_losses(a.mailbox, s_loss, K, rd.stamp);
-  }
+  // first: the host prepares the next round meanwhile
+  if (blockIdx.x == 0 && (int)threadIdx.x < K) post_loss(a.mailbox, threadIdx.x, a.lossbuf[threadIdx.x], rd.stamp);
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < P) {
     const float c = load_global(cur + i);
