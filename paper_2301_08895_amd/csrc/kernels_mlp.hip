@@ -2043,7 +2043,7 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
       g.rows_per_upload = p.Bp;
       g.ksteps_total = g.ksteps_per_split = p.dp[l + 1] / BK;
       g.maskT = at<uint16_t>(a, p.off_ht[l]); g.ldmaskT = p.ldm;
-      if ((have_bits >> l) & 1u) g.maskbits = at<uint32_t>(a, p.off_maskbits[l]);   // the 128-row kernel ignores it
+      if ((have_bits >> l) & 1u) g.maskbits = at<uint32_t>(a, p.off_maskbits[l]);   // the tile kernel ignores it
       g.out = l >= 2 ? at<uint16_t>(a, p.off_dz[l]) : nullptr; g.ldo = (size_t)p.ld[l];
       g.outT = at<uint16_t>(a, p.off_dzt[l]); g.ldoT = p.ldm;
       g.colsum = at<float>(a, p.off_colsum[l]); g.ldcs = (size_t)p.dp[l];
