@@ -6,18 +6,16 @@
 #include <atomic>
 #include <chrono>
 #include <cmath>
-#include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
-#include <functional>
 #include <memory>
 #include <mutex>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
+#include "host_pool.h"
 #include "kernels.h"
 #include "sched.h"
 
@@ -500,60 +498,27 @@ int abs_round(abs_ctx* ctx, int32_t n_rounds) {
 }
 
 // ---- batched simulations: S handles of one shape advance together, one set of launches per round
-// The host threads of a batch beside the caller's: created with it and joined when it is destroyed, asleep
-// between calls (started and joined by every call they cost 10-20 us each, so a call had one per 32
-// simulations, and the host's part bounded the round: figures at abs_batch_create).
-namespace {
-class HostPool {
- public:
-  explicit HostPool(int n) {
-    try {
-      for (int k = 1; k <= n; ++k) threads_.emplace_back([this, k] { loop(k); });
-    } catch (const std::system_error&) {}          // fewer threads than asked for (perhaps none) also do
-  }
-  ~HostPool() {
-    { std::lock_guard<std::mutex> g(m_); stop_ = true; }
-    wake_.notify_all();
-    for (std::thread& t : threads_) t.join();
-  }
-  int size() const { return (int)threads_.size(); }
-  // thread k = 1 .. size() runs job(k); returns at once, `job` must live until wait() has returned
-  void start(const std::function<void(int)>& job) {
-    { std::lock_guard<std::mutex> g(m_); job_ = &job; running_ = size(); ++calls_; }
-    wake_.notify_all();
-  }
-  void wait() {
-    std::unique_lock<std::mutex> g(m_);
-    idle_.wait(g, [this] { return running_ == 0; });
-    job_ = nullptr;
-  }
-
- private:
-  void loop(int k) {
-    uint64_t seen = 0;
-    std::unique_lock<std::mutex> g(m_);
-    for (;;) {
-      wake_.wait(g, [&] { return stop_ || calls_ != seen; });
-      if (stop_) return;
-      seen = calls_;
-      const std::function<void(int)>* job = job_;
-      g.unlock();
-      (*job)(k);
-      g.lock();
-      if (--running_ == 0) idle_.notify_one();
-    }
-  }
-  std::mutex m_;
-  std::condition_variable wake_, idle_;
-  const std::function<void(int)>* job_ = nullptr;
-  uint64_t calls_ = 0;
-  int running_ = 0;
-  bool stop_ = false;
-  std::vector<std::thread> threads_;
-};
-}  // namespace
-
 constexpr int kBatchGroups = 4;            // a large batch advances as up to this many groups
+
+// Host threads of a batched round of S simulations of the regression models, the caller included.  Selection,
+// descriptor and Eq. 4-6 take the host about a microsecond per simulation and round (16 workers), and a phase
+// change as long as a few simulations: a thread per 32 simulations however many calls run side by
+// side, and from 64 simulations on eight while their sum over the process's calls stays at half of the CPUs
+// (SpinBudget).  Microseconds per round with 2 / 4 / 8 threads: linear, 64 simulations 30 / 27 / 25, 128: 40 / 35 / 31;
+// softmax, 64: 64 / 57 / 52, 128: 98 / 83 / 75.  Below 64 the caller alone is faster (linear, 16: 23.1, two 25.0).
+// Four batches of 64 from as many threads: 56 us a round with two threads each, up to 30 ms with eight on 16 CPUs.
+namespace {
+int half_the_cpus() { return std::max(1, (int)std::thread::hardware_concurrency() / 2); }
+int least_threads(int S) { return std::max(1, std::min({8, S / 32, half_the_cpus()})); }
+int most_threads(int S) { return S >= 64 ? std::min(8, half_the_cpus()) : 1; }
+SpinBudget& batch_threads() {
+  static SpinBudget budget(half_the_cpus());
+  return budget;
+}
+// CPUs that other processes use, or a quota, can be short all the same: a phase without a wait for the device that
+// took this long means that a thread was not running.  The batch then keeps to its least for a while.
+constexpr double kStarvedPhase = 5e-3, kStarvedFor = 10.0;      // seconds
+}  // namespace
 struct abs_batch {
   std::vector<abs_ctx*> ctx;
   hipStream_t stream = nullptr;            // the handles' stream
@@ -567,6 +532,7 @@ struct abs_batch {
   LossMailbox* d_box = nullptr;
   char* d_slots = nullptr;                 // softmax: per-upload gradient slots and losses of all simulations
   std::unique_ptr<HostPool> pool;          // regression models: the further host threads of a round
+  std::chrono::steady_clock::time_point few_until{};             // ... only the least of them before this moment
   uint64_t rounds = 0;
   std::string err;
 };
@@ -678,32 +644,23 @@ int abs_batch_create(abs_ctx** ctxs, int32_t n, void* d_workspace, size_t worksp
   }
   if (!hip(hipMemcpyAsync(b->d_args, args.data(), (size_t)n * sizeof(RegressionArgs), hipMemcpyHostToDevice, b->stream), "hipMemcpyAsync")) return ABS_E_HIP;
   if (!hip(hipStreamSynchronize(b->stream), "hipStreamSynchronize")) return ABS_E_HIP;
-  // A simulation's selection, descriptor and Eq. 4-6 take the host about a microsecond per round (16 workers),
-  // and the threads' phase changes as long as a few simulations: eight threads from 64 simulations on.
-  // (microseconds per round, one thread per 32 simulations started by every call / these: linear, 64
-  // simulations 30-36 / 30, 128 38-44 / 35, 256 57 / 52; softmax 64 64-71 / 60, 128 90 / 80; a thread per
-  // eight simulations below 64: linear 16 23.1 / 25.0, 32 26.4 / 29.3, softmax 16 40.8 / 42.8.)
-  const int helpers = n >= 64 ? std::min(8, (int)std::thread::hardware_concurrency() / 2) - 1 : 0;
-  if (helpers > 0) b->pool.reset(new HostPool(helpers));
+  if (most_threads(n) > 1) b->pool.reset(new HostPool(most_threads(n) - 1));
   *out = b.release();
   return ABS_OK;
 }
 
-// The host part of a batched round (select, descriptor, mailbox, Eq. 4-6 per simulation) is
-// independent per simulation, so large batches spread it over the batch's threads: thread k owns simulations lo + k, lo + k + T, ... of the group [lo, hi) in
-// hand.  A round of a group has two parallel phases around the launch; workers spin on a phase
-// counter (a round lasts tens of microseconds).
+// The host part of a batched round (select, descriptor, mailbox, Eq. 4-6 per simulation) is independent per
+// simulation, so large batches spread it over the batch's threads: thread k of T owns simulations lo + k,
+// lo + k + T, ... of the group [lo, hi) in hand.  A round of a group has two parallel phases around the launch
+// (Team: a round lasts tens of microseconds).
 namespace {
 struct BatchRoundState {
   abs_batch* b;
-  int S, T;
   std::vector<std::vector<Upload>> sel;
   std::vector<uint32_t> stamp;
   std::vector<int> kmax, rc, bad_sim;          // per thread
-  std::atomic<int> phase{0};                   // bumped for every parallel phase; `kind` says which
-  int kind = 0;                                // 0: prepare, 1: finish, -1: exit (written before the bump)
-  int lo = 0, hi = 0;                          // the group of simulations this phase is about
-  std::atomic<int> done{0};
+  int kind = 0;                                // this phase: 0: prepare, 1: finish
+  int lo = 0, hi = 0;                          // ... and the group of simulations it is about
   std::atomic<bool> abort{false};
   int buf = 0;
 
@@ -726,7 +683,7 @@ struct BatchRoundState {
     abort.store(true);
     return true;
   }
-  void prepare(int k) {                        // select the uploads, write the descriptors
+  void prepare(int k, int T) {                 // select the uploads, write the descriptors
     int km = 0;
     for (int i = lo + k; i < hi; i += T) {
       abs_ctx* ctx = b->ctx[(size_t)i];
@@ -740,7 +697,7 @@ struct BatchRoundState {
     }
     kmax[(size_t)k] = km;
   }
-  void finish(int k) {                         // wait for the losses, apply Eq. 4-6
+  void finish(int k, int T) {                  // wait for the losses, apply Eq. 4-6
     for (int i = lo + k; i < hi; i += T) {
       const LossMailbox* box = b->h_box + i;
       const int K = (int)sel[(size_t)i].size();
@@ -762,37 +719,21 @@ struct BatchRoundState {
       if (r != ABS_OK && rc[(size_t)k] == ABS_OK) { rc[(size_t)k] = r; bad_sim[(size_t)k] = i; }
     }
   }
-  void worker(int k) {
-    int seen = 0;
-    for (;;) {
-      int p;
-      while ((p = phase.load(std::memory_order_acquire)) == seen) {
-#if defined(__x86_64__)
-        __builtin_ia32_pause();
-#endif
-      }
-      if (kind < 0) return;
-      seen = p;
-      if (kind == 0) prepare(k); else finish(k);
-      done.fetch_add(1, std::memory_order_release);
-    }
-  }
-  // run one phase for simulations [lo_, hi_) on all threads (this one is thread 0); returns the
-  // first failing simulation's code
-  int run(int kind_, int lo_, int hi_) {
-    done.store(0, std::memory_order_relaxed);
+  void work(int k, int T) { if (kind == 0) prepare(k, T); else finish(k, T); }
+  // run one phase for simulations [lo_, hi_) on all threads of the team; returns the first failing
+  // simulation's code
+  int run(Team& team, int kind_, int lo_, int hi_) {
     wait_t0 = std::chrono::steady_clock::now();
     kind = kind_; lo = lo_; hi = hi_;
-    phase.fetch_add(1, std::memory_order_release);
-    if (kind_ == 0) prepare(0); else finish(0);
-    for (uint64_t spin = 1; done.load(std::memory_order_acquire) != T - 1; ++spin) {
-      if (kind_ == 1 && (spin & 0x3FFF) == 0 && !abort.load()) stream_failed();   // the others may still wait for mailboxes
-#if defined(__x86_64__)
-      __builtin_ia32_pause();
-#endif
+    if (kind_ == 0) std::fill(kmax.begin(), kmax.end(), 0);
+    team.phase([this] { if (kind == 1 && !abort.load()) stream_failed(); });    // the others may still wait for mailboxes
+    if (kind_ == 0 && team.size() > 1 && seconds_since(wait_t0) > kStarvedPhase) {
+      team.keep_least();
+      b->few_until = std::chrono::steady_clock::now() + std::chrono::duration_cast<std::chrono::steady_clock::duration>(
+                                                           std::chrono::duration<double>(kStarvedFor));
     }
     int first = -2, code = ABS_OK;
-    for (int k = 0; k < T; ++k)
+    for (size_t k = 0; k < rc.size(); ++k)
       if (rc[(size_t)k] != ABS_OK && (first == -2 || bad_sim[(size_t)k] < first)) { first = bad_sim[(size_t)k]; code = rc[(size_t)k]; }
     if (code != ABS_OK && first >= 0) b->err = "simulation " + std::to_string(first) + ": " + b->ctx[(size_t)first]->err;
     return code;
@@ -845,13 +786,12 @@ int abs_batch_round(abs_batch* b, int32_t n_rounds) {
   if (chain_model(c0.model)) return batch_round_mlp(b, n_rounds);
   BatchRoundState st;
   st.b = b;
-  st.S = S;
-  st.T = 1 + (b->pool ? b->pool->size() : 0);
+  const size_t max_threads = 1 + (size_t)(b->pool ? b->pool->size() : 0);
   st.sel.resize((size_t)S);
   st.stamp.resize((size_t)S);
-  st.kmax.assign((size_t)st.T, 0);
-  st.rc.assign((size_t)st.T, ABS_OK);
-  st.bad_sim.assign((size_t)st.T, -1);
+  st.kmax.assign(max_threads, 0);
+  st.rc.assign(max_threads, ABS_OK);
+  st.bad_sim.assign(max_threads, -1);
   // Large batches advance as G groups, staggered in time: while the device works on one group's
   // round the host finishes and prepares another's (Eq. 5 makes a simulation's next selection wait
   // for its own losses, not for the other groups').
@@ -876,18 +816,16 @@ int abs_batch_round(abs_batch* b, int32_t n_rounds) {
     for (int g = 1; g < G && e == hipSuccess; ++g) e = hipStreamWaitEvent(gstream[g], b->ev_in, 0);
     if (e != hipSuccess) { b->err = std::string("hipStreamWaitEvent: ") + hipGetErrorString(e); return ABS_E_HIP; }
   }
-  const std::function<void(int)> work = [&st](int k) { st.worker(k); };
-  if (st.T > 1) b->pool->start(work);       // from here on every path waits for them
   bool inflight[kBatchGroups] = {};
-  auto finish = [&](int g) {
+  auto finish = [&](Team& team, int g) {
     inflight[g] = false;
-    return st.run(1, lo[g], hi[g]);
+    return st.run(team, 1, lo[g], hi[g]);
   };
-  auto start = [&](int g) {
-    int r = st.run(0, lo[g], hi[g]);
+  auto start = [&](Team& team, int g) {
+    int r = st.run(team, 0, lo[g], hi[g]);
     if (r != ABS_OK) return r;
     int Kmax = 0;
-    for (int k = 0; k < st.T; ++k) Kmax = std::max(Kmax, st.kmax[(size_t)k]);
+    for (int k : st.kmax) Kmax = std::max(Kmax, k);
     const size_t off = (size_t)lo[g] * b->rd_stride, n = (size_t)(hi[g] - lo[g]);
     hipError_t e = hipMemcpyAsync(b->d_rds[st.buf] + off, b->h_rds[st.buf] + off, n * b->rd_stride, hipMemcpyHostToDevice, gstream[g]);
     if (e == hipSuccess && c0.U > 1)
@@ -901,25 +839,26 @@ int abs_batch_round(abs_batch* b, int32_t n_rounds) {
     return (int)ABS_OK;
   };
   int rc = ABS_OK;
-  for (int32_t it = 0; it < n_rounds && rc == ABS_OK; ++it) {
-    st.buf = (int)(it & 1);
-    for (int g = 0; g < G && rc == ABS_OK; ++g) {
-      if (inflight[g]) rc = finish(g);
-      if (rc == ABS_OK) rc = start(g);
+  {
+    const int least = least_threads(S), wish = std::chrono::steady_clock::now() < b->few_until ? least : most_threads(S);
+    Team team(b->pool.get(), batch_threads(), least, std::max(least, wish), [&st](int k, int T) { st.work(k, T); });
+    for (int32_t it = 0; it < n_rounds && rc == ABS_OK; ++it) {
+      st.buf = (int)(it & 1);
+      for (int g = 0; g < G && rc == ABS_OK; ++g) {
+        if (inflight[g]) rc = finish(team, g);
+        if (rc == ABS_OK) rc = start(team, g);
+      }
+      if (rc == ABS_OK) b->rounds += 1;
     }
-    if (rc == ABS_OK) b->rounds += 1;
+    // rounds still on the device are completed also after an error (their uploads are selected and
+    // their kernels enqueued); the first error is the one reported
+    for (int g = 0; g < G; ++g) {
+      if (!inflight[g]) continue;
+      const std::string first = b->err;
+      const int r = finish(team, g);
+      if (rc == ABS_OK) rc = r; else b->err = first;
+    }
   }
-  // rounds still on the device are completed also after an error (their uploads are selected and
-  // their kernels enqueued); the first error is the one reported
-  for (int g = 0; g < G; ++g) {
-    if (!inflight[g]) continue;
-    const std::string first = b->err;
-    const int r = finish(g);
-    if (rc == ABS_OK) rc = r; else b->err = first;
-  }
-  st.kind = -1;
-  st.phase.fetch_add(1, std::memory_order_release);
-  if (st.T > 1) b->pool->wait();
   if (G > 1 && n_rounds > 0) {
     hipError_t e = hipSuccess;
     for (int g = 1; g < G && e == hipSuccess; ++g) {

@@ -1,0 +1,115 @@
+// Driver of csrc/host_pool.h for the sanitizers (see test_host_pool.py): every check aborts with a message.
+#include <cstdio>
+#include <cstdlib>
+#include <new>
+
+#include "../paper_2301_08895_amd/csrc/host_pool.h"
+
+using namespace abs_impl;
+
+static thread_local long t_allocs_left = -1;       // >= 0: that many allocations of this thread still succeed
+void* operator new(std::size_t n) {
+  if (t_allocs_left == 0) throw std::bad_alloc();
+  if (t_allocs_left > 0) --t_allocs_left;
+  if (void* p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
+
+#define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "line %d: %s\n", __LINE__, #c); std::abort(); } } while (0)
+
+// phases in which item i belongs to thread i % T: every item is taken exactly once, whatever T becomes
+struct Call {
+  std::vector<int> items = std::vector<int>(37, 0);
+  void work(int k, int T) { for (size_t i = (size_t)k; i < items.size(); i += (size_t)T) ++items[i]; }
+  void phases(Team& team, int n) {
+    for (int p = 0; p < n; ++p) team.phase([] {});
+  }
+  void done(int n) { for (int v : items) CHECK(v == n); }
+};
+
+static void alone(HostPool& pool, SpinBudget& budget) {
+  for (int call = 0; call < 40; ++call) {
+    Call c;
+    Team team(&pool, budget, 2, 8, [&](int k, int T) { c.work(k, T); });
+    CHECK(team.size() == 8 && budget.used() == 8);
+    c.phases(team, 5);
+    if (call % 3 == 0) { team.keep_least(); CHECK(team.size() == 2 && budget.used() == 2); }
+    c.phases(team, 5);
+    c.done(10);
+  }
+  CHECK(budget.used() == 0);
+}
+
+// Four calls at once: each keeps its least once all of them are there, and the sum stays at the budget.
+static void together() {
+  SpinBudget budget(8);
+  std::atomic<int> here{0}, settled{0};
+  auto caller = [&] {
+    HostPool pool(7);
+    for (int call = 0; call < 10; ++call) {
+      Call c;
+      {
+        Team team(&pool, budget, 2, 8, [&](int k, int T) { c.work(k, T); });
+        ++here;
+        while (here.load() < 4 * (call + 1)) { cpu_relax(); std::this_thread::yield(); }
+        c.phases(team, 1);
+        ++settled;
+        while (settled.load() < 4 * (call + 1)) { cpu_relax(); std::this_thread::yield(); }
+        CHECK(team.size() == 2);
+        CHECK(budget.used() <= 8);
+        c.phases(team, 20);
+        ++here; --here;
+      }
+      c.done(21);
+    }
+  };
+  std::vector<std::thread> t;
+  for (int i = 0; i < 4; ++i) t.emplace_back(caller);
+  for (std::thread& x : t) x.join();
+  CHECK(budget.used() == 0);
+}
+
+static void thrown(HostPool& pool, SpinBudget& budget) {
+  for (int i = 0; i < 20; ++i) {
+    bool caught = false;
+    try {
+      Team team(&pool, budget, 2, 8, [&](int k, int) { if (k == 0) throw std::bad_alloc(); });
+      team.phase([] {});
+    } catch (const std::bad_alloc&) { caught = true; }
+    CHECK(caught && budget.used() == 0);
+  }
+}
+
+static void short_of_memory(SpinBudget& budget) {
+  for (long left = 0; left < 12; ++left) {
+    t_allocs_left = left;
+    HostPool pool(7);
+    t_allocs_left = -1;
+    CHECK(pool.size() <= 7);
+    Call c;
+    Team team(&pool, budget, 2, 8, [&](int k, int T) { c.work(k, T); });
+    CHECK(team.size() == 1 + pool.size());
+    c.phases(team, 3);
+    c.done(3);
+  }
+}
+
+int main() {
+  SpinBudget budget(8);
+  HostPool pool(7);
+  alone(pool, budget);
+  thrown(pool, budget);
+  alone(pool, budget);
+  short_of_memory(budget);
+  together();
+  {
+    Call c;                                         // no pool at all
+    Team team(nullptr, budget, 1, 1, [&](int k, int T) { c.work(k, T); });
+    c.phases(team, 4);
+    c.done(4);
+  }
+  std::puts("ok");
+  return 0;
+}

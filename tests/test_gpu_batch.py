@@ -363,3 +363,39 @@ def test_many_short_calls_equal_one_long_call(S):
             s.close()
     for (m0, t0), (m1, t1) in zip(*out):
         assert np.array_equal(m0, m1) and np.array_equal(t0, t1)
+
+
+def test_batches_driven_from_several_threads_at_once():
+    """Calls that run side by side share the process's budget of host threads (a call's number of them changes
+    while it runs); results are those of the batches driven one after the other."""
+    import threading
+    import torch
+    base = workloads.scaled_preset(1, M=1000, dims=[12, 1], N=5, B=4, K0=2)
+    d = workloads.make_inputs(base)
+    out = []
+    for at_once in (False, True):
+        batches, sims = [], []
+        for b in range(4):
+            with torch.cuda.stream(torch.cuda.Stream()):
+                sims.append([lib.Simulation(dict(p, seed_sim=p["seed_sim"] + 1000 * b), d) for p in _variants(base, 64 + b)])
+                batches.append(lib.Batch(sims[-1]))
+
+        def drive(b):
+            for n in (1, 7, 40):
+                batches[b].round(n)
+        threads = [threading.Thread(target=drive, args=(b,)) for b in range(4)]
+        for t in threads:
+            t.start()
+            if not at_once:
+                t.join()
+        for t in threads:
+            t.join()
+        out.append([(s.model().copy(), s.trace().copy()) for ss in sims for s in ss])
+        for b in batches:
+            b.close()
+        for ss in sims:
+            for s in ss:
+                s.close()
+    assert len(out[0]) == len(out[1]) == 4 * 64 + 6
+    for (m0, t0), (m1, t1) in zip(*out):
+        assert np.array_equal(m0, m1) and np.array_equal(t0, t1)
