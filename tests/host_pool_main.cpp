@@ -45,22 +45,24 @@ static void alone(HostPool& pool, SpinBudget& budget) {
 // Four calls at once: each keeps its least once all of them are there, and the sum stays at the budget.
 static void together() {
   SpinBudget budget(8);
-  std::atomic<int> here{0}, settled{0};
+  std::atomic<int> here{0}, settled{0}, checked{0};
+  auto meet = [](std::atomic<int>& at, int call) {          // all four callers get here
+    ++at;
+    while (at.load() < 4 * (call + 1)) { cpu_relax(); std::this_thread::yield(); }
+  };
   auto caller = [&] {
     HostPool pool(7);
     for (int call = 0; call < 10; ++call) {
       Call c;
       {
         Team team(&pool, budget, 2, 8, [&](int k, int T) { c.work(k, T); });
-        ++here;
-        while (here.load() < 4 * (call + 1)) { cpu_relax(); std::this_thread::yield(); }
+        meet(here, call);
         c.phases(team, 1);
-        ++settled;
-        while (settled.load() < 4 * (call + 1)) { cpu_relax(); std::this_thread::yield(); }
+        meet(settled, call);
         CHECK(team.size() == 2);
-        CHECK(budget.used() <= 8);
+        CHECK(budget.used() == 8);
+        meet(checked, call);                         // (a call that ends and begins anew may take more for one phase)
         c.phases(team, 20);
-        ++here; --here;
       }
       c.done(21);
     }

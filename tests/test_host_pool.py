@@ -17,5 +17,5 @@ def test_team_phases(sanitizer, tmp_path):
                         os.path.join(ROOT, "tests", "host_pool_main.cpp"), "-o", exe],
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout
-    r = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=120)
+    r = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout == "ok\n", f"sanitizer report or crash:\n{r.stderr[-3000:]}"
