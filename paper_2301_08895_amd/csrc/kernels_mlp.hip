@@ -1933,25 +1933,16 @@ unsigned mlp_forward(const MlpArgs& a, const uint16_t* Xsrc, const RoundDesc& rd
 // Output layer of a training pass: logits, loss sums per 32 rows, dZ_L in both orientations and its
 // column sums, in one kernel (mlp_logits_ce_kernel).
 void launch_logits_ce(const MlpArgs& a, const RoundDesc& rd, int rows, double arows, const float* wbase,
-                      const uint16_t* sbase, bool own, bool gather_t, hipStream_t s, LaunchHook* hook) {
+                      const uint16_t* sbase, bool own, int gather_blocks, hipStream_t s, LaunchHook* hook) {
   const MlpPlan& p = a.plan;
   const int L = p.L;
   LogitsCeArgs c{};
-  if (gather_t) {
-    GatherT gt{};
-    gt.X = a.X; gt.d0 = p.d[0]; gt.dp0 = p.dp[0];
-    gt.rowidx = at<uint32_t>(a, p.off_rowidx);
-    gt.XgT = at<uint16_t>(a, p.off_xgt); gt.ldt = p.ldm;
-    gt.blocks = (rows / 64) * ((p.dp[0] + 255) / 256);
-    if (gt.blocks <= kGatherRide) {
-      plan_note("with_gather_t", 64, 256, 1);
-      c.gt = gt;
-    } else {
-      kbegin(hook, KK_MLP_GATHER_T, 0, arows * p.d[0] * 4.0);
-      plan_note("gather_t", 64, 64, 1);
-      ABS_LAUNCH_K(mlp_gather_t_kernel, dim3(rows / 64, p.dp[0] / 64), dim3(256), s, gt.X, gt.d0, gt.rowidx, gt.XgT, gt.ldt);
-      kend(hook, KK_MLP_GATHER_T);
-    }
+  if (gather_blocks) {
+    c.gt.X = a.X; c.gt.d0 = p.d[0]; c.gt.dp0 = p.dp[0];
+    c.gt.rowidx = at<uint32_t>(a, p.off_rowidx);
+    c.gt.XgT = at<uint16_t>(a, p.off_xgt); c.gt.ldt = p.ldm;
+    c.gt.blocks = gather_blocks;
+    plan_note("with_gather_t", 64, 256, 1);
   }
   c.H = at<uint16_t>(a, p.off_h[L - 1]); c.ldh = (size_t)p.ld[L - 1];
   c.ksteps = p.dp[L - 1] / BK;
@@ -2026,7 +2017,8 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
                                            (long)step * (long)p.B, s, hook);
 
     // ---- output layer: loss and output gradient, already scaled by the uploads' coefficients
-    launch_logits_ce(a, rd, rows, arows, wbase, sbase, own, !wg0_direct, s, hook);
+    const int gather_blocks = wg0_direct ? 0 : (rows / 64) * ((p.dp[0] + 255) / 256);
+    launch_logits_ce(a, rd, rows, arows, wbase, sbase, own, gather_blocks <= kGatherRide ? gather_blocks : 0, s, hook);
     const int loss_blocks = p.Bp / kCeRows;          // row blocks of the loss sums per upload
 
     // ---- input gradients back through W_{L-1} .. W_1 (none is needed for the first layer)
@@ -2067,6 +2059,16 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
       else                    launch_gemm<EPI_DGRAD, false, true, 0>(g, rd, rows, p.dp[l], 1, s);
       dz_transposed = next_transposed;
       kend(hook, kind);
+    }
+
+    if (gather_blocks > kGatherRide) {
+      // (right before its reader, which then finds it in the caches; ahead of the output layer the first layer's
+      // weight gradient took 73 instead of 59 us at 16384 x 1024)
+      kbegin(hook, KK_MLP_GATHER_T, 0, arows * p.d[0] * 4.0);
+      plan_note("gather_t", 64, 64, 1);
+      ABS_LAUNCH_K(mlp_gather_t_kernel, dim3(rows / 64, p.dp[0] / 64), dim3(256), s, a.X, p.d[0], (const uint32_t*)rowidx,
+                   at<uint16_t>(a, p.off_xgt), p.ldm);
+      kend(hook, KK_MLP_GATHER_T);
     }
 
     // ---- weight gradients.  U = 1: one contraction over all stacked rows = the K-of-N
