@@ -474,7 +474,7 @@ __device__ __forceinline__ void ring_wait_barrier() {
 //  * tiles travel global -> LDS by DMA through a ring of RING k-steps, RING - 1 of them on
 //    their way at any time (one wait, one barrier and one batch of requests per stage);
 //  * a wavefront owns a 64 x 64 sub-tile (2 x 2 blocks of MFMA 32x32x16, the fewest fragment bytes per
-//    flop that 64 accumulator registers allow), and the KG wavefront groups of a workgroup share the
+//    flop that 64 accumulator registers allow), and the KG wavefront groups of a workgroup (1, 2 or 4) share the
 //    CONTRACTION of a step, not its columns: two wavefronts per SIMD cover each other's fragment reads
 //    without staging a byte more.  At the end the groups exchange blocks through LDS, every group adds
 //    and finishes OWN of its sub-tile's four blocks (always in group order);
@@ -486,11 +486,11 @@ __device__ __forceinline__ void ring_wait_barrier() {
 // per clock from beyond its L1 whatever the ring's depth, about 30 KB in flight over the latency of a miss.
 // A tile row is 128 bytes; its 16-byte chunk c is stored at position c ^ ((row >> 1) & 7): the 16 lanes
 // that one cycle of a 128-bit LDS read serves (16 consecutive rows of a fragment) then cover all 64 banks.
-template <int T>
+template <int T, int KG_>
 struct TileCfg {
   static constexpr int WS = T / 64;                      // 64 x 64 sub-tiles along each side
-  static constexpr int KG = T == 128 ? 2 : 4;            // wavefront groups along the contraction
-  static constexpr int NW = WS * WS * KG, NT = NW * 64;  // wavefronts (8; 4 for the 64 x 64 tile), threads
+  static constexpr int KG = KG_;                         // wavefront groups along the contraction
+  static constexpr int NW = WS * WS * KG, NT = NW * 64;  // wavefronts, threads
   static constexpr int OWN = 4 / KG;                     // blocks a wavefront finishes
   static constexpr int kStage = 2 * T * BK;              // elements of a k-step's tiles
   static constexpr int kRed = WS * WS * 4 * (KG - 1) * 1024 * 2;   // exchanged blocks (in elements of 2 bytes)
@@ -498,9 +498,9 @@ struct TileCfg {
   static constexpr int kOut = 2 * T * kPitch + (T / 32) * T * 2;   // both orientations, column sums per 32 rows
 };
 
-template <int T, int EPI, bool GATHER, bool PER_UPLOAD, int TAG, int RING>
-__global__ __launch_bounds__(TileCfg<T>::NT, 2) void mlp_tile_kernel(GemmArgs g, RoundDesc rd) {
-  using Cfg = TileCfg<T>;
+template <int T, int KGS, int EPI, bool GATHER, bool PER_UPLOAD, int TAG, int RING>
+__global__ __launch_bounds__((TileCfg<T, KGS>::NT), 2) void mlp_tile_kernel(GemmArgs g, RoundDesc rd) {
+  using Cfg = TileCfg<T, KGS>;
   constexpr int NW = Cfg::NW, NT = Cfg::NT, KG = Cfg::KG, OWN = Cfg::OWN;
   constexpr bool kLocal = EPI == EPI_WGRAD && TAG >= 4;  // local SGD: the epilogue takes the step (LocalUpdate)
   constexpr bool kStageT = (EPI == EPI_RELU || EPI == EPI_DGRAD || kLocal);
@@ -626,6 +626,14 @@ __global__ __launch_bounds__(TileCfg<T>::NT, 2) void mlp_tile_kernel(GemmArgs g,
 #pragma unroll
         for (int j = 0; j < 2; ++j)
           acc[2 * i + j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[s][i], vb[s][j], acc[2 * i + j], 0, 0, 0);
+    }
+    if (KG == 1) {
+      // issue order: the first fragments, then one read behind each MFMA (left to the compiler: first-layer
+      // weight gradient 2048 x 1152 over 8192 rows 50.6 instead of 46.2 us)
+      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+      for (int i = 0; i < 12; ++i) { __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); }
+      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
     }
   }
 #undef ABS_TILE_DMA
@@ -782,6 +790,212 @@ __global__ __launch_bounds__(TileCfg<T>::NT, 2) void mlp_tile_kernel(GemmArgs g,
         const int rb = q / T, nl = q % T;
         g.colsum[(size_t)((m0 >> 6) + rb) * g.ldcs + n0 + nl] = sC[2 * rb * T + nl] + sC[(2 * rb + 1) * T + nl];
       }
+    }
+  }
+}
+
+// ------------------------------------------------------------------ the GEMM on tiles of 128 x 256
+// Products of uploads whose padded rows are not whole 256-row tiles (or whose gathered rows are not whole
+// k-steps), once they are many: half of the bytes per flop of a 128 x 128 tile's columns, and two workgroups per
+// CU, so that one's multiplications cover the other's barriers and epilogue.  One LDS stage; the next
+// k-step's tiles are on their way in registers (two stages would leave room for one workgroup).
+// 256 threads = 2 x 2 wavefronts of 64 x 128 (2 x 4 blocks of MFMA 32x32x16, 128 accumulator registers).  LDS layout
+// as in mlp_tile_kernel.
+constexpr int TNW = 256;
+constexpr int kWideMain = (TM + TNW) * BK;               // elements of a k-step's tiles (48 KB)
+constexpr int kWidePitch = 64 + 8;                       // of a wavefront's staged results [128 n][64 m]
+constexpr int kWideEpi = 4 * 128 * kWidePitch;
+template <int EPI, bool GATHER, bool PER_UPLOAD, int TAG>
+__global__ __launch_bounds__(256, 2) void mlp_wide_kernel(GemmArgs g, RoundDesc rd) {
+  constexpr bool kStageT = EPI == EPI_RELU || EPI == EPI_DGRAD;
+  __shared__ __attribute__((aligned(16))) uint16_t smem[kStageT ? kWideEpi : kWideMain];
+  __shared__ uint32_t s_row[GATHER ? TM : 1];
+  static_assert(kWideEpi >= kWideMain && kWideEpi * 2 + TM * 4 <= 80 * 1024, "two workgroups per CU");
+
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int bx = blockIdx.x;
+  if (EPI == EPI_WGRAD && (g.pig_blocks | g.bias_blocks)) {      // (see mlp_tile_kernel)
+    const int own = (int)gridDim.x - g.pig_blocks - g.bias_blocks;
+    if (bx >= own + g.pig_blocks) {
+      rider_bias<false>(g, rd, bx - own - g.pig_blocks, (float*)smem);
+      return;
+    }
+    if (bx >= own) { piggy_update<256, false>(g, bx - own, smem); return; }
+  }
+  const int xcd = bx & 7, jx = bx >> 3;                          // block -> tile as in mlp_tile_kernel
+  const int trow = xcd * g.rows_per_xcd + jx / g.nt;
+  if (trow >= g.mt * g.nsplit) return;
+  const int zsplit = trow / g.mt;
+  const int m0 = (trow - zsplit * g.mt) * TM, n0 = (jx % g.nt) * TNW;
+  const int ks0 = zsplit * g.ksteps_per_split;
+  const int ks1 = min(g.ksteps_total, ks0 + g.ksteps_per_split);
+
+  if (EPI == EPI_DGRAD && g.pub_rowloss && blockIdx.x == 0) publish_upload_losses(g, rd.K, rd.stamp);
+
+  const uint16_t* Bt = g.Bt;
+  uint32_t slot = 0;
+  if (PER_UPLOAD) {
+    slot = g.by_upload ? (uint32_t)(m0 / g.rows_per_upload) : rd.w[m0 / g.rows_per_upload].slot;
+    Bt += (size_t)slot * g.bt_slot_stride;
+  }
+  // thread t moves the 16-byte column t & 7 of rows (t >> 3) + 32 i of both tiles
+  const int r0 = t >> 3, c8 = (t & 7) * 8;
+  const int st_off = r0 * BK + (((t & 7) ^ ((r0 >> 1) & 7)) << 3);
+  const uint16_t* pa[4];
+  if (GATHER) {
+    if (t < TM) {
+      uint32_t row;
+      if (g.gen_rows) {
+        bool real;
+        row = gen_row_of(g, rd, m0 + t, &real);
+        if (n0 == 0) gen_row_store(g, m0 + t, row, real);
+      } else {
+        row = g.a_rowidx[m0 + t];
+      }
+      s_row[t] = row;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) pa[i] = g.A + (size_t)s_row[r0 + 32 * i] * g.lda + c8;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) pa[i] = g.A + (size_t)(m0 + r0 + 32 * i) * g.lda + c8;
+  }
+  const uint16_t* const pb = Bt + (size_t)(n0 + r0) * g.ldb + c8;
+  const size_t b_step = 32 * g.ldb;
+
+  f32x16_t acc[2][4];
+#pragma unroll
+  for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < 4; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+
+  u32x4_t ra[4], rb[8];
+#define ABS_FETCH(ks_)                                                                                      \
+  {                                                                                                         \
+    const int k0_ = (ks_) * BK;                                                                             \
+    const bool in_ = !GATHER || k0_ + c8 < g.a_kvalid;      /* padding of gathered rows reads as zero */    \
+    _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                           \
+      ra[i] = in_ ? *(const u32x4_t*)(pa[i] + k0_) : u32x4_t{0, 0, 0, 0};                                   \
+    _Pragma("unroll") for (int i = 0; i < 8; ++i) rb[i] = *(const u32x4_t*)(pb + i * b_step + k0_);         \
+  }
+  const int lr = lane & 31, lk = lane >> 5;
+  const int fa_row = (wm * 64 + lr) * BK, fb_row = TM * BK + (wn * 128 + lr) * BK;
+  const int sw = (lr >> 1) & 7;
+  if (ks0 < ks1) ABS_FETCH(ks0);
+  for (int ks = ks0; ks < ks1; ++ks) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *(u32x4_t*)&smem[st_off + 32 * i * BK] = ra[i];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) *(u32x4_t*)&smem[TM * BK + st_off + 32 * i * BK] = rb[i];
+    __syncthreads();
+    if (ks + 1 < ks1) ABS_FETCH(ks + 1);
+    // fragments of sub-step s + 1 are read while the MFMAs of sub-step s run
+    bf16x8_t fa[2][2], fb[2][4];
+#define ABS_FRAGS(set, s_)                                                                                            \
+  {                                                                                                                   \
+    const int ch_ = ((((s_) << 1) | lk) ^ sw) << 3;                                                                   \
+    _Pragma("unroll") for (int i = 0; i < 2; ++i) fa[set][i] = *(const bf16x8_t*)&smem[fa_row + i * 32 * BK + ch_];   \
+    _Pragma("unroll") for (int i = 0; i < 4; ++i) fb[set][i] = *(const bf16x8_t*)&smem[fb_row + i * 32 * BK + ch_];   \
+  }
+    ABS_FRAGS(0, 0);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if (s < 3) ABS_FRAGS((s + 1) & 1, s + 1);
+#pragma unroll
+      for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < 4; ++ni)
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s & 1][mi], fb[s & 1][ni], acc[mi][ni], 0, 0, 0);
+    }
+#undef ABS_FRAGS
+    // issue order: the first fragments, then one read behind each of a sub-step's first six MFMAs
+    __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+#pragma unroll
+      for (int i = 0; i < 6; ++i) { __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); }
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+    __syncthreads();
+  }
+#undef ABS_FETCH
+
+  // ---- epilogue: a wavefront's own 64 x 128 block (accumulator layout as in mlp_tile_kernel)
+  const int lrow4 = lk * 4, mrow = m0 + wm * 64, ncol = n0 + wn * 128;
+  const float* bias = nullptr;
+  if (EPI == EPI_RELU || EPI == EPI_LOGITS) bias = g.bias + (size_t)slot * g.bias_slot_stride;
+  float* outf = g.outf;
+  if (EPI == EPI_WGRAD) outf += (size_t)zsplit * g.split_stride;
+  uint16_t* const sE = smem + wave * (128 * kWidePitch);
+  if (EPI == EPI_DGRAD) {
+    // the ReLU mask, H_l^T, as whole 128-byte rows; a lane later replaces the 4 entries it read by its 4 results
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int q = lane + 64 * i, nl = q >> 3, ch = (q & 7) * 8;
+      *(uint4*)&sE[nl * kWidePitch + ch] = *(const uint4*)(g.maskT + (size_t)(ncol + nl) * g.ldmaskT + mrow + ch);
+    }
+  }
+  float cs[4] = {0.f, 0.f, 0.f, 0.f};     // EPI_DGRAD: column sums over the 64 rows
+#pragma unroll
+  for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < 4; ++ni) {
+      const int nl = ni * 32 + lr, n = ncol + nl;
+      float bv = 0.f;
+      if (EPI == EPI_RELU || EPI == EPI_LOGITS) bv = n < g.n_valid ? bias[n] : 0.f;
+#pragma unroll
+      for (int rg = 0; rg < 4; ++rg) {
+        const int ml = mi * 32 + rg * 8 + lrow4;
+        uint16_t h[4];
+        uint2 hm = make_uint2(0, 0);
+        if (EPI == EPI_DGRAD) hm = *(const uint2*)&sE[nl * kWidePitch + ml];
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+          const size_t m = (size_t)(mrow + ml + rr);
+          float v = acc[mi][ni][rg * 4 + rr];
+          if (EPI == EPI_RELU) {
+            v = fmaxf(v + bv, 0.f);
+          } else if (EPI == EPI_LOGITS) {
+            outf[m * g.ldof + n] = v + bv;
+          } else if (EPI == EPI_DGRAD) {
+            const uint32_t pair = rr < 2 ? hm.x : hm.y;
+            v = ((pair >> ((rr & 1) * 16)) & 0x7FFFu) ? v : 0.f;
+          } else {
+            outf[m * g.ldof + n] = v;
+          }
+          if (kStageT) {
+            h[rr] = f32_to_bf16(v);
+            if (EPI == EPI_DGRAD) cs[ni] += __uint_as_float((uint32_t)h[rr] << 16);
+            if (g.out) g.out[m * g.ldo + n] = h[rr];
+          }
+        }
+        if (kStageT) {
+          uint2 o;
+          o.x = h[0] | ((uint32_t)h[1] << 16);
+          o.y = h[2] | ((uint32_t)h[3] << 16);
+          *(uint2*)&sE[nl * kWidePitch + ml] = o;
+        }
+      }
+    }
+  if (EPI == EPI_DGRAD) {
+    // (the two half-wavefronts hold alternate groups of 4 rows)
+#pragma unroll
+    for (int ni = 0; ni < 4; ++ni) {
+      const float c = cs[ni] + __shfl_xor(cs[ni], 32, 64);
+      if (lane < 32) g.colsum[(size_t)(mrow >> 6) * g.ldcs + ncol + ni * 32 + lr] = c;
+    }
+  }
+  if (kStageT) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int q = lane + 64 * i, nl = q >> 3, ch = (q & 7) * 8;
+      *(uint4*)(g.outT + (size_t)(ncol + nl) * g.ldoT + mrow + ch) = *(const uint4*)&sE[nl * kWidePitch + ch];
     }
   }
 }
@@ -1598,6 +1812,13 @@ int pick_split(int tiles, int ksteps, int slots, double tile_bytes, double step_
 bool wgrad_wide_tiles(int Mdim, int Ndim, int ksteps) {
   return Ndim % 128 == 0 && (Mdim / 128) * (Ndim / 128) * std::min(ksteps / 8, kMaxSplit) >= 256;
 }
+// ... or tiles of 128 x 256: two workgroups per CU with at least 25 k-steps each, in few splits (us of this product
+// and the next, which carries its update, with 128 x 128 / 128 x 256 tiles: 3200 x 2048 over 4096 rows 96 / 89, 8192:
+// 185 / 147; 1920 x 2048 over 8192: 96 / 97, 16384: 181 / 161; 3200 x 512 over 16384: 77 / 86).
+bool wgrad_256_columns(int Mdim, int Ndim, int ksteps) {
+  const int tiles = (Mdim / 128) * (Ndim / 256);
+  return Ndim % 256 == 0 && tiles >= 100 && tiles * ksteps >= 12800;
+}
 // Row-range splits of layer l's weight-gradient contraction over `rows` stacked rows
 // (per_upload > 0: local SGD, one split per upload).
 int wgrad_split(const MlpPlan& p, int l, int rows, int per_upload) {
@@ -1605,6 +1826,8 @@ int wgrad_split(const MlpPlan& p, int l, int rows, int per_upload) {
   const int ksteps = rows / BK;
   if (p.dp[l] % TM3 == 0 && p.dp[l + 1] % TN3 == 0)
     return pick_split((p.dp[l] / TM3) * (p.dp[l + 1] / TN3), ksteps, 256, 256.0 * 256 * 4, 2.0, 0.0);
+  if (wgrad_256_columns(p.dp[l], p.dp[l + 1], ksteps))
+    return pick_split((p.dp[l] / 128) * (p.dp[l + 1] / 256), ksteps, 512, 128.0 * 256 * 4, 1.5, 0.0);
   if (wgrad_wide_tiles(p.dp[l], p.dp[l + 1], ksteps))
     return pick_split((p.dp[l] / 128) * (p.dp[l + 1] / 128), ksteps, 512, 128.0 * 128 * 4, 0.5, 0.0);
   return pick_split((p.dp[l] / 64) * (p.dp[l + 1] / 64), ksteps, 512, 64.0 * 64 * 4, 0.25, 0.0);
@@ -1834,26 +2057,48 @@ bool launch_gemm(GemmArgs g, const RoundDesc& rd, int Mdim, int Ndim, int nsplit
     ABS_LAUNCH_K((mlp_gemm256_kernel<EPI, GATHER, PER_UPLOAD, TAG>), dim3(8 * g.rows_per_xcd * g.nt + g.pig_blocks + g.bias_blocks), dim3(512), s, g, rd);
     return true;
   }
+  // 128 x 256 tiles once they are two workgroups for every CU (below, 128 x 128 tiles in two workgroups per CU; us at
+  // uploads of 128 rows with 128 x 128 / 128 x 256: first layer 8192 x 2048 x 1024 57 / 49.5, 16384 x 2048 x 3072
+  // 258 / 217, hidden 8192 x 2048 x 2048 91 / 77, 16384 x 1024 x 1024 49 / 46; at half of that, 8192 x 1024 x 1024,
+  // 27 / 33).
+  if constexpr (TAG < 2) {
+    if (EPI == EPI_WGRAD ? wgrad_256_columns(Mdim, Ndim, g.ksteps_total)
+                         : Ndim % TNW == 0 && (Mdim / TM) * (Ndim / TNW) * nsplit >= 512) {
+      g.mt = Mdim / TM;
+      g.nt = Ndim / TNW;
+      g.rows_per_xcd = (g.mt * nsplit + 7) / 8;
+      plan_note(EPI == EPI_RELU ? "fwd_wide" : EPI == EPI_LOGITS ? "logits_wide" : EPI == EPI_DGRAD ? "dgrad_wide" : "wgrad_wide", TM, TNW, nsplit);
+      ABS_LAUNCH_K((mlp_wide_kernel<EPI, GATHER, PER_UPLOAD, TAG>), dim3(8 * g.rows_per_xcd * g.nt + g.pig_blocks + g.bias_blocks), dim3(256), s, g, rd);
+      return false;
+    }
+  }
   // 128-wide tiles once 64-wide ones would be more than the two workgroups a CU holds (a 64-wide workgroup
   // stages twice the bytes per flop, but a CU draws at most 23-32 bytes per clock from beyond the L1, so
   // a product spread over twice the CUs or in two workgroups per CU is the faster one; 3072 x 1024, us with
   // 64 / 128 wide tiles at 2048 rows: 31.5 / 35.1, 2560: 44.8 / 36.5, 3072: 46.3 / 37.0, 4608: 70.1 / 69.3).
+  // Up to one 128-wide tile per CU the two wavefront groups of a workgroup share the contraction (KG = 2); with
+  // more tiles than CUs each takes four wavefronts and a ring of two, so that two fit a CU and the second
+  // covers the first one's barriers and epilogue (us with KG = 2 / 1: 8192 x 1024 x 1024 31.4 / 26.9, first layer
+  // 8192 x 1024 x 3072 48 / 44, 8192 x 2048 x 2048 102 / 91).
   const bool wide = EPI == EPI_WGRAD ? wgrad_wide_tiles(Mdim, Ndim, g.ksteps_total)
                                      : Ndim % 128 == 0 && (Mdim / 128) * (Ndim / 128) * nsplit > 128;
   const int tile = wide ? 128 : 64;
   g.mt = Mdim / tile;
   g.nt = Ndim / tile;
   g.rows_per_xcd = (g.mt * nsplit + 7) / 8;
+  const bool pairs = wide && g.mt * g.nt * nsplit > 256;
   const dim3 grid(8 * g.rows_per_xcd * g.nt + g.pig_blocks + g.bias_blocks);
-  plan_note(EPI == EPI_RELU ? "fwd_tile" : EPI == EPI_LOGITS ? "logits_tile" : EPI == EPI_DGRAD ? "dgrad_tile" : TAG >= 4 ? "wgrad_step_tile" : "wgrad_tile", tile, tile, nsplit);
+  plan_note((std::string(EPI == EPI_RELU ? "fwd" : EPI == EPI_LOGITS ? "logits" : EPI == EPI_DGRAD ? "dgrad" : TAG >= 4 ? "wgrad_step" : "wgrad") +
+             (pairs ? "_tile2" : "_tile")).c_str(), tile, tile, nsplit);
   // Ring depths: forward and input-gradient products keep three steps on their way (64-wide: 64 KB, two
   // workgroups per CU; 8 steps and one workgroup: the evaluation's logits 22.5 instead of 16.8 us; 3 steps: cfg 3's
   // first layer 22.4 instead of 18.4).  A weight gradient carries the previous layer's update as extra
   // workgroups and leaves LDS for several of them per CU (128-wide, ring of 4 and one workgroup:
   // cfg 5's output layer 39 instead of 33 us).
   constexpr int kRing128 = EPI == EPI_WGRAD ? 2 : 4, kRing64 = EPI == EPI_WGRAD ? 3 : 4;
-  if (wide) ABS_LAUNCH_K((mlp_tile_kernel<128, EPI, GATHER, PER_UPLOAD, TAG, kRing128>), grid, dim3(TileCfg<128>::NT), s, g, rd);
-  else      ABS_LAUNCH_K((mlp_tile_kernel<64, EPI, GATHER, PER_UPLOAD, TAG, kRing64>), grid, dim3(TileCfg<64>::NT), s, g, rd);
+  if (pairs)     ABS_LAUNCH_K((mlp_tile_kernel<128, 1, EPI, GATHER, PER_UPLOAD, TAG, 2>), grid, dim3(TileCfg<128, 1>::NT), s, g, rd);
+  else if (wide) ABS_LAUNCH_K((mlp_tile_kernel<128, 2, EPI, GATHER, PER_UPLOAD, TAG, kRing128>), grid, dim3(TileCfg<128, 2>::NT), s, g, rd);
+  else           ABS_LAUNCH_K((mlp_tile_kernel<64, 4, EPI, GATHER, PER_UPLOAD, TAG, kRing64>), grid, dim3(TileCfg<64, 4>::NT), s, g, rd);
   return false;
 }
 

@@ -54,6 +54,10 @@ def test_softmax():
     (dict(M=8192, dims=[256, 128, 256, 100], n_classes=100, N=8, B=128, n_slow=0, lr=5e-4), 12, 2049),
     # 256 classes and passes of 128 * 256 rows: the logits product itself runs on the 256 x 256 tile kernel
     (dict(M=65536, dims=[128, 256, 256], n_classes=256, N=128, B=256, K0=4, n_slow=0, lr=2e-4), 3, 40_000),
+    # ... and passes of 20 000 rows, which are too few tiles for it, on pairs of 128 x 128 workgroups per CU; uploads
+    # of five row tiles and passes of 82 000 rows: logits in 128 x 256 tiles
+    (dict(M=65536, dims=[128, 256, 256], n_classes=256, N=128, B=256, K0=4, n_slow=0, lr=2e-4), 3, 20_000),
+    (dict(M=90000, dims=[72, 200, 250], n_classes=250, N=128, B=640, K0=2, n_slow=0, lr=2e-4), 2, 81_900),
 ])
 def test_mlp(over, T, rows):
     _check(workloads.scaled_preset(3, **over), T, rows, 2e-3)

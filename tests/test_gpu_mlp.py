@@ -108,6 +108,11 @@ def test_sampled_kernel_timing_changes_nothing():
     (dict(M=6400, dims=[1096, 64, 10], N=64, K0=64, B=100, n_slow=0, lr=2e-4), 2),
     # a weight gradient long enough for 128-wide tiles (128 k-steps, 128 padded classes)
     (dict(M=12800, dims=[64, 2048, 100], n_classes=100, N=64, K0=64, B=128, n_slow=0, lr=1e-4), 2),
+    # the fewest 128 x 256 tiles (512; ragged widths, a k-step with 8 valid columns), in a weight gradient
+    # too (104 tiles over 128 k-steps); one column tile fewer: two 128 x 128 workgroups per CU
+    (dict(M=25600, dims=[72, 1000, 1010, 10], N=128, K0=128, B=100, n_slow=0, lr=1e-4), 1),
+    (dict(M=25600, dims=[72, 1650, 2040, 10], N=64, K0=64, B=120, n_slow=0, lr=1e-4), 1),
+    (dict(M=25600, dims=[200, 700, 1000, 26], n_classes=26, N=60, K0=60, B=128, n_slow=0, lr=1e-4), 2),
 ])
 def test_tile_kernel_edges(over, T):
     """The tile kernel where its remainders are: short rings, zero-filled columns of gathered rows, both tile sizes."""

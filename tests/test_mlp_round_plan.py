@@ -14,3 +14,23 @@ def test_the_transposed_minibatch_is_written_right_before_its_reader():
     names = [item.split(":")[0] for item in _plan([2000, 1024, 1024, 10], 64, 128, 64)]
     at = names.index("gather_t")
     assert names[at + 1].startswith("wgrad") and names[at - 1].startswith("dgrad"), names
+
+
+def _items(dims, N, B, K, kind, U=1):
+    return [item for item in _plan(dims, N, B, K, U) if item.startswith(kind)]
+
+
+def test_tiles_of_products_with_more_tiles_than_cus():
+    """Uploads of 128 rows: 128 x 256 tiles from 512 of them on, below that pairs of 128 x 128 workgroups per CU, and one
+    workgroup per CU only while there is no second one."""
+    wide = [1024, 2048, 2048, 10]
+    assert _items(wide, 128, 128, 64, "fwd") == ["fwd_wide:128x256/1"] * 2
+    assert _items(wide, 128, 128, 64, "dgrad") == ["dgrad_wide:128x256/1"] * 2
+    assert _items(wide, 128, 128, 63, "fwd") == ["fwd_tile2:128x128/1"] * 2          # 504 tiles of 128 x 256
+    assert _items(wide, 128, 128, 17, "dgrad") == ["dgrad_tile2:128x128/1"] * 2      # 272 tiles of 128 x 128
+    assert _items(wide, 128, 128, 16, "fwd") == ["fwd_tile:128x128/1"] * 2           # 256
+    # gathered rows that are no whole k-steps stay off the 256 x 256 kernel whatever the uploads' rows
+    assert _items([3000, 2048, 2048, 100], 128, 256, 32, "fwd")[0] == "fwd_wide:128x256/1"
+    # weight gradients: 25 k-steps for each of two workgroups per CU, in few splits
+    assert _items([3200, 2048, 10], 128, 128, 64, "wgrad")[0] == "wgrad_wide:128x256/2"
+    assert _items([3200, 512, 10], 128, 128, 128, "wgrad")[0].startswith("wgrad_tile2:128x128/")
