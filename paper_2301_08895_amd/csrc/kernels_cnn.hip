@@ -141,12 +141,11 @@ __global__ __launch_bounds__(256) void cnn_conv_pool_fwd_kernel(CnnDev d, RoundD
 // cnn_conv_pool_fwd_kernel, so the results are bitwise the same.  Bound by the vector ALU and the LDS reads that feed
 // it, behind the latency of fetching image and filters; 160 rows of the 5 x 5 workload: 32 us in two launches of 256
 // threads, 15 us this way.
-constexpr int kFwdThreads = 1024;
-template <int KS>
+template <int KS, int NT>
 __device__ __forceinline__ void conv_pool_stage(const float* sx, int Cin, int Sin, const float* sw, const float* sb,
                                                 int Cout, int Sp, int k, float* s_out, float* g_out, uint8_t* g_arg) {
   const int win = Sp * Sp, Cop = (Cout + 1) & ~1, items = Cop / 2 * win;
-  for (int o = threadIdx.x; o < items; o += kFwdThreads) {
+  for (int o = threadIdx.x; o < items; o += NT) {
     const int co = o / win * 2, wi = o - o / win * win, pi = wi / Sp, pj = wi - pi * Sp;
     float a[2][4];
 #pragma unroll
@@ -210,8 +209,8 @@ __host__ __device__ __forceinline__ FwdLds fwd_lds(const CnnPlan& p) {
   o.total = o.p1 + p.C1 * p.S1 * p.S1;
   return o;
 }
-template <int KS>
-__global__ __launch_bounds__(kFwdThreads) void cnn_fwd_kernel(CnnDev d, RoundDesc rd) {
+template <int KS, int NT>
+__global__ __launch_bounds__(NT) void cnn_fwd_kernel(CnnDev d, RoundDesc rd) {
   extern __shared__ __attribute__((aligned(16))) float sm[];
   const CnnPlan& p = d.p;
   const int r = blockIdx.x, a = r / p.B, t = threadIdx.x, k = KS ? KS : p.k, kk = k * k;
@@ -226,37 +225,35 @@ __global__ __launch_bounds__(kFwdThreads) void cnn_fwd_kernel(CnnDev d, RoundDes
   }
   const int n_in = p.C0 * p.S * p.S;
   const float* src = d.X + row * (uint64_t)n_in;
-  for (int i = t; i < n_in; i += kFwdThreads) sm[i] = src[i];
+  for (int i = t; i < n_in; i += NT) sm[i] = src[i];
   const int c1p = (p.C1 + 1) & ~1, c2p = (p.C2 + 1) & ~1;
-  for (int i = t; i < p.C0 * kk * c1p; i += kFwdThreads) {
+  for (int i = t; i < p.C0 * kk * c1p; i += NT) {
     const int q = i / c1p, co = i - q * c1p;
     sm[at.w0 + i] = co < p.C1 ? w[p.w_off[0] + (size_t)q * p.C1 + co] : 0.f;
   }
-  for (int i = t; i < p.C1 * kk * c2p; i += kFwdThreads) {
+  for (int i = t; i < p.C1 * kk * c2p; i += NT) {
     const int q = i / c2p, co = i - q * c2p;
     sm[at.w1 + i] = co < p.C2 ? w[p.w_off[1] + (size_t)q * p.C2 + co] : 0.f;
   }
-  for (int i = t; i < p.C1 + p.C2; i += kFwdThreads) sm[at.b + i] = i < p.C1 ? w[p.b_off[0] + i] : w[p.b_off[1] + i - p.C1];
+  for (int i = t; i < p.C1 + p.C2; i += NT) sm[at.b + i] = i < p.C1 ? w[p.b_off[0] + i] : w[p.b_off[1] + i - p.C1];
   __syncthreads();
   const int n1 = p.C1 * p.S1 * p.S1;
-  conv_pool_stage<KS>(sm, p.C0, p.S, sm + at.w0, sm + at.b, p.C1, p.S1, k, sm + at.p1,
+  conv_pool_stage<KS, NT>(sm, p.C0, p.S, sm + at.w0, sm + at.b, p.C1, p.S1, k, sm + at.p1,
                       wsp<float>(d, p.off_p1) + (size_t)r * n1, wsp<uint8_t>(d, p.off_a1) + (size_t)r * n1);
   __syncthreads();
-  conv_pool_stage<KS>(sm + at.p1, p.C1, p.S1, sm + at.w1, sm + at.b + p.C1, p.C2, p.S2, k, nullptr,
+  conv_pool_stage<KS, NT>(sm + at.p1, p.C1, p.S1, sm + at.w1, sm + at.b + p.C1, p.C2, p.S2, k, nullptr,
                       wsp<float>(d, p.off_p2) + (size_t)r * p.F0, wsp<uint8_t>(d, p.off_a2) + (size_t)r * p.F0);
 }
 
 // The dense stack.  A workgroup takes G stacked rows of one upload; the rows' values of a feature sit next
 // to each other in LDS ([feature][row]), so one read feeds a weight's G sums.
-constexpr int kDenseThreads = 1024;
-
 // out[j][b] = bias[j] + sum_i in[i][b] W[i][j].  The workgroup is cut into slices of the input features,
 // each with a thread per column (neighbouring threads read neighbouring weights, sixteen of a column in
 // flight); the slices' sums are added in slice order.
-template <int G>
+template <int G, int NT>
 __device__ __forceinline__ void dense_rows(const float* s_in, int Fin, const float* W, const float* bias, int Fout,
                                            int nb, bool relu, float* s_part, float* s_out, float* g_out) {
-  const int fr = min((Fout + 31) & ~31, kDenseThreads), nz = kDenseThreads / fr, len = (Fin + nz - 1) / nz;
+  const int fr = min((Fout + 31) & ~31, NT), nz = NT / fr, len = (Fin + nz - 1) / nz;
   const int t = threadIdx.x, z = t / fr, j = t - z * fr;
   const float b0 = bias[min(t / G, Fout - 1)];             // (on its way under the sums)
   float acc[G];
@@ -282,7 +279,7 @@ __device__ __forceinline__ void dense_rows(const float* s_in, int Fin, const flo
     for (int q = 0; q < G; ++q) s_part[(z * fr + j) * G + q] = acc[q];
   }
   __syncthreads();
-  for (int o = t; o < Fout * G; o += kDenseThreads) {
+  for (int o = t; o < Fout * G; o += NT) {
     const int jo = o / G, q = o - jo * G;
     float v = o == t ? b0 : bias[jo];
     for (int zz = 0; zz < nz; ++zz) v += s_part[(zz * fr + jo) * G + q];
@@ -295,11 +292,11 @@ __device__ __forceinline__ void dense_rows(const float* s_in, int Fin, const flo
 
 // dIn[i][b] = gate(b, i) ? sum_j dOut[j][b] W[i][j] : 0: sixteen neighbouring lanes take input feature i and
 // read its row of weights in pieces of 64 bytes.
-template <int G, typename Gate>
+template <int G, int NT, typename Gate>
 __device__ __forceinline__ void dense_rows_back(const float* s_dout, int Fout, const float* W, int Fin, int nb,
                                                 Gate gate, float* s_din, float* g_din) {
   const int l = threadIdx.x & 15;
-  constexpr int kStep = kDenseThreads / 16;
+  constexpr int kStep = NT / 16;
   for (int i0 = threadIdx.x >> 4; i0 < Fin; i0 += 2 * kStep) {        // features i0 and i0 + kStep together
     float acc[2][G];
 #pragma unroll
@@ -340,6 +337,74 @@ __device__ __forceinline__ void dense_rows_back(const float* s_dout, int Fout, c
   __syncthreads();
 }
 
+// The same where a launch has workgroups enough to fill the chip several times over: a thread per column, all
+// input features in order, and on the way back a thread per input feature - no exchange between threads, which is what
+// the forms above pay for their fetches in flight.
+template <int G, int NT>
+__device__ __forceinline__ void dense_cols(const float* s_in, int Fin, const float* W, const float* bias, int Fout,
+                                           int nb, bool relu, float* s_out, float* g_out) {
+  for (int j = threadIdx.x; j < Fout; j += NT) {
+    float acc[G];
+    const float bv = bias[j];
+#pragma unroll
+    for (int q = 0; q < G; ++q) acc[q] = bv;
+    int i = 0;
+    for (; i + 8 <= Fin; i += 8) {
+      float wv[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) wv[e] = W[(size_t)(i + e) * Fout + j];
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int q = 0; q < G; ++q) acc[q] = fmaf(s_in[(i + e) * G + q], wv[e], acc[q]);
+    }
+    for (; i < Fin; ++i) {
+      const float wv = W[(size_t)i * Fout + j];
+#pragma unroll
+      for (int q = 0; q < G; ++q) acc[q] = fmaf(s_in[i * G + q], wv, acc[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      const float v = relu ? fmaxf(acc[q], 0.f) : acc[q];
+      s_out[j * G + q] = v;
+      if (g_out && q < nb) g_out[(size_t)q * Fout + j] = v;
+    }
+  }
+  __syncthreads();
+}
+template <int G, int NT, typename Gate>
+__device__ __forceinline__ void dense_cols_back(const float* s_dout, int Fout, const float* W, int Fin, int nb,
+                                                Gate gate, float* s_din, float* g_din) {
+  for (int i = threadIdx.x; i < Fin; i += NT) {
+    float acc[G];
+#pragma unroll
+    for (int q = 0; q < G; ++q) acc[q] = 0.f;
+    const float* wr = W + (size_t)i * Fout;
+    int j = 0;
+    for (; j + 8 <= Fout; j += 8) {
+      float wv[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) wv[e] = wr[j + e];
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int q = 0; q < G; ++q) acc[q] = fmaf(s_dout[(j + e) * G + q], wv[e], acc[q]);
+    }
+    for (; j < Fout; ++j) {
+      const float wv = wr[j];
+#pragma unroll
+      for (int q = 0; q < G; ++q) acc[q] = fmaf(s_dout[j * G + q], wv, acc[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      const float v = q < nb && gate(q, i) ? acc[q] : 0.f;
+      if (s_din) s_din[i * G + q] = v;
+      if (q < nb) g_din[(size_t)q * Fin + i] = v;
+    }
+  }
+  __syncthreads();
+}
+
 // The dense stack for a group of up to G rows of one upload (training) or of the evaluation pass:
 // forward at the rows' model version, per-row loss, and (training) back down to the gradient of the
 // second pooled map; every dZ carries the upload's coefficient of Eq. 3.
@@ -347,8 +412,8 @@ __device__ __forceinline__ void dense_rows_back(const float* s_dout, int Fout, c
 // round of few rows takes small groups (a workgroup per CU) and slices within them.  5 uploads of 32 rows, 400-120-84-10:
 // 59 us with 20 workgroups of 256 threads (8 rows each, a thread per column); of 1024 threads, 80 for 2 rows
 // each 27 us, 160 for a row each 23.
-template <int G>
-__global__ __launch_bounds__(kDenseThreads) void cnn_dense_kernel(CnnDev d, RoundDesc rd, float* eval_loss, float* eval_hit) {
+template <int G, int NT, bool COLS>
+__global__ __launch_bounds__(NT) void cnn_dense_kernel(CnnDev d, RoundDesc rd, float* eval_loss, float* eval_hit) {
   extern __shared__ __attribute__((aligned(16))) float sm[];
   const CnnPlan& p = d.p;
   const int t = threadIdx.x;
@@ -358,7 +423,7 @@ __global__ __launch_bounds__(kDenseThreads) void cnn_dense_kernel(CnnDev d, Roun
   const int nb = min(G, min(p.B - g * G, d.n_rows - r0));
   if (nb <= 0) return;
   float* sPart = sm;
-  float* sH0 = sPart + kDenseThreads * G;
+  float* sH0 = sPart + (COLS ? 0 : NT * G);
   float* sH1 = sH0 + G * p.F0;
   float* sH2 = sH1 + G * p.F1;
   float* sZ = sH2 + G * p.F2;
@@ -366,18 +431,26 @@ __global__ __launch_bounds__(kDenseThreads) void cnn_dense_kernel(CnnDev d, Roun
   float* sD1 = sD2 + G * p.F2;          // dZ of the first dense layer
   const float* w = slot_of(d, rd, a);
   const float* p2 = wsp<const float>(d, p.off_p2) + (size_t)r0 * p.F0;
-  for (int i = t; i < G * p.F0; i += kDenseThreads) {
+  for (int i = t; i < G * p.F0; i += NT) {
     const int q = i / p.F0, f = i - q * p.F0;
     sH0[f * G + q] = q < nb ? p2[i] : 0.f;
   }
   __syncthreads();
   const bool train = eval_loss == nullptr;
+  auto fwd = [&](const float* s_in, int Fin, const float* W, const float* bias, int Fout, bool relu, float* s_out, float* g_out) {
+    if constexpr (COLS) dense_cols<G, NT>(s_in, Fin, W, bias, Fout, nb, relu, s_out, g_out);
+    else dense_rows<G, NT>(s_in, Fin, W, bias, Fout, nb, relu, sPart, s_out, g_out);
+  };
+  auto back = [&](const float* s_dout, int Fout, const float* W, int Fin, auto gate, float* s_din, float* g_din) {
+    if constexpr (COLS) dense_cols_back<G, NT>(s_dout, Fout, W, Fin, nb, gate, s_din, g_din);
+    else dense_rows_back<G, NT>(s_dout, Fout, W, Fin, nb, gate, s_din, g_din);
+  };
   const int y = t < nb ? wsp<const int32_t>(d, p.off_label)[r0 + t] : 0;
-  dense_rows<G>(sH0, p.F0, w + p.w_off[2], w + p.b_off[2], p.F1, nb, true, sPart, sH1,
+  fwd(sH0, p.F0, w + p.w_off[2], w + p.b_off[2], p.F1, true, sH1,
                 train ? wsp<float>(d, p.off_h1) + (size_t)r0 * p.F1 : nullptr);
-  dense_rows<G>(sH1, p.F1, w + p.w_off[3], w + p.b_off[3], p.F2, nb, true, sPart, sH2,
+  fwd(sH1, p.F1, w + p.w_off[3], w + p.b_off[3], p.F2, true, sH2,
                 train ? wsp<float>(d, p.off_h2) + (size_t)r0 * p.F2 : nullptr);
-  dense_rows<G>(sH2, p.F2, w + p.w_off[4], w + p.b_off[4], p.C, nb, false, sPart, sZ, nullptr);
+  fwd(sH2, p.F2, w + p.w_off[4], w + p.b_off[4], p.C, false, sZ, nullptr);
   if (t < nb) {
     // softmax cross-entropy of row t; dZ = c (p - onehot) with the upload's coefficient of Eq. 3
     float* z = sZ + t;
@@ -403,16 +476,14 @@ __global__ __launch_bounds__(kDenseThreads) void cnn_dense_kernel(CnnDev d, Roun
   }
   if (!train) return;
   __syncthreads();
-  dense_rows_back<G>(sZ, p.C, w + p.w_off[4], p.F2, nb, [&](int b, int i) { return sH2[i * G + b] > 0.f; }, sD2,
+  back(sZ, p.C, w + p.w_off[4], p.F2, [&](int b, int i) { return sH2[i * G + b] > 0.f; }, sD2,
                      wsp<float>(d, p.off_dz2) + (size_t)r0 * p.F2);
-  dense_rows_back<G>(sD2, p.F2, w + p.w_off[3], p.F1, nb, [&](int b, int i) { return sH1[i * G + b] > 0.f; }, sD1,
+  back(sD2, p.F2, w + p.w_off[3], p.F1, [&](int b, int i) { return sH1[i * G + b] > 0.f; }, sD1,
                      wsp<float>(d, p.off_dz1) + (size_t)r0 * p.F1);
   // (a window is dead exactly where its pooled value is zero)
-  dense_rows_back<G>(sD1, p.F1, w + p.w_off[2], p.F0, nb, [&](int b, int i) { return sH0[i * G + b] > 0.f; }, nullptr,
+  back(sD1, p.F1, w + p.w_off[2], p.F0, [&](int b, int i) { return sH0[i * G + b] > 0.f; }, nullptr,
                      wsp<float>(d, p.off_dp2) + (size_t)r0 * p.F0);
 }
-
-constexpr int kBwdThreads = 1024;
 
 // A kernel argument's value, opaque: a choice among several members of an argument struct otherwise becomes an
 // indexed load from a copy of the whole struct in scratch memory.
@@ -431,6 +502,7 @@ __host__ __device__ __forceinline__ int dense_wgrad_tiles(const CnnPlan& p, int 
 __host__ __device__ __forceinline__ int dense_wgrad_blocks(const CnnPlan& p) {
   return dense_wgrad_tiles(p, 0) + dense_wgrad_tiles(p, 1) + dense_wgrad_tiles(p, 2);
 }
+template <int NT>
 __device__ __forceinline__ void dense_wgrad_block(const CnnDev& d, const RoundDesc& rd, int blk, float* lds) {
   const CnnPlan& p = d.p;
   const int per = dense_wgrad_blocks(p);
@@ -451,34 +523,43 @@ __device__ __forceinline__ void dense_wgrad_block(const CnnDev& d, const RoundDe
   const int nj = (Fout + 63) / 64, i0 = tile / nj * 64, j0 = (tile % nj) * 64;
   float* s_in = lds;               // [32 rows][64]
   float* s_dz = lds + 32 * 64;     // [32 rows][64]
+  constexpr int RPT = 1024 / NT;         // input features per thread, NT / 16 apart
   const int t = threadIdx.x, il = t >> 4, jl = (t & 15) * 4;
-  float g[4] = {0.f, 0.f, 0.f, 0.f};
+  float g[RPT][4];
+#pragma unroll
+  for (int q = 0; q < RPT; ++q) g[q][0] = g[q][1] = g[q][2] = g[q][3] = 0.f;
   for (int b0 = 0; b0 < p.B; b0 += 32) {
     const int nr = min(32, p.B - b0);
     const size_t r0 = (size_t)a * p.B + b0;
-    for (int e = t; e < 32 * 64; e += kBwdThreads) {
+    for (int e = t; e < 32 * 64; e += NT) {
       const int r = e >> 6, i = i0 + (e & 63), j = j0 + (e & 63);
       s_in[e] = r < nr ? (i < Fin ? in[(r0 + r) * Fin + i] : 1.f) : 0.f;
       s_dz[e] = r < nr && j < Fout ? dz[(r0 + r) * Fout + j] : 0.f;
     }
     __syncthreads();
     for (int r = 0; r < nr; ++r) {
-      const float x = s_in[r * 64 + il];
       const float4 v = *(const float4*)(s_dz + r * 64 + jl);
-      g[0] = fmaf(x, v.x, g[0]); g[1] = fmaf(x, v.y, g[1]); g[2] = fmaf(x, v.z, g[2]); g[3] = fmaf(x, v.w, g[3]);
+#pragma unroll
+      for (int q = 0; q < RPT; ++q) {
+        const float x = s_in[r * 64 + il + q * (NT / 16)];
+        g[q][0] = fmaf(x, v.x, g[q][0]); g[q][1] = fmaf(x, v.y, g[q][1]);
+        g[q][2] = fmaf(x, v.z, g[q][2]); g[q][3] = fmaf(x, v.w, g[q][3]);
+      }
     }
     __syncthreads();
   }
-  const int i = i0 + il;
-  if (i > Fin) return;
   float* priv = wsp<float>(d, p.off_priv) + (size_t)a * p.slot_stride;
   const float* cur = slot_of(d, rd, a);
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int j = j0 + jl + e;
-    if (j < Fout) {
-      const size_t at = i < Fin ? w_at + (size_t)i * Fout + j : b_at + (size_t)j;
-      priv[at] = d.step < 0 ? g[e] : cur[at] - g[e];
+  for (int q = 0; q < RPT; ++q) {
+    const int i = i0 + il + q * (NT / 16);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int j = j0 + jl + e;
+      if (i <= Fin && j < Fout) {
+        const size_t at = i < Fin ? w_at + (size_t)i * Fout + j : b_at + (size_t)j;
+        priv[at] = d.step < 0 ? g[q][e] : cur[at] - g[q][e];
+      }
     }
   }
 }
@@ -512,14 +593,15 @@ __device__ __forceinline__ void cnn_losses(const CnnDev& d, const RoundDesc& rd,
 // A convolution's share of one row's gradient from LDS: sum over the pooling windows of the gradient
 // times the input under the window's maximum (gw: gradient and offset of the maximum in an input plane,
 // per output channel and window); `sp` neighbouring threads share an entry's windows.
+template <int NT>
 __device__ __forceinline__ void conv_wgrad_stage(const float* sx, int Cin, int Sin, const float2* gw, int Cout, int win,
                                                  int k, float* out) {
   const int nW = Cin * k * k * Cout, n = nW + Cout;
   int sp = 1;
-  while (sp < 8 && n * sp * 2 <= 2 * kBwdThreads) sp *= 2;
-  const int rounds = (n * sp + kBwdThreads - 1) / kBwdThreads;
+  while (sp < 8 && n * sp * 2 <= 2 * NT) sp *= 2;
+  const int rounds = (n * sp + NT - 1) / NT;
   for (int it = 0; it < rounds; ++it) {
-    const int idx = it * kBwdThreads + (int)threadIdx.x, e = idx / sp, h = idx - e * sp;
+    const int idx = it * NT + (int)threadIdx.x, e = idx / sp, h = idx - e * sp;
     float acc = 0.f;
     if (e < nW) {
       const int co = e % Cout, q = e / Cout, ci = q / (k * k), u = (q / k) % k, v = q % k;
@@ -566,11 +648,11 @@ __host__ __device__ __forceinline__ BwdLds bwd_lds(const CnnPlan& p) {
   if (o.total < 4 * 1024) o.total = 4 * 1024;        // (dense_wgrad_block)
   return o;
 }
-template <int KS>
-__global__ __launch_bounds__(kBwdThreads) void cnn_bwd_kernel(CnnDev d, RoundDesc rd, int rows, LossMailbox* mailbox) {
+template <int KS, int NT>
+__global__ __launch_bounds__(NT) void cnn_bwd_kernel(CnnDev d, RoundDesc rd, int rows, LossMailbox* mailbox) {
   extern __shared__ __attribute__((aligned(16))) float sm[];
   const CnnPlan& p = d.p;
-  if ((int)blockIdx.x >= rows) { dense_wgrad_block(d, rd, (int)blockIdx.x - rows, sm); return; }
+  if ((int)blockIdx.x >= rows) { dense_wgrad_block<NT>(d, rd, (int)blockIdx.x - rows, sm); return; }
   if (blockIdx.x == 0) cnn_losses(d, rd, mailbox);
   const int r = blockIdx.x, a = r / p.B, t = threadIdx.x, k = KS ? KS : p.k, kk = k * k;
   const BwdLds at = bwd_lds(p);
@@ -580,23 +662,23 @@ __global__ __launch_bounds__(kBwdThreads) void cnn_bwd_kernel(CnnDev d, RoundDes
   float2* g1 = (float2*)(sm + at.g1); float2* g0 = (float2*)(sm + at.g0);
   const int n_in = p.C0 * p.S * p.S;
   const float* src = d.X + (size_t)wsp<const uint32_t>(d, p.off_rowidx)[r] * n_in;
-  for (int i = t; i < side * side * at.pc; i += kBwdThreads) sdc[i] = 0.f;
-  for (int i = t; i < p.C1 * kk * p.C2; i += kBwdThreads) {
+  for (int i = t; i < side * side * at.pc; i += NT) sdc[i] = 0.f;
+  for (int i = t; i < p.C1 * kk * p.C2; i += NT) {
     const int q = i / p.C2, co = i - q * p.C2, ci = q / kk, tap = q - ci * kk;
     sw[(tap * Cp + co) * at.pw + ci] = w[p.w_off[1] + i];
   }
   const int npad = Cp - p.C2;            // channels of the padding: a zero gradient times any number but these
-  for (int i = t; i < kk * npad * at.pw; i += kBwdThreads) {
+  for (int i = t; i < kk * npad * at.pw; i += NT) {
     const int q = i / at.pw, tap = q / npad;
     sw[(tap * Cp + p.C2 + q - tap * npad) * at.pw + i - q * at.pw] = 0.f;
   }
-  for (int i = t; i < n_in; i += kBwdThreads) sx[i] = src[i];
-  for (int i = t; i < n1; i += kBwdThreads) sp1[i] = wsp<const float>(d, p.off_p1)[(size_t)r * n1 + i];
+  for (int i = t; i < n_in; i += NT) sx[i] = src[i];
+  for (int i = t; i < n1; i += NT) sp1[i] = wsp<const float>(d, p.off_p1)[(size_t)r * n1 + i];
   __syncthreads();
   const float* dp2 = wsp<const float>(d, p.off_dp2) + (size_t)r * p.F0;
   const uint8_t* a2 = wsp<const uint8_t>(d, p.off_a2) + (size_t)r * p.F0;
   const int win2 = p.S2 * p.S2;
-  for (int o = t; o < p.F0; o += kBwdThreads) {
+  for (int o = t; o < p.F0; o += NT) {
     const int m = a2[o], co = o / win2, wi = o - co * win2, pi = wi / p.S2, pj = wi - pi * p.S2;
     // (a dead window contributes 0 x the corner of its inputs)
     const bool live = m != kDead;
@@ -612,7 +694,7 @@ __global__ __launch_bounds__(kBwdThreads) void cnn_bwd_kernel(CnnDev d, RoundDes
   const int pos = p.S1 * p.S1, mt = (pos + 15) / 16, nt = (p.C1 + 15) / 16;
   const int lane = t & 63, wave = t >> 6, l15 = lane & 15, l4 = lane >> 4;
   const uint8_t* a1 = wsp<const uint8_t>(d, p.off_a1) + (size_t)r * n1;
-  for (int item = wave; item < mt * nt; item += kBwdThreads / 64) {
+  for (int item = wave; item < mt * nt; item += NT / 64) {
     const int m0 = item % mt * 16, c0 = item / mt * 16;
     const int pm = min(m0 + l15, pos - 1);
     const float* pa = sdc + ((pm / p.S1 + k - 1) * side + pm % p.S1 + k - 1) * at.pc + l4;
@@ -644,15 +726,15 @@ __global__ __launch_bounds__(kBwdThreads) void cnn_bwd_kernel(CnnDev d, RoundDes
       }
     }
   }
-  conv_wgrad_stage(sp1, p.C1, p.S1, g1, p.C2, win2, k, wsp<float>(d, p.off_grow2) + (size_t)r * (p.C1 * kk * p.C2 + p.C2));
+  conv_wgrad_stage<NT>(sp1, p.C1, p.S1, g1, p.C2, win2, k, wsp<float>(d, p.off_grow2) + (size_t)r * (p.C1 * kk * p.C2 + p.C2));
   __syncthreads();
-  conv_wgrad_stage(sx, p.C0, p.S, g0, p.C1, pos, k, wsp<float>(d, p.off_grow1) + (size_t)r * (p.C0 * kk * p.C1 + p.C1));
+  conv_wgrad_stage<NT>(sx, p.C0, p.S, g0, p.C1, pos, k, wsp<float>(d, p.off_grow1) + (size_t)r * (p.C0 * kk * p.C1 + p.C1));
 }
 // The same for shapes whose stages do not fit the LDS together: dense shares and losses only.
-__global__ __launch_bounds__(kBwdThreads) void cnn_dense_wgrad_kernel(CnnDev d, RoundDesc rd, LossMailbox* mailbox) {
+__global__ __launch_bounds__(1024) void cnn_dense_wgrad_kernel(CnnDev d, RoundDesc rd, LossMailbox* mailbox) {
   __shared__ __attribute__((aligned(16))) float lds[4 * 1024];
   if (blockIdx.x == 0) cnn_losses(d, rd, mailbox);
-  dense_wgrad_block(d, rd, blockIdx.x, lds);
+  dense_wgrad_block<1024>(d, rd, blockIdx.x, lds);
 }
 
 // Gradient of the first pooled map of row r: the second convolution's output gradient is non-zero
@@ -842,8 +924,17 @@ size_t conv_fwd_lds(const CnnPlan& p, int layer) {
 }
 // (what decides whether a shape is accepted: 8 rows' values of the dense stack)
 size_t dense_lds(const CnnPlan& p) { return (size_t)8 * (p.F0 + 2 * p.F1 + 2 * p.F2 + p.C) * 4; }
-size_t dense_group_lds(const CnnPlan& p, int G) { return ((size_t)G * (p.F0 + 2 * p.F1 + 2 * p.F2 + p.C) + (size_t)kDenseThreads * G) * 4; }
+size_t dense_group_lds(const CnnPlan& p, int G, int nt) { return ((size_t)G * (p.F0 + 2 * p.F1 + 2 * p.F2 + p.C) + (size_t)nt * G) * 4; }
 constexpr size_t kMaxLds = 150 * 1024;
+// Threads of a workgroup that has a stacked row to itself.  While a CU has two rows at most, 1024: what counts is how long
+// one row takes.  With more rows to do, as few as still fill a CU with the workgroups that its LDS holds: small
+// stages are mostly barriers and idle wavefronts at 1024 (8192 rows of 1 x 18 x 18, 4-8 channels: forward 81 us,
+// backward 216; with 256 threads 33 and 76; of 3 x 32 x 32, 6-16: 278 -> 204 with 256, 831 -> 669 with 512 and 979 with
+// 256; 32-32 channels: forward 655, with 512 threads 710).
+int row_threads(int rows, size_t lds, bool with_512) {
+  const size_t per_cu = (size_t)160 * 1024 / lds;
+  return rows <= 512 ? 1024 : per_cu >= 5 ? 256 : with_512 && per_cu >= 2 ? 512 : 1024;
+}
 size_t conv_wgrad_lds(const CnnPlan& p, int layer) {
   const int Cin = layer ? p.C1 : p.C0, Cout = layer ? p.C2 : p.C1, Sin = layer ? p.S1 : p.S, Sp = layer ? p.S2 : p.S1;
   return ((size_t)Cin * Sin * Sin + 2 * (size_t)Cout * Sp * Sp) * 4;
@@ -857,11 +948,14 @@ void launch_conv_fwd(const CnnDev& d, const RoundDesc& rd, int rows, hipStream_t
   const CnnPlan& p = d.p;
   const size_t fused = (size_t)fwd_lds(p).total * 4;
   if (fused <= kMaxLds) {
-    switch (p.k) {
-      case 3: cnn_fwd_kernel<3><<<dim3(rows), dim3(kFwdThreads), fused, s>>>(d, rd); break;
-      case 5: cnn_fwd_kernel<5><<<dim3(rows), dim3(kFwdThreads), fused, s>>>(d, rd); break;
-      default: cnn_fwd_kernel<0><<<dim3(rows), dim3(kFwdThreads), fused, s>>>(d, rd);
+#define ABS_FWD(NT)                                                                              \
+    switch (p.k) {                                                                               \
+      case 3: cnn_fwd_kernel<3, NT><<<dim3(rows), dim3(NT), fused, s>>>(d, rd); break;           \
+      case 5: cnn_fwd_kernel<5, NT><<<dim3(rows), dim3(NT), fused, s>>>(d, rd); break;           \
+      default: cnn_fwd_kernel<0, NT><<<dim3(rows), dim3(NT), fused, s>>>(d, rd);                 \
     }
+    if (row_threads(rows, fused, false) == 256) { ABS_FWD(256) } else { ABS_FWD(1024) }
+#undef ABS_FWD
     return;
   }
   // (both convolutions' filters and maps do not fit the LDS together)
@@ -876,19 +970,19 @@ void launch_conv_fwd(const CnnDev& d, const RoundDesc& rd, int rows, hipStream_t
 }
 
 // Rows per workgroup of the dense stack: few while there are CUs without a workgroup (160 rows: 23 us one by one,
-// 27 in twos, 34 in fours), more for long launches (every group fetches all dense weights from the L2).
+// 27 in twos, 34 in fours; every group fetches all dense weights from the L2), and with groups of 8 rows for most CUs
+// the form without exchanges, earlier where the sums are short (400-120-84-10, us in fours / eights: 640 rows 34 / 56,
+// 2048 64 / 56, 8192 197 / 84; 1152-256-128-10: 86 / 146, 168 / 150, 656 / 401; 72-40-24-10: 20 / 20, 36 / 20, 87 / 23).
 void launch_dense(const CnnDev& d, const RoundDesc& rd, int uploads, hipStream_t s, float* eval_loss, float* eval_hit) {
   const CnnPlan& p = d.p;
   auto groups = [&](int G) { return uploads * ((p.B + G - 1) / G); };
-  const dim3 block(kDenseThreads);
-  if (groups(1) <= 256)
-    cnn_dense_kernel<1><<<dim3(groups(1)), block, dense_group_lds(p, 1), s>>>(d, rd, eval_loss, eval_hit);
-  else if (groups(2) <= 256)
-    cnn_dense_kernel<2><<<dim3(groups(2)), block, dense_group_lds(p, 2), s>>>(d, rd, eval_loss, eval_hit);
-  else if (groups(4) <= 512 || dense_group_lds(p, 8) > kMaxLds)
-    cnn_dense_kernel<4><<<dim3(groups(4)), block, dense_group_lds(p, 4), s>>>(d, rd, eval_loss, eval_hit);
-  else
-    cnn_dense_kernel<8><<<dim3(groups(8)), block, dense_group_lds(p, 8), s>>>(d, rd, eval_loss, eval_hit);
+#define ABS_DENSE(G, NT, COLS) \
+  cnn_dense_kernel<G, NT, COLS><<<dim3(groups(G)), dim3(NT), dense_group_lds(p, G, COLS ? 0 : NT), s>>>(d, rd, eval_loss, eval_hit)
+  if (groups(8) >= (p.F0 + p.F1 + p.F2 <= 150 ? 80 : 192)) ABS_DENSE(8, 256, true);
+  else if (groups(1) <= 256) ABS_DENSE(1, 1024, false);
+  else if (groups(2) <= 256) ABS_DENSE(2, 1024, false);
+  else                       ABS_DENSE(4, 1024, false);
+#undef ABS_DENSE
 }
 
 CnnDev dev_of(const CnnArgs& a) {
@@ -992,12 +1086,16 @@ hipError_t launch_cnn_round(const CnnArgs& a, const RoundDesc& rd, hipStream_t s
     hook->begin(KK_CNN_CONV_BWD, 2.0 * ar * n1 * kk * p.C2 + fd + (f1 + f2) / 4.0,
                 ar * 4.0 * (p.C0 * (double)p.S * p.S + 3.0 * n1 + 3.0 * p.F0 + 2.0 * p.F1 + 2.0 * p.F2 + p.C) + (double)n_dense * 8.0);
     if (fused <= kMaxLds) {
-      const dim3 grid(rows + dense_blocks), block(kBwdThreads);
-      switch (p.k) {
-        case 3: cnn_bwd_kernel<3><<<grid, block, fused, s>>>(d, rd, rows, box); break;
-        case 5: cnn_bwd_kernel<5><<<grid, block, fused, s>>>(d, rd, rows, box); break;
-        default: cnn_bwd_kernel<0><<<grid, block, fused, s>>>(d, rd, rows, box);
+      const dim3 grid(rows + dense_blocks);
+#define ABS_BWD(NT)                                                                              \
+      switch (p.k) {                                                                             \
+        case 3: cnn_bwd_kernel<3, NT><<<grid, dim3(NT), fused, s>>>(d, rd, rows, box); break;    \
+        case 5: cnn_bwd_kernel<5, NT><<<grid, dim3(NT), fused, s>>>(d, rd, rows, box); break;    \
+        default: cnn_bwd_kernel<0, NT><<<grid, dim3(NT), fused, s>>>(d, rd, rows, box);          \
       }
+      const int nt = row_threads(rows, fused, true);
+      if (nt == 256) { ABS_BWD(256) } else if (nt == 512) { ABS_BWD(512) } else { ABS_BWD(1024) }
+#undef ABS_BWD
     } else {
       switch (p.k) {
         case 3: cnn_conv2_bwd_kernel<3><<<dim3(rows), dim3(256), conv2_bwd_lds(p), s>>>(d, rd); break;
@@ -1006,7 +1104,7 @@ hipError_t launch_cnn_round(const CnnArgs& a, const RoundDesc& rd, hipStream_t s
       }
       cnn_conv_wgrad_rows_kernel<<<dim3(rows), dim3(256), conv_wgrad_lds(p, 1), s>>>(d, 1);
       cnn_conv_wgrad_rows_kernel<<<dim3(rows), dim3(256), conv_wgrad_lds(p, 0), s>>>(d, 0);
-      cnn_dense_wgrad_kernel<<<dim3(dense_blocks), dim3(kBwdThreads), 0, s>>>(d, rd, box);
+      cnn_dense_wgrad_kernel<<<dim3(dense_blocks), dim3(1024), 0, s>>>(d, rd, box);
     }
     hook->end(KK_CNN_CONV_BWD);
     hook->begin(KK_CNN_COMBINE, (double)p.P * rd.K, 4.0 * (ar * (double)p.w_off[2] + (double)rd.K * n_dense + 2.0 * p.P));
@@ -1049,11 +1147,15 @@ hipError_t launch_cnn_eval(const CnnArgs& a, uint32_t slot, const EvalArgs& e, h
 hipError_t cnn_prepare() {
   // stages whose LDS need exceeds the default limit must opt in once per process
   static hipError_t done = [] {
-    const void* fns[] = {(const void*)cnn_fwd_kernel<0>, (const void*)cnn_fwd_kernel<3>, (const void*)cnn_fwd_kernel<5>,
-                         (const void*)cnn_conv_pool_fwd_kernel<0>, (const void*)cnn_conv_pool_fwd_kernel<3>,
-                         (const void*)cnn_conv_pool_fwd_kernel<5>, (const void*)cnn_dense_kernel<1>, (const void*)cnn_dense_kernel<2>, (const void*)cnn_dense_kernel<4>,
-                         (const void*)cnn_dense_kernel<8>, (const void*)cnn_bwd_kernel<0>, (const void*)cnn_bwd_kernel<3>,
-                         (const void*)cnn_bwd_kernel<5>, (const void*)cnn_conv2_bwd_kernel<0>, (const void*)cnn_conv2_bwd_kernel<3>, (const void*)cnn_conv2_bwd_kernel<5>,
+    const void* fns[] = {(const void*)cnn_fwd_kernel<0, 256>, (const void*)cnn_fwd_kernel<3, 256>, (const void*)cnn_fwd_kernel<5, 256>,
+                         (const void*)cnn_fwd_kernel<0, 1024>, (const void*)cnn_fwd_kernel<3, 1024>, (const void*)cnn_fwd_kernel<5, 1024>,
+                         (const void*)cnn_conv_pool_fwd_kernel<0>, (const void*)cnn_conv_pool_fwd_kernel<3>, (const void*)cnn_conv_pool_fwd_kernel<5>,
+                         (const void*)cnn_dense_kernel<1, 1024, false>, (const void*)cnn_dense_kernel<2, 1024, false>,
+                         (const void*)cnn_dense_kernel<4, 1024, false>, (const void*)cnn_dense_kernel<8, 256, true>,
+                         (const void*)cnn_bwd_kernel<0, 256>, (const void*)cnn_bwd_kernel<3, 256>, (const void*)cnn_bwd_kernel<5, 256>,
+                         (const void*)cnn_bwd_kernel<0, 512>, (const void*)cnn_bwd_kernel<3, 512>, (const void*)cnn_bwd_kernel<5, 512>,
+                         (const void*)cnn_bwd_kernel<0, 1024>, (const void*)cnn_bwd_kernel<3, 1024>, (const void*)cnn_bwd_kernel<5, 1024>,
+                         (const void*)cnn_conv2_bwd_kernel<0>, (const void*)cnn_conv2_bwd_kernel<3>, (const void*)cnn_conv2_bwd_kernel<5>,
                          (const void*)cnn_conv_wgrad_rows_kernel};
     hipError_t e = hipSuccess;
     for (const void* f : fns)

@@ -95,6 +95,20 @@ def test_evaluation_against_the_oracle():
     ref.close()
 
 
+def test_evaluation_in_long_passes():
+    """Passes long enough for the dense form with a thread per column, the last one ragged."""
+    p = _small(M=5000, N=16, B=130)
+    d, Xe, ye = workloads.make_split(p, 2 * 16 * 130 + 1051)
+    sim = lib.Simulation(p, d)
+    sim.round(3)
+    loss, acc = sim.evaluate(Xe, ye, -1)
+    want_loss, want_acc, margin = evaluate(p, sim.model().astype(np.float64), Xe.astype(np.float64), ye)
+    sim.close()
+    unsure = int(np.sum(margin < 1e-4 * max(1.0, float(np.abs(margin).max()))))
+    assert loss == pytest.approx(want_loss, rel=1e-5)
+    assert abs(acc - want_acc) * len(ye) <= unsure + 1e-9
+
+
 def test_two_runs_are_bitwise_identical_and_a_batch_equals_its_members():
     p = _small()
     d = workloads.make_inputs(p)
@@ -140,6 +154,14 @@ def test_unsupported_settings_are_refused():
     (dict(N=6, K0=6, k_mode=1, B=70), 3),                          # 2 rows per workgroup of the dense stack, more than 32 per upload
     (dict(N=8, K0=8, k_mode=1, B=130), 2),                         # 4 rows
     (dict(N=16, K0=16, k_mode=1, B=135, M=4000), 2),               # 8 rows
+    # more than two rows per CU: workgroups of 256 threads for small stages, of 512 for the full network's backward half
+    (dict(S=11, k=2, C1=3, C2=6, N=8, K0=8, k_mode=1, B=65), 2),
+    (dict(C0=3, S=32, k=5, C1=6, C2=16, F1=120, F2=84, C=10, N=20, K0=20, k_mode=1, B=27, M=4000), 2),
+    (dict(C0=3, S=32, k=5, C1=6, C2=16, F1=120, F2=84, C=10, N=20, K0=20, k_mode=1, B=27, M=4000, U=2, lr=1e-3), 1),
+    # a group of 8 rows per CU, the last one ragged: a thread per column, and more columns than threads.  (One round: in the
+    # second of these a pooling window's two candidates differ by less than the forward pass's rounding, which moves the
+    # first filters' update by 7.5e-5 of its norm, in every form of the dense stack: inside the stated bar, not the guard.)
+    (dict(F1=300, F2=270, C=19, N=16, K0=16, k_mode=1, B=127, M=4000), 1),
     (dict(C0=4, S=62, C1=10, C2=8, N=2, K0=1, B=3, M=60, lr=1e-4), 3),            # the backward half does not fit the LDS at once
     (dict(C0=4, S=62, k=7, C1=14, C2=32, N=2, K0=1, B=3, M=60, lr=1e-4), 3),      # nor do both convolutions
     (dict(C0=4, S=62, k=7, C1=14, C2=32, N=2, K0=1, B=3, M=60, lr=1e-4, U=2), 2),
