@@ -1890,10 +1890,9 @@ bool mlp_plan(const abs_config& c, MlpPlan& p, const char** why) {
   p.off_rowloss = take(Mp * 4);
   for (int l = 1; l <= L; ++l) p.off_colsum[l] = take(Mp / (l == L ? kCeRows : 64) * p.dp[l] * 4);
   for (int l = 1; l < L; ++l) p.off_maskbits[l] = take(round_up(Mp, 256) * round_up((size_t)p.dp[l], 256) / 8);
-  for (int l = 0; l < L; ++l)
-    p.off_partial[l] = take((size_t)p.dp[l] * (p.dp[l + 1] + kPartialPad) * 4 *
-                            (p.U > 1 ? std::max<size_t>(kMaxSplit, (size_t)c.N) : (size_t)kMaxSplit));
-  if (p.U > 1) {
+  if (p.U == 1) {          // (a local step is taken in the weight gradient's epilogue: no partials)
+    for (int l = 0; l < L; ++l) p.off_partial[l] = take((size_t)p.dp[l] * (p.dp[l + 1] + kPartialPad) * 4 * kMaxSplit);
+  } else {
     p.off_priv = take((size_t)c.N * p.slot_stride * 4);
     p.off_priv_shadow = take((size_t)c.N * p.shadow_stride * 2);
     p.off_lossacc = take((size_t)c.N * 4);
@@ -2358,8 +2357,10 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
       const int nsplit = wgrad_split(p, l, rows, local ? K : 0);
       g.ksteps_total = ksteps;
       g.ksteps_per_split = local ? p.Bp / BK : (ksteps + nsplit - 1) / nsplit;
-      g.outf = at<float>(a, p.off_partial[l]); g.ldof = (size_t)p.dp[l + 1] + kPartialPad;
-      g.split_stride = (size_t)p.dp[l] * (p.dp[l + 1] + kPartialPad);
+      if (!local) {
+        g.outf = at<float>(a, p.off_partial[l]); g.ldof = (size_t)p.dp[l + 1] + kPartialPad;
+        g.split_stride = (size_t)p.dp[l] * (p.dp[l + 1] + kPartialPad);
+      }
       int run_parts = 0;
       const int run_q = local ? 0 : wgrad_runs(p, l, rows, nsplit, &run_parts);
       if (run_q) { g.sk_q = run_q; }

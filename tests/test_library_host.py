@@ -136,3 +136,20 @@ def test_batch_and_evaluate_argument_errors_without_a_gpu():
         lib.abs_batch_create([])
     assert lib.abs_batch_workspace_size([a.handle, b.handle]) == 0     # no batch, no size
     a.close(); b.close()
+
+
+def test_workspace_of_local_sgd_holds_no_weight_gradient_partials():
+    """U > 1 takes the step in the weight gradient's epilogue: beside what U = 1 needs without its partials (16 per layer)
+    the workspace holds the uploads' private models, their losses and the averaged change, and nothing else."""
+    up = lambda v, m: (v + m - 1) // m * m
+    for dims, N in (([3072, 2048, 2048, 100], 128), ([200, 96, 10], 8)):
+        p = workloads.scaled_preset(3, M=12800, dims=dims, n_classes=dims[-1], N=N, K0=2, n_slow=0)
+        one, local = (lib.abs_workspace_size(lib.make_config(dict(p, U=U))) for U in (1, 10))
+        pad = [up(d, 128) for d in dims]
+        pad[-1] = 64 if dims[-1] <= 64 else pad[-1]
+        layers = range(len(dims) - 1)
+        partials = sum(pad[l] * (pad[l + 1] + 32) * 4 * 16 for l in layers)
+        slot = up(sum(dims[l] * dims[l + 1] + dims[l + 1] for l in layers), 64) * 4
+        shadow = up(sum(pad[l + 1] * (pad[l] + 64) + (pad[l] * (pad[l + 1] + 64) if l else 0) for l in layers), 128) * 2
+        private = N * (slot + shadow + 4) + slot
+        assert abs((local - (one - partials)) - private) <= 256 * 8, (dims, N, local, one, partials, private)
