@@ -1808,9 +1808,12 @@ int pick_split(int tiles, int ksteps, int slots, double tile_bytes, double step_
 
 // Whether a weight gradient off the large-tile kernel takes 128-wide tiles: a long contraction that can
 // still be cut into a workgroup per CU (cfg 5's output layer, 2048 x 128 over 8192 / 32768 rows: 33 / 62 us
-// against 39 / 71 with 64-wide tiles, which read the activations twice; short ones are faster with 64).
-bool wgrad_wide_tiles(int Mdim, int Ndim, int ksteps) {
-  return Ndim % 128 == 0 && (Mdim / 128) * (Ndim / 128) * std::min(ksteps / 8, kMaxSplit) >= 256;
+// against 39 / 71 with 64-wide tiles, which read the activations twice; short ones are faster with 64).  Local steps are
+// cut into the uploads and no further (us with 64 / 128-wide tiles, 2048 x 128: 2 uploads of 4096 rows, 32 workgroups
+// of 128, 22 / 46, 64 of 128 rows 51 / 43; 512 x 2048, 2 of 4096 rows, 128 workgroups, 38 / 53; 1152 x 640, 8 of 128 rows,
+// 360 workgroups, 18.7 / 14.6).
+bool wgrad_wide_tiles(int Mdim, int Ndim, int ksteps, int uploads) {
+  return Ndim % 128 == 0 && (Mdim / 128) * (Ndim / 128) * (uploads ? uploads : std::min(ksteps / 8, kMaxSplit)) >= 256;
 }
 // ... or tiles of 128 x 256: two workgroups per CU with at least 25 k-steps each, in few splits (us of this product
 // and the next, which carries its update, with 128 x 128 / 128 x 256 tiles: 3200 x 2048 over 4096 rows 96 / 89, 8192:
@@ -1828,7 +1831,7 @@ int wgrad_split(const MlpPlan& p, int l, int rows, int per_upload) {
     return pick_split((p.dp[l] / TM3) * (p.dp[l + 1] / TN3), ksteps, 256, 256.0 * 256 * 4, 2.0, 0.0);
   if (wgrad_256_columns(p.dp[l], p.dp[l + 1], ksteps))
     return pick_split((p.dp[l] / 128) * (p.dp[l + 1] / 256), ksteps, 512, 128.0 * 256 * 4, 1.5, 0.0);
-  if (wgrad_wide_tiles(p.dp[l], p.dp[l + 1], ksteps))
+  if (wgrad_wide_tiles(p.dp[l], p.dp[l + 1], ksteps, 0))
     return pick_split((p.dp[l] / 128) * (p.dp[l + 1] / 128), ksteps, 512, 128.0 * 128 * 4, 0.5, 0.0);
   return pick_split((p.dp[l] / 64) * (p.dp[l + 1] / 64), ksteps, 512, 64.0 * 64 * 4, 0.25, 0.0);
 }
@@ -2079,7 +2082,7 @@ bool launch_gemm(GemmArgs g, const RoundDesc& rd, int Mdim, int Ndim, int nsplit
   // more tiles than CUs each takes four wavefronts and a ring of two, so that two fit a CU and the second
   // covers the first one's barriers and epilogue (us with KG = 2 / 1: 8192 x 1024 x 1024 31.4 / 26.9, first layer
   // 8192 x 1024 x 3072 48 / 44, 8192 x 2048 x 2048 102 / 91).
-  const bool wide = EPI == EPI_WGRAD ? wgrad_wide_tiles(Mdim, Ndim, g.ksteps_total)
+  const bool wide = EPI == EPI_WGRAD ? wgrad_wide_tiles(Mdim, Ndim, g.ksteps_total, TAG >= 4 ? nsplit : 0)
                                      : Ndim % 128 == 0 && (Mdim / 128) * (Ndim / 128) * nsplit > 128;
   const int tile = wide ? 128 : 64;
   g.mt = Mdim / tile;

@@ -67,6 +67,8 @@ def test_mlp_local_steps(over, T):
     (dict(U=2, M=6400, dims=[328, 200, 10], N=64, K0=64, B=3, n_slow=0, lr=1e-3), 3),
     # 128-wide tiles (a long contraction over many uploads)
     (dict(U=2, M=12800, dims=[64, 2040, 100], n_classes=100, N=64, K0=64, B=128, n_slow=0, lr=1e-4), 2),
+    # few uploads of many rows: 64-wide tiles over a long contraction
+    (dict(U=2, M=12800, dims=[64, 2040, 100], n_classes=100, N=2, K0=2, B=2500, n_slow=0, lr=1e-4), 2),
 ])
 def test_local_step_in_the_weight_gradient(over, T):
     """The step taken in the weight gradient's epilogue at the edges of its tiles, in both copies of the weights."""

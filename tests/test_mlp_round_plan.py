@@ -34,3 +34,10 @@ def test_tiles_of_products_with_more_tiles_than_cus():
     # weight gradients: 25 k-steps for each of two workgroups per CU, in few splits
     assert _items([3200, 2048, 10], 128, 128, 64, "wgrad")[0] == "wgrad_wide:128x256/2"
     assert _items([3200, 512, 10], 128, 128, 128, "wgrad")[0].startswith("wgrad_tile2:128x128/")
+
+
+def test_tiles_of_local_steps_follow_the_number_of_uploads():
+    """The contraction of a local step is not cut beyond the uploads: few uploads of many rows keep 64-wide tiles."""
+    assert _items([512, 2048, 100], 4, 4096, 2, "wgrad", U=2)[:2] == ["wgrad_step_tile:64x64/2"] * 2
+    assert _items([64, 2048, 100], 64, 128, 64, "wgrad", U=2)[:2] == ["wgrad_step_tile2:128x128/64"] * 2
+    assert _items([512, 2048, 100], 4, 4096, 4, "wgrad", U=2)[1] == "wgrad_step_tile:128x128/4"      # 4 x 16 x 4 workgroups
