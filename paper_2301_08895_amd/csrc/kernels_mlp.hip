@@ -44,11 +44,14 @@ constexpr int BK = 64;    // contraction elements per main-loop step
 constexpr int kMaxSplit = 16;
 // Row pitches of the bf16 operand arrays are the padded width plus this many elements (128 B):
 // with a pitch that is a multiple of 4 KB the same 128-byte column of every row of a tile maps
-// to one L2 channel, and all workgroups walk the k dimension in step.
+// to one L2 channel, and all workgroups walk the k dimension in step.  The pad behind a row of a weight copy is
+// also read as data: gathered rows fetch the 64 elements behind the first row where a k-step reaches beyond d_0, so
+// it must be a k-step long and stays zero in every shadow slot (mlp_prepare clears them, nothing writes there).
 #ifndef ABS_PITCH_PAD
 #define ABS_PITCH_PAD 64
 #endif
 constexpr int kPitchPad = ABS_PITCH_PAD;
+static_assert(kPitchPad >= BK && kPitchPad % 8 == 0, "the pad of a row is a gathered k-step's zeros");
 constexpr int kPartialPad = 32;         // the same for the fp32 weight-gradient partials (floats)
 
 size_t round_up(size_t x, size_t m) { return (x + m - 1) / m * m; }

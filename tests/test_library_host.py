@@ -153,3 +153,15 @@ def test_workspace_of_local_sgd_holds_no_weight_gradient_partials():
         shadow = up(sum(pad[l + 1] * (pad[l] + 64) + (pad[l] * (pad[l + 1] + 64) if l else 0) for l in layers), 128) * 2
         private = N * (slot + shadow + 4) + slot
         assert abs((local - (one - partials)) - private) <= 256 * 8, (dims, N, local, one, partials, private)
+
+
+def test_a_row_pitch_without_room_for_the_zeros_does_not_compile():
+    """Gathered rows read the pad behind a weight row as their zeros: a build with a shorter pad is refused."""
+    import subprocess
+    from paper_2301_08895_amd import build
+    src = os.path.join(ROOT, "paper_2301_08895_amd", "csrc", "kernels_mlp.hip")
+    for pad, ok in ((0, False), (32, False), (64, True), (128, True)):
+        r = subprocess.run([build.hipcc(), "-x", "hip", "-std=c++17", "-fsyntax-only", "--cuda-host-only",
+                            f"-DABS_PITCH_PAD={pad}", src], capture_output=True, text=True)
+        assert (r.returncode == 0) == ok, (pad, r.stderr[-2000:])
+        assert ok or "gathered k-step" in r.stderr
