@@ -178,7 +178,8 @@ int abs_get_model(abs_ctx* ctx, int64_t version, float* h_out, size_t n_floats);
  * per-sample loss f(w; xi) of Eq. 1 over the n_rows evaluation rows, *h_accuracy the fraction of
  * rows whose largest logit is the label (ties: the lowest class; NaN for the linear model).
  *  d_X, d_y   DEVICE, caller-owned, [n_rows, d_0] and [n_rows] in the dtypes of the training
- *             payload; read only.  1 <= n_rows < 2^32.
+ *             payload; read only, aligned like their elements (rows of an MLP that do not start
+ *             at a multiple of 16 bytes are copied within the workspace first).  1 <= n_rows < 2^32.
  * The forward pass is the training one (MLP: bf16 weights of that version, bf16 hidden
  * activations, fp32 logits); row losses are added in a fixed order in fp64.  Runs on the
  * handle's stream after the rounds enqueued so far and synchronises it.  The version must still

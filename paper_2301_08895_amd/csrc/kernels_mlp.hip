@@ -1745,14 +1745,26 @@ __global__ void mlp_fill_zero_kernel(uint4* p, size_t n16) {
 }
 
 // ------------------------------------------------------------------ held-out evaluation
-// Sequential evaluation rows row0 .. row0 + n in the index arrays of the forward pass; the
-// padding rows read a valid row and carry label -1.
-__global__ void mlp_eval_index_kernel(uint32_t* rowidx, int32_t* label, const int32_t* y, int64_t row0, int n,
+// Sequential evaluation rows row0 .. row0 + n in the index arrays of the forward pass (x_row0: where row row0 is in
+// the matrix that pass reads); the padding rows read a valid row and carry label -1.
+__global__ void mlp_eval_index_kernel(uint32_t* rowidx, int32_t* label, const int32_t* y, int64_t row0, int64_t x_row0, int n,
                                       int rows) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= rows) return;
-  rowidx[m] = (uint32_t)(row0 + (m < n ? m : 0));
+  rowidx[m] = (uint32_t)(x_row0 + (m < n ? m : 0));
   label[m] = m < n ? y[row0 + m] : -1;
+}
+
+// A pass's rows from a caller's matrix that is not 16-byte aligned (a view into a larger buffer): the forward pass
+// requests 16-byte pieces straight into LDS, which need the alignment, so the rows go through the workspace.
+__global__ void mlp_eval_align_kernel(const uint16_t* X, uint4* out, size_t n8) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n8) return;
+  const uint16_t* v = X + i * 8;
+  uint4 o;
+  o.x = v[0] | ((uint32_t)v[1] << 16); o.y = v[2] | ((uint32_t)v[3] << 16);
+  o.z = v[4] | ((uint32_t)v[5] << 16); o.w = v[6] | ((uint32_t)v[7] << 16);
+  out[i] = o;
 }
 
 // One wavefront per row of the logits: -log softmax(z)_y and whether the first largest logit
@@ -2450,16 +2462,28 @@ hipError_t launch_mlp_eval(const MlpArgs& a, uint32_t slot, const EvalArgs& e, h
   uint32_t* rowidx = at<uint32_t>(a, p.off_rowidx);
   int32_t* label = at<int32_t>(a, p.off_label);
   hipError_t err = launch_eval_clear(e, s);
+  const bool aligned = ((uintptr_t)e.X & 15) == 0;
   for (int64_t row0 = 0; row0 < e.n_rows && err == hipSuccess; row0 += p.Mp) {
     const int n = (int)(e.n_rows - row0 < p.Mp ? e.n_rows - row0 : p.Mp);
+    const uint16_t* X = (const uint16_t*)e.X;
+    if (!aligned) {
+      // (the transposed minibatch's place, dp_0 x ldm elements: every round that reads it writes it first)
+      uint16_t* const staged = at<uint16_t>(a, p.off_xgt);
+      const size_t n8 = (size_t)n * p.d[0] / 8;
+      hook->begin(KK_EVAL, 0, 4.0 * n * p.d[0]);
+      mlp_eval_align_kernel<<<dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s>>>(X + (size_t)row0 * p.d[0], (uint4*)staged, n8);
+      hook->end(KK_EVAL);
+      X = staged;
+    }
     RoundDesc rd{};                               // every block of Bp rows uses the same version
     rd.K = (n + p.Bp - 1) / p.Bp;
     for (int k = 0; k < rd.K; ++k) rd.w[k].slot = slot;
     const int rows = rd.K * p.Bp;
     hook->begin(KK_EVAL, 0, 12.0 * n);
-    mlp_eval_index_kernel<<<dim3((rows + 255) / 256), dim3(256), 0, s>>>(rowidx, label, (const int32_t*)e.y, row0, n, rows);
+    mlp_eval_index_kernel<<<dim3((rows + 255) / 256), dim3(256), 0, s>>>(rowidx, label, (const int32_t*)e.y, row0,
+                                                                              aligned ? row0 : 0, n, rows);
     hook->end(KK_EVAL);
-    mlp_forward(a, (const uint16_t*)e.X, rd, rows, (double)n, at<float>(a, p.off_ring), at<uint16_t>(a, p.off_shadow),
+    mlp_forward(a, X, rd, rows, (double)n, at<float>(a, p.off_ring), at<uint16_t>(a, p.off_shadow),
                 false, false, -1, s, hook);
     hook->begin(KK_EVAL, 8.0 * n * p.d[p.L], 4.0 * n * p.d[p.L]);
     const dim3 grid((n + 3) / 4), block(256);

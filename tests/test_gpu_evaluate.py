@@ -78,3 +78,36 @@ def test_version_outside_the_ring_is_an_error():
 def test_mlp_full_width_several_passes():
     """The 3072-512-10 workload's layer shapes, evaluation set larger than two passes of N * Bp rows."""
     _check(workloads.scaled_preset(3, M=6400), 10, 9001, 2e-3)
+
+
+@pytest.mark.parametrize("over", [
+    dict(M=4096, dims=[200, 96, 10], N=8, B=40, n_slow=2, lr=1e-3),                      # 64-wide tiles, ragged k-steps
+    dict(M=8192, dims=[256, 256, 512, 10], N=6, B=256, K0=2, n_slow=1, lr=5e-4),         # whole k-steps
+])
+def test_evaluation_rows_at_any_address(over):
+    """A view that starts 2, 4, 8 or 14 bytes into a buffer gives what the aligned copy gives, bit for bit."""
+    import torch
+    p = workloads.scaled_preset(3, **over)
+    rows = 2 * p["N"] * ((p["B"] + 127) // 128 * 128) + 77
+    d, Xe, ye = workloads.make_split(p, rows)
+    sim = lib.Simulation(p, d)
+    sim.round(5)
+    X = torch.from_numpy(Xe.view(np.int16)).cuda().reshape(-1)
+    y = torch.from_numpy(ye).cuda()
+    out = torch.zeros(2, dtype=torch.float64, device="cuda")
+    got = []
+    for offset in (0, 1, 2, 4, 7):
+        buf = torch.zeros(X.numel() + 8, dtype=torch.int16, device="cuda")
+        buf[offset:offset + X.numel()] = X
+        ptr = buf.data_ptr() + 2 * offset
+        assert ptr % 16 == 2 * offset
+        got.append(lib.abs_evaluate(sim.handle, -1, ptr, y.data_ptr(), rows))
+        lib.abs_evaluate_static(sim.handle, -1, ptr, y.data_ptr(), rows, out.data_ptr())
+        torch.cuda.synchronize()
+        got.append(tuple(out.tolist()))
+    assert all(g == got[0] for g in got), got
+    model = sim.round(3).model()
+    sim.close()
+    ref = lib.Simulation(p, d)
+    assert np.array_equal(ref.round(8).model(), model)
+    ref.close()
