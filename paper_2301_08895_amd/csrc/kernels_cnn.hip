@@ -1083,9 +1083,9 @@ hipError_t launch_cnn_round(const CnnArgs& a, const RoundDesc& rd, hipStream_t s
     const size_t fused = (size_t)bwd_lds(p).total * 4;
     const unsigned dense_blocks = (unsigned)(rd.K * dense_wgrad_blocks(p));
     LossMailbox* box = local ? nullptr : a.mailbox;
-    hook->begin(KK_CNN_CONV_BWD, 2.0 * ar * n1 * kk * p.C2 + fd + (f1 + f2) / 4.0,
-                ar * 4.0 * (p.C0 * (double)p.S * p.S + 3.0 * n1 + 3.0 * p.F0 + 2.0 * p.F1 + 2.0 * p.F2 + p.C) + (double)n_dense * 8.0);
     if (fused <= kMaxLds) {
+      hook->begin(KK_CNN_CONV_BWD, 2.0 * ar * n1 * kk * p.C2 + fd + (f1 + f2) / 4.0,
+                  ar * 4.0 * (p.C0 * (double)p.S * p.S + 3.0 * n1 + 3.0 * p.F0 + 2.0 * p.F1 + 2.0 * p.F2 + p.C) + (double)n_dense * 8.0);
       const dim3 grid(rows + dense_blocks);
 #define ABS_BWD(NT)                                                                              \
       switch (p.k) {                                                                             \
@@ -1096,17 +1096,23 @@ hipError_t launch_cnn_round(const CnnArgs& a, const RoundDesc& rd, hipStream_t s
       const int nt = row_threads(rows, fused, true);
       if (nt == 256) { ABS_BWD(256) } else if (nt == 512) { ABS_BWD(512) } else { ABS_BWD(1024) }
 #undef ABS_BWD
+      hook->end(KK_CNN_CONV_BWD);
     } else {
+      hook->begin(KK_CNN_CONV_BWD, 2.0 * ar * n1 * kk * p.C2, ar * 4.0 * (p.F0 + n1));
       switch (p.k) {
         case 3: cnn_conv2_bwd_kernel<3><<<dim3(rows), dim3(256), conv2_bwd_lds(p), s>>>(d, rd); break;
         case 5: cnn_conv2_bwd_kernel<5><<<dim3(rows), dim3(256), conv2_bwd_lds(p), s>>>(d, rd); break;
         default: cnn_conv2_bwd_kernel<0><<<dim3(rows), dim3(256), conv2_bwd_lds(p), s>>>(d, rd);
       }
+      hook->end(KK_CNN_CONV_BWD);
+      hook->begin(KK_CNN_CONV_WGRAD, (f1 + f2) / 4.0, ar * 4.0 * (p.C0 * (double)p.S * p.S + 2.0 * n1 + p.F0));
       cnn_conv_wgrad_rows_kernel<<<dim3(rows), dim3(256), conv_wgrad_lds(p, 1), s>>>(d, 1);
       cnn_conv_wgrad_rows_kernel<<<dim3(rows), dim3(256), conv_wgrad_lds(p, 0), s>>>(d, 0);
+      hook->end(KK_CNN_CONV_WGRAD);
+      hook->begin(KK_CNN_DENSE_WGRAD, fd, (double)n_dense * 8.0 + ar * 4.0 * (p.F0 + 2.0 * p.F1 + 2.0 * p.F2 + p.C));
       cnn_dense_wgrad_kernel<<<dim3(dense_blocks), dim3(1024), 0, s>>>(d, rd, box);
+      hook->end(KK_CNN_DENSE_WGRAD);
     }
-    hook->end(KK_CNN_CONV_BWD);
     hook->begin(KK_CNN_COMBINE, (double)p.P * rd.K, 4.0 * (ar * (double)p.w_off[2] + (double)rd.K * n_dense + 2.0 * p.P));
     if (local) {
       cnn_conv_step_kernel<<<dim3((unsigned)((p.w_off[2] + 255) / 256), (unsigned)rd.K), dim3(256), 0, s>>>(d, rd);

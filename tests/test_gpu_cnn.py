@@ -172,3 +172,19 @@ def test_kernel_forms(over, T):
     res = run_pair(p, T, checkpoints=(1,))
     assert_trace_equal(res, 1e-4)
     check_models(res, FP32_TOL, label=p["name"], guard=GUARD)
+
+
+@pytest.mark.parametrize("over,kinds", [
+    (dict(), {"cnn_conv_fwd", "cnn_dense", "cnn_conv_bwd", "cnn_combine"}),
+    (dict(C0=4, S=62, C1=10, C2=8, N=2, K0=1, B=3, M=60, lr=1e-4),
+     {"cnn_conv_fwd", "cnn_dense", "cnn_conv_bwd", "cnn_conv_wgrad", "cnn_dense_wgrad", "cnn_combine"}),
+])
+def test_every_launch_is_booked_under_its_own_kind(over, kinds):
+    """A backward half whose stages do not fit the LDS together is launches of its own, each with its time and work."""
+    p = _small(**over)
+    sim = lib.Simulation(p, workloads.make_inputs(p), profile=1)
+    sim.round(3)
+    stats = {s["name"]: s for s in sim.kernel_stats()}
+    sim.close()
+    assert set(stats) == kinds
+    assert all(s["launches"] == 3 and s["total_ms"] > 0 and s["flops"] > 0 and s["bytes"] > 0 for s in stats.values())
