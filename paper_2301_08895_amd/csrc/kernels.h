@@ -26,19 +26,16 @@ enum KernelKind {
   KK_LINREG_ROUND = 0,
   KK_SOFTMAX_ROWS,
   KK_SOFTMAX_UPDATE,
-  KK_MLP_INDEX,
   KK_MLP_GATHER_T,
   KK_MLP_FWD_L1,
   KK_MLP_FWD_HIDDEN,
   KK_MLP_FWD_LOGITS,
   KK_MLP_LOGITS_CE,
-  KK_MLP_LOSS,
   KK_MLP_DGRAD_OUT,
   KK_MLP_DGRAD,
   KK_MLP_WGRAD_L1,
   KK_MLP_WGRAD,
   KK_MLP_UPDATE,
-  KK_MLP_BIAS_LOSS,
   KK_LOCAL_STEPS,
   KK_DELTA_UPDATE,
   KK_EVAL,
@@ -61,7 +58,7 @@ struct RegressionArgs {
   int d, C, B;
   uint64_t shard_rows;   // rows per worker shard
   uint64_t batch_key;    // stream_key(seed, kStreamBatch)
-  LossMailbox* mailbox;  // per-upload mean minibatch losses + completion stamp (device-visible host memory)
+  LossMailbox* mailbox;  // per-upload mean minibatch losses, each word with the round's stamp (device-visible host memory)
   // softmax scratch
   float* dz;             // [N*B][16]
   float* rowloss;        // [N*B]

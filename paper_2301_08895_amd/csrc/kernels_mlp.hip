@@ -309,7 +309,8 @@ __device__ __forceinline__ void bias_block(const BiasCore& a, int blk, FirstRow 
 // bf16 copies.  The contraction is not split (range z = the rows of upload z), so the accumulators hold
 // the whole gradient and the epilogue takes the step itself: no partial is written and read back, and
 // the update needs no launch (the bias update and the losses ride in this and in the input gradient's launch).
-// Bound by the model's own bytes: 10 (12 with a row-major copy) per weight and upload instead of 22.
+// Bound by the model's own bytes: 10 (12 with a row-major copy) per weight and upload; with the partial written and
+// read back, 18 (20).
 // 3072-512-10, 8 uploads of 10 steps x 128 rows: update kernels 56 us, losses and biases 9 us of a step gone,
 // first layer's product 15.5 -> 28.4 us; a round 1229 -> 711 us.
 // `own`: the model is private copy z of `cur`, else ring slot rd.w[z].slot.
@@ -1947,7 +1948,7 @@ struct NullHook : LaunchHook {
   void end(int) override {}
 };
 
-// The three uses of the update kernels:
+// The two uses of the update kernels:
 //   UPD_GLOBAL  w^{t+1} = w^t - sum of the split partials                    (U = 1, Eq. 3)
 //   UPD_DELTA   w^{t+1} = w^t - D, D = the averaged change of the uploads    (U > 1, Eq. 3)
 // each also writes the bf16 copies of what it produced.
@@ -2045,10 +2046,14 @@ inline bool gemm_is_big(bool gather, bool per_upload, const GemmArgs& g, int Mdi
 template <int EPI, bool GATHER, bool PER_UPLOAD, int TAG = 0>
 bool launch_gemm(GemmArgs g, const RoundDesc& rd, int Mdim, int Ndim, int nsplit, hipStream_t s) {
   g.nsplit = nsplit;
+  // (TAG 2, 3 and 4: the caller picks them with this very test, only the large-tile kernel reads such an A)
+  constexpr bool kBigOnly = TAG >= 2 && TAG <= 4;
   const bool big = g.sk_q > 0 || gemm_is_big(GATHER, PER_UPLOAD, g, Mdim, Ndim, nsplit);
-  if (TAG == 3 && !big) {      // the caller picks TAG 3 with this very test: only the large-tile kernel reads a transposed A
-    std::fprintf(stderr, "libabs: transposed-A product outside the large-tile kernel\n");
-    std::abort();
+  if constexpr (kBigOnly) {
+    if (!big) {
+      std::fprintf(stderr, "libabs: gathered or transposed A outside the large-tile kernel\n");
+      std::abort();
+    }
   }
   if (big && g.sk_q > 0) {
     // runs of sk_q k-steps across the tiles: one workgroup per run
@@ -2074,48 +2079,50 @@ bool launch_gemm(GemmArgs g, const RoundDesc& rd, int Mdim, int Ndim, int nsplit
     ABS_LAUNCH_K((mlp_gemm256_kernel<EPI, GATHER, PER_UPLOAD, TAG>), dim3(8 * g.rows_per_xcd * g.nt + g.pig_blocks + g.bias_blocks), dim3(512), s, g, rd);
     return true;
   }
-  // 128 x 256 tiles once they are two workgroups for every CU (below, 128 x 128 tiles in two workgroups per CU; us at
-  // uploads of 128 rows with 128 x 128 / 128 x 256: first layer 8192 x 2048 x 1024 57 / 49.5, 16384 x 2048 x 3072
-  // 258 / 217, hidden 8192 x 2048 x 2048 91 / 77, 16384 x 1024 x 1024 49 / 46; at half of that, 8192 x 1024 x 1024,
-  // 27 / 33).
-  if constexpr (TAG < 2) {
-    if (EPI == EPI_WGRAD ? wgrad_256_columns(Mdim, Ndim, g.ksteps_total)
-                         : Ndim % TNW == 0 && (Mdim / TM) * (Ndim / TNW) * nsplit >= 512) {
-      g.mt = Mdim / TM;
-      g.nt = Ndim / TNW;
-      g.rows_per_xcd = (g.mt * nsplit + 7) / 8;
-      plan_note(EPI == EPI_RELU ? "fwd_wide" : EPI == EPI_LOGITS ? "logits_wide" : EPI == EPI_DGRAD ? "dgrad_wide" : "wgrad_wide", TM, TNW, nsplit);
-      ABS_LAUNCH_K((mlp_wide_kernel<EPI, GATHER, PER_UPLOAD, TAG>), dim3(8 * g.rows_per_xcd * g.nt + g.pig_blocks + g.bias_blocks), dim3(256), s, g, rd);
-      return false;
+  if constexpr (!kBigOnly) {
+    // 128 x 256 tiles once they are two workgroups for every CU (below, 128 x 128 tiles in two workgroups per CU; us at
+    // uploads of 128 rows with 128 x 128 / 128 x 256: first layer 8192 x 2048 x 1024 57 / 49.5, 16384 x 2048 x 3072
+    // 258 / 217, hidden 8192 x 2048 x 2048 91 / 77, 16384 x 1024 x 1024 49 / 46; at half of that, 8192 x 1024 x 1024,
+    // 27 / 33).
+    if constexpr (TAG < 2) {
+      if (EPI == EPI_WGRAD ? wgrad_256_columns(Mdim, Ndim, g.ksteps_total)
+                           : Ndim % TNW == 0 && (Mdim / TM) * (Ndim / TNW) * nsplit >= 512) {
+        g.mt = Mdim / TM;
+        g.nt = Ndim / TNW;
+        g.rows_per_xcd = (g.mt * nsplit + 7) / 8;
+        plan_note(EPI == EPI_RELU ? "fwd_wide" : EPI == EPI_LOGITS ? "logits_wide" : EPI == EPI_DGRAD ? "dgrad_wide" : "wgrad_wide", TM, TNW, nsplit);
+        ABS_LAUNCH_K((mlp_wide_kernel<EPI, GATHER, PER_UPLOAD, TAG>), dim3(8 * g.rows_per_xcd * g.nt + g.pig_blocks + g.bias_blocks), dim3(256), s, g, rd);
+        return false;
+      }
     }
+    // 128-wide tiles once 64-wide ones would be more than the two workgroups a CU holds (a 64-wide workgroup
+    // stages twice the bytes per flop, but a CU draws at most 23-32 bytes per clock from beyond the L1, so
+    // a product spread over twice the CUs or in two workgroups per CU is the faster one; 3072 x 1024, us with
+    // 64 / 128 wide tiles at 2048 rows: 31.5 / 35.1, 2560: 44.8 / 36.5, 3072: 46.3 / 37.0, 4608: 70.1 / 69.3).
+    // Up to one 128-wide tile per CU the two wavefront groups of a workgroup share the contraction (KG = 2); with
+    // more tiles than CUs each takes four wavefronts and a ring of two, so that two fit a CU and the second
+    // covers the first one's barriers and epilogue (us with KG = 2 / 1: 8192 x 1024 x 1024 31.4 / 26.9, first layer
+    // 8192 x 1024 x 3072 48 / 44, 8192 x 2048 x 2048 102 / 91).
+    const bool wide = EPI == EPI_WGRAD ? wgrad_wide_tiles(Mdim, Ndim, g.ksteps_total, TAG >= 4 ? nsplit : 0)
+                                       : Ndim % 128 == 0 && (Mdim / 128) * (Ndim / 128) * nsplit > 128;
+    const int tile = wide ? 128 : 64;
+    g.mt = Mdim / tile;
+    g.nt = Ndim / tile;
+    g.rows_per_xcd = (g.mt * nsplit + 7) / 8;
+    const bool pairs = wide && g.mt * g.nt * nsplit > 256;
+    const dim3 grid(8 * g.rows_per_xcd * g.nt + g.pig_blocks + g.bias_blocks);
+    plan_note((std::string(EPI == EPI_RELU ? "fwd" : EPI == EPI_LOGITS ? "logits" : EPI == EPI_DGRAD ? "dgrad" : TAG >= 4 ? "wgrad_step" : "wgrad") +
+               (pairs ? "_tile2" : "_tile")).c_str(), tile, tile, nsplit);
+    // Ring depths: forward and input-gradient products keep three steps on their way (64-wide: 64 KB, two
+    // workgroups per CU; 8 steps and one workgroup: the evaluation's logits 22.5 instead of 16.8 us; 3 steps: cfg 3's
+    // first layer 22.4 instead of 18.4).  A weight gradient carries the previous layer's update as extra
+    // workgroups and leaves LDS for several of them per CU (128-wide, ring of 4 and one workgroup:
+    // cfg 5's output layer 39 instead of 33 us).
+    constexpr int kRing128 = EPI == EPI_WGRAD ? 2 : 4, kRing64 = EPI == EPI_WGRAD ? 3 : 4;
+    if (pairs)     ABS_LAUNCH_K((mlp_tile_kernel<128, 1, EPI, GATHER, PER_UPLOAD, TAG, 2>), grid, dim3(TileCfg<128, 1>::NT), s, g, rd);
+    else if (wide) ABS_LAUNCH_K((mlp_tile_kernel<128, 2, EPI, GATHER, PER_UPLOAD, TAG, kRing128>), grid, dim3(TileCfg<128, 2>::NT), s, g, rd);
+    else           ABS_LAUNCH_K((mlp_tile_kernel<64, 4, EPI, GATHER, PER_UPLOAD, TAG, kRing64>), grid, dim3(TileCfg<64, 4>::NT), s, g, rd);
   }
-  // 128-wide tiles once 64-wide ones would be more than the two workgroups a CU holds (a 64-wide workgroup
-  // stages twice the bytes per flop, but a CU draws at most 23-32 bytes per clock from beyond the L1, so
-  // a product spread over twice the CUs or in two workgroups per CU is the faster one; 3072 x 1024, us with
-  // 64 / 128 wide tiles at 2048 rows: 31.5 / 35.1, 2560: 44.8 / 36.5, 3072: 46.3 / 37.0, 4608: 70.1 / 69.3).
-  // Up to one 128-wide tile per CU the two wavefront groups of a workgroup share the contraction (KG = 2); with
-  // more tiles than CUs each takes four wavefronts and a ring of two, so that two fit a CU and the second
-  // covers the first one's barriers and epilogue (us with KG = 2 / 1: 8192 x 1024 x 1024 31.4 / 26.9, first layer
-  // 8192 x 1024 x 3072 48 / 44, 8192 x 2048 x 2048 102 / 91).
-  const bool wide = EPI == EPI_WGRAD ? wgrad_wide_tiles(Mdim, Ndim, g.ksteps_total, TAG >= 4 ? nsplit : 0)
-                                     : Ndim % 128 == 0 && (Mdim / 128) * (Ndim / 128) * nsplit > 128;
-  const int tile = wide ? 128 : 64;
-  g.mt = Mdim / tile;
-  g.nt = Ndim / tile;
-  g.rows_per_xcd = (g.mt * nsplit + 7) / 8;
-  const bool pairs = wide && g.mt * g.nt * nsplit > 256;
-  const dim3 grid(8 * g.rows_per_xcd * g.nt + g.pig_blocks + g.bias_blocks);
-  plan_note((std::string(EPI == EPI_RELU ? "fwd" : EPI == EPI_LOGITS ? "logits" : EPI == EPI_DGRAD ? "dgrad" : TAG >= 4 ? "wgrad_step" : "wgrad") +
-             (pairs ? "_tile2" : "_tile")).c_str(), tile, tile, nsplit);
-  // Ring depths: forward and input-gradient products keep three steps on their way (64-wide: 64 KB, two
-  // workgroups per CU; 8 steps and one workgroup: the evaluation's logits 22.5 instead of 16.8 us; 3 steps: cfg 3's
-  // first layer 22.4 instead of 18.4).  A weight gradient carries the previous layer's update as extra
-  // workgroups and leaves LDS for several of them per CU (128-wide, ring of 4 and one workgroup:
-  // cfg 5's output layer 39 instead of 33 us).
-  constexpr int kRing128 = EPI == EPI_WGRAD ? 2 : 4, kRing64 = EPI == EPI_WGRAD ? 3 : 4;
-  if (pairs)     ABS_LAUNCH_K((mlp_tile_kernel<128, 1, EPI, GATHER, PER_UPLOAD, TAG, 2>), grid, dim3(TileCfg<128, 1>::NT), s, g, rd);
-  else if (wide) ABS_LAUNCH_K((mlp_tile_kernel<128, 2, EPI, GATHER, PER_UPLOAD, TAG, kRing128>), grid, dim3(TileCfg<128, 2>::NT), s, g, rd);
-  else           ABS_LAUNCH_K((mlp_tile_kernel<64, 4, EPI, GATHER, PER_UPLOAD, TAG, kRing64>), grid, dim3(TileCfg<64, 4>::NT), s, g, rd);
   return false;
 }
 
@@ -2192,7 +2199,7 @@ unsigned mlp_forward(const MlpArgs& a, const uint16_t* Xsrc, const RoundDesc& rd
   return have_bits;
 }
 
-// Output layer of a training pass: logits, loss sums per 32 rows, dZ_L in both orientations and its
+// Output layer of a training pass: logits, loss sums per 128 rows, dZ_L in both orientations and its
 // column sums, in one kernel (mlp_logits_ce_kernel).
 void launch_logits_ce(const MlpArgs& a, const RoundDesc& rd, int rows, double arows, const float* wbase,
                       const uint16_t* sbase, bool own, int gather_blocks, hipStream_t s, LaunchHook* hook) {
