@@ -190,7 +190,8 @@ struct CnnPlan {
   size_t off_p2, off_a2;              // second pooled map [F0] (the dense stack's input) and the same
   size_t off_h1, off_h2;              // dense activations
   size_t off_dz1, off_dz2, off_dz3;   // dense output gradients (coefficient of Eq. 3 included)
-  size_t off_dp2, off_dp1;            // gradients of the pooled maps (zero where the window is dead)
+  size_t off_dp2, off_dp1;            // gradients of the pooled maps (zero where the window is dead); the first only where
+                                      // the backward half is launches of its own
   size_t off_lossbuf;                 // [N] mean minibatch loss per upload
   int U;                              // local steps per job
   size_t off_rowloss;                 // per-row losses

@@ -926,6 +926,7 @@ size_t conv_fwd_lds(const CnnPlan& p, int layer) {
 size_t dense_lds(const CnnPlan& p) { return (size_t)8 * (p.F0 + 2 * p.F1 + 2 * p.F2 + p.C) * 4; }
 size_t dense_group_lds(const CnnPlan& p, int G, int nt) { return ((size_t)G * (p.F0 + 2 * p.F1 + 2 * p.F2 + p.C) + (size_t)nt * G) * 4; }
 constexpr size_t kMaxLds = 150 * 1024;
+bool bwd_fused(const CnnPlan& p) { return (size_t)bwd_lds(p).total * 4 <= kMaxLds; }
 // Threads of a workgroup that has a stacked row to itself.  While a CU has two rows at most, 1024: what counts is how long
 // one row takes.  With more rows to do, as few as still fill a CU with the workgroups that its LDS holds: small
 // stages are mostly barriers and idle wavefronts at 1024 (8192 rows of 1 x 18 x 18, 4-8 channels: forward 81 us,
@@ -1046,7 +1047,8 @@ bool cnn_plan(const abs_config& c, CnnPlan& p, const char** why) {
   p.off_dz2 = off;     off = up(off + Rm * p.F2 * 4);
   p.off_dz3 = off;     off = up(off + Rm * p.C * 4);
   p.off_dp2 = off;     off = up(off + Rm * p.F0 * 4);
-  p.off_dp1 = off;     off = up(off + Rm * n1 * 4);
+  // (the fused backward half keeps this gradient in LDS)
+  p.off_dp1 = off;     if (!bwd_fused(p)) off = up(off + Rm * n1 * 4);
   p.off_lossbuf = off; off = up(off + (size_t)p.N * 4);
   p.off_rowloss = off; off = up(off + Rm * 4);
   p.U = c.U < 1 ? 1 : c.U;
@@ -1083,7 +1085,7 @@ hipError_t launch_cnn_round(const CnnArgs& a, const RoundDesc& rd, hipStream_t s
     const size_t fused = (size_t)bwd_lds(p).total * 4;
     const unsigned dense_blocks = (unsigned)(rd.K * dense_wgrad_blocks(p));
     LossMailbox* box = local ? nullptr : a.mailbox;
-    if (fused <= kMaxLds) {
+    if (bwd_fused(p)) {
       hook->begin(KK_CNN_CONV_BWD, 2.0 * ar * n1 * kk * p.C2 + fd + (f1 + f2) / 4.0,
                   ar * 4.0 * (p.C0 * (double)p.S * p.S + 3.0 * n1 + 3.0 * p.F0 + 2.0 * p.F1 + 2.0 * p.F2 + p.C) + (double)n_dense * 8.0);
       const dim3 grid(rows + dense_blocks);

@@ -165,3 +165,16 @@ def test_a_row_pitch_without_room_for_the_zeros_does_not_compile():
                             f"-DABS_PITCH_PAD={pad}", src], capture_output=True, text=True)
         assert (r.returncode == 0) == ok, (pad, r.stderr[-2000:])
         assert ok or "gathered k-step" in r.stderr
+
+
+def test_workspace_of_the_convolutional_model_by_the_row():
+    """What one more row of a minibatch costs; the gradient of the first pooled map is in memory only where the backward
+    half's stages do not fit the LDS at once."""
+    for (C0, S, C1, C2, F1, F2, C, k), apart in (((3, 32, 6, 16, 120, 84, 10, 5), False), ((4, 62, 10, 8, 24, 12, 4, 3), True)):
+        p = workloads.scaled_preset(6, M=200_000, N=100, dims=[C0 * S * S, C1, C2, F1, F2, C, C0, k], n_classes=C)
+        a, b = (lib.abs_workspace_size(lib.make_config(dict(p, B=B))) for B in (100, 200))
+        S1 = (S - k + 1) // 2
+        n1, F0 = C1 * S1 * S1, C2 * ((S1 - k + 1) // 2) ** 2
+        grow = (C0 * k * k + 1) * C1 + (C1 * k * k + 1) * C2
+        words = 3 + n1 + F0 + 2 * (F1 + F2) + C + F0 + grow + 2 + (n1 if apart else 0)
+        assert abs((b - a) / 10_000 - (4 * words + n1 + F0)) < 1, (S, (b - a) / 10_000, 4 * words + n1 + F0)
