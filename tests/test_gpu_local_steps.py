@@ -9,9 +9,12 @@ from parity_util import run_pair, assert_trace_equal, check_models
 pytestmark = pytest.mark.gpu
 
 
-def _check(res, tol, loss_rtol):
+BF16_GUARD = 5e-3   # per-tensor norms of the MLP runs, as for U = 1 (measured at most 1.2e-3)
+
+
+def _check(res, tol, loss_rtol, guard=None):
     assert_trace_equal(res, loss_rtol)
-    check_models(res, tol)
+    check_models(res, tol, guard=guard)
 
 
 @pytest.mark.parametrize("over,T", [
@@ -53,7 +56,7 @@ def test_softmax_local_steps(over, T):
 ])
 def test_mlp_local_steps(over, T):
     p = workloads.scaled_preset(3, **over)
-    _check(run_pair(p, T, checkpoints=(1, 5)), 2e-2, 2e-3)       # the bf16 workloads' tolerance
+    _check(run_pair(p, T, checkpoints=(1, 5)), 2e-2, 2e-3, BF16_GUARD)       # the bf16 workloads' tolerance
 
 
 @pytest.mark.parametrize("over,T", [
@@ -67,19 +70,43 @@ def test_mlp_local_steps(over, T):
     (dict(U=2, M=6400, dims=[328, 200, 10], N=64, K0=64, B=3, n_slow=0, lr=1e-3), 3),
     # 128-wide tiles (a long contraction over many uploads)
     (dict(U=2, M=12800, dims=[64, 2040, 100], n_classes=100, N=64, K0=64, B=128, n_slow=0, lr=1e-4), 2),
+    # later steps read both bf16 copies that the earlier ones wrote, at steps large enough to tell an old copy: every
+    # tile form with ragged edges (64-wide; 128-wide, 256 workgroups and more; the large-tile kernel).  Measured at most
+    # 2.7e-3; in the oracle, the last 8 columns of the second layer's copies left as the job's first step saw them move
+    # an update by 9e-3 (64-wide) and 6e-3 (large tiles), 64 columns by 7e-3 (128-wide).
+    (dict(U=5, M=2400, dims=[1000, 521, 299, 26], n_classes=26, N=4, B=90, n_slow=0, lr=2e-3), 2),
+    (dict(U=4, M=12800, dims=[64, 2040, 100], n_classes=100, N=16, K0=16, B=120, n_slow=0, lr=2e-3), 2),
+    (dict(U=3, M=12800, dims=[200, 1100, 1140, 100], n_classes=100, N=8, K0=8, B=50, n_slow=0, lr=2e-3), 2),
+    (dict(U=4, M=6400, dims=[512, 200, 500, 10], N=64, K0=64, B=3, n_slow=0, lr=5e-3), 2),
     # few uploads of many rows: 64-wide tiles over a long contraction
     (dict(U=2, M=12800, dims=[64, 2040, 100], n_classes=100, N=2, K0=2, B=2500, n_slow=0, lr=1e-4), 2),
 ])
 def test_local_step_in_the_weight_gradient(over, T):
     """The step taken in the weight gradient's epilogue at the edges of its tiles, in both copies of the weights."""
     p = workloads.scaled_preset(3, **over)
-    _check(run_pair(p, T, checkpoints=(1,)), 2e-2, 2e-3)
+    _check(run_pair(p, T, checkpoints=(1,)), 2e-2, 2e-3, BF16_GUARD)
+
+
+def test_two_runs_of_mlp_local_steps_are_bitwise_identical():
+    """Private models are stepped in place by the launch that read them last (64-wide tiles and the large-tile kernel)."""
+    import paper_2301_08895_amd as lib
+    for over in (dict(U=4, M=2400, dims=[1000, 521, 299, 26], n_classes=26, N=4, B=90, n_slow=0, lr=2e-4),
+                 dict(U=3, M=6400, dims=[512, 200, 500, 10], N=64, K0=64, B=3, n_slow=0, lr=1e-3)):
+        p = workloads.scaled_preset(3, **over)
+        d = workloads.make_inputs(p)
+        runs = []
+        for _ in range(2):
+            sim = lib.Simulation(p, d)
+            sim.round(6)
+            runs.append((sim.model().copy(), sim.trace().copy()))
+            sim.close()
+        assert np.array_equal(runs[0][0], runs[1][0]) and np.array_equal(runs[0][1], runs[1][1])
 
 
 def test_cfg3_shape_local_steps():
     """The 3072-512-10 workload at its real layer and batch shapes (shorter dataset) with U = 2."""
     p = workloads.scaled_preset(3, M=6400, U=2)
-    _check(run_pair(p, 8, checkpoints=(1,)), 2e-2, 2e-3)
+    _check(run_pair(p, 8, checkpoints=(1,)), 2e-2, 2e-3, BF16_GUARD)
 
 
 def test_local_sgd_equals_the_hand_worked_run():
