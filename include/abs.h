@@ -273,7 +273,9 @@ void abs_destroy(abs_ctx* ctx);
  *                     abs_batch_workspace_size() bytes, 256-byte aligned, used by the batch until
  *                     abs_batch_destroy (may be NULL when the size is 0).  The library itself
  *                     allocates only pinned host memory (descriptors, loss mailboxes), three
- *                     streams and a few events.  The batch
+ *                     streams and a few events; a batch of 64 regression simulations and more has up to
+ *                     seven host threads, asleep between calls (inside a call they share half of the
+ *                     CPUs with the calls of other batches).  The batch
  *                     borrows the handles: they must outlive it, and stay usable on their own
  *                     (abs_get_model, abs_trace, abs_evaluate, abs_round) between batch calls.
  *  abs_batch_round    n_rounds rounds of every simulation (each continues from its own round

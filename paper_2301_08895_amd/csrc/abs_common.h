@@ -49,8 +49,8 @@ struct WorkerDesc {
 // The losses travel through a small mailbox in device-visible host memory, which the host polls: word a is
 // the loss of upload a (low half) together with the round's stamp (high half), written in ONE 8-byte store.
 // A word that carries the stamp carries its loss, so nothing has to be ordered: no fence between losses and
-// a separate stamp, which cost a trip over the host link before the host could go on (a round of one linear
-// simulation 13.8 -> 13.1 us, of one softmax simulation 16.5 -> 15.9).
+// a separate stamp, which cost a trip over the host link before the host could go on (about 0.5 us of the 13 to 16 us of
+// a round of one linear or softmax simulation; two boxes differ by more).
 struct LossMailbox {
   volatile uint64_t word[ABS_MAX_WORKERS];
   bool posted(int a, uint32_t stamp) const { return (uint32_t)(word[a] >> 32) == stamp; }

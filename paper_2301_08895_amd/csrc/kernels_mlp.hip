@@ -118,11 +118,13 @@ __global__ __launch_bounds__(256) void mlp_gather_t_kernel(const uint16_t* X, in
 
 // The same by the last workgroups of the output-layer kernel's launch: it needs nothing but the drawn rows,
 // and that launch's own workgroups (one per 128 rows) leave most CUs idle.  Blocks of 64 rows x 256 columns,
-// all of a thread's loads in flight together.  The kernel's LDS lets a CU hold one workgroup, so beyond
-// kGatherRide blocks (two waves) the launch of its own above is the faster one (microseconds per round, own
-// launch / riding: 1024 x 3072, 192 blocks 60.1 / 55.9; 8192 x 1024, 512 blocks 227 / 220; 8192 x 2048,
-// 1024 blocks 86 / 91; 32768 x 3072, 6144 blocks 1234 / 1326; blocks of this form in a launch of
-// their own 1250).
+// all of a thread's loads in flight together.  The kernel's LDS lets a CU hold one workgroup (98, 131 or 147 KB for
+// up to 64, 128 or 256 classes), so beyond kGatherRide blocks (two waves) the launch of its own is the faster one.
+// Sum of a round's kernels, us, own launch / riding, by blocks and classes: 1000-520-C, 64 blocks 46 / 42 (10), 52 / 47
+// (100), 60 / 55 (256), 512 blocks 84 / 80, 96 / 90, 101 / 95; 200-1024-C, 128 blocks 77 / 69, 83 / 84, 105 / 97; 3000-2048-C,
+// 768 blocks 205 / 201, 217 / 216, 238 / 238, 1536 blocks 307 / 323, 321 / 323, 357 / 362.  With a second hidden layer
+// the copy waits longer for its reader: 1000-1024-1024-10, 512 blocks 202 / 198, but 1000-2048-2048-10, 256 blocks 277 / 280,
+// 512-1920-1920-50, 512 blocks 75 / 82 (the copy, the output layer and the first weight gradient).
 constexpr int kGatherRide = 512;
 constexpr int kGatherPitch = 256 + 2;      // the 8 blocks of 8 rows a wavefront reads start 8 banks apart
 struct GatherT {
