@@ -515,9 +515,6 @@ SpinBudget& batch_threads() {
   static SpinBudget budget(half_the_cpus());
   return budget;
 }
-// CPUs that other processes use, or a quota, can be short all the same: a phase without a wait for the device that
-// took this long means that a thread was not running.  The batch then keeps to its least for a while.
-constexpr double kStarvedPhase = 5e-3, kStarvedFor = 10.0;      // seconds
 }  // namespace
 struct abs_batch {
   std::vector<abs_ctx*> ctx;
@@ -532,7 +529,7 @@ struct abs_batch {
   LossMailbox* d_box = nullptr;
   char* d_slots = nullptr;                 // softmax: per-upload gradient slots and losses of all simulations
   std::unique_ptr<HostPool> pool;          // regression models: the further host threads of a round
-  std::chrono::steady_clock::time_point few_until{};             // ... only the least of them before this moment
+  StarvedWatch watch;                                            // ... only the least of them while those are starved
   uint64_t rounds = 0;
   std::string err;
 };
@@ -727,11 +724,8 @@ struct BatchRoundState {
     kind = kind_; lo = lo_; hi = hi_;
     if (kind_ == 0) std::fill(kmax.begin(), kmax.end(), 0);
     team.phase([this] { if (kind == 1 && !abort.load()) stream_failed(); });    // the others may still wait for mailboxes
-    if (kind_ == 0 && team.size() > 1 && seconds_since(wait_t0) > kStarvedPhase) {
+    if (kind_ == 0 && team.size() > 1 && b->watch.phase_took(std::chrono::steady_clock::now(), seconds_since(wait_t0)))
       team.keep_least();
-      b->few_until = std::chrono::steady_clock::now() + std::chrono::duration_cast<std::chrono::steady_clock::duration>(
-                                                           std::chrono::duration<double>(kStarvedFor));
-    }
     int first = -2, code = ABS_OK;
     for (size_t k = 0; k < rc.size(); ++k)
       if (rc[(size_t)k] != ABS_OK && (first == -2 || bad_sim[(size_t)k] < first)) { first = bad_sim[(size_t)k]; code = rc[(size_t)k]; }
@@ -840,7 +834,7 @@ int abs_batch_round(abs_batch* b, int32_t n_rounds) {
   };
   int rc = ABS_OK;
   {
-    const int least = least_threads(S), wish = std::chrono::steady_clock::now() < b->few_until ? least : most_threads(S);
+    const int least = least_threads(S), wish = b->watch.starved(std::chrono::steady_clock::now()) ? least : most_threads(S);
     Team team(b->pool.get(), batch_threads(), least, std::max(least, wish), [&st](int k, int T) { st.work(k, T); });
     for (int32_t it = 0; it < n_rounds && rc == ABS_OK; ++it) {
       st.buf = (int)(it & 1);

@@ -97,6 +97,33 @@ class SpinBudget {
   std::atomic<int> used_{0};
 };
 
+// CPUs that other processes use, or a quota, can be short all the same.  Told of every phase that waits for nothing
+// but its threads, this says when they did not get to run for a share of the time that fewer threads would win back:
+// phases of kLong and more for over a tenth of the time, at least three close together.  A thread that was held up
+// once costs that one phase, not ten seconds with two threads for eight (64 simulations: linear 25 -> 30 us a
+// round, softmax 52 -> 64).
+class StarvedWatch {
+ public:
+  using Clock = std::chrono::steady_clock;
+  // true: from now on, for kFew, the least threads do
+  bool phase_took(Clock::time_point now, double seconds) {
+    if (last_ != Clock::time_point{}) lost_ = std::max(0.0, lost_ - kShare * std::chrono::duration<double>(now - last_).count());
+    last_ = now;
+    if (seconds > kLong) lost_ += std::min(seconds, kMost);
+    if (lost_ <= kEnough) return false;
+    lost_ = 0.0;
+    until_ = now + kFew;
+    return true;
+  }
+  bool starved(Clock::time_point now) const { return now < until_; }
+
+ private:
+  static constexpr double kLong = 5e-3, kMost = 8e-3, kEnough = 20e-3, kShare = 0.1;      // seconds; share of the time
+  static constexpr std::chrono::seconds kFew{10};
+  Clock::time_point last_{}, until_{};
+  double lost_ = 0.0;
+};
+
 // The threads of one call: the caller (thread 0) and helpers 1 .. size() - 1 of a pool.
 class Team {
  public:

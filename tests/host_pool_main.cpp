@@ -98,6 +98,29 @@ static void short_of_memory(SpinBudget& budget) {
   }
 }
 
+// One thread held up now and then leaves the batch its threads; threads that do not run much of the time do not,
+// and not for ever.
+static void watched() {
+  using namespace std::chrono;
+  StarvedWatch::Clock::time_point t = StarvedWatch::Clock::now();
+  StarvedWatch once, seldom, often, slow;
+  CHECK(!once.starved(t) && !once.phase_took(t, 5.0) && !once.starved(t));
+  for (int i = 0; i < 100000; ++i) {
+    t += microseconds(50);
+    CHECK(!once.phase_took(t, 20e-6));
+  }
+  for (int i = 0; i < 200; ++i) {                    // 5 ms in every 100
+    t += milliseconds(100);
+    CHECK(!seldom.phase_took(t, 6e-3));
+  }
+  int phases = 1;
+  for (; !often.phase_took(t, 10e-3); ++phases) { CHECK(phases < 10); t += milliseconds(12); }
+  CHECK(phases >= 3 && often.starved(t) && often.starved(t + seconds(9)) && !often.starved(t + seconds(11)));
+  t += seconds(11);
+  CHECK(!often.phase_took(t, 10e-3));                // starts anew
+  for (phases = 1; !slow.phase_took(t, 6e-3); ++phases) { CHECK(phases < 20); t += milliseconds(20); }
+}
+
 int main() {
   SpinBudget budget(8);
   HostPool pool(7);
@@ -106,6 +129,7 @@ int main() {
   alone(pool, budget);
   short_of_memory(budget);
   together();
+  watched();
   {
     Call c;                                         // no pool at all
     Team team(nullptr, budget, 1, 1, [&](int k, int T) { c.work(k, T); });
