@@ -467,6 +467,16 @@ __device__ __forceinline__ void lds_dma16_raw(const uint16_t* gsrc, uint16_t* ld
                : "memory");
 }
 
+// ... to a byte offset in LDS (uniform: scalar arithmetic only, so that m0 is never written by a vector instruction
+// right before the request, which needs more wait states than the one here), 16 or 4 bytes per lane.
+__device__ __forceinline__ uint32_t lds_offset(const void* p) { return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p; }
+__device__ __forceinline__ void lds_dma16_at(const uint16_t* gsrc, uint32_t lds) {
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(gsrc), "{m0}"(lds) : "memory");
+}
+__device__ __forceinline__ void lds_dma4_at(const uint32_t* gsrc, uint32_t lds) {
+  asm volatile("s_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(gsrc), "{m0}"(lds) : "memory");
+}
+
 // A ring's hand-over: at most N of this wavefront's requests are still on their way (the later stages'),
 // its own LDS reads are done, and everybody has got here.
 template <int N>
@@ -1013,18 +1023,30 @@ __global__ __launch_bounds__(256, 2) void mlp_wide_kernel(GemmArgs g, RoundDesc 
 // tile is the bytes staged per flop: a 256 x 256 tile stages 64 KB per 8.4 MFLOP, two
 // thirds of what the 128 x 256 tile needs.  Tiles go from global memory straight into
 // LDS (global_load_lds_dwordx4: lane l of a wavefront fills bytes [16 l, 16 l + 16) of a
-// 1 KB LDS block, i.e. 8 rows of 128 B), two stages, so the loads of step k+1 are in
-// flight during all of step k and there is one barrier per step.  The XOR swizzle is
+// 1 KB LDS block, i.e. 8 rows of 128 B).  The XOR swizzle is
 // applied on the global side: the lane that fills chunk position p of row r fetches
 // logical chunk p ^ ((r >> 1) & 7).
+// A k-step is four turns of 16 MFMAs per wavefront (half of A times half of B).  The two wavefronts of a SIMD are one
+// half-turn apart (the second one's extra barrier before the loop): while one multiplies, the other reads its next
+// fragments and requests, so the matrix pipes do not wait for a k-step's first fragments, nor for the address
+// unit to take 64 requests in a row.  A half of A or B is requested again as soon as both groups have it in registers,
+// for the k-step after the next: a request is seven turns in flight (1.75 k-steps; with two stages filled and
+// drained whole it was one), counted (vmcnt) and never drained inside the loop.
+// us, the loop with one barrier and a drained stage per k-step / this one, same box, 32768 rows (outputs bit for bit the same):
+// weight gradient 2048 x 2048 222 / 201, 3072 x 2048 from gathered rows 381 / 344, forward 2048 x 2048 with one output 240 / 220
+// (row-major A) and 246 / 230 (transposed A), first layer from 3072 gathered features 358 / 326.  Without its requests the loop takes
+// 161 us (1.70 PFLOP/s), with all of them hitting the L2 183.  Tried on it: requests in front of the fragment reads (+3 to
+// +9 %), between the MFMAs (+6 to +9 %), requests of the next-but-one turn so that no read is waited for in front of a barrier
+// (+1 %), s_setprio around the MFMAs (nothing: kept out).
 // Needs: row count and column count multiples of 256, GATHER with d_0 equal to the padded
 // k extent (d_0 % 128 == 0: a gathered row is read over the whole k range).
 constexpr int TM3 = 256, TN3 = 256;
 constexpr int kStage3 = (TM3 + TN3) * BK;            // elements per LDS stage (64 KB)
+constexpr int kHalf3 = 128 * BK;                     // elements of a half of a k-step's A or B (16 KB)
 constexpr int kEpiPitch3 = 64 + 8;                   // per wavefront: staging [64 n][72] and [64 m][72]
 constexpr int kEpiElems3 = 8 * 2 * 64 * kEpiPitch3;   // 147456 B
 constexpr int kSmem3 = 2 * kStage3 > kEpiElems3 ? 2 * kStage3 : kEpiElems3;
-static_assert(kSmem3 * 2 <= 160 * 1024, "LDS budget");
+static_assert(kSmem3 * 2 + 8 * 1024 <= 160 * 1024, "LDS budget");
 
 template <int EPI, bool GATHER, bool PER_UPLOAD, int TAG>
 __global__ __launch_bounds__(512, 1) void mlp_gemm256_kernel(GemmArgs g, RoundDesc rd) {
@@ -1039,9 +1061,9 @@ __global__ __launch_bounds__(512, 1) void mlp_gemm256_kernel(GemmArgs g, RoundDe
   constexpr bool kLocal = EPI == EPI_WGRAD && TAG >= 4;
   constexpr bool kATR = (EPI == EPI_WGRAD && (TAG == 2 || TAG == 4)) || ((EPI == EPI_RELU || EPI == EPI_DGRAD) && TAG == 3);
   constexpr bool kARows = kATR && EPI == EPI_WGRAD;      // the k rows of A are gathered through a_rowidx
-  __shared__ __attribute__((aligned(16))) uint16_t smem[kSmem3];
+  __shared__ __attribute__((aligned(16))) uint16_t smem[kSmem3 + (kARows ? 4 * 1024 : 0)];
 
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave >> 2, wn = wave & 3;
   const int bx = blockIdx.x;
   if (EPI == EPI_WGRAD && (g.pig_blocks | g.bias_blocks)) {
@@ -1099,80 +1121,79 @@ __global__ __launch_bounds__(512, 1) void mlp_gemm256_kernel(GemmArgs g, RoundDe
     Bt += (size_t)slot * g.bt_slot_stride;
   }
 
-  // DMA assignment: wavefront w, instruction i fills rows (4 w + i) 8 .. + 8 of a tile;
-  // lane l handles row + (l >> 3), chunk position l & 7.
-  const int dr = wave * 32 + (lane >> 3);                  // row for i = 0; + 8 i
+  // Requests.  A half of A (h = 0, 1) is rows h 64 .. + 64 of both wavefront rows' 128, a half of B columns
+  // h 32 .. + 32 of the four wavefront columns' 64: 16 KB each, two 1 KB requests per wavefront.  A request fills 8
+  // rows of 128 bytes, lane l chunk position l & 7 of row l >> 3 (chunk swizzle (row >> 1) & 7).  kATR: a half of A is k rows
+  // h 32 .. + 32 of all 256 columns; a request fills two rows of 512 bytes, lane l 16 bytes of row l >> 5; the 64-byte
+  // blocks of a row are stored at position b ^ (row & 3), so that the four rows one transposing read touches cover all banks.
   const int pc = lane & 7;
-  const int c_even = (pc ^ (((lane >> 4)) & 7)) * 8;        // (r >> 1) & 7 for i even
-  const int c_odd = (pc ^ ((4 + (lane >> 4)) & 7)) * 8;     //               for i odd
-  const uint16_t *pa0 = nullptr, *pa1 = nullptr, *pa2 = nullptr, *pa3 = nullptr;
-  // kATR: a k-step's A tile is 64 gathered rows x 256 columns (512 B per row); a DMA instruction
-  // fills two rows, wavefront w takes rows 8 w .. 8 w + 7.  Lane l of instruction q handles row
-  // 8 w + 2 q + (l >> 5) and chunk position l & 31; the 64-byte blocks of a row are stored at block
-  // position b ^ (row & 3), so that the four rows one transposing read touches cover all banks.
-  const int atr_row = wave * 8 + (lane >> 5);                 // + 2 q
+  const int c_even = (pc ^ (((lane >> 4)) & 7)) * 8;        // (row >> 1) & 7 for request 0
+  const int c_odd = (pc ^ ((4 + (lane >> 4)) & 7)) * 8;     //                for request 1
+  const int dr = (wave >> 2) * 128 + (wave & 3) * 16 + (lane >> 3);         // A row of request 0, half 0
+  const uint16_t* pa[4] = {nullptr, nullptr, nullptr, nullptr};              // (GATHER) [2 half + request]
+  const uint16_t *va0 = nullptr, *va1 = nullptr;                             // a lane's pieces of A at k-step 0, else
+  const int atr_row = wave * 4 + (lane >> 5);                                // k row of request 0, half 0 (kATR)
   const int atr_c = lane & 31;
-  const int atr_col_even = m0 + (((((atr_c >> 2) ^ (lane >> 5)) << 2) | (atr_c & 3)) << 3);          // q even
-  const int atr_col_odd = m0 + (((((atr_c >> 2) ^ (2 + (lane >> 5))) << 2) | (atr_c & 3)) << 3);     // q odd
-  uint32_t aidx0 = 0, aidx1 = 0, aidx2 = 0, aidx3 = 0;       // dataset rows of the next tile to request
+  const int atr_col0 = m0 + (((((atr_c >> 2) ^ (lane >> 5)) << 2) | (atr_c & 3)) << 3);          // request 0
+  const int atr_col1 = m0 + (((((atr_c >> 2) ^ (2 + (lane >> 5))) << 2) | (atr_c & 3)) << 3);    // request 1
   if (kATR) {
-  } else if (GATHER) {
-    uint32_t ri[4];
-    if (g.gen_rows) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        bool real;
-        ri[i] = gen_row_of(g, rd, m0 + dr + 8 * i, &real);
-        if (n0 == 0 && pc == 0) gen_row_store(g, m0 + dr + 8 * i, ri[i], real);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) ri[i] = g.a_rowidx[m0 + dr + 8 * i];
+    if (!kARows) {
+      va0 = g.A + ((size_t)ks0 * BK + atr_row) * g.lda + atr_col0;
+      va1 = g.A + ((size_t)ks0 * BK + atr_row + 2) * g.lda + atr_col1;
     }
-    pa0 = g.A + (size_t)ri[0] * g.lda + c_even;
-    pa1 = g.A + (size_t)ri[1] * g.lda + c_odd;
-    pa2 = g.A + (size_t)ri[2] * g.lda + c_even;
-    pa3 = g.A + (size_t)ri[3] * g.lda + c_odd;
+  } else if (GATHER) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int m = m0 + dr + (q >> 1) * 64 + (q & 1) * 8;
+      uint32_t row;
+      if (g.gen_rows) {
+        bool real;
+        row = gen_row_of(g, rd, m, &real);
+        if (n0 == 0 && pc == 0) gen_row_store(g, m, row, real);
+      } else {
+        row = g.a_rowidx[m];
+      }
+      pa[q] = g.A + (size_t)row * g.lda + (size_t)ks0 * BK + ((q & 1) ? c_odd : c_even);
+    }
   } else {
-    const uint16_t* base = g.A + (size_t)(m0 + dr) * g.lda;
-    pa0 = base + c_even; pa1 = base + 8 * g.lda + c_odd;
-    pa2 = base + 16 * g.lda + c_even; pa3 = base + 24 * g.lda + c_odd;
+    va0 = g.A + (size_t)(m0 + dr) * g.lda + (size_t)ks0 * BK + c_even;
+    va1 = g.A + (size_t)(m0 + dr + 8) * g.lda + (size_t)ks0 * BK + c_odd;
   }
-  const uint16_t* bbase = Bt + (size_t)(n0 + dr) * g.ldb;
-  const uint16_t* pb0 = bbase + c_even;
-  const uint16_t* pb1 = bbase + 8 * g.ldb + c_odd;
-  const uint16_t* pb2 = bbase + 16 * g.ldb + c_even;
-  const uint16_t* pb3 = bbase + 24 * g.ldb + c_odd;
-  uint16_t* const dmaA = smem + wave * 4 * 512;              // 512 elements = 1 KB per instruction
-  uint16_t* const dmaB = smem + TM3 * BK + wave * 4 * 512;
-
-  // (kATR) the four dataset rows this lane requests for k-step ks
-#define ABS_AIDX(ks)                                                              \
-  if (kARows) {                                                                   \
-    const uint32_t* ri_ = g.a_rowidx + (size_t)(ks) * BK + atr_row;               \
-    aidx0 = ri_[0]; aidx1 = ri_[2]; aidx2 = ri_[4]; aidx3 = ri_[6];               \
-  } else {                                                                        \
-    aidx0 = (uint32_t)((ks) * BK + atr_row);                                      \
-    aidx1 = aidx0 + 2; aidx2 = aidx0 + 4; aidx3 = aidx0 + 6;                      \
+  const int br = (wave >> 1) * 64 + (wave & 1) * 16 + (lane >> 3);          // B row of request 0, half 0
+  const uint16_t* const vb0 = Bt + (size_t)(n0 + br) * g.ldb + (size_t)ks0 * BK + c_even;
+  const uint16_t* const vb1 = Bt + (size_t)(n0 + br + 8) * g.ldb + (size_t)ks0 * BK + c_odd;
+  const uint32_t dmaA = lds_offset(smem) + (uint32_t)wave * 2048u;           // this wavefront's 2 KB of a half
+  const uint32_t dmaB = dmaA + 4 * kHalf3 * 2;
+  const int nks = ks1 - ks0;
+  // (kARows) The dataset rows of a k-step travel through a ring of four steps in LDS as well, each wavefront's 8 (16
+  // bytes per parity of lane >> 5) as a request of its own: a register load would be counted with the tile requests,
+  // and the wait for it would empty the pipeline.
+  u32x4_t aidx = {0, 0, 0, 0};                                               // [2 half + request] of the k-step to request next
+  const uint16_t* const idx_ring = smem + (kARows ? kSmem3 + wave * 128 : 0);   // 256 bytes per wavefront, 2 KB per step
+  const uint32_t idx_dma = lds_offset(smem) + kSmem3 * 2 + (uint32_t)wave * 256u;
+  const uint32_t* const idx_src = kARows ? g.a_rowidx + (size_t)ks0 * BK + ((lane >> 1) & 1) * 32 + wave * 4 + (lane & 1) * 2 + ((lane >> 2) & 1) : nullptr;
+#define ABS_DMA_IDX(j_) if (kARows) lds_dma4_at(idx_src + (size_t)min(j_, nks - 1) * BK, idx_dma + (uint32_t)((j_) & 3) * 2048u);
+#define ABS_DMA_A(j_, st_, h_)                                                                                \
+  {                                                                                                           \
+    const uint32_t a_ = dmaA + ((st_) * 2 + (h_)) * kHalf3 * 2;                                               \
+    if (kARows) {                                                                                             \
+      lds_dma16_at(g.A + (size_t)aidx[2 * (h_)] * g.lda + atr_col0, a_);                                      \
+      lds_dma16_at(g.A + (size_t)aidx[2 * (h_) + 1] * g.lda + atr_col1, a_ + 1024);                           \
+    } else if (kATR) {                                                                                        \
+      const size_t o_ = (size_t)((j_) * BK + (h_) * 32) * g.lda;                                              \
+      lds_dma16_at(va0 + o_, a_); lds_dma16_at(va1 + o_, a_ + 1024);                                          \
+    } else if (GATHER) {                                                                                      \
+      lds_dma16_at(pa[2 * (h_)] + (j_) * BK, a_); lds_dma16_at(pa[2 * (h_) + 1] + (j_) * BK, a_ + 1024);      \
+    } else {                                                                                                  \
+      const size_t o_ = (size_t)(j_) * BK + (size_t)(h_) * 64 * g.lda;                                        \
+      lds_dma16_at(va0 + o_, a_); lds_dma16_at(va1 + o_, a_ + 1024);                                          \
+    }                                                                                                         \
   }
-#define ABS_DMA(ks, stage)                                                        \
-  {                                                                               \
-    const int k0_ = (ks) * BK;                                                    \
-    uint16_t* a_ = dmaA + (stage) * kStage3;                                      \
-    uint16_t* b_ = dmaB + (stage) * kStage3;                                      \
-    if (kATR) {                                                                   \
-      lds_dma16_raw(g.A + (size_t)aidx0 * g.lda + atr_col_even, a_);              \
-      lds_dma16_raw(g.A + (size_t)aidx1 * g.lda + atr_col_odd, a_ + 512);         \
-      lds_dma16_raw(g.A + (size_t)aidx2 * g.lda + atr_col_even, a_ + 1024);       \
-      lds_dma16_raw(g.A + (size_t)aidx3 * g.lda + atr_col_odd, a_ + 1536);        \
-      lds_dma16_raw(pb0 + k0_, b_);        lds_dma16_raw(pb1 + k0_, b_ + 512);    \
-      lds_dma16_raw(pb2 + k0_, b_ + 1024); lds_dma16_raw(pb3 + k0_, b_ + 1536);   \
-    } else {                                                                      \
-      lds_dma16(pa0 + k0_, a_);        lds_dma16(pa1 + k0_, a_ + 512);            \
-      lds_dma16(pa2 + k0_, a_ + 1024); lds_dma16(pa3 + k0_, a_ + 1536);           \
-      lds_dma16(pb0 + k0_, b_);        lds_dma16(pb1 + k0_, b_ + 512);            \
-      lds_dma16(pb2 + k0_, b_ + 1024); lds_dma16(pb3 + k0_, b_ + 1536);           \
-    }                                                                             \
+#define ABS_DMA_B(j_, st_, h_)                                                                                \
+  {                                                                                                           \
+    const uint32_t b_ = dmaB + ((st_) * 2 + (h_)) * kHalf3 * 2;                                               \
+    const size_t o_ = (size_t)(j_) * BK + (size_t)(h_) * 32 * g.ldb;                                          \
+    lds_dma16_at(vb0 + o_, b_); lds_dma16_at(vb1 + o_, b_ + 1024);                                            \
   }
 
   // ---- main loop on MFMA 16x16x32.  A wavefront's 128 x 64 sub-tile is 8 x 4 blocks of 16 x 16
@@ -1180,9 +1201,7 @@ __global__ __launch_bounds__(512, 1) void mlp_gemm256_kernel(GemmArgs g, RoundDe
   // operand block, and accumulator register r of a block is row 4 (l >> 4) + r, column l & 15.
   // Per flop this form moves a quarter of the accumulator registers in and out of the matrix pipe
   // that the 32x32x16 form does: on random operands the pipes alone sustain 2.18 instead of
-  // 1.86 PFLOP/s before the chip lowers its clock, and the products got 3-7 % faster.  The
-  // fragments of a 32-wide sub-step are read in halves (rows 0-63, rows 64-127 of A; B once per
-  // sub-step) one half ahead of the MFMAs that use them, pinned there with sched_group_barrier.
+  // 1.86 PFLOP/s before the chip lowers its clock.
   f32x4_t acc[8][4];
 #pragma unroll
   for (int a = 0; a < 8; ++a)
@@ -1191,87 +1210,109 @@ __global__ __launch_bounds__(512, 1) void mlp_gemm256_kernel(GemmArgs g, RoundDe
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[a][b][r] = 0.f;
   const int lr = lane & 15, lk = lane >> 4;
-  const int fa_row = (wm * 128 + lr) * BK, fb_row = TM3 * BK + (wn * 64 + lr) * BK;
   const int sw = (lr >> 1) & 7;
   const int ch0 = (lk ^ sw) << 3, ch1 = ((4 | lk) ^ sw) << 3;
+  const int fa_row = (wm * 64 + lr) * BK, fb_row = 4 * kHalf3 + (wn * 32 + lr) * BK;
   // kATR (A stored [k][m]): a block's fragment is two transposing reads.  Such a read works on groups
   // of 16 lanes: lane s of a group points at 4 consecutive columns of row s / 4 of a 4 x 16 piece and
   // receives column s of its 4 rows.  Quarter-wavefront q takes k rows 8 q .. 8 q + 7 of the 32-row
   // sub-step (pieces at rows + 0 and + 4), all quarters the same 16 columns; the block position is
   // XORed with the row's low bits (= s / 4) as stored.
   const int t16s = lane & 15, t16r = t16s >> 2;
-  int fa_tr[8];
+  int fa_tr[4];                                              // blocks 2 i, 2 i + 1 of the wavefront's eight
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
-    fa_tr[a] = (t16r + 8 * lk) * TM3 + (wm * 4 + ((a >> 1) ^ t16r)) * 32 + 16 * (a & 1) + 4 * (t16s & 3);
-  if (ks0 < ks1) {
-    if (kATR) ABS_AIDX(ks0);
-    ABS_DMA(ks0, 0);
-    if (kATR) ABS_AIDX(min(ks0 + 1, ks1 - 1));
-    for (int ks = ks0; ks < ks1; ++ks) {
-      const int stage = (ks - ks0) & 1;
-      __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): this wavefront's part of tile ks is in LDS
-      __syncthreads();                         // ... and everybody's; everybody is done with tile ks-1
-      if (ks + 1 < ks1) ABS_DMA(ks + 1, stage ^ 1);
-      if (kATR) ABS_AIDX(min(ks + 2, ks1 - 1));
-      const uint16_t* sS = smem + stage * kStage3;
-      bf16x8_t fa[2][4], fb[2][4];
-#define ABS_LOAD_A(set, s_, h_)                                                                                    \
-  _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                                  \
-    if (kATR) {                                                                                                    \
-      typedef short s16x4_ __attribute__((ext_vector_type(4)));                                                    \
-      const uint16_t* q_ = sS + fa_tr[(h_) * 4 + i] + (s_) * 32 * TM3;                                             \
-      union { s16x4_ h[2]; bf16x8_t v; } u_;                                                                       \
-      u_.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_*)(q_));          \
-      u_.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_*)(q_ + 4 * TM3)); \
-      fa[set][i] = u_.v;                                                                                           \
-    } else {                                                                                                       \
-      fa[set][i] = *(const bf16x8_t*)&sS[fa_row + ((h_) * 4 + i) * 16 * BK + ((s_) ? ch1 : ch0)];                  \
-    }                                                                                                              \
+  for (int i = 0; i < 4; ++i) fa_tr[i] = (t16r + 8 * lk) * TM3 + (wm * 4 + (i ^ t16r)) * 32 + 4 * (t16s & 3);
+  // fragments of a half of A: four blocks of rows, both 32-wide sub-steps [2 block + sub-step]; kATR: eight blocks, one sub-step
+  bf16x8_t fa[8], fbx[2][2], fby[2][2];
+#define ABS_LOAD_A(st_, h_)                                                                                           \
+  _Pragma("unroll") for (int q_ = 0; q_ < 8; ++q_) {                                                                  \
+    if (kATR) {                                                                                                       \
+      typedef short s16x4_ __attribute__((ext_vector_type(4)));                                                       \
+      const uint16_t* p_ = smem + fa_tr[q_ >> 1] + ((st_) * 2 + (h_)) * kHalf3 + (q_ & 1) * 16;                       \
+      union { s16x4_ h[2]; bf16x8_t v; } u_;                                                                          \
+      u_.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_*)(p_));             \
+      u_.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_*)(p_ + 4 * TM3));   \
+      fa[q_] = u_.v;                                                                                                  \
+    } else {                                                                                                          \
+      fa[q_] = *(const bf16x8_t*)&smem[fa_row + ((q_ & 1) ? ch1 : ch0) + ((st_) * 2 + (h_)) * kHalf3 + (q_ >> 1) * 16 * BK]; \
+    }                                                                                                                 \
   }
-#define ABS_LOAD_B(set, s_)     _Pragma("unroll") for (int i = 0; i < 4; ++i) fb[set][i] = *(const bf16x8_t*)&sS[fb_row + i * 16 * BK + ((s_) ? ch1 : ch0)];
-#define ABS_MMA(h_, aset, bset)                                                          \
-  _Pragma("unroll") for (int i = 0; i < 4; ++i)                                          \
-    _Pragma("unroll") for (int b = 0; b < 4; ++b)                                        \
-      acc[(h_) * 4 + i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[aset][i], fb[bset][b], acc[(h_) * 4 + i][b], 0, 0, 0);
-      ABS_LOAD_B(0, 0); ABS_LOAD_A(0, 0, 0);
-      ABS_LOAD_A(1, 0, 1);                       ABS_MMA(0, 0, 0);
-      ABS_LOAD_B(1, 1); ABS_LOAD_A(0, 1, 0);     ABS_MMA(1, 1, 0);
-      ABS_LOAD_A(1, 1, 1);                       ABS_MMA(0, 0, 1);
-                                                 ABS_MMA(1, 1, 1);
-#undef ABS_LOAD_A
-#undef ABS_LOAD_B
-#undef ABS_MMA
-      // issue order: the first fragments, then the reads of the next half spread between the
-      // 16 MFMAs of the current one (a transposed A block takes two reads)
-      if (kATR) {
-        __builtin_amdgcn_sched_group_barrier(0x100, 12, 0);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) { __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); }
-        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-#pragma unroll
-        for (int i = 0; i < 12; ++i) { __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); }
-        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) { __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); }
-        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-      } else {
-        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { __builtin_amdgcn_sched_group_barrier(0x008, 2, 0); __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); }
-        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) { __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); }
-        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { __builtin_amdgcn_sched_group_barrier(0x008, 2, 0); __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); }
-        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);
+#define ABS_LOAD_B(dst_, st_, h_)                                                                                     \
+  _Pragma("unroll") for (int s_ = 0; s_ < 2; ++s_) _Pragma("unroll") for (int j_ = 0; j_ < 2; ++j_)                   \
+    dst_[j_][s_] = *(const bf16x8_t*)&smem[fb_row + (s_ ? ch1 : ch0) + ((st_) * 2 + (h_)) * kHalf3 + j_ * 16 * BK];
+  // multiply the halves in the registers, between two barriers
+#define ABS_MMA(ha_, hb_, b_)                                                                                         \
+  __builtin_amdgcn_sched_barrier(0);                                                                                  \
+  if (kATR) {                                                                                                         \
+    _Pragma("unroll") for (int i_ = 0; i_ < 8; ++i_) _Pragma("unroll") for (int j_ = 0; j_ < 2; ++j_)                 \
+      acc[i_][(hb_) * 2 + j_] =                                                                                       \
+          __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i_], b_[j_][ha_], acc[i_][(hb_) * 2 + j_], 0, 0, 0);             \
+  } else {                                                                                                            \
+    _Pragma("unroll") for (int s_ = 0; s_ < 2; ++s_) _Pragma("unroll") for (int i_ = 0; i_ < 4; ++i_)                 \
+      _Pragma("unroll") for (int j_ = 0; j_ < 2; ++j_)                                                                \
+        acc[(ha_) * 4 + i_][(hb_) * 2 + j_] =                                                                         \
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[2 * i_ + s_], b_[j_][s_], acc[(ha_) * 4 + i_][(hb_) * 2 + j_], 0, 0, 0); \
+  }                                                                                                                   \
+  __builtin_amdgcn_sched_barrier(0);                                                                                  \
+  asm volatile("s_barrier" ::: "memory");
+#define ABS_TURN(i_)                                                                                                  \
+  if (left >= 2)      ring_wait_barrier<kARows ? 13 : 12>();       /* (kARows: one request of indices among them) */  \
+  else if (left == 1) ring_wait_barrier<10 - 2 * (i_)>();                                                             \
+  else                ring_wait_barrier<(i_) == 0 ? 2 : 0>();
+#define ABS_STEP(X_, Y_, st_)                                                                                         \
+  {                                                                                                                   \
+    const int left = nks - 1 - j;                                                                                     \
+    ABS_LOAD_A(st_, 0);                                                                                               \
+    if (kARows) aidx = *(const u32x4_t*)(idx_ring + ((j + 2) & 3) * 1024 + (lane >> 5) * 8);                          \
+    if (left >= 2) { ABS_DMA_IDX(j + 4); ABS_DMA_B(j + 2, st_, 0); }                                                  \
+    ABS_TURN(0); ABS_MMA(0, 0, X_);                                                                                   \
+    ABS_LOAD_B(Y_, st_, 1);                                                                                           \
+    if (left >= 2) ABS_DMA_A(j + 2, st_, 0);                                                                          \
+    ABS_TURN(1); ABS_MMA(0, 1, Y_);                                                                                   \
+    ABS_LOAD_A(st_, 1);                                                                                               \
+    if (left >= 2) ABS_DMA_B(j + 2, st_, 1);                                                                          \
+    ABS_TURN(2); ABS_MMA(1, 1, Y_);                                                                                   \
+    if (left >= 1) ABS_LOAD_B(Y_, (st_) ^ 1, 0);                                                                      \
+    if (left >= 2) ABS_DMA_A(j + 2, st_, 1);                                                                          \
+    ABS_TURN(3); ABS_MMA(1, 0, X_);                                                                                   \
+  }
+  if (nks > 0) {
+    if (kARows) {
+      const uint32_t* r0 = g.a_rowidx + (size_t)ks0 * BK + atr_row;
+      const uint32_t* r1 = r0 + (nks > 1 ? BK : 0);
+      ABS_DMA_IDX(2); ABS_DMA_IDX(3);
+      aidx = u32x4_t{r0[0], r0[2], r0[32], r0[34]};
+      const u32x4_t a1 = {r1[0], r1[2], r1[32], r1[34]};
+      ABS_DMA_B(0, 0, 0); ABS_DMA_A(0, 0, 0); ABS_DMA_B(0, 0, 1); ABS_DMA_A(0, 0, 1);
+      aidx = a1;
+    } else {
+      ABS_DMA_B(0, 0, 0); ABS_DMA_A(0, 0, 0); ABS_DMA_B(0, 0, 1); ABS_DMA_A(0, 0, 1);
     }
+    if (nks > 1) {
+      ABS_DMA_B(1, 1, 0); ABS_DMA_A(1, 1, 0); ABS_DMA_B(1, 1, 1); ABS_DMA_A(1, 1, 1);
+      ring_wait_barrier<12>();
+    } else {
+      ring_wait_barrier<4>();
+    }
+    ABS_LOAD_B(fbx, 0, 0);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // (requested again in the first turn)
+    if (wm) asm volatile("s_barrier" ::: "memory");
+    for (int j = 0;;) {
+      ABS_STEP(fbx, fby, 0);
+      if (++j >= nks) break;
+      ABS_STEP(fby, fbx, 1);
+      if (++j >= nks) break;
+    }
+    if (!wm) asm volatile("s_barrier" ::: "memory");
   }
-#undef ABS_DMA
-#undef ABS_AIDX
+#undef ABS_STEP
+#undef ABS_TURN
+#undef ABS_MMA
+#undef ABS_LOAD_B
+#undef ABS_LOAD_A
+#undef ABS_DMA_B
+#undef ABS_DMA_A
+#undef ABS_DMA_IDX
   __syncthreads();      // all fragment reads done before the staging area is reused
 
   // ---- epilogue: bf16 outputs leave through this wavefront's private LDS staging, half of the

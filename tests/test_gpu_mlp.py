@@ -118,3 +118,28 @@ def test_tile_kernel_edges(over, T):
     """The tile kernel where its remainders are: short rings, zero-filled columns of gathered rows, both tile sizes."""
     p = workloads.scaled_preset(3, **over)
     _check(run_pair(p, T, checkpoints=(1,)))
+
+
+@pytest.mark.parametrize("d0,h1,h2,K,T", [
+    (128, 512, 512, 64, 2),        # 2 k-steps in the first layer: no turn of the loop requests anything
+    (384, 768, 512, 64, 2),        # 6 and 12
+    (512, 512, 768, 64, 2),        # 8 in every product
+    (768, 2048, 1024, 37, 2),      # weight gradients too, one straight from the dataset: seven ranges of 19 and one of 15
+])
+def test_large_tile_kernel_by_number_of_k_steps(d0, h1, h2, K, T):
+    """The 256 x 256 kernel over short and odd contractions, against the oracle, and two runs bit for bit: a request that
+    overtakes a reader of its place in LDS changes a handful of blocks of 16 x 16, differently each time."""
+    import paper_2301_08895_amd as lib
+    p = workloads.scaled_preset(3, M=64 * K, dims=[d0, h1, h2, 10], N=K, K0=K, B=256, n_slow=0, lr=1e-4)
+    plan = lib.abs_mlp_round_plan(lib.make_config(p), K)
+    assert plan.count("256x256") >= 4, plan
+    res = run_pair(p, T, checkpoints=(1,))
+    _check(res)
+    d = workloads.make_inputs(p)
+    runs = []
+    for _ in range(2):
+        sim = lib.Simulation(p, d)
+        sim.round(4)
+        runs.append(sim.model().copy())
+        sim.close()
+    assert np.array_equal(runs[0], runs[1])
