@@ -1722,6 +1722,153 @@ __global__ __launch_bounds__(256, 1) void mlp_logits_ce_kernel(LogitsCeArgs a, R
   }
 }
 
+// The same for rounds of few rows (ce_rows), where the kernel above leaves most CUs idle and each busy one waits
+// for its own long stream of tiles (0.9 us a k-step of 64, bound by what one CU has in flight: some 32 KB): a workgroup owns 32 rows, its four wavefronts share the CONTRACTION (pairs of
+// 32-wide sub-steps p, p + 4, ...), and operands go from memory straight into registers, the next pair's on their
+// way under this one's products.  The
+// four partial logits meet in LDS, summed in wavefront order; then a wavefront has 8 whole rows, 16 lanes to a row.
+// us, 128-row / 32-row workgroups: 1024 x 512, 10 classes 9.0 / 6.7, 4096 x 1024 12.9 / 7.8, 1152 x 300, 26 classes 8.2 / 6.5,
+// 8192 x 2048, 100 classes 33 / 28.  Eight wavefronts to the contraction: 7.3 instead of 7.8 for 4096 x 1024, but
+// 46 instead of 28 with 100 classes (more lines asked for than the L1 can hold until their other half is).
+constexpr int kCeFewRows = 32;
+template <int CB>                        // blocks of 16 classes that are computed: 16 CB >= C, at most 8
+__global__ __launch_bounds__(256, 1) void mlp_logits_ce_few_kernel(LogitsCeArgs a, RoundDesc rd) {
+  constexpr int kBlk = 320;              // floats of a block of partial logits: 64 x 4, quarter-wavefronts 16 further apart
+  constexpr int kRedFloats = 4 * 2 * CB * kBlk;
+  constexpr int NP = CB <= 4 ? 64 : 128; // padded class count dp_L
+  constexpr int kPitchD = NP + 8, kPitchT = kCeFewRows + 8;
+  constexpr int kSmemBytes = kRedFloats * 4 > 64 * kGatherPitch * 2 ? kRedFloats * 4 : 64 * kGatherPitch * 2;
+  __shared__ __attribute__((aligned(16))) unsigned char smem_raw[kSmemBytes];
+  __shared__ __attribute__((aligned(16))) uint16_t sD[kCeFewRows * kPitchD], sT[NP * kPitchT];
+  __shared__ float s_loss[kCeFewRows];
+  if (const int own = (int)gridDim.x - a.gt.blocks; (int)blockIdx.x >= own) {
+    gather_t_block(a.gt, (int)blockIdx.x - own, (uint16_t*)smem_raw);
+    return;
+  }
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int m0 = blockIdx.x * kCeFewRows;
+  const int up = m0 / a.rows_per_upload;
+  const uint32_t slot = a.by_upload ? (uint32_t)up : rd.w[up].slot;
+  const float coef = rd.w[up].c;
+  const int l16 = lane & 15, lq = lane >> 4;
+  const uint16_t* const ph = a.H + (size_t)(m0 + l16) * a.ldh + lq * 8;
+  const uint16_t* const pw = a.Wt + (size_t)slot * a.w_slot_stride + (size_t)l16 * a.ldw + lq * 8;
+  f32x4_t acc[2][CB];
+#pragma unroll
+  for (int b = 0; b < CB; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[0][b][r] = acc[1][b][r] = 0.f;
+  struct Frags { bf16x8_t h[2][2], w[CB][2]; };
+  auto load = [&](Frags& f, int p) {
+    const size_t k0 = (size_t)p * BK;    // (the two halves of a 128-byte line one after the other: the second finds it in the L1)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) f.h[i][s] = *(const bf16x8_t*)(ph + (size_t)(16 * i) * a.ldh + k0 + 32 * s);
+#pragma unroll
+    for (int b = 0; b < CB; ++b)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) f.w[b][s] = *(const bf16x8_t*)(pw + (size_t)(16 * b) * a.ldw + k0 + 32 * s);
+  };
+  auto multiply = [&](const Frags& f) {  // block (i, b): class 16 b + 4 (l / 16) + r of row 16 i + l % 16
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int b = 0; b < CB; ++b)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[b][s], f.h[i][s], acc[i][b], 0, 0, 0);
+  };
+  Frags f0, f1;
+  int p = wave;
+  if (p < a.ksteps) load(f0, p);
+  // what the epilogue needs from memory: labels and biases (padding classes -inf: they drop out of max and sum)
+  int lab[2]; float bias[CB];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) lab[q] = a.label[m0 + wave * 8 + q * 4 + lq];
+#pragma unroll
+  for (int b = 0; b < CB; ++b) bias[b] = b * 16 + l16 < a.C ? (a.bias + (size_t)slot * a.bias_slot_stride)[b * 16 + l16] : -INFINITY;
+  while (p < a.ksteps) {
+    if (p + 4 < a.ksteps) load(f1, p + 4);
+    multiply(f0);
+    p += 4;
+    if (p >= a.ksteps) break;
+    if (p + 4 < a.ksteps) load(f0, p + 4);
+    multiply(f1);
+    p += 4;
+  }
+  float* const red = (float*)smem_raw;   // [wavefront][i][b][kBlk]
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int b = 0; b < CB; ++b)
+      *(f32x4_t*)&red[((wave * 2 + i) * CB + b) * kBlk + lane * 4 + lq * 16] = acc[i][b];
+  __syncthreads();
+  // row 8 wave + 4 q + lq of the workgroup, classes l16, l16 + 16, ...
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int ml = wave * 8 + q * 4 + lq;
+    const float* const at_row = red + (size_t)(ml >> 4) * CB * kBlk + (l16 >> 2) * 80 + (ml & 15) * 4 + (l16 & 3);
+    float z[CB], zmax = -INFINITY;
+#pragma unroll
+    for (int b = 0; b < CB; ++b) {
+      float v = at_row[b * kBlk];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) v += at_row[(w * 2 * CB + b) * kBlk];
+      z[b] = v + bias[b];
+      zmax = fmaxf(zmax, z[b]);
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, o, 64));
+    float ssum = 0.f, zy = 0.f;
+#pragma unroll
+    for (int b = 0; b < CB; ++b) {
+      const float dz = z[b] - zmax;
+      zy = b * 16 + l16 == lab[q] ? dz : zy;
+      z[b] = __expf(dz);
+      ssum += z[b];
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) { ssum += __shfl_xor(ssum, o, 64); zy += __shfl_xor(zy, o, 64); }
+    const float cr = lab[q] >= 0 ? coef : 0.f;             // c_k (softmax - onehot), zero for padding rows
+    const float scale = cr / ssum;
+    if (l16 == 0) s_loss[ml] = lab[q] >= 0 ? logf(ssum) - zy : 0.f;
+#pragma unroll
+    for (int b = 0; b < NP / 16; ++b) {
+      const float v = b < CB ? z[b < CB ? b : 0] * scale - (b * 16 + l16 == lab[q] ? cr : 0.f) : 0.f;
+      const uint16_t h = __builtin_bit_cast(uint16_t, (__bf16)v);
+      sD[ml * kPitchD + b * 16 + l16] = h;
+      sT[(b * 16 + l16) * kPitchT + ml] = h;
+    }
+  }
+  __syncthreads();
+  if (t == 0) {
+    float l = 0.f;
+#pragma unroll
+    for (int r = 0; r < kCeFewRows; ++r) l += s_loss[r];
+    a.rowloss[blockIdx.x] = l;
+  }
+  for (int q = t; q < kCeFewRows * (NP / 8); q += 256) {
+    const int row = q / (NP / 8), ch = q % (NP / 8);
+    *(uint4*)(a.dZ + (size_t)(m0 + row) * a.lddz + ch * 8) = *(const uint4*)&sD[row * kPitchD + ch * 8];
+  }
+  for (int q = t; q < NP * (kCeFewRows / 8); q += 256) {
+    const int n = q / (kCeFewRows / 8), rb8 = (q % (kCeFewRows / 8)) * 8;
+    *(uint4*)(a.dZT + (size_t)n * a.lddzt + m0 + rb8) = *(const uint4*)&sT[n * kPitchT + rb8];
+  }
+  if (t < NP) {                          // the bias gradient's share of these rows, in row order
+    float c = 0.f;
+#pragma unroll
+    for (int p8 = 0; p8 < kCeFewRows / 8; ++p8) {
+      const uint4 v = *(const uint4*)&sT[t * kPitchT + p8 * 8];
+      c += __uint_as_float(v.x << 16); c += __uint_as_float(v.x & 0xFFFF0000u);
+      c += __uint_as_float(v.y << 16); c += __uint_as_float(v.y & 0xFFFF0000u);
+      c += __uint_as_float(v.z << 16); c += __uint_as_float(v.z & 0xFFFF0000u);
+      c += __uint_as_float(v.w << 16); c += __uint_as_float(v.w & 0xFFFF0000u);
+    }
+    a.colsum[(size_t)blockIdx.x * a.ldcs + t] = c;
+  }
+}
+
 // ------------------------------------------------------------------ update + snapshot
 // The update as a kernel of its own (a TileUpdate for a whole matrix): the averaged change of the uploads
 // of local SGD, matrices whose rows are not 16-byte aligned, a round's last layer, the bf16 copies of w^0.
@@ -1950,7 +2097,7 @@ bool mlp_plan(const abs_config& c, MlpPlan& p, const char** why) {
     p.off_dzt[l] = take(p.ldm * p.dp[l] * 2);
   }
   p.off_rowloss = take(Mp * 4);
-  for (int l = 1; l <= L; ++l) p.off_colsum[l] = take(Mp / (l == L ? kCeRows : 64) * p.dp[l] * 4);
+  for (int l = 1; l <= L; ++l) p.off_colsum[l] = take(Mp / (l == L ? kCeFewRows : 64) * p.dp[l] * 4);
   for (int l = 1; l < L; ++l) p.off_maskbits[l] = take(round_up(Mp, 256) * round_up((size_t)p.dp[l], 256) / 8);
   if (p.U == 1) {          // (a local step is taken in the weight gradient's epilogue: no partials)
     for (int l = 0; l < L; ++l) p.off_partial[l] = take((size_t)p.dp[l] * (p.dp[l + 1] + kPartialPad) * 4 * kMaxSplit);
@@ -2242,6 +2389,18 @@ unsigned mlp_forward(const MlpArgs& a, const uint16_t* Xsrc, const RoundDesc& rd
   return have_bits;
 }
 
+// Rows per workgroup of the output-layer kernel.  32-row workgroups each read all of W_L^T, 128-row ones a quarter as
+// often, so the line lies where their number outweighs what they read: up to 32 classes at three 32-row workgroups
+// per CU, beyond (a workgroup's W_L^T is the larger operand) at half a one, or at one where the contraction is
+// long.  us of a round with 32 / 128 rows: 512-256-10, 16384 rows 65 / 70, 24576: 79.7 / 80.6, 32768: 103.9 / 103.5;
+// 512-2048-30, 16384: 205 / 208, 32768: 369 / 358; 512-256-100, 4096: 59.0 / 61.5, 6144: 68.1 / 66.6, 8192: 69.6 / 68.0;
+// 512-1536-100, 8192: 115.6 / 114.3; 512-2048-100, 8192: 133 / 138, 10240: 189 / 175.
+int ce_rows(const MlpPlan& p, int rows) {
+  const bool few = p.d[p.L] <= 32 ? rows <= 24576
+                 : p.dp[p.L] <= 128 && (rows <= 4096 || (rows <= 8192 && p.dp[p.L - 1] >= 2048));
+  return few ? kCeFewRows : kCeRows;
+}
+
 // Output layer of a training pass: logits, loss sums per 128 rows, dZ_L in both orientations and its
 // column sums, in one kernel (mlp_logits_ce_kernel).
 void launch_logits_ce(const MlpArgs& a, const RoundDesc& rd, int rows, double arows, const float* wbase,
@@ -2268,10 +2427,20 @@ void launch_logits_ce(const MlpArgs& a, const RoundDesc& rd, int rows, double ar
   c.dZT = at<uint16_t>(a, p.off_dzt[L]); c.lddzt = p.ldm;
   c.rowloss = at<float>(a, p.off_rowloss);
   c.colsum = at<float>(a, p.off_colsum[L]); c.ldcs = (size_t)p.dp[L];
+  const int block_rows = ce_rows(p, rows);
   kbegin(hook, KK_MLP_LOGITS_CE, 2.0 * arows * p.d[L - 1] * p.d[L] + arows * p.d[L] * 8.0,
               arows * (p.d[L - 1] * 2.0 + p.d[L] * 4.0 + (c.gt.blocks ? p.d[0] * 4.0 : 0.0)));
-  plan_note("logits_ce", kCeRows, p.dp[L], 1);
-  const dim3 grid(rows / kCeRows + c.gt.blocks), block(256);
+  plan_note("logits_ce", block_rows, p.dp[L], 1);
+  const dim3 grid(rows / block_rows + c.gt.blocks), block(256);
+  if (block_rows == kCeFewRows) {
+    switch ((p.d[L] + 15) / 16) {
+#define ABS_CASE(cb) case cb: ABS_LAUNCH_K((mlp_logits_ce_few_kernel<cb>), grid, block, s, c, rd); break;
+      ABS_CASE(1) ABS_CASE(2) ABS_CASE(3) ABS_CASE(4) ABS_CASE(5) ABS_CASE(6) ABS_CASE(7) ABS_CASE(8)
+#undef ABS_CASE
+    }
+    kend(hook, KK_MLP_LOGITS_CE);
+    return;
+  }
   switch (p.dp[L] / 64) {
     case 1: ABS_LAUNCH_K((mlp_logits_ce_kernel<2>), grid, block, s, c, rd); break;
     case 2: ABS_LAUNCH_K((mlp_logits_ce_kernel<4>), grid, block, s, c, rd); break;
@@ -2331,7 +2500,7 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
     // ---- output layer: loss and output gradient, already scaled by the uploads' coefficients
     const int gather_blocks = wg0_direct ? 0 : (rows / 64) * ((p.dp[0] + 255) / 256);
     launch_logits_ce(a, rd, rows, arows, wbase, sbase, own, gather_blocks <= kGatherRide ? gather_blocks : 0, s, hook);
-    const int loss_blocks = p.Bp / kCeRows;          // row blocks of the loss sums per upload
+    const int loss_blocks = p.Bp / ce_rows(p, rows);          // row blocks of the loss sums per upload
 
     // ---- input gradients back through W_{L-1} .. W_1 (none is needed for the first layer)
     // (dZ_l likewise: read row-major only by the next product down; when writer and reader both run on
@@ -2404,7 +2573,7 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
       bias.col_begin[l] = bias_cols; bias_cols += p.d[l + 1];
       bias.colsum[l] = at<float>(a, p.off_colsum[l + 1]); bias.ldcs[l] = (size_t)p.dp[l + 1];
       bias.b_off[l] = p.b_off[l];
-      bias.prow[l] = (local ? p.Bp : rows) / (l == L - 1 ? kCeRows : 64);
+      bias.prow[l] = (local ? p.Bp : rows) / (l == L - 1 ? ce_rows(p, rows) : 64);
     }
     bias.col_begin[L] = bias_cols;
     bias.w_cur = local ? wbase : ring + (size_t)rd.slot_cur * p.slot_stride;

@@ -143,3 +143,19 @@ def test_large_tile_kernel_by_number_of_k_steps(d0, h1, h2, K, T):
         runs.append(sim.model().copy())
         sim.close()
     assert np.array_equal(runs[0], runs[1])
+
+
+@pytest.mark.parametrize("d1,C,N,B", [
+    (40, 2, 3, 1),            # one block of 16 classes, two of the four wavefronts without a share of the contraction
+    (200, 17, 5, 130),        # two blocks, one class in the second; an upload of eight row blocks
+    (384, 64, 4, 100),        # four, all 64 padded classes in use
+    (500, 65, 3, 40),         # five: classes padded to 128
+    (320, 128, 32, 128),      # eight, the most rows
+    (320, 128, 33, 128),      # one upload more: workgroups of 128 rows
+])
+def test_output_layer_of_few_rows(d1, C, N, B):
+    """The output layer in workgroups of 32 rows: contractions that leave wavefronts without a share, every padding of the classes."""
+    import paper_2301_08895_amd as lib
+    p = workloads.scaled_preset(3, M=max(1024, N * B), dims=[64, d1, C], n_classes=C, N=N, K0=N, B=B, n_slow=0, lr=5e-4)
+    assert f"logits_ce:{128 if N == 33 else 32}x" in lib.abs_mlp_round_plan(lib.make_config(p), N)
+    _check(run_pair(p, 4, checkpoints=(1,)))
