@@ -125,7 +125,9 @@ __global__ __launch_bounds__(256) void mlp_gather_t_kernel(const uint16_t* X, in
 // 768 blocks 205 / 201, 217 / 216, 238 / 238, 1536 blocks 307 / 323, 321 / 323, 357 / 362.  With a second hidden layer
 // the copy waits longer for its reader: 1000-1024-1024-10, 512 blocks 202 / 198, but 1000-2048-2048-10, 256 blocks 277 / 280,
 // 512-1920-1920-50, 512 blocks 75 / 82 (the copy, the output layer and the first weight gradient).
-constexpr int kGatherRide = 512;
+// The 32-row form of that kernel leaves a CU room for more workgroups: there 768 ride (3072-512-10, 768 blocks, a round
+// 80 / 78.6 us, with split weight gradients 79 / 74; 3072-256-10, 384 blocks each way the same).
+constexpr int kGatherRide = 512, kGatherRideFew = 768;
 constexpr int kGatherPitch = 256 + 2;      // the 8 blocks of 8 rows a wavefront reads start 8 banks apart
 struct GatherT {
   int blocks;                              // row blocks x column blocks that ride; 0: none
@@ -1501,6 +1503,301 @@ __global__ __launch_bounds__(512, 1) void mlp_gemm256_kernel(GemmArgs g, RoundDe
   }
 }
 
+// ------------------------------------------------------------------ weight gradients that take the step themselves
+// Eq. 2 / Eq. 3 for ALL weight matrices of a round (or of a local step) in one launch.  Where the contraction of a
+// weight gradient is not split - a round of few rows, or one upload's rows in local SGD - a workgroup's accumulators
+// hold the whole gradient of its tile, so its epilogue reads the model, takes the step and writes the fp32 model and both
+// bf16 copies: no partial goes to memory and back, no update needs a launch, and the layers' products, which depend
+// on nothing but the backward pass, fill the CUs side by side.  The biases ride as the last workgroups.
+//   uploads = 1, sel 0:  w^{t+1} = w^t - sum over all stacked rows (Eq. 3)
+//   uploads = K, sel 1:  a local step on the private models; sel 2: the first one, from the uploads' ring slots (Eq. 2)
+// DIRECT: layer 0's A operand is the dataset as it lies in memory, [k = gathered rows][m], read through the
+// transposing LDS read (see mlp_gemm256_kernel), instead of a transposed copy of the minibatch.
+// What bounds it: the bytes a CU draws from beyond its L1 (a 128 x 128 tile 0.65 us a k-step, 64 x 64 0.2 us), then 2 us of start
+// (arguments, first tiles) and 2-4 us of epilogue.  us of the launches it replaces / its own: 3072-512-10, 1024 rows
+// 22.1 (three launches) / 11.3, 1000-520-300-26, 1152 rows 23.4 (four) / 8.9, 3072-1024-1024-10, 4096 rows 89 (four) / 73.
+struct StepLayer {
+  const uint16_t* A; size_t lda;         // H_l^T [dp_in][lda]; layer 0: the transposed minibatch or, DIRECT, the dataset
+  const uint16_t* Bt; size_t ldb;        // dZ_{l+1}^T [dp_out][ldb]
+  int mt, nt;                            // tiles
+  int d_in, d_out, dp_out;
+  const float* cur; float* next;         // fp32 [d_in][d_out]; models `stride` floats apart
+  uint16_t* wn; size_t ldwn; uint16_t* wt; size_t ldwt;     // bf16 copies (wn may be null)
+};
+struct StepArgs {
+  int L, uploads, sel, ksteps;           // k-steps of an upload's (uploads = 1: all) rows
+  const uint32_t* rowidx;
+  size_t stride, shadow_stride;
+  int first[8];                          // first workgroup of each layer, then (from [L]) of the biases
+  int bias_per;
+  StepLayer l[ABS_MAX_LAYERS];
+  BiasCore bias;
+};
+
+// Tiles of TMx x TNx, NW wavefronts in 64 x 64 sub-tiles (2 x 2 blocks of MFMA 32x32x16) and KG groups along the
+// contraction of a k-step, as in mlp_tile_kernel.
+template <int TMx, int TNx, int NW_>
+struct StepCfg {
+  static constexpr int WSM = TMx / 64, WSN = TNx / 64, NW = NW_, NT = NW * 64, KG = NW / (WSM * WSN), OWN = 4 / KG;
+  static constexpr int NIA = TMx / (8 * NW), NIB = TNx / (8 * NW);             // requests per wavefront and k-step
+  static constexpr int kStage = (TMx + TNx) * BK;
+  static constexpr int kRed = WSM * WSN * 4 * (KG - 1) * 1024 * 2;             // exchanged blocks (in elements of 2 bytes) ...
+  static constexpr int kPitchT = TMx + 8, kPitchN = TNx + 8;
+  static constexpr int kOut = TNx * kPitchT + TMx * kPitchN;                   // ... and, after them, both orientations
+  static constexpr int smem(int ring) {
+    const int a = ring * kStage, b = kRed > kOut ? kRed : kOut;
+    return a > b ? a : b;
+  }
+  static constexpr int kIdx = 4 * NW * 128;                                    // ring of row indices: 4 steps x 256 bytes per wavefront
+};
+
+template <int TMx, int TNx, int NW_, int RING, bool ATR>
+__device__ __forceinline__ void step_tile(const StepArgs& g, const StepLayer& ly, const RoundDesc& rd, int z, int m0, int n0, uint16_t* smem) {
+  using Cfg = StepCfg<TMx, TNx, NW_>;
+  constexpr int NW = Cfg::NW, NT = Cfg::NT, KG = Cfg::KG, OWN = Cfg::OWN, NIA = Cfg::NIA, NIB = Cfg::NIB;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int kg = wave / (Cfg::WSM * Cfg::WSN), wsub = wave % (Cfg::WSM * Cfg::WSN);
+  const int wm = wsub / Cfg::WSN, wn = wsub % Cfg::WSN;
+  const int nks = g.ksteps;
+  const size_t kbase = (size_t)z * nks * BK;               // first stacked row of this contraction
+
+  // requests, k contiguous: 8 rows of 128 bytes (see mlp_tile_kernel)
+  const int c8 = ((lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7)) * 8;
+  const int rq = 8 * wave + (lane >> 3);
+  const uint16_t* pa[NIA]; const uint16_t* pb[NIB];
+#pragma unroll
+  for (int i = 0; i < NIB; ++i)          // (a tile may be wider than the layer: the columns beyond are dropped)
+    pb[i] = ly.Bt + (size_t)min(n0 + rq + 8 * NW * i, ly.dp_out - 1) * ly.ldb + kbase + c8;
+  // layer 0: RPR gathered rows of TMx columns each; their 64-byte blocks are stored at position b ^ f(row), so that
+  // the four rows one transposing read touches cover all banks.  Columns beyond d_0 re-read the row's first ones (dropped).
+  constexpr int RPR = 512 / TMx, LPR = 64 / RPR;           // rows of a request, lanes per row
+  const int ar = RPR * wave + lane / LPR;                  // k row of request 0 (+ RPR NW i)
+  const int asw = TMx == 128 ? (ar & 3) : ((ar >> 1) & 1);
+  int acol = m0 + ((((lane % LPR) >> 2) ^ asw) * 4 + (lane & 3)) * 8;
+  if (ATR && acol >= ly.d_in) acol = 0;
+  const uint32_t* const idx = g.rowidx + kbase;
+  uint32_t ai[NIA];
+  uint16_t* const idx_ring = smem + Cfg::smem(RING) + wave * 128;
+  const uint32_t idx_dma = lds_offset(idx_ring);
+  const int ip = lane % (RPR * NIA);                       // this lane's entry of a request of indices: request ip / RPR, row ip % RPR
+  const uint32_t* const idx_src = idx + RPR * (wave + NW * (ip / RPR)) + ip % RPR;
+  const int idx_at = (lane / LPR) * 2;                     // (in elements of 2 bytes)
+  if (!ATR) {
+#pragma unroll
+    for (int i = 0; i < NIA; ++i) pa[i] = ly.A + (size_t)(m0 + rq + 8 * NW * i) * ly.lda + kbase + c8;
+  }
+  const uint32_t dma = lds_offset(smem) + (uint32_t)wave * 1024u;
+#define ABS_STEP_DMA(ks_, st_)                                                                                        \
+  {                                                                                                                   \
+    const uint32_t a_ = dma + (uint32_t)(st_) * (Cfg::kStage * 2);                                                    \
+    _Pragma("unroll") for (int i = 0; i < NIA; ++i)                                                                   \
+      lds_dma16_at(ATR ? ly.A + (size_t)ai[i] * ly.lda + acol : pa[i] + (ks_) * BK, a_ + i * NW * 1024);              \
+    _Pragma("unroll") for (int i = 0; i < NIB; ++i)                                                                   \
+      lds_dma16_at(pb[i] + (ks_) * BK, a_ + TMx * BK * 2 + i * NW * 1024);                                            \
+  }
+#define ABS_STEP_IDX(ks_) if (ATR) lds_dma4_at(idx_src + (size_t)min(ks_, nks - 1) * BK, idx_dma + (uint32_t)((ks_) & 3) * (NW * 256));
+
+  // The model elements of the lane's own blocks, asked for before everything else where there are registers for them.
+  constexpr bool kEarly = OWN == 1;
+  const float* const cur = ly.cur + (g.sel == 0 ? (size_t)0 : (size_t)(g.sel == 1 ? (uint32_t)z : rd.w[z].slot) * g.stride);
+  float* const next = ly.next + (size_t)z * g.stride;
+  const int lk = lane >> 5, lcol = lane & 31, lrow4 = lk * 4;
+  float wv[OWN][16];
+  auto load_model = [&]() {
+#pragma unroll
+    for (int j = 0; j < OWN; ++j) {
+      const int b = kg * OWN + j;
+      const int i0 = m0 + wm * 64 + (b >> 1) * 32 + lrow4, n = n0 + wn * 64 + (b & 1) * 32 + lcol;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int i = i0 + (r >> 2) * 8 + (r & 3);
+        wv[j][r] = i < ly.d_in && n < ly.d_out ? cur[(size_t)i * ly.d_out + n] : 0.f;
+      }
+    }
+  };
+  if (kEarly) load_model();
+  f32x16_t acc[4];                       // block 2 mi + ni of the 64 x 64 sub-tile
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
+  const int lr = lane & 31;
+  const int fa = (wm * 64 + lr) * BK, fb = TMx * BK + (wn * 64 + lr) * BK;
+  const int sw = (lr >> 1) & 7;
+  // transposing reads: 16 lanes take 4 k rows x 16 columns; lanes 0-15 / 16-31 the block's columns 0-15 / 16-31 of k rows
+  // 0 .. 7 of a 16-wide sub-step, lanes 32-63 of rows 8 .. 15 (two reads of 4 rows each)
+  const int t16 = lane & 15, tr = t16 >> 2, th = (lane >> 4) & 1;
+  constexpr int SUB = 4 / KG;            // 16-wide sub-steps of a k-step per wavefront group
+  if (ATR) {
+    uint32_t a0[RING - 1][NIA];
+#pragma unroll
+    for (int j = 0; j < RING - 1; ++j)
+#pragma unroll
+      for (int i = 0; i < NIA; ++i) a0[j][i] = idx[(size_t)min(j, nks - 1) * BK + ar + RPR * NW * i];
+    uint32_t an[NIA];
+#pragma unroll
+    for (int i = 0; i < NIA; ++i) an[i] = idx[(size_t)min(RING - 1, nks - 1) * BK + ar + RPR * NW * i];
+    ABS_STEP_IDX(RING); ABS_STEP_IDX(RING + 1); ABS_STEP_IDX(RING + 2);
+#pragma unroll
+    for (int j = 0; j < RING - 1; ++j) {
+#pragma unroll
+      for (int i = 0; i < NIA; ++i) ai[i] = a0[j][i];
+      if (j < nks) ABS_STEP_DMA(j, j);
+    }
+#pragma unroll
+    for (int i = 0; i < NIA; ++i) ai[i] = an[i];
+  } else {
+#pragma unroll
+    for (int j = 0; j < RING - 1; ++j)
+      if (j < nks) ABS_STEP_DMA(j, j);
+  }
+  int stage = 0;
+  for (int ks = 0; ks < nks; ++ks) {
+    if (ks + RING - 1 <= nks) ring_wait_barrier<(RING - 2) * (NIA + NIB)>();   // step ks has landed for every wavefront; and
+    else                      ring_wait_barrier<0>();                          // everybody is done with step ks - 1
+    if (ks + RING - 1 < nks) {
+      ABS_STEP_IDX(ks + RING + 3);
+      ABS_STEP_DMA(ks + RING - 1, stage == 0 ? RING - 1 : stage - 1);
+      if (ATR) {
+#pragma unroll
+        for (int i = 0; i < NIA; ++i) ai[i] = *(const uint32_t*)(idx_ring + ((ks + RING) & 3) * (NW * 128) + i * RPR * 2 + idx_at);
+      }
+    }
+    const uint16_t* sS = smem + stage * Cfg::kStage;
+    stage = stage + 1 == RING ? 0 : stage + 1;
+    bf16x8_t va[SUB][2], vb[SUB][2];
+#pragma unroll
+    for (int s = 0; s < SUB; ++s) {
+      const int sub = kg * SUB + s;
+      const int ch = (((sub << 1) | lk) ^ sw) << 3;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (ATR) {
+          typedef short s16x4_ __attribute__((ext_vector_type(4)));
+          const int row = sub * 16 + lk * 8 + tr;
+          const int f0 = TMx == 128 ? (row & 3) : ((row >> 1) & 1);            // (rows 4 apart: the same swizzle)
+          const uint16_t* q = sS + row * TMx + ((wm * 2 + i) ^ f0) * 32 + th * 16 + (t16 & 3) * 4;
+          union { s16x4_ h[2]; bf16x8_t v; } u;
+          u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_*)(q));
+          u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_*)(q + 4 * TMx));
+          va[s][i] = u.v;
+        } else {
+          va[s][i] = *(const bf16x8_t*)&sS[fa + i * 32 * BK + ch];
+        }
+        vb[s][i] = *(const bf16x8_t*)&sS[fb + i * 32 * BK + ch];
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[2 * i + j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[s][i], vb[s][j], acc[2 * i + j], 0, 0, 0);
+    }
+  }
+#undef ABS_STEP_DMA
+#undef ABS_STEP_IDX
+
+  // ---- epilogue.  Accumulator register r of lane l holds C[8 (r/4) + 4 (l/32) + r%4][l%32] of its block.
+  if (!kEarly) load_model();
+  float* const red = (float*)smem;
+  uint16_t* const sT = smem;                               // results [n][kPitchT]
+  uint16_t* const sN = smem + TNx * Cfg::kPitchT;          // results [m][kPitchN]
+  __syncthreads();                                         // all fragment reads done before LDS is reused
+  // blocks of other groups to their owners: [sub-tile][block][source group][quarter][lane]
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int owner = b / OWN;
+    if (owner != kg) {
+      float4* q = (float4*)(red + ((wsub * 4 + b) * (KG - 1) + (kg < owner ? kg : kg - 1)) * 1024) + lane;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) q[r * 64] = make_float4(acc[b][4 * r], acc[b][4 * r + 1], acc[b][4 * r + 2], acc[b][4 * r + 3]);
+    }
+  }
+  f32x16_t fin[OWN];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+    if (b / OWN == kg) fin[b % OWN] = acc[b];
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < OWN; ++j) {
+    const float4* q = (const float4*)(red + (wsub * 4 + kg * OWN + j) * (KG - 1) * 1024) + lane;
+#pragma unroll
+    for (int o = 0; o < KG - 1; ++o)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float4 v = q[o * 256 + r * 64];
+        fin[j][4 * r] += v.x; fin[j][4 * r + 1] += v.y; fin[j][4 * r + 2] += v.z; fin[j][4 * r + 3] += v.w;
+      }
+  }
+  __syncthreads();                                         // the exchanged blocks have been read
+#pragma unroll
+  for (int j = 0; j < OWN; ++j) {
+    const int b = kg * OWN + j;
+    const int bm = wm * 64 + (b >> 1) * 32, nl = wn * 64 + (b & 1) * 32 + lcol, n = n0 + nl;
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg) {
+      const int ml = bm + rg * 8 + lrow4;
+      uint16_t h[4];
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+        const int i = m0 + ml + rr;
+        const bool ok = i < ly.d_in && n < ly.d_out;       // padding stays zero in both copies
+        const float v = ok ? wv[j][rg * 4 + rr] - fin[j][rg * 4 + rr] : 0.f;
+        if (ok) next[(size_t)i * ly.d_out + n] = v;
+        h[rr] = f32_to_bf16(v);
+        if (ly.wn) sN[(ml + rr) * Cfg::kPitchN + nl] = h[rr];
+      }
+      uint2 o;
+      o.x = h[0] | ((uint32_t)h[1] << 16);
+      o.y = h[2] | ((uint32_t)h[3] << 16);
+      *(uint2*)&sT[nl * Cfg::kPitchT + ml] = o;
+    }
+  }
+  __syncthreads();
+  uint16_t* const wt = ly.wt + (size_t)z * g.shadow_stride;
+#pragma unroll
+  for (int i = 0; i < TMx * TNx / 8 / NT; ++i) {
+    const int q = t + NT * i, nl = q / (TMx / 8), ch = (q % (TMx / 8)) * 8;
+    if (n0 + nl < ly.d_out) *(uint4*)(wt + (size_t)(n0 + nl) * ly.ldwt + m0 + ch) = *(const uint4*)&sT[nl * Cfg::kPitchT + ch];
+  }
+  if (ly.wn) {
+    uint16_t* const wr = ly.wn + (size_t)z * g.shadow_stride;
+#pragma unroll
+    for (int i = 0; i < TMx * TNx / 8 / NT; ++i) {
+      const int q = t + NT * i, ml = q / (TNx / 8), ch = (q % (TNx / 8)) * 8;
+      if (m0 + ml < ly.d_in) *(uint4*)(wr + (size_t)(m0 + ml) * ly.ldwn + n0 + ch) = *(const uint4*)&sN[ml * Cfg::kPitchN + ch];
+    }
+  }
+}
+
+template <int TMx, int TNx, int NW, int RING, int PER_SIMD, bool DIRECT>
+__global__ __launch_bounds__(NW * 64, PER_SIMD) void mlp_step_kernel(StepArgs g, RoundDesc rd) {
+  using Cfg = StepCfg<TMx, TNx, NW>;
+  __shared__ __attribute__((aligned(16))) uint16_t smem[Cfg::smem(RING) + (DIRECT ? Cfg::kIdx : 0)];
+  static_assert((Cfg::smem(RING) + Cfg::kIdx) * 2 * (PER_SIMD * 4 / NW) <= 160 * 1024, "LDS budget");
+  const int bx = blockIdx.x;
+  int l = 0, first = 0;
+#pragma unroll
+  for (int q = 1; q < 8; ++q)
+    if (q <= g.L && bx >= g.first[q]) { l = q; first = g.first[q]; }
+  if (l == g.L) {
+    const int b = bx - first, up = b / g.bias_per;
+    const BiasCore& u = g.bias;
+    const size_t from = g.sel == 0 ? (size_t)0 : (size_t)(g.sel == 1 ? (uint32_t)up : rd.w[up].slot) * g.stride;
+    bias_block(u, b - up * g.bias_per, [&](int l) { return up * u.prow[l]; }, u.w_cur + from, u.w_next + (size_t)up * g.stride, (float*)smem);
+    return;
+  }
+  const StepLayer ly = g.l[l];
+  // the tiles (upload, row, column: columns fastest) in eight contiguous ranges, one per XCD
+  const int b = bx - first, tiles = g.uploads * ly.mt * ly.nt, per = (tiles + 7) >> 3;
+  const int idx = (b & 7) * per + (b >> 3);
+  if ((b >> 3) >= per || idx >= tiles) return;
+  const int n0 = (idx % ly.nt) * TNx, row = idx / ly.nt, m0 = (row % ly.mt) * TMx, z = row / ly.mt;
+  if constexpr (DIRECT) {
+    if (l == 0) { step_tile<TMx, TNx, NW, RING, true>(g, ly, rd, z, m0, n0, smem); return; }
+  }
+  step_tile<TMx, TNx, NW, RING, false>(g, ly, rd, z, m0, n0, smem);
+}
+
 // ------------------------------------------------------------------ output layer: logits, loss, dZ_L
 // The last layer's product, the softmax cross-entropy and the output gradient in one kernel: the
 // class count is at most 256, so a workgroup that owns 128 stacked rows owns their whole logit rows
@@ -2449,6 +2746,75 @@ void launch_logits_ce(const MlpArgs& a, const RoundDesc& rd, int rows, double ar
   kend(hook, KK_MLP_LOGITS_CE);
 }
 
+// Whether a round of `rows` stacked rows at U = 1 takes its steps in mlp_step_kernel, and with which tiles (0: split
+// weight gradients, partials and updates).  Unsplit, the contraction may have at most 64 k-steps (at 96 3072-512-10
+// takes 110 us a round against 97), and with tiles of 128 x 128 there is a limit to the work too, beyond which the 256 x 256
+// kernel's fewer bytes per flop win over its partials.  128 x 128 from 128 such tiles on, 64 x 64 below.
+// us of a round with split weight gradients / 64 x 64 / 128 x 128 tiles, by rows:
+//   3072-512-10   1024: 53.5 / 46.3 / 48.4   4096: 80 / 75 / 81       1000-520-300-26  512: 59 / 45 / 49   3072: 61 / 50 / 55
+//   512-256-10    4096: 50 / 44 / 59         8192: 53 / 59 / 89       2048-1024-10    1024: 52 / 49 / 45   4096: 90 / 93 / 87
+//   3072-1024-1024-10  512: 84 / 72 / 67     2048: 132 / 121 / 112    4096: 177 / 186 / 164   8192: 265 / 314 / 280
+//   3072-2048-2048-100 512: 147 / 136 / 122  1024: 198 / 186 / 165    4096: 400 / 470 / 376
+//   3072-4096-4096-100 1024: 392 / 400 / 342 2048: 570 / 641 / 534    4096: 691 / 965 / 743
+int step_tiles(const MlpPlan& p, int rows) {
+  const long ksteps = rows / BK;
+  if (ksteps > 64) return 0;
+  long tiles = 0;
+  for (int l = 0; l < p.L; ++l) tiles += (long)(p.dp[l] / 128) * ((p.dp[l + 1] + 127) / 128);
+  if (tiles < 128) return 64;
+  return tiles * ksteps <= 60000 ? 128 : 0;
+}
+// Blocks of the transposed minibatch (64 rows x 256 columns).
+int gather_t_blocks(const MlpPlan& p, int rows) { return (rows / 64) * ((p.dp[0] + 255) / 256); }
+// 128 x 128 tiles: one workgroup per CU with three k-steps on their way while the tiles do not outnumber the CUs (us, one /
+// two workgroups: 2048-1024-10, 136 tiles, 4096 rows 87 / 95; 3072-1024-1024-10, 264 tiles, 2048 rows 119 / 114) ...
+bool step_pairs(const MlpPlan& p) {
+  int tiles = 0;
+  for (int l = 0; l < p.L; ++l) tiles += (p.dp[l] / 128) * ((p.dp[l + 1] + 127) / 128);
+  return tiles > 256;
+}
+// ... and the pairs read the first layer's minibatch rows where they lie if its transposed copy is beyond what rides for
+// nothing (a k-step then touches 64 rows all over the dataset: 0.86 instead of 0.65 us; 3072-1024-1024-10, 4096 rows, 768
+// blocks, 164 us a round against 174 with the copy, 2048 rows, 384 blocks 113.6 / 112.2, 3072-2048-2048-100, 384 blocks 224 / 216).
+bool step_direct(const MlpPlan& p, int rows) { return step_tiles(p, rows) == 128 && step_pairs(p) && gather_t_blocks(p, rows) > 512; }
+
+// All weight matrices and biases of a round at U = 1, w^t -> w^{t+1}, in one launch (mlp_step_kernel).
+void launch_steps(const MlpArgs& a, const RoundDesc& rd, int rows, double arows, int tile, bool direct, const BiasCore& bias, int bias_cols,
+                  hipStream_t s, LaunchHook* hook) {
+  const MlpPlan& p = a.plan;
+  float* ring = at<float>(a, p.off_ring);
+  uint16_t* shadow = at<uint16_t>(a, p.off_shadow) + (size_t)rd.slot_next * p.shadow_stride;
+  StepArgs g{};
+  g.L = p.L; g.uploads = 1; g.sel = 0; g.ksteps = rows / BK;
+  g.rowidx = at<uint32_t>(a, p.off_rowidx);
+  g.bias = bias; g.bias_per = (bias_cols + 15) / 16;
+  int first = 0;
+  double flops = 0.0, bytes = 0.0;
+  for (int l = 0; l < p.L; ++l) {
+    StepLayer& y = g.l[l];
+    y.A = l > 0 ? at<uint16_t>(a, p.off_ht[l]) : direct ? a.X : at<uint16_t>(a, p.off_xgt); y.lda = l == 0 && direct ? (size_t)p.d[0] : p.ldm;
+    y.Bt = at<uint16_t>(a, p.off_dzt[l + 1]); y.ldb = p.ldm;
+    g.first[l] = first; y.mt = p.dp[l] / tile; y.nt = (p.dp[l + 1] + tile - 1) / tile;
+    first += (y.mt * y.nt + 7) / 8 * 8;
+    y.d_in = p.d[l]; y.d_out = p.d[l + 1]; y.dp_out = p.dp[l + 1];
+    y.cur = ring + (size_t)rd.slot_cur * p.slot_stride + p.w_off[l];
+    y.next = ring + (size_t)rd.slot_next * p.slot_stride + p.w_off[l];
+    y.wn = l >= 1 ? shadow + p.wn_off[l] : nullptr; y.ldwn = (size_t)p.ld[l + 1];
+    y.wt = shadow + p.wt_off[l]; y.ldwt = (size_t)p.ld[l];
+    flops += 2.0 * arows * p.d[l] * p.d[l + 1];
+    bytes += arows * (p.d[l] + p.d[l + 1]) * 2.0 + (double)p.d[l] * p.d[l + 1] * (l >= 1 ? 12.0 : 10.0);
+  }
+  for (int l = p.L; l < 8; ++l) g.first[l] = first;
+  kbegin(hook, KK_MLP_WGRAD_L1, flops, bytes);
+  plan_note(direct ? "steps_x" : tile == 128 && step_pairs(p) ? "steps2" : "steps", tile, tile, 1);
+  const dim3 grid(first + g.bias_per);
+  if (tile == 64)         ABS_LAUNCH_K((mlp_step_kernel<64, 64, 4, 4, 2, false>), grid, dim3(256), s, g, rd);
+  else if (direct)        ABS_LAUNCH_K((mlp_step_kernel<128, 128, 8, 2, 4, true>), grid, dim3(512), s, g, rd);
+  else if (step_pairs(p)) ABS_LAUNCH_K((mlp_step_kernel<128, 128, 8, 2, 4, false>), grid, dim3(512), s, g, rd);
+  else                    ABS_LAUNCH_K((mlp_step_kernel<128, 128, 8, 4, 2, false>), grid, dim3(512), s, g, rd);
+  kend(hook, KK_MLP_WGRAD_L1);
+}
+
 }  // namespace
 
 hipError_t mlp_prepare(const MlpArgs& a, hipStream_t s) {
@@ -2498,8 +2864,11 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
                                            (long)step * (long)p.B, s, hook);
 
     // ---- output layer: loss and output gradient, already scaled by the uploads' coefficients
-    const int gather_blocks = wg0_direct ? 0 : (rows / 64) * ((p.dp[0] + 255) / 256);
-    launch_logits_ce(a, rd, rows, arows, wbase, sbase, own, gather_blocks <= kGatherRide ? gather_blocks : 0, s, hook);
+    const int stile = local ? 0 : step_tiles(p, rows);
+    const bool sdirect = stile && step_direct(p, rows);
+    const int gather_blocks = (stile ? sdirect : wg0_direct) ? 0 : gather_t_blocks(p, rows);
+    const bool gather_rides = gather_blocks <= (ce_rows(p, rows) == kCeFewRows ? kGatherRideFew : kGatherRide);
+    launch_logits_ce(a, rd, rows, arows, wbase, sbase, own, gather_rides ? gather_blocks : 0, s, hook);
     const int loss_blocks = p.Bp / ce_rows(p, rows);          // row blocks of the loss sums per upload
 
     // ---- input gradients back through W_{L-1} .. W_1 (none is needed for the first layer)
@@ -2542,7 +2911,7 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
       kend(hook, kind);
     }
 
-    if (gather_blocks > kGatherRide) {
+    if (!gather_rides) {
       // (right before its reader, which then finds it in the caches; ahead of the output layer the first layer's
       // weight gradient took 73 instead of 59 us at 16384 x 1024)
       kbegin(hook, KK_MLP_GATHER_T, 0, arows * p.d[0] * 4.0);
@@ -2578,6 +2947,10 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
     bias.col_begin[L] = bias_cols;
     bias.w_cur = local ? wbase : ring + (size_t)rd.slot_cur * p.slot_stride;
     bias.w_next = local ? priv : ring + (size_t)rd.slot_next * p.slot_stride;
+    if (stile) {
+      launch_steps(a, rd, rows, arows, stile, sdirect, bias, bias_cols, s, hook);
+      continue;
+    }
     int pend = -1, pend_split = 0, pend_q = 0;   // layer whose partials are complete and whose update is still due (its splits or run length)
     for (int li = 0; li < L; ++li) {
       const int l = local ? L - 1 - li : li;

@@ -159,3 +159,20 @@ def test_output_layer_of_few_rows(d1, C, N, B):
     p = workloads.scaled_preset(3, M=max(1024, N * B), dims=[64, d1, C], n_classes=C, N=N, K0=N, B=B, n_slow=0, lr=5e-4)
     assert f"logits_ce:{128 if N == 33 else 32}x" in lib.abs_mlp_round_plan(lib.make_config(p), N)
     _check(run_pair(p, 4, checkpoints=(1,)))
+
+
+@pytest.mark.parametrize("dims,N,B,item", [
+    ([40, 24, 3], 1, 1, "steps:64x64/1"),                      # two k-steps: shorter than the ring
+    ([3072, 512, 10], 32, 100, "steps:64x64/1"),               # 64 k-steps, the most
+    ([512, 64, 10], 33, 128, "wgrad_tile:64x64/11"),           # two more: split weight gradients, partials, an update
+    ([1000, 2040, 10], 2, 60, "steps:128x128/1"),              # 144 tiles of 128 x 128, ragged in both directions
+    ([2048, 2040, 26], 3, 128, "steps2:128x128/1"),            # 272: two workgroups per CU
+    ([3000, 1400, 10], 24, 100, "steps_x:128x128/1"),          # the dataset in place of its transposed copy, columns beyond d_0
+    ([3000, 1400, 700, 130], 22, 128, "steps_x:128x128/1"),    # ... three layers, two column tiles of classes
+])
+def test_steps_taken_in_the_weight_gradients(dims, N, B, item):
+    """All matrices of a round stepped in one launch, at both tile sizes and with either first operand."""
+    import paper_2301_08895_amd as lib
+    p = workloads.scaled_preset(3, M=max(512, 2 * N * B), dims=dims, n_classes=dims[-1], N=N, K0=N, B=B, n_slow=0, lr=1e-4)
+    assert item in lib.abs_mlp_round_plan(lib.make_config(p), N).split()
+    _check(run_pair(p, 3, checkpoints=(1,)))
