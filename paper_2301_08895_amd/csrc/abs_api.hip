@@ -56,7 +56,7 @@ size_t param_count(const abs_config& c) {
 // Workspace of the two regression models.
 struct RegPlan {
   size_t slot_stride;   // floats
-  size_t off_ring, off_dz, off_rowloss, off_rowidx, off_delta, off_lossbuf, off_eval, total;
+  size_t off_ring, off_dz, off_rowloss, off_rowidx, off_delta, off_lossbuf, off_slice, off_eval, total;
 };
 
 bool validate(const abs_config& c, std::string& why) {
@@ -121,6 +121,8 @@ void reg_plan(const abs_config& c, RegPlan& p) {
   p.off_rowidx = o;  o = round_up(o + rows * 4, 256);
   p.off_delta = o;   if (c.U > 1) o = round_up(o + (size_t)c.N * p.slot_stride * 4, 256);
   p.off_lossbuf = o; if (c.U > 1) o = round_up(o + (size_t)c.N * 4, 256);
+  p.off_slice = o;
+  if (c.model == ABS_MODEL_SOFTMAX) o = round_up(o + softmax_local_slice_bytes(c.dims[0], c.dims[1], c.B, c.U, c.N), 256);
   p.off_eval = o;    o = round_up(o + eval_scratch_bytes(kEvalChunk), 256);
   p.total = o;
 }
@@ -442,6 +444,7 @@ static void fill_regression_args(const abs_ctx* ctx, RegressionArgs& ra) {
   ra.U = cfg.U;
   ra.delta = (float*)(ctx->ws + ctx->rplan.off_delta);
   ra.lossbuf = (float*)(ctx->ws + ctx->rplan.off_lossbuf);
+  ra.slice = (float*)(ctx->ws + ctx->rplan.off_slice);
 }
 
 int abs_round(abs_ctx* ctx, int32_t n_rounds) {

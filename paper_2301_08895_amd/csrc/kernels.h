@@ -67,6 +67,7 @@ struct RegressionArgs {
   int U;
   float* delta;          // [N][slot_stride]
   float* lossbuf;        // [N]
+  float* slice;          // softmax in slices: scratch per upload (softmax_local_slice_bytes), else not read
 };
 
 hipError_t launch_linreg_round(const RegressionArgs& a, const RoundDesc& rd, hipStream_t s,
@@ -94,6 +95,11 @@ bool softmax_local_fused_ok(int B, int U);
 hipError_t launch_softmax_local_fused(const RegressionArgs* a1, const RoundDesc* rd1, const RegressionArgs* d_args,
                                       const char* d_rds, size_t stride, int S, int d, int C, int B, int U, int Kmax,
                                       hipStream_t s);
+// The same for one simulation's round of few uploads, in slices of the features over eight workgroups each and a launch per
+// step; the same bits.  The scratch, for the uploads of N workers (0 bytes: the shape never runs in slices), is a.slice.
+bool softmax_local_sliced_ok(int d, int C, int B, int U, int K);
+size_t softmax_local_slice_bytes(int d, int C, int B, int U, int N);
+hipError_t launch_softmax_local_sliced(const RegressionArgs& a, const RoundDesc& rd, hipStream_t s);
 // whether batched rounds of this shape use the per-upload slots (else they need not be allocated)
 bool regression_batch_uses_slots(bool softmax, int B);
 

@@ -238,6 +238,9 @@ hipError_t launch_regression_local_round(const RegressionArgs& a, const RoundDes
   hook->begin(KK_LOCAL_STEPS, rows * a.d * (softmax ? a.C : 1) * 4.0, rows * (a.d + 1) * 4.0);
   if (!softmax) {
     linreg_local_kernel<<<dim3(rd.K), dim3(kLocWaves * 64), 0, s>>>(a, rd);
+  } else if (softmax_local_sliced_ok(a.d, a.C, a.B, a.U, rd.K)) {
+    const hipError_t e = launch_softmax_local_sliced(a, rd, s);
+    if (e != hipSuccess) return e;
   } else if (softmax_local_fused_ok(a.B, a.U)) {
     const hipError_t e = launch_softmax_local_fused(&a, &rd, nullptr, nullptr, 0, 1, a.d, a.C, a.B, a.U, rd.K, s);
     if (e != hipSuccess) return e;

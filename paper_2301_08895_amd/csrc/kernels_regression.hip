@@ -923,6 +923,252 @@ __global__ __launch_bounds__(kFuseThreads, TR == 16 ? 2 : 4) void softmax_local_
   softmax_upload_any<C, TR, true>(a, *(const RoundDesc*)(rds + (size_t)blockIdx.y * stride), blockIdx.x);
 }
 
+// ------------------------------------------------------------------ local steps of few uploads, sliced by features
+// One simulation's round has K^t uploads, and the kernel above walks an upload's U B rows in one workgroup: 40 tiles
+// of 16 rows in a chain of 2.9 us each on 16 of 256 CUs (784 x 10, 16 uploads of 10 steps of 64 rows: 118 us).  Here an
+// upload has eight workgroups, slice s taking exactly the features that wavefront s has there (blocks s, s + 8, ... of 16),
+// and a step is cut where its only exchange is: launch u adds the eight slices' partial logits of step u - 1, forms dZ
+// (every slice for itself: B x 16 values), its features' gradient and model, and leaves its partial logits of step u.
+// The launch boundary is the barrier; U + 1 launches of 8 us, bound by chains of latencies: arguments and rows 1.6, the rows'
+// requests (64 of them all over the dataset) 1.4, softmax 1.0, gradient 1.0, logits 0.8, launch to launch 1.  All sums run in the order of the kernel above, operand by
+// operand, so the two give the same bits (a batch of simulations, which has uploads enough, keeps that one).
+constexpr int kSliceMaxUploads = 32, kSliceMinB = 33, kSliceMaxB = 256;
+constexpr int kSlices = kFuseWaves;
+// scratch per upload, floats: two sets of partial logits [slice][row][16], the running loss of [row % 16][class]
+// dataset rows and labels of three steps (launch u leaves those of step u + 1 while its own rows are on their way)
+__host__ __device__ inline size_t slice_floats(int B) { return (size_t)2 * kSlices * B * 16 + 256 + 6 * (size_t)B; }
+
+template <int C>
+__global__ __launch_bounds__(512) void softmax_slice_kernel(RegressionArgs a, RoundDesc rd, int u) {
+  constexpr int NB = kWregNB, kMaxTiles = kSliceMaxB / 16;
+  __shared__ __align__(16) float s_w[NB * 64 * 4];         // the slice's model after step u - 1: lane (m16, g4)'s four elements of each block
+  __shared__ float s_dz[kSliceMaxB * 16];
+  __shared__ float s_term[kSliceMaxB];
+  __shared__ __align__(16) uint32_t s_row[2][kSliceMaxB];  // dataset rows of steps u - 1 and u, the last one repeated to a whole tile
+  __shared__ int s_lab[kSliceMaxB];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int slice = blockIdx.x, up = blockIdx.y;
+  const int m16 = lane & 15, g4 = lane >> 4;
+  const int d = a.d, B = a.B, ntiles = (B + 15) >> 4;
+  const WorkerDesc w = rd.w[up];
+  const float* const Wv = a.ring + (size_t)w.slot * a.slot_stride;
+  float* const part = a.delta + (size_t)up * a.slot_stride;      // the private model between launches, at the end the upload
+  float* const scratch = a.slice + (size_t)up * slice_floats(B);
+  const float* const zin = scratch + (size_t)((u & 1) ^ 1) * kSlices * B * 16;
+  float* const zout = scratch + (size_t)(u & 1) * kSlices * B * 16;
+  float* const lossst = scratch + (size_t)2 * kSlices * B * 16;
+  uint32_t* const rows3 = (uint32_t*)(lossst + 256);       // [step % 3][row]
+  int* const labels3 = (int*)(rows3 + 3 * B);
+  const int prev3 = (u + 2) % 3, cur3 = u % 3, next3 = (u + 1) % 3;
+  const bool back = u > 0, ahead = u < a.U;
+
+  // wavefront w < 7: block bi = w of the slice, features 16 blk ..; lane (m16, g4) has W[16 blk + 4 g4 + v][m16]
+  const int blk = slice + kFuseWaves * wave, f0 = 16 * blk + 4 * g4;
+  const bool mine = wave < NB && (wave < NB - 1 || 16 * blk <= d);
+  f32x4_ wreg = {0.f, 0.f, 0.f, 0.f}, w0 = {0.f, 0.f, 0.f, 0.f};
+  if (mine && m16 < C) {
+    const float* const src = u <= 1 ? Wv : part;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (f0 < d || (f0 == d && v == 0)) {
+        wreg[v] = src[(f0 + v) * C + m16];
+        if (!ahead) w0[v] = Wv[(f0 + v) * C + m16];
+      }
+  }
+  // what the softmax needs is asked for first: loads come back in order, and the rows below may be far away
+  float zp[kSliceMaxB / 32][kSlices];
+  if (back) {
+#pragma unroll
+    for (int q = 0; q < kSliceMaxB / 32; ++q) {
+      const int r = (t >> 4) + 32 * q;
+      if (r < B) {
+#pragma unroll
+        for (int s = 0; s < kSlices; ++s) zp[q][s] = zin[((size_t)s * B + r) * 16 + m16];
+      }
+    }
+    if (t < B) s_lab[t] = labels3[prev3 * B + t];
+  }
+  // thread t < 256: row t of step u - 1, the others row t - 256 of step u
+  {
+    const int i = t & 255, b = min(i, B - 1);
+    if (u == 0) {
+      if (t >= 256 && i < 16 * ntiles) s_row[1][i] = (uint32_t)batch_row(w, a.batch_key, a.shard_rows, (uint32_t)b);
+    } else if (i < 16 * ntiles) {
+      s_row[t >> 8][i] = rows3[(t < 256 ? prev3 : cur3) * B + b];      // (step U's are not there, and not used)
+    }
+  }
+  __syncthreads();
+  int next_label = 0;
+  // the rows of the step ahead, for the logits: wavefront w takes tiles w and w + 8 (features beyond d: the row's first
+  // ones, replaced when they are used)
+  float4 av[2][NB];
+  if (ahead) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int tile = wave + 8 * q;
+      if (tile < ntiles) {
+        const float* const src = a.X + (uint64_t)s_row[1][16 * tile + m16] * (uint64_t)d;
+#pragma unroll
+        for (int bi = 0; bi < NB; ++bi) {
+          const int kk = 16 * (slice + kFuseWaves * bi) + 4 * g4;
+          av[q][bi] = load_global_f4(src + (kk < d ? kk : 0));
+        }
+      }
+    }
+  }
+  if (slice == 0 && t < B) {
+    if (u == 0) {
+      rows3[t] = s_row[1][t];
+      labels3[t] = load_global((const int32_t*)a.y + s_row[1][t]);
+    }
+    if (u + 1 < a.U) {
+      const uint32_t r = (uint32_t)batch_row(w, a.batch_key, a.shard_rows, (uint32_t)((u + 1) * B + t));
+      rows3[next3 * B + t] = r;
+      next_label = load_global((const int32_t*)a.y + r);
+    }
+  }
+  if (back) {
+    // the step's features for the gradient: x~[row 16 tile + 4 g4 + j][16 blk + m16], four tiles ahead
+    const int f = 16 * blk + m16;
+    float xg[4][4];
+    auto load_rows = [&](int tile0) {    // (rows beyond B: the last one, features beyond d: the last one; replaced when they are used)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (tile0 + q < ntiles) {
+          const uint4 r = *(const uint4*)&s_row[0][16 * (tile0 + q) + 4 * g4];
+          const float* const x = a.X + min(f, d - 1);
+          xg[q][0] = load_global(x + (uint64_t)r.x * (uint64_t)d); xg[q][1] = load_global(x + (uint64_t)r.y * (uint64_t)d);
+          xg[q][2] = load_global(x + (uint64_t)r.z * (uint64_t)d); xg[q][3] = load_global(x + (uint64_t)r.w * (uint64_t)d);
+        }
+    };
+    if (mine) load_rows(0);
+#pragma unroll
+    for (int q = 0; q < kSliceMaxB / 32; ++q) {
+      const int r = (t >> 4) + 32 * q, c = m16;
+      if (32 * q < 16 * ntiles) {
+        const int label = r < B ? s_lab[r] : -1;
+        float zz = 0.f;
+        if (r < B) {
+          zz = zp[q][0];
+#pragma unroll
+          for (int s = 1; s < kSlices; ++s) zz += zp[q][s];
+        }
+        if (c >= C) zz = -INFINITY;
+        const float zmax = row16_max(zz);
+        const float e = c < C ? expf(zz - zmax) : 0.f;
+        const float ssum = row16_sum(e);
+        const float p = e / ssum;
+        s_dz[r * 16 + c] = r < B && c < C ? w.c * (p - (c == label ? 1.f : 0.f)) : 0.f;
+        if (c == label) s_term[r] = logf(ssum) - (zz - zmax);
+      }
+    }
+    __syncthreads();
+    if (mine) {
+      f32x4_ G = {0.f, 0.f, 0.f, 0.f};
+      for (int t0 = 0; t0 < ntiles; t0 += 4) {
+        if (t0) load_rows(t0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (t0 + q < ntiles) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              G = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                  16 * (t0 + q) + 4 * g4 + j < B ? (f < d ? xg[q][j] : f == d ? 1.f : 0.f) : 0.f, s_dz[(16 * (t0 + q) + 4 * g4 + j) * 16 + m16], G, 0, 0, 0);
+          }
+      }
+      if (f0 <= d) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) wreg[i] -= G[i];
+      }
+      if (m16 < C) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (f0 < d || (f0 == d && v == 0)) part[(f0 + v) * C + m16] = ahead ? wreg[v] : w0[v] - wreg[v];
+      }
+    }
+    if (slice == 0 && t < 256) {         // the losses, row slot by row slot and tile after tile as above
+      float loss = u == 1 ? 0.f : lossst[t];
+      for (int tile = 0; tile < ntiles; ++tile) {
+        const int r = 16 * tile + (t >> 4);
+        if (r < B && s_lab[r] == m16) loss += s_term[r];
+      }
+      lossst[t] = loss;
+      if (!ahead) {
+        loss = row16_sum(loss);
+        if (m16 == 0) s_w[t >> 4] = loss;
+      }
+    }
+    if (!ahead) {
+      __syncthreads();
+      if (slice == 0 && t == 0) {
+        float l = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) l += s_w[v];
+        a.lossbuf[up] = l / (float)(a.U * B);
+      }
+      return;
+    }
+  }
+  if (slice == 0 && t < B && u + 1 < a.U) labels3[next3 * B + t] = next_label;
+  if (wave < NB) *(f32x4_*)&s_w[(wave * 64 + lane) * 4] = wreg;
+  __syncthreads();
+  f32x4_ wb[NB];
+#pragma unroll
+  for (int bi = 0; bi < NB; ++bi) wb[bi] = *(const f32x4_*)&s_w[(bi * 64 + lane) * 4];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int tile = wave + 8 * q;
+    if (tile < ntiles) {
+      f32x4_ z0 = {0.f, 0.f, 0.f, 0.f}, z1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int bi = 0; bi < NB; ++bi) {
+        if (bi < NB - 1 || 16 * (slice + kFuseWaves * bi) <= d) {
+          f32x4_& z = (bi & 1) ? z1 : z0;
+          const int kk = 16 * (slice + kFuseWaves * bi) + 4 * g4;
+          if (kk >= d) av[q][bi] = make_float4(kk == d ? 1.f : 0.f, 0.f, 0.f, 0.f);
+          z = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q][bi].x, wb[bi][0], z, 0, 0, 0);
+          z = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q][bi].y, wb[bi][1], z, 0, 0, 0);
+          z = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q][bi].z, wb[bi][2], z, 0, 0, 0);
+          z = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q][bi].w, wb[bi][3], z, 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = 16 * tile + 4 * g4 + i;
+        if (r < B) zout[((size_t)slice * B + r) * 16 + m16] = z0[i] + z1[i];
+      }
+    }
+  }
+  static_assert(kMaxTiles <= 16, "two tiles per wavefront");
+}
+
+// Whether a round of K uploads of one simulation runs in slices: the model in registers in the other form (the orders match),
+// at least three tiles a step (a launch costs what two and a half tiles do there), rows that a workgroup's LDS holds, and
+// few enough uploads that eight workgroups each find a place at once.  us of a round, a workgroup per upload / slices, 784 x 10:
+// B = 64, U = 10: K = 4 128 / 90, 16 130 / 96, 32 132 / 122, 64 139 / 215; K = 16: B = 32, U = 10 73 / 81, B = 48, U = 2 33.8 / 30.4,
+// B = 128, U = 4 105 / 67, B = 250, U = 8 373 / 192.
+static int fuse_form(int d, int C, int rows);
+bool softmax_local_sliced_ok(int d, int C, int B, int U, int K) {
+  return U > 1 && K <= kSliceMaxUploads && B >= kSliceMinB && B <= kSliceMaxB && softmax_local_fused_ok(B, U) && fuse_form(d, C, B * U) == kWreg;
+}
+size_t softmax_local_slice_bytes(int d, int C, int B, int U, int N) {
+  return softmax_local_sliced_ok(d, C, B, U, 1) ? (size_t)(N < kSliceMaxUploads ? N : kSliceMaxUploads) * slice_floats(B) * 4 : 0;
+}
+hipError_t launch_softmax_local_sliced(const RegressionArgs& a, const RoundDesc& rd, hipStream_t s) {
+  const dim3 grid(kSlices, rd.K), block(512);
+  for (int u = 0; u <= a.U; ++u) {
+    switch (a.C) {
+#define ABS_CASE(c) case c: softmax_slice_kernel<c><<<grid, block, 0, s>>>(a, rd, u); break;
+      ABS_CASE(2) ABS_CASE(3) ABS_CASE(4) ABS_CASE(5) ABS_CASE(6) ABS_CASE(7) ABS_CASE(8) ABS_CASE(9)
+      ABS_CASE(10) ABS_CASE(11) ABS_CASE(12) ABS_CASE(13) ABS_CASE(14) ABS_CASE(15) ABS_CASE(16)
+#undef ABS_CASE
+      default: return hipErrorInvalidValue;
+    }
+    if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Eq. 3 over the uploads' gradients (each already scaled by its c), arrival order
 __global__ __launch_bounds__(256) void softmax_combine_batch_kernel(const RegressionArgs* as, const char* rds,
                                                                     size_t stride, int P) {

@@ -122,3 +122,25 @@ def test_local_sgd_equals_the_hand_worked_run():
     sim.close()
     for t, l in losses.items():
         assert np.int32(tr[t][10]).view(np.float32) == np.float32(l)
+
+
+@pytest.mark.parametrize("d,C,N,B,U,K", [
+    (4, 2, 3, 33, 2, 3),           # the shortest minibatch, a tile of one row; one block of features, in slice 0 alone
+    (784, 10, 6, 64, 3, 4),
+    (892, 16, 5, 50, 4, 5),        # the widest model
+    (128, 3, 4, 256, 8, 2),        # the most rows: two tiles per wavefront
+    (788, 7, 33, 40, 2, 32),       # the most uploads
+    (788, 7, 33, 40, 2, 33),       # ... one more: a workgroup per upload
+])
+def test_sliced_softmax_steps_give_the_bits_of_the_batched_kernel(d, C, N, B, U, K):
+    """One simulation's local steps run in slices of the features, a batch's in one workgroup per upload: the same sums in the same order."""
+    import paper_2301_08895_amd as lib
+    p = workloads.scaled_preset(2, M=max(600, 10 * N), dims=[d, C], n_classes=C, N=N, B=B, U=U, K0=K, k_mode=1, lr=0.5 / d)
+    data = workloads.make_inputs(p)
+    alone = lib.Simulation(p, data)
+    alone.round(5)
+    other = lib.Simulation(p, data)
+    batch = lib.Batch([other])
+    batch.round(5)
+    assert np.array_equal(alone.model(), other.model()) and np.array_equal(alone.trace(), other.trace())
+    batch.close(); alone.close(); other.close()
