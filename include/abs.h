@@ -50,7 +50,9 @@ enum {
   ABS_E_WORKSPACE = -2,  /* workspace smaller than abs_workspace_size()                 */
   ABS_E_HIP = -3,        /* a HIP runtime call failed                                   */
   ABS_E_VERSION = -4,    /* requested model version is no longer (or not yet) in the ring */
-  ABS_E_NONFINITE = -5,  /* a worker loss came back non-finite                          */
+  ABS_E_NONFINITE = -5,  /* a worker loss came back non-finite (the round is not counted; with a fixed
+                            or replayed wait count the one behind it may have been started, and the
+                            two oldest versions of the ring are gone)                       */
   ABS_E_REPLAY = -6      /* k_mode 2: the replay array has no entry for this round      */
 };
 

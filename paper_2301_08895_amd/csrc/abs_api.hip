@@ -190,8 +190,9 @@ struct abs_ctx : public LaunchHook {
   RegPlan rplan{};
   MlpArgs margs{};
   CnnArgs cargs{};
-  LossMailbox* h_box = nullptr;   // pinned, device-visible
+  LossMailbox* h_box = nullptr;   // pinned, device-visible [2]: abs_round posts round t's losses to the one of its parity
   LossMailbox* d_box = nullptr;   // the device's address of h_box
+  int lost = 0;                   // 1: the last call failed with the next round already started, which overwrites one more version
   int device = -1;                // the GPU the handle was created on
   void* static_scratch = nullptr; // that GPU's copy of the evaluation scratch (abs_evaluate_static)
   std::string err;
@@ -244,14 +245,14 @@ struct abs_ctx : public LaunchHook {
   // Spin until the device has posted the K losses of the round with this stamp; every so often ask the
   // runtime whether the stream has failed or drained without them, and give up after
   // mailbox_timeout_s(), so neither a broken launch nor a stream that never gets to run can hang the host.
-  int wait_mailbox(uint32_t stamp, int K) {
+  int wait_mailbox(const LossMailbox* box, uint32_t stamp, int K) {
     const auto t0 = std::chrono::steady_clock::now();
     for (int a = 0; a < K; ++a) {
-      for (uint64_t spin = 1; !h_box->posted(a, stamp); ++spin) {
+      for (uint64_t spin = 1; !box->posted(a, stamp); ++spin) {
         if ((spin & 0x3FFF) == 0) {
           const hipError_t q = hipStreamQuery(stream);
           if (q == hipSuccess) {
-            if (h_box->posted(a, stamp)) break;
+            if (box->posted(a, stamp)) break;
             err = "stream drained but the loss mailbox was not written";
             return ABS_E_HIP;
           }
@@ -339,9 +340,9 @@ int abs_create(const abs_config* cfg, const void* d_X, const void* d_y, const fl
     if (c->h_box) (void)hipHostFree(c->h_box);
     return ABS_E_HIP;
   };
-  hipError_t e = hipHostMalloc((void**)&c->h_box, sizeof(LossMailbox), hipHostMallocMapped);
+  hipError_t e = hipHostMalloc((void**)&c->h_box, 2 * sizeof(LossMailbox), hipHostMallocMapped);
   if (e != hipSuccess) { c->h_box = nullptr; return fail("hipHostMalloc", e); }
-  std::memset(c->h_box, 0, sizeof(LossMailbox));
+  std::memset(c->h_box, 0, 2 * sizeof(LossMailbox));
   e = hipHostGetDevicePointer((void**)&c->d_box, c->h_box, 0);
   if (e != hipSuccess) return fail("hipHostGetDevicePointer", e);
 
@@ -358,7 +359,6 @@ int abs_create(const abs_config* cfg, const void* d_X, const void* d_y, const fl
     c->margs.y = (const int32_t*)d_y;
     c->margs.shard_rows = shard;
     c->margs.batch_key = bkey;
-    c->margs.mailbox = c->d_box;
     c->slot_stride = c->margs.plan.slot_stride;
     c->off_ring = c->margs.plan.off_ring;
   } else if (cfg->model == ABS_MODEL_CNN) {
@@ -369,7 +369,6 @@ int abs_create(const abs_config* cfg, const void* d_X, const void* d_y, const fl
     c->cargs.y = (const int32_t*)d_y;
     c->cargs.shard_rows = shard;
     c->cargs.batch_key = bkey;
-    c->cargs.mailbox = c->d_box;
     c->slot_stride = c->cargs.plan.slot_stride;
     c->off_ring = c->cargs.plan.off_ring;
     e = cnn_prepare();
@@ -426,7 +425,7 @@ static void fill_round_desc(const abs_ctx* ctx, const std::vector<Upload>& sel, 
   }
 }
 
-static void fill_regression_args(const abs_ctx* ctx, RegressionArgs& ra) {
+static void fill_regression_args(const abs_ctx* ctx, RegressionArgs& ra, LossMailbox* mailbox) {
   const abs_config& cfg = ctx->cfg;
   ra.X = (const float*)ctx->dX;
   ra.y = ctx->dy;
@@ -437,7 +436,7 @@ static void fill_regression_args(const abs_ctx* ctx, RegressionArgs& ra) {
   ra.B = cfg.B;
   ra.shard_rows = (uint64_t)(cfg.M / cfg.N);
   ra.batch_key = stream_key(cfg.seed, kStreamBatch);
-  ra.mailbox = ctx->d_box;
+  ra.mailbox = mailbox;
   ra.dz = (float*)(ctx->ws + ctx->rplan.off_dz);
   ra.rowloss = (float*)(ctx->ws + ctx->rplan.off_rowloss);
   ra.rowidx = (uint32_t*)(ctx->ws + ctx->rplan.off_rowidx);
@@ -447,15 +446,55 @@ static void fill_regression_args(const abs_ctx* ctx, RegressionArgs& ra) {
   ra.slice = (float*)(ctx->ws + ctx->rplan.off_slice);
 }
 
+// A round whose losses abs_round has not looked at yet.
+namespace {
+struct RoundAhead {
+  bool live = false;
+  int64_t t = 0; int K = 0; uint32_t stamp = 0;
+  int pos_of[ABS_MAX_WORKERS];
+  Scheduler::Saved saved;
+};
+// Waits for them and gives them to the scheduler; on failure the scheduler is back where it was when the round had been
+// launched, as if nothing had been done after it.
+int collect(abs_ctx* ctx, RoundAhead& r) {
+  r.live = false;
+  const LossMailbox* const box = ctx->h_box + (r.t & 1);
+  int rc = ctx->wait_mailbox(box, r.stamp, r.K);
+  if (rc == ABS_OK) {
+    float losses[ABS_MAX_WORKERS];
+    for (int a = 0; a < r.K; ++a) losses[a] = box->loss(r.pos_of[a]);
+    rc = ctx->sched->set_losses(r.saved, r.K, losses, ctx->err);
+  }
+  if (rc != ABS_OK) {
+    ctx->sched->restore(r.saved);
+  }
+  return rc;
+}
+}  // namespace
+
 int abs_round(abs_ctx* ctx, int32_t n_rounds) {
   if (!ctx || n_rounds < 0) return ABS_E_ARG;
   const abs_config& cfg = ctx->cfg;
   std::vector<Upload> sel;
   RoundDesc rd;
   std::memset(&rd, 0, sizeof(rd));
+  // With a fixed or replayed wait count the next round does not depend on this one's losses (Eq. 5 is not used): it is
+  // selected and launched before they are looked at, one round ahead and not beyond this call, so that the device finds
+  // its next kernel waiting (us of a round before / now: linear, 2 uploads of 32 rows, 13.1 / 9.0, softmax 784 x 10, 4 of 64, 16.3 / 13.9).
+  // Profiled rounds drain the stream anyway.
+  const bool ahead = cfg.device_mode && !cfg.profile && (cfg.k_mode == ABS_K_FIXED || cfg.k_mode == ABS_K_REPLAY);
+  RoundAhead prev;
   for (int32_t it = 0; it < n_rounds; ++it) {
     int rc = ctx->sched->select(sel, ctx->err);
-    if (rc != ABS_OK) return rc;
+    if (rc != ABS_OK) {
+      if (prev.live) {                   // the earlier round's failure is the one to report
+        const std::string why = ctx->err;
+        const int rc0 = collect(ctx, prev);
+        if (rc0 != ABS_OK) return rc0;
+        ctx->err = why;
+      }
+      return rc;
+    }
     const int64_t t = ctx->sched->round();
     const int K = (int)sel.size();
     if (!cfg.device_mode) {
@@ -466,26 +505,50 @@ int abs_round(abs_ctx* ctx, int32_t n_rounds) {
     int pos_of[ABS_MAX_WORKERS];
     fill_round_desc(ctx, sel, t, rd, pos_of);
     ctx->timing = cfg.profile == 1 || (cfg.profile > 1 && t % cfg.profile == 0);
+    LossMailbox* const d_box = ctx->d_box + (t & 1);
     hipError_t e;
     if (cfg.model == ABS_MODEL_MLP) {
+      ctx->margs.mailbox = d_box;
       e = launch_mlp_round(ctx->margs, rd, ctx->stream, ctx);
     } else if (cfg.model == ABS_MODEL_CNN) {
+      ctx->cargs.mailbox = d_box;
       e = launch_cnn_round(ctx->cargs, rd, ctx->stream, ctx);
     } else {
       RegressionArgs ra;
-      fill_regression_args(ctx, ra);
+      fill_regression_args(ctx, ra, d_box);
       if (cfg.U > 1)
         e = launch_regression_local_round(ra, rd, cfg.model == ABS_MODEL_SOFTMAX, ctx->stream, ctx);
       else
         e = cfg.model == ABS_MODEL_LINEAR ? launch_linreg_round(ra, rd, ctx->stream, ctx)
                                           : launch_softmax_round(ra, rd, ctx->stream, ctx);
     }
-    if (e != hipSuccess) { ctx->err = std::string("kernel launch: ") + hipGetErrorString(e); return ABS_E_HIP; }
+    if (e != hipSuccess) {
+      if (prev.live) {
+        const int rc0 = collect(ctx, prev);
+        if (rc0 != ABS_OK) return rc0;
+      }
+      ctx->err = std::string("kernel launch: ") + hipGetErrorString(e);
+      return ABS_E_HIP;
+    }
+    ctx->lost = 0;
+    if (ahead) {
+      if (prev.live) {
+        rc = collect(ctx, prev);
+        if (rc != ABS_OK) { ctx->lost = 1; return rc; }
+      }
+      prev.live = true; prev.t = t; prev.K = K; prev.stamp = rd.stamp;
+      std::copy(pos_of, pos_of + K, prev.pos_of);
+      ctx->sched->save(prev.saved);
+      rc = ctx->sched->complete(sel, nullptr, false, ctx->err);
+      if (rc != ABS_OK) return rc;
+      continue;
+    }
     // Eq. 5 needs this round's losses before the next round can be selected.  They arrive in
     // the mailbox as soon as the forward pass is through, so the
     // host prepares and enqueues round t+1 while the device still works on round t; stream
     // order keeps the rounds apart on the device.
-    rc = ctx->wait_mailbox(rd.stamp, K);
+    const LossMailbox* const box = ctx->h_box + (t & 1);
+    rc = ctx->wait_mailbox(box, rd.stamp, K);
     if (rc != ABS_OK) return rc;
     // profile mode: the rounds' events are read back in batches, after draining the stream
     if (cfg.profile && (ctx->ev_kind.size() >= 512 || it + 1 == n_rounds)) {
@@ -493,9 +556,14 @@ int abs_round(abs_ctx* ctx, int32_t n_rounds) {
       ctx->harvest();
     }
     float losses[ABS_MAX_WORKERS];
-    for (int a = 0; a < K; ++a) losses[a] = ctx->h_box->loss(pos_of[a]);
+    for (int a = 0; a < K; ++a) losses[a] = box->loss(pos_of[a]);
     rc = ctx->sched->complete(sel, losses, true, ctx->err);
     if (rc != ABS_OK) return rc;
+  }
+  if (prev.live) {
+    const int rc = collect(ctx, prev);
+    if (rc != ABS_OK) ctx->lost = 0;     // nothing was started after it
+    return rc;
   }
   return ABS_OK;
 }
@@ -635,8 +703,7 @@ int abs_batch_create(abs_ctx** ctxs, int32_t n, void* d_workspace, size_t worksp
   if (plan.slots) b->d_slots = ws + plan.off_slots;
   std::vector<RegressionArgs> args((size_t)n);
   for (int32_t i = 0; i < n; ++i) {
-    fill_regression_args(ctxs[i], args[(size_t)i]);
-    args[(size_t)i].mailbox = b->d_box + i;          // the batch's own mailboxes
+    fill_regression_args(ctxs[i], args[(size_t)i], b->d_box + i);      // the batch's own mailboxes
     if (b->d_slots) {
       args[(size_t)i].delta = (float*)b->d_slots + (size_t)i * plan.sim_floats;
       args[(size_t)i].lossbuf = args[(size_t)i].delta + plan.slot_floats;
@@ -875,7 +942,7 @@ int abs_get_model(abs_ctx* ctx, int64_t version, float* h_out, size_t n_floats) 
   if (n_floats != ctx->P) { ctx->err = "n_floats must equal the parameter count"; return ABS_E_ARG; }
   const int64_t t = ctx->sched->round();
   if (version < 0) version = t;
-  if (version > t || version < t - (ctx->R - 1) + 0 || version < 0) {
+  if (version > t || version < t - (ctx->R - 1) + 2 * ctx->lost || version < 0) {
     ctx->err = "model version not in the ring"; return ABS_E_VERSION;
   }
   const char* src = ctx->ws + ctx->off_ring + (size_t)(version % ctx->R) * ctx->slot_stride * sizeof(float);
@@ -893,7 +960,7 @@ static int enqueue_evaluation(abs_ctx* ctx, int64_t version, const void* d_X, co
   if (n_rows < 1 || n_rows > 0xFFFFFFFFll) { ctx->err = "n_rows must be in [1, 2^32)"; return ABS_E_ARG; }
   const int64_t t = ctx->sched->round();
   if (version < 0) version = t;
-  if (version > t || version < t - (ctx->R - 1) || version < 0) {
+  if (version > t || version < t - (ctx->R - 1) + 2 * ctx->lost || version < 0) {
     ctx->err = "model version not in the ring"; return ABS_E_VERSION;
   }
   const abs_config& cfg = ctx->cfg;

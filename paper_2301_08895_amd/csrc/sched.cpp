@@ -92,15 +92,43 @@ int Scheduler::next_wait_count(int K_now, double loss_t) const {
   return std::min(N_, std::max(1, cand));
 }
 
+int Scheduler::mean_loss(const float* worker_loss, int K, double* mean, std::string& err) {
+  double s = 0.0;
+  for (int a = 0; a < K; ++a) s += (double)worker_loss[a];
+  *mean = s / (double)K;
+  if (!std::isfinite(*mean)) { err = "non-finite minibatch loss"; return ABS_E_NONFINITE; }
+  return ABS_OK;
+}
+
+void Scheduler::save(Saved& s) const {
+  s.t = t_; s.K = K_; s.loss0 = loss0_; s.now = now_; s.uploads = uploads_; s.restarts = restarts_;
+  s.tau = tau_; s.ver = ver_; s.job = job_; s.fin = fin_;
+  s.trace_words = trace_.size();
+}
+
+void Scheduler::restore(const Saved& s) {
+  t_ = s.t; K_ = s.K; loss0_ = s.loss0; now_ = s.now; uploads_ = s.uploads; restarts_ = s.restarts;
+  tau_ = s.tau; ver_ = s.ver; job_ = s.job; fin_ = s.fin;
+  trace_.resize(s.trace_words);
+}
+
+int Scheduler::set_losses(const Saved& s, int K, const float* worker_loss, std::string& err) {
+  double loss = 0.0;
+  const int rc = mean_loss(worker_loss, K, &loss, err);
+  if (rc != ABS_OK) return rc;
+  if (s.t == 0) loss0_ = loss;
+  const float lf = (float)loss;
+  std::memcpy(trace_.data() + s.trace_words + 10, &lf, 4);
+  return ABS_OK;
+}
+
 int Scheduler::complete(const std::vector<Upload>& sel, const float* worker_loss, bool have_loss,
                         std::string& err) {
   const int K = (int)sel.size();
   double loss_t = std::numeric_limits<double>::quiet_NaN();
   if (have_loss) {
-    double s = 0.0;
-    for (int a = 0; a < K; ++a) s += (double)worker_loss[a];
-    loss_t = s / (double)K;
-    if (!std::isfinite(loss_t)) { err = "non-finite minibatch loss"; return ABS_E_NONFINITE; }
+    const int rc = mean_loss(worker_loss, K, &loss_t, err);
+    if (rc != ABS_OK) return rc;
     if (t_ == 0) loss0_ = loss_t;
   }
   std::vector<char>& in_sel = in_sel_;

@@ -36,12 +36,25 @@ class Scheduler {
 
   const std::vector<int32_t>& trace() const { return trace_; }
 
+  // Fixed and replayed wait counts: nothing of the next round depends on this round's losses, so the host may go on
+  // without them: save() before complete(..., nullptr, false, ...), then set_losses() for the round that was
+  // saved, or back to it with restore() if they cannot be had or are not finite.
+  struct Saved {
+    int64_t t; int K; double loss0; uint64_t now, uploads, restarts;
+    std::vector<int32_t> tau; std::vector<int64_t> ver; std::vector<uint32_t> job; std::vector<uint64_t> fin;
+    size_t trace_words;
+  };
+  void save(Saved& s) const;
+  void restore(const Saved& s);
+  int set_losses(const Saved& s, int K, const float* worker_loss, std::string& err);
+
   static uint64_t time_ticks(const abs_config& cfg, int32_t n, int64_t j);
 
  private:
   bool over_stale(int tau, int K) const;
   int  threshold_floor(int K) const;
   int  next_wait_count(int K_now, double loss_t) const;
+  static int mean_loss(const float* worker_loss, int K, double* mean, std::string& err);
 
   abs_config cfg_;
   std::vector<int32_t> replay_;

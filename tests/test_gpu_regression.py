@@ -113,3 +113,37 @@ def test_softmax_first_round_equals_the_hand_worked_values():
     batch.close()
     assert np.allclose(sim.model(), w1, rtol=0, atol=1e-7)
     sim.close()
+
+
+@pytest.mark.parametrize("k_mode", [1, 2])
+@pytest.mark.parametrize("model", [1, 2])
+def test_rounds_started_ahead_of_a_failure_are_not_counted(model, k_mode):
+    """Fixed and replayed wait counts launch a round before the last one's losses are looked at.  A loss that is not
+    finite ends the call at its own round all the same: trace, model and the next call as on a handle that looks at every
+    round's losses first (a profiled one)."""
+    import paper_2301_08895_amd as lib
+    p = workloads.scaled_preset(model, M=4000, N=4, B=4, K0=2, k_mode=k_mode, tau_cap=3, a=1, n_slow=0)
+    d = workloads.make_inputs(p)
+    d["X"][1234] = np.nan
+    ends = []
+    for profile in (0, 1):
+        sim = lib.Simulation(p, d, profile=profile, **({"k_replay": [2, 3, 1, 4] * 500} if k_mode == 2 else {}))
+        for n in (1, 2, 7, 1990):
+            try:
+                sim.round(n)
+            except lib.AbsError as e:
+                assert e.code == -5
+                break
+        else:
+            raise AssertionError("no round drew the row")
+        t = lib.abs_rounds_done(sim.handle)
+        tr = sim.trace()
+        with pytest.raises(lib.AbsError):
+            sim.round(1)                       # the same round again
+        ends.append((t, tr.copy(), sim.model(t).copy(), lib.abs_rounds_done(sim.handle)))
+        with pytest.raises(lib.AbsError):
+            sim.model(t + 1)
+        sim.close()
+    a, b = ends
+    assert a[0] == b[0] == a[3] == b[3] and a[0] > 10
+    assert np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
