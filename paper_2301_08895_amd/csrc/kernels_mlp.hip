@@ -2778,14 +2778,33 @@ bool step_pairs(const MlpPlan& p) {
 // blocks, 164 us a round against 174 with the copy, 2048 rows, 384 blocks 113.6 / 112.2, 3072-2048-2048-100, 384 blocks 224 / 216).
 bool step_direct(const MlpPlan& p, int rows) { return step_tiles(p, rows) == 128 && step_pairs(p) && gather_t_blocks(p, rows) > 512; }
 
-// All weight matrices and biases of a round at U = 1, w^t -> w^{t+1}, in one launch (mlp_step_kernel).
+// The same for a local step of K uploads: their rows are contractions of their own, so it is the private models' bytes that
+// count, and one launch for all layers, with tiles of half the models' rows, moves them faster than the products one by one
+// (256 x 256 tiles with an epilogue of 4 us and nothing beside it); up to 32 k-steps an upload, 64 x 64 tiles while the wider
+// ones would be few.  us of a round, a launch per layer / 64 x 64 / 128 x 128: 3072-512-10, U = 10, 128 rows: K = 2 510 / 456 /
+// 431, 8 669 / 646 / 591, 32 1878 / 1902 / 1778; 3072-1024-1024-10, K = 8, U = 5 879 / 786 / 711; 3072-2048-2048-100, K = 8, U = 3, 256
+// rows 1383 / 1426 / 1242; 512-512-10, K = 8, U = 10, 1024 rows 556 / 481 / 494, U = 4, 2048: 259 / 233 / 251, 4096: 431 / 403 / 446;
+// 512-2048-100, U = 4: K = 2, 1024 rows (160 tiles of 128) 302 / 269 / 278, K = 4, 1536 rows (320) 477 / 454 / 435.
+int local_step_tiles(const MlpPlan& p, int K) {
+  if (p.Bp / BK > 32) return 0;
+  long tiles = 0;
+  for (int l = 0; l < p.L; ++l) tiles += (long)(p.dp[l] / 128) * ((p.dp[l + 1] + 127) / 128);
+  return tiles * K <= 192 ? 64 : 128;
+}
+
+// All weight matrices and biases in one launch (mlp_step_kernel): w^t -> w^{t+1} of a round at U = 1, or a local step of
+// the uploads' private models (own: from themselves, else from the uploads' ring slots).
 void launch_steps(const MlpArgs& a, const RoundDesc& rd, int rows, double arows, int tile, bool direct, const BiasCore& bias, int bias_cols,
-                  hipStream_t s, LaunchHook* hook) {
+                  bool own, hipStream_t s, LaunchHook* hook) {
   const MlpPlan& p = a.plan;
   float* ring = at<float>(a, p.off_ring);
-  uint16_t* shadow = at<uint16_t>(a, p.off_shadow) + (size_t)rd.slot_next * p.shadow_stride;
+  uint16_t* shadow = p.U > 1 ? at<uint16_t>(a, p.off_priv_shadow) : at<uint16_t>(a, p.off_shadow) + (size_t)rd.slot_next * p.shadow_stride;
+  float* const priv = at<float>(a, p.off_priv);
   StepArgs g{};
-  g.L = p.L; g.uploads = 1; g.sel = 0; g.ksteps = rows / BK;
+  const bool local = p.U > 1;
+  const int up = local ? rd.K : 1;
+  g.L = p.L; g.uploads = up; g.sel = local ? (own ? 1 : 2) : 0; g.ksteps = rows / up / BK;
+  g.stride = p.slot_stride; g.shadow_stride = p.shadow_stride;
   g.rowidx = at<uint32_t>(a, p.off_rowidx);
   g.bias = bias; g.bias_per = (bias_cols + 15) / 16;
   int first = 0;
@@ -2795,23 +2814,26 @@ void launch_steps(const MlpArgs& a, const RoundDesc& rd, int rows, double arows,
     y.A = l > 0 ? at<uint16_t>(a, p.off_ht[l]) : direct ? a.X : at<uint16_t>(a, p.off_xgt); y.lda = l == 0 && direct ? (size_t)p.d[0] : p.ldm;
     y.Bt = at<uint16_t>(a, p.off_dzt[l + 1]); y.ldb = p.ldm;
     g.first[l] = first; y.mt = p.dp[l] / tile; y.nt = (p.dp[l + 1] + tile - 1) / tile;
-    first += (y.mt * y.nt + 7) / 8 * 8;
+    first += (up * y.mt * y.nt + 7) / 8 * 8;
     y.d_in = p.d[l]; y.d_out = p.d[l + 1]; y.dp_out = p.dp[l + 1];
-    y.cur = ring + (size_t)rd.slot_cur * p.slot_stride + p.w_off[l];
-    y.next = ring + (size_t)rd.slot_next * p.slot_stride + p.w_off[l];
+    y.cur = (!local ? ring + (size_t)rd.slot_cur * p.slot_stride : own ? priv : ring) + p.w_off[l];
+    y.next = (local ? priv : ring + (size_t)rd.slot_next * p.slot_stride) + p.w_off[l];
     y.wn = l >= 1 ? shadow + p.wn_off[l] : nullptr; y.ldwn = (size_t)p.ld[l + 1];
     y.wt = shadow + p.wt_off[l]; y.ldwt = (size_t)p.ld[l];
     flops += 2.0 * arows * p.d[l] * p.d[l + 1];
-    bytes += arows * (p.d[l] + p.d[l + 1]) * 2.0 + (double)p.d[l] * p.d[l + 1] * (l >= 1 ? 12.0 : 10.0);
+    bytes += arows * (p.d[l] + p.d[l + 1]) * 2.0 + (double)up * p.d[l] * p.d[l + 1] * (l >= 1 ? 12.0 : 10.0);
   }
   for (int l = p.L; l < 8; ++l) g.first[l] = first;
   kbegin(hook, KK_MLP_WGRAD_L1, flops, bytes);
-  plan_note(direct ? "steps_x" : tile == 128 && step_pairs(p) ? "steps2" : "steps", tile, tile, 1);
-  const dim3 grid(first + g.bias_per);
-  if (tile == 64)         ABS_LAUNCH_K((mlp_step_kernel<64, 64, 4, 4, 2, false>), grid, dim3(256), s, g, rd);
-  else if (direct)        ABS_LAUNCH_K((mlp_step_kernel<128, 128, 8, 2, 4, true>), grid, dim3(512), s, g, rd);
-  else if (step_pairs(p)) ABS_LAUNCH_K((mlp_step_kernel<128, 128, 8, 2, 4, false>), grid, dim3(512), s, g, rd);
-  else                    ABS_LAUNCH_K((mlp_step_kernel<128, 128, 8, 4, 2, false>), grid, dim3(512), s, g, rd);
+  const bool pairs = tile == 128 && (local || step_pairs(p));
+  if (local) { for (int l = 0; l < p.L; ++l) plan_note(pairs ? "wgrad_step_tile2" : "wgrad_step_tile", tile, tile, up); }
+  else       plan_note(direct ? "steps_x" : pairs ? "steps2" : "steps", tile, tile, 1);
+  const dim3 grid(first + up * g.bias_per);
+  if (tile == 64 && local) ABS_LAUNCH_K((mlp_step_kernel<64, 64, 4, 2, 3, false>), grid, dim3(256), s, g, rd);
+  else if (tile == 64)     ABS_LAUNCH_K((mlp_step_kernel<64, 64, 4, 4, 2, false>), grid, dim3(256), s, g, rd);
+  else if (direct)         ABS_LAUNCH_K((mlp_step_kernel<128, 128, 8, 2, 4, true>), grid, dim3(512), s, g, rd);
+  else if (pairs)          ABS_LAUNCH_K((mlp_step_kernel<128, 128, 8, 2, 4, false>), grid, dim3(512), s, g, rd);
+  else                     ABS_LAUNCH_K((mlp_step_kernel<128, 128, 8, 4, 2, false>), grid, dim3(512), s, g, rd);
   kend(hook, KK_MLP_WGRAD_L1);
 }
 
@@ -2864,8 +2886,8 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
                                            (long)step * (long)p.B, s, hook);
 
     // ---- output layer: loss and output gradient, already scaled by the uploads' coefficients
-    const int stile = local ? 0 : step_tiles(p, rows);
-    const bool sdirect = stile && step_direct(p, rows);
+    const int stile = local ? local_step_tiles(p, K) : step_tiles(p, rows);
+    const bool sdirect = !local && stile && step_direct(p, rows);
     const int gather_blocks = (stile ? sdirect : wg0_direct) ? 0 : gather_t_blocks(p, rows);
     const bool gather_rides = gather_blocks <= (ce_rows(p, rows) == kCeFewRows ? kGatherRideFew : kGatherRide);
     launch_logits_ce(a, rd, rows, arows, wbase, sbase, own, gather_rides ? gather_blocks : 0, s, hook);
@@ -2948,7 +2970,7 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
     bias.w_cur = local ? wbase : ring + (size_t)rd.slot_cur * p.slot_stride;
     bias.w_next = local ? priv : ring + (size_t)rd.slot_next * p.slot_stride;
     if (stile) {
-      launch_steps(a, rd, rows, arows, stile, sdirect, bias, bias_cols, s, hook);
+      launch_steps(a, rd, rows, arows, stile, sdirect, bias, bias_cols, own, s, hook);
       continue;
     }
     int pend = -1, pend_split = 0, pend_q = 0;   // layer whose partials are complete and whose update is still due (its splits or run length)

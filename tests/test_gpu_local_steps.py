@@ -144,3 +144,18 @@ def test_sliced_softmax_steps_give_the_bits_of_the_batched_kernel(d, C, N, B, U,
     batch.round(5)
     assert np.array_equal(alone.model(), other.model()) and np.array_equal(alone.trace(), other.trace())
     batch.close(); alone.close(); other.close()
+
+
+@pytest.mark.parametrize("dims,N,B,U,item", [
+    ([40, 24, 3], 2, 1, 3, "wgrad_step_tile:64x64/2"),
+    ([200, 1000, 10], 6, 300, 2, "wgrad_step_tile:64x64/6"),            # 144 tiles of 128 x 128
+    ([200, 1000, 10], 9, 300, 2, "wgrad_step_tile2:128x128/9"),         # 216
+    ([1000, 1030, 700, 130], 3, 60, 3, "wgrad_step_tile2:128x128/3"),   # ragged, three layers, two column tiles of classes
+    ([72, 300, 10], 2, 2048, 2, "wgrad_step_tile:64x64/2"),             # the most rows
+])
+def test_local_steps_of_all_layers_in_one_launch(dims, N, B, U, item):
+    import paper_2301_08895_amd as lib
+    p = workloads.scaled_preset(3, M=max(512, 2 * N * B), dims=dims, n_classes=dims[-1], N=N, K0=N, B=B, n_slow=0, U=U, lr=2e-4)
+    plan = lib.abs_mlp_round_plan(lib.make_config(p), N).split()
+    assert plan.count(item) == U * (len(dims) - 1), plan
+    _check(run_pair(p, 2, checkpoints=(1,)), 2e-2, 2e-3, guard=BF16_GUARD)
