@@ -248,94 +248,119 @@ __global__ __launch_bounds__(NT) void cnn_fwd_kernel(CnnDev d, RoundDesc rd) {
 // The dense stack.  A workgroup takes G stacked rows of one upload; the rows' values of a feature sit next
 // to each other in LDS ([feature][row]), so one read feeds a weight's G sums.
 // out[j][b] = bias[j] + sum_i in[i][b] W[i][j].  The workgroup is cut into slices of the input features,
-// each with a thread per column (neighbouring threads read neighbouring weights, sixteen of a column in
-// flight); the slices' sums are added in slice order.
-template <int G, int NT>
-__device__ __forceinline__ void dense_rows(const float* s_in, int Fin, const float* W, const float* bias, int Fout,
-                                           int nb, bool relu, float* s_part, float* s_out, float* g_out) {
-  const int fr = min((Fout + 31) & ~31, NT), nz = NT / fr, len = (Fin + nz - 1) / nz;
-  const int t = threadIdx.x, z = t / fr, j = t - z * fr;
-  const float b0 = bias[min(t / G, Fout - 1)];             // (on its way under the sums)
-  float acc[G];
+// each with a thread per column (neighbouring threads read neighbouring weights, NW of a column in
+// flight); the slices' sums are added in slice order.  Weights do not depend on the rows, so a thread's first NW are
+// asked for (load) stages before they are used (run).
+template <int G, int NT, int NW>
+struct DenseRows {
+  const float *W, *bias;
+  int Fout, fr, nz, z, j, i, i1, last;
+  uint32_t col;
+  float b0, wv[NW];
+  __device__ __forceinline__ void load(const float* W_, const float* bias_, int Fin_, int Fout_) {
+    W = W_; bias = bias_; Fout = Fout_;
+    fr = min((Fout + 31) & ~31, NT); nz = NT / fr;
+    const int len = (Fin_ + nz - 1) / nz, t = threadIdx.x;
+    z = t / fr; j = t - z * fr;
+    i = min(z * len, Fin_); i1 = z < nz && j < Fout ? min(Fin_, i + len) : i;
+    b0 = bias[min(t / G, Fout - 1)];
+    last = max(0, i1 - 1); col = (uint32_t)min(j, Fout - 1);
+    request();
+  }
+  __device__ __forceinline__ void request() {              // (without a branch: past the slice its last row again, past the layer the last column)
 #pragma unroll
-  for (int q = 0; q < G; ++q) acc[q] = 0.f;
-  if (z < nz && j < Fout) {
-    int i = z * len;
-    const int i1 = min(Fin, i + len);
-    for (; i < i1; i += 16) {
-      float wv[16];
+    for (int e = 0; e < NW; ++e) wv[e] = W[(uint32_t)(min(i + e, last) * Fout) + col];
+  }
+  __device__ __forceinline__ void run(const float* s_in, int nb, bool relu, float* s_part, float* s_out, float* g_out) {
+    const int t = threadIdx.x;
+    float acc[G];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) wv[e] = W[(size_t)min(i + e, i1 - 1) * Fout + j];
+    for (int q = 0; q < G; ++q) acc[q] = 0.f;
+    while (i < i1) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e)
+      for (int e = 0; e < NW; ++e)
         if (i + e < i1) {
 #pragma unroll
           for (int q = 0; q < G; ++q) acc[q] = fmaf(s_in[(i + e) * G + q], wv[e], acc[q]);
         }
+      i += NW;
+      if (i < i1) request();
     }
-  }
-  if (z < nz) {
+    if (z < nz) {
 #pragma unroll
-    for (int q = 0; q < G; ++q) s_part[(z * fr + j) * G + q] = acc[q];
+      for (int q = 0; q < G; ++q) s_part[(z * fr + j) * G + q] = acc[q];
+    }
+    __syncthreads();
+    for (int o = t; o < Fout * G; o += NT) {
+      const int jo = o / G, q = o - jo * G;
+      float v = o == t ? b0 : bias[jo];
+      for (int zz = 0; zz < nz; ++zz) v += s_part[(zz * fr + jo) * G + q];
+      if (relu) v = fmaxf(v, 0.f);
+      s_out[o] = v;
+      if (g_out && q < nb) g_out[(size_t)q * Fout + jo] = v;
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  for (int o = t; o < Fout * G; o += NT) {
-    const int jo = o / G, q = o - jo * G;
-    float v = o == t ? b0 : bias[jo];
-    for (int zz = 0; zz < nz; ++zz) v += s_part[(zz * fr + jo) * G + q];
-    if (relu) v = fmaxf(v, 0.f);
-    s_out[o] = v;
-    if (g_out && q < nb) g_out[(size_t)q * Fout + jo] = v;
-  }
-  __syncthreads();
-}
+};
 
 // dIn[i][b] = gate(b, i) ? sum_j dOut[j][b] W[i][j] : 0: sixteen neighbouring lanes take input feature i and
-// read its row of weights in pieces of 64 bytes.
-template <int G, int NT, typename Gate>
-__device__ __forceinline__ void dense_rows_back(const float* s_dout, int Fout, const float* W, int Fin, int nb,
-                                                Gate gate, float* s_din, float* g_din) {
-  const int l = threadIdx.x & 15;
-  constexpr int kStep = NT / 16;
-  for (int i0 = threadIdx.x >> 4; i0 < Fin; i0 += 2 * kStep) {        // features i0 and i0 + kStep together
-    float acc[2][G];
+// read its row of weights in pieces of 64 bytes, NF features (NT / 16 apart) together; the first pieces ahead as above.
+template <int G, int NT, int NF>
+struct DenseRowsBack {
+  static constexpr int kStep = NT / 16;
+  const float* W;
+  int Fin, Fout;
+  float wv[NF][8];
+  __device__ __forceinline__ void load(const float* W_, int Fout_, int Fin_) {
+    W = W_; Fout = Fout_; Fin = Fin_;
+    request(threadIdx.x >> 4, threadIdx.x & 15);
+  }
+  __device__ __forceinline__ void request(int i0, int j) {
 #pragma unroll
-    for (int q = 0; q < G; ++q) acc[0][q] = acc[1][q] = 0.f;
-    const float* wr[2] = {W + (size_t)i0 * Fout, W + (size_t)min(i0 + kStep, Fin - 1) * Fout};
-    for (int j = l; j < Fout; j += 128) {
-      float wv[2][8];
+    for (int h = 0; h < NF; ++h)
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int e = 0; e < 8; ++e) wv[h][e] = W[(uint32_t)(min(i0 + h * kStep, Fin - 1) * Fout + min(j + 16 * e, Fout - 1))];
+  }
+  template <typename Gate>
+  __device__ __forceinline__ void run(const float* s_dout, int nb, Gate gate, float* s_din, float* g_din) {
+    const int l = threadIdx.x & 15, first = threadIdx.x >> 4;
+    for (int i0 = first; i0 < Fin; i0 += NF * kStep) {
+      float acc[NF][G];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) wv[h][e] = wr[h][min(j + 16 * e, Fout - 1)];
+      for (int h = 0; h < NF; ++h)
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (j + 16 * e < Fout) {
+        for (int q = 0; q < G; ++q) acc[h][q] = 0.f;
+      for (int j = l; j < Fout; j += 128) {
+        if (i0 != first || j != l) request(i0, j);
 #pragma unroll
-          for (int q = 0; q < G; ++q) {
-            const float dz = s_dout[(j + 16 * e) * G + q];
-            acc[0][q] = fmaf(dz, wv[0][e], acc[0][q]);
-            acc[1][q] = fmaf(dz, wv[1][e], acc[1][q]);
+        for (int e = 0; e < 8; ++e)
+          if (j + 16 * e < Fout) {
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+              const float dz = s_dout[(j + 16 * e) * G + q];
+#pragma unroll
+              for (int h = 0; h < NF; ++h) acc[h][q] = fmaf(dz, wv[h][e], acc[h][q]);
+            }
           }
-        }
-    }
+      }
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int i = i0 + h * kStep;
+      for (int h = 0; h < NF; ++h) {
+        const int i = i0 + h * kStep;
 #pragma unroll
-      for (int q = 0; q < G; ++q) {
+        for (int q = 0; q < G; ++q) {
 #pragma unroll
-        for (int o = 8; o > 0; o >>= 1) acc[h][q] += __shfl_xor(acc[h][q], o, 16);
-        if (l == q && i < Fin) {
-          const float v = q < nb && gate(q, i) ? acc[h][q] : 0.f;
-          if (s_din) s_din[i * G + q] = v;
-          if (q < nb) g_din[(size_t)q * Fin + i] = v;
+          for (int o = 8; o > 0; o >>= 1) acc[h][q] += __shfl_xor(acc[h][q], o, 16);
+          if (l == q && i < Fin) {
+            const float v = q < nb && gate(q, i) ? acc[h][q] : 0.f;
+            if (s_din) s_din[i * G + q] = v;
+            if (q < nb) g_din[(size_t)q * Fin + i] = v;
+          }
         }
       }
     }
+    __syncthreads();
   }
-  __syncthreads();
-}
+};
 
 // The same where a launch has workgroups enough to fill the chip several times over: a thread per column, all
 // input features in order, and on the way back a thread per input feature - no exchange between threads, which is what
@@ -411,7 +436,8 @@ __device__ __forceinline__ void dense_cols_back(const float* s_dout, int Fout, c
 // Every stage is a chain of weight fetches from the L2: what bounds it is how many are in flight, so a
 // round of few rows takes small groups (a workgroup per CU) and slices within them.  5 uploads of 32 rows, 400-120-84-10:
 // 59 us with 20 workgroups of 256 threads (8 rows each, a thread per column); of 1024 threads, 80 for 2 rows
-// each 27 us, 160 for a row each 23.
+// each 27 us, 160 for a row each 23, and 20.4 since each stage's first weights are asked for stages ahead (784-10-20-200-100-20,
+// four local steps, a round 337 -> 319).  More of them (32 and 4 features instead of 16 and 2) spill: 25.6.
 template <int G, int NT, bool COLS>
 __global__ __launch_bounds__(NT) void cnn_dense_kernel(CnnDev d, RoundDesc rd, float* eval_loss, float* eval_hit) {
   extern __shared__ __attribute__((aligned(16))) float sm[];
@@ -431,26 +457,36 @@ __global__ __launch_bounds__(NT) void cnn_dense_kernel(CnnDev d, RoundDesc rd, f
   float* sD1 = sD2 + G * p.F2;          // dZ of the first dense layer
   const float* w = slot_of(d, rd, a);
   const float* p2 = wsp<const float>(d, p.off_p2) + (size_t)r0 * p.F0;
+  constexpr int kAhead = 16, kFeatures = 2;
+  DenseRows<G, NT, kAhead> f1;
+  DenseRows<G, NT, 16> f2;
+  DenseRows<G, NT, 4> f3;
+  if constexpr (!COLS) {
+    f1.load(w + p.w_off[2], w + p.b_off[2], p.F0, p.F1);
+    f2.load(w + p.w_off[3], w + p.b_off[3], p.F1, p.F2);
+    f3.load(w + p.w_off[4], w + p.b_off[4], p.F2, p.C);
+  }
   for (int i = t; i < G * p.F0; i += NT) {
     const int q = i / p.F0, f = i - q * p.F0;
     sH0[f * G + q] = q < nb ? p2[i] : 0.f;
   }
   __syncthreads();
   const bool train = eval_loss == nullptr;
-  auto fwd = [&](const float* s_in, int Fin, const float* W, const float* bias, int Fout, bool relu, float* s_out, float* g_out) {
-    if constexpr (COLS) dense_cols<G, NT>(s_in, Fin, W, bias, Fout, nb, relu, s_out, g_out);
-    else dense_rows<G, NT>(s_in, Fin, W, bias, Fout, nb, relu, sPart, s_out, g_out);
-  };
-  auto back = [&](const float* s_dout, int Fout, const float* W, int Fin, auto gate, float* s_din, float* g_din) {
-    if constexpr (COLS) dense_cols_back<G, NT>(s_dout, Fout, W, Fin, nb, gate, s_din, g_din);
-    else dense_rows_back<G, NT>(s_dout, Fout, W, Fin, nb, gate, s_din, g_din);
-  };
   const int y = t < nb ? wsp<const int32_t>(d, p.off_label)[r0 + t] : 0;
-  fwd(sH0, p.F0, w + p.w_off[2], w + p.b_off[2], p.F1, true, sH1,
-                train ? wsp<float>(d, p.off_h1) + (size_t)r0 * p.F1 : nullptr);
-  fwd(sH1, p.F1, w + p.w_off[3], w + p.b_off[3], p.F2, true, sH2,
-                train ? wsp<float>(d, p.off_h2) + (size_t)r0 * p.F2 : nullptr);
-  fwd(sH2, p.F2, w + p.w_off[4], w + p.b_off[4], p.C, false, sZ, nullptr);
+  float* const h1 = train ? wsp<float>(d, p.off_h1) + (size_t)r0 * p.F1 : nullptr;
+  float* const h2 = train ? wsp<float>(d, p.off_h2) + (size_t)r0 * p.F2 : nullptr;
+  DenseRowsBack<G, NT, 2> b3, b2;
+  DenseRowsBack<G, NT, kFeatures> b1;
+  if constexpr (COLS) {
+    dense_cols<G, NT>(sH0, p.F0, w + p.w_off[2], w + p.b_off[2], p.F1, nb, true, sH1, h1);
+    dense_cols<G, NT>(sH1, p.F1, w + p.w_off[3], w + p.b_off[3], p.F2, nb, true, sH2, h2);
+    dense_cols<G, NT>(sH2, p.F2, w + p.w_off[4], w + p.b_off[4], p.C, nb, false, sZ, nullptr);
+  } else {
+    f1.run(sH0, nb, true, sPart, sH1, h1);
+    if (train) { b3.load(w + p.w_off[4], p.C, p.F2); b2.load(w + p.w_off[3], p.F2, p.F1); }
+    f2.run(sH1, nb, true, sPart, sH2, h2);
+    f3.run(sH2, nb, false, sPart, sZ, nullptr);
+  }
   if (t < nb) {
     // softmax cross-entropy of row t; dZ = c (p - onehot) with the upload's coefficient of Eq. 3
     float* z = sZ + t;
@@ -476,13 +512,23 @@ __global__ __launch_bounds__(NT) void cnn_dense_kernel(CnnDev d, RoundDesc rd, f
   }
   if (!train) return;
   __syncthreads();
-  back(sZ, p.C, w + p.w_off[4], p.F2, [&](int b, int i) { return sH2[i * G + b] > 0.f; }, sD2,
-                     wsp<float>(d, p.off_dz2) + (size_t)r0 * p.F2);
-  back(sD2, p.F2, w + p.w_off[3], p.F1, [&](int b, int i) { return sH1[i * G + b] > 0.f; }, sD1,
-                     wsp<float>(d, p.off_dz1) + (size_t)r0 * p.F1);
   // (a window is dead exactly where its pooled value is zero)
-  back(sD1, p.F1, w + p.w_off[2], p.F0, [&](int b, int i) { return sH0[i * G + b] > 0.f; }, nullptr,
-                     wsp<float>(d, p.off_dp2) + (size_t)r0 * p.F0);
+  auto gate2 = [&](int b, int i) { return sH2[i * G + b] > 0.f; };
+  auto gate1 = [&](int b, int i) { return sH1[i * G + b] > 0.f; };
+  auto gate0 = [&](int b, int i) { return sH0[i * G + b] > 0.f; };
+  float* const dz2 = wsp<float>(d, p.off_dz2) + (size_t)r0 * p.F2;
+  float* const dz1 = wsp<float>(d, p.off_dz1) + (size_t)r0 * p.F1;
+  float* const dp2 = wsp<float>(d, p.off_dp2) + (size_t)r0 * p.F0;
+  if constexpr (COLS) {
+    dense_cols_back<G, NT>(sZ, p.C, w + p.w_off[4], p.F2, nb, gate2, sD2, dz2);
+    dense_cols_back<G, NT>(sD2, p.F2, w + p.w_off[3], p.F1, nb, gate1, sD1, dz1);
+    dense_cols_back<G, NT>(sD1, p.F1, w + p.w_off[2], p.F0, nb, gate0, nullptr, dp2);
+  } else {
+    b1.load(w + p.w_off[2], p.F1, p.F0);
+    b3.run(sZ, nb, gate2, sD2, dz2);
+    b2.run(sD2, nb, gate1, sD1, dz1);
+    b1.run(sD1, nb, gate0, nullptr, dp2);
+  }
 }
 
 // A kernel argument's value, opaque: a choice among several members of an argument struct otherwise becomes an
