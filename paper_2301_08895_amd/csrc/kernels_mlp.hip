@@ -309,14 +309,10 @@ __device__ __forceinline__ void bias_block(const BiasCore& a, int blk, FirstRow 
   }
 }
 
-// Local SGD (Eq. 2): the weight gradient of one step of upload z, W_l of its private model and the two
-// bf16 copies.  The contraction is not split (range z = the rows of upload z), so the accumulators hold
-// the whole gradient and the epilogue takes the step itself: no partial is written and read back, and
-// the update needs no launch (the bias update and the losses ride in this and in the input gradient's launch).
-// Bound by the model's own bytes: 10 (12 with a row-major copy) per weight and upload; with the partial written and
-// read back, 18 (20).
-// 3072-512-10, 8 uploads of 10 steps x 128 rows: update kernels 56 us, losses and biases 9 us of a step gone,
-// first layer's product 15.5 -> 28.4 us; a round 1229 -> 711 us.
+// Local SGD (Eq. 2) with more rows an upload than mlp_step_kernel takes (local_step_tiles): the weight gradient of one step of
+// upload z, W_l of its private model and the two bf16 copies.  The contraction is not split (range z = the rows of upload z), so
+// the accumulators hold the whole gradient and the epilogue takes the step itself: no partial is written and read back, and the
+// update needs no launch (the bias update and the losses ride in this and in the input gradient's launch).
 // `own`: the model is private copy z of `cur`, else ring slot rd.w[z].slot.
 struct LocalUpdate {
   int own;
@@ -449,16 +445,11 @@ __device__ __forceinline__ void piggy_update(const GemmArgs& g, int b, uint16_t*
   }
 }
 
-__device__ __forceinline__ void lds_dma16(const uint16_t* gsrc, uint16_t* lds_block) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)gsrc,
-                                   (__attribute__((address_space(3))) void*)lds_block, 16, 0, 0);
-}
-
-// The same request written out by hand.  The compiler makes every LDS read that it cannot tell
-// apart from a pending global->LDS request wait for all of them, and it cannot for the
+// A global -> LDS request, written out by hand: the compiler makes every LDS read that it cannot tell
+// apart from a pending request of its own wait for all of them, and it cannot for the
 // transposing read: a k-step would then start by waiting for the tile it has just requested.
-// Requests issued this way are invisible to that bookkeeping; the loop's own vmcnt(0) and
-// barrier order them against the reads.  The LDS base travels in m0, which the register
+// Requests issued this way are invisible to that bookkeeping; the loops' own counted waits and
+// barriers order them against the reads.  The LDS base travels in m0, which the register
 // allocator hands over through the "{m0}" constraint (it knows the register is written).
 __device__ __forceinline__ void lds_dma16_raw(const uint16_t* gsrc, uint16_t* lds_block) {
   const uint32_t lds = __builtin_amdgcn_readfirstlane(

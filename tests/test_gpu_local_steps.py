@@ -159,3 +159,15 @@ def test_local_steps_of_all_layers_in_one_launch(dims, N, B, U, item):
     plan = lib.abs_mlp_round_plan(lib.make_config(p), N).split()
     assert plan.count(item) == U * (len(dims) - 1), plan
     _check(run_pair(p, 2, checkpoints=(1,)), 2e-2, 2e-3, guard=BF16_GUARD)
+
+
+@pytest.mark.parametrize("dims,N,B,item", [
+    ([72, 300, 10], 2, 2050, "wgrad_step_tile:64x64/2"),       # one row tile more than mlp_step_kernel takes: a launch per layer
+    ([256, 4096, 10], 8, 2304, "wgrad_x_step:256x256/8"),      # ... the first on the 256 x 256 kernel, from the dataset
+])
+def test_local_steps_of_many_rows(dims, N, B, item):
+    import paper_2301_08895_amd as lib
+    p = workloads.scaled_preset(3, M=2 * N * B, dims=dims, n_classes=dims[-1], N=N, K0=N, B=B, n_slow=0, U=2, lr=1e-4)
+    plan = lib.abs_mlp_round_plan(lib.make_config(p), N).split()
+    assert item in plan and sum(i.startswith("with_biases") for i in plan) == 2, plan
+    _check(run_pair(p, 1), 2e-2, 2e-3, guard=BF16_GUARD)
