@@ -2740,7 +2740,9 @@ void launch_logits_ce(const MlpArgs& a, const RoundDesc& rd, int rows, double ar
 // Whether a round of `rows` stacked rows at U = 1 takes its steps in mlp_step_kernel, and with which tiles (0: split
 // weight gradients, partials and updates).  Unsplit, the contraction may have at most 64 k-steps (at 96 3072-512-10
 // takes 110 us a round against 97), and with tiles of 128 x 128 there is a limit to the work too, beyond which the 256 x 256
-// kernel's fewer bytes per flop win over its partials.  128 x 128 from 128 such tiles on, 64 x 64 below.
+// kernel's fewer bytes per flop win over its partials.  128 x 128 from 128 such tiles on, 64 x 64 below; where even these
+// are few, the split ones win earlier (us of a round, split / 64 x 64: 512-128-10, 18 tiles, 3072 rows 36.8 / 36.8, 4096: 37.4 / 40.7;
+// 880-73-100, 32 tiles, 3072: 44.9 / 44.6, 4096: 45.7 / 47.5; 1024-128-100, 36 tiles, 4096: 55.4 / 47.8).
 // us of a round with split weight gradients / 64 x 64 / 128 x 128 tiles, by rows:
 //   3072-512-10   1024: 53.5 / 46.3 / 48.4   4096: 80 / 75 / 81       1000-520-300-26  512: 59 / 45 / 49   3072: 61 / 50 / 55
 //   512-256-10    4096: 50 / 44 / 59         8192: 53 / 59 / 89       2048-1024-10    1024: 52 / 49 / 45   4096: 90 / 93 / 87
@@ -2750,8 +2752,12 @@ void launch_logits_ce(const MlpArgs& a, const RoundDesc& rd, int rows, double ar
 int step_tiles(const MlpPlan& p, int rows) {
   const long ksteps = rows / BK;
   if (ksteps > 64) return 0;
-  long tiles = 0;
-  for (int l = 0; l < p.L; ++l) tiles += (long)(p.dp[l] / 128) * ((p.dp[l + 1] + 127) / 128);
+  long tiles = 0, small = 0;
+  for (int l = 0; l < p.L; ++l) {
+    tiles += (long)(p.dp[l] / 128) * ((p.dp[l + 1] + 127) / 128);
+    small += (long)(p.dp[l] / 64) * (p.dp[l + 1] / 64);
+  }
+  if (small <= 32 && ksteps > 48) return 0;
   if (tiles < 128) return 64;
   return tiles * ksteps <= 60000 ? 128 : 0;
 }

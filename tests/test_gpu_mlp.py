@@ -164,7 +164,8 @@ def test_output_layer_of_few_rows(d1, C, N, B):
 @pytest.mark.parametrize("dims,N,B,item", [
     ([40, 24, 3], 1, 1, "steps:64x64/1"),                      # two k-steps: shorter than the ring
     ([3072, 512, 10], 32, 100, "steps:64x64/1"),               # 64 k-steps, the most
-    ([512, 64, 10], 33, 128, "wgrad_tile:64x64/11"),           # two more: split weight gradients, partials, an update
+    ([512, 128, 10], 24, 128, "steps:64x64/1"),                # 48, the most for as few as 18 tiles
+    ([512, 64, 10], 33, 128, "wgrad_tile:64x64/11"),           # 66: split weight gradients, partials, an update
     ([1000, 2040, 10], 2, 60, "steps:128x128/1"),              # 144 tiles of 128 x 128, ragged in both directions
     ([2048, 2040, 26], 3, 128, "steps2:128x128/1"),            # 272: two workgroups per CU
     ([3000, 1400, 10], 24, 100, "steps_x:128x128/1"),          # the dataset in place of its transposed copy, columns beyond d_0
