@@ -50,9 +50,7 @@ enum {
   ABS_E_WORKSPACE = -2,  /* workspace smaller than abs_workspace_size()                 */
   ABS_E_HIP = -3,        /* a HIP runtime call failed                                   */
   ABS_E_VERSION = -4,    /* requested model version is no longer (or not yet) in the ring */
-  ABS_E_NONFINITE = -5,  /* a worker loss came back non-finite (the round is not counted; with a fixed
-                            or replayed wait count the one behind it may have been started, and the
-                            two oldest versions of the ring are gone)                       */
+  ABS_E_NONFINITE = -5,  /* a worker loss came back non-finite (the round is not counted)    */
   ABS_E_REPLAY = -6      /* k_mode 2: the replay array has no entry for this round      */
 };
 
@@ -165,13 +163,17 @@ int abs_create(const abs_config* cfg, const void* d_X, const void* d_y, const fl
  * workers' U local steps of Eq. 2 and the update of Eq. 3).  Returns when the
  * host has every round's trace record, i.e. after the last round's losses arrived;
  * the tail of that round's device work (backward pass, update, snapshot) may still be
- * running on the stream.  abs_get_model and abs_destroy synchronise the stream. */
+ * running on the stream.  abs_get_model and abs_destroy synchronise the stream.
+ * After an error the rounds before the failing one are counted; the next call goes on with that one, with
+ * the result it would have had. */
 int abs_round(abs_ctx* ctx, int32_t n_rounds);
 
 /* Copy global model w^version (fp32, boundary layout, n_floats = parameter count)
  * to host memory; version -1 = the latest.  Synchronises the stream.  (Plumbing: the
  * paper's server simply holds w^t; the versions still readable are those of the ring,
- * t - tau_cap - 2 .. t, ABS_E_VERSION otherwise.) */
+ * t - tau_cap - 2 .. t, ABS_E_VERSION otherwise.  A round that failed, and with a fixed or replayed
+ * wait count the one started behind it, is not counted but has taken its place in the ring: until as
+ * many rounds have been counted the oldest version, or the two oldest, is refused.) */
 int abs_get_model(abs_ctx* ctx, int64_t version, float* h_out, size_t n_floats);
 
 /*

@@ -192,7 +192,12 @@ struct abs_ctx : public LaunchHook {
   CnnArgs cargs{};
   LossMailbox* h_box = nullptr;   // pinned, device-visible [2]: abs_round posts round t's losses to the one of its parity
   LossMailbox* d_box = nullptr;   // the device's address of h_box
-  int lost = 0;                   // 1: the last call failed with the next round already started, which overwrites one more version
+  // The newest version that a launch may have written, rounds that failed included: the ring holds version v while v > written - R.
+  int64_t written = 0;
+  // Rounds before this one are on the stream: a call of abs_round that fails leaves up to two of them behind, uncounted.  They
+  // have their models (one of which the second may have overwritten since), so they are not launched again: the next call takes
+  // their losses, and what they wrote stands.
+  int64_t enqueued = 0;
   int device = -1;                // the GPU the handle was created on
   void* static_scratch = nullptr; // that GPU's copy of the evaluation scratch (abs_evaluate_static)
   std::string err;
@@ -202,6 +207,9 @@ struct abs_ctx : public LaunchHook {
   std::vector<int> ev_kind;
   size_t ev_used = 0;
   bool timing = false;                 // this round's launches are bracketed (profile: every round or every n-th)
+
+  bool pending() const { return enqueued > sched->round(); }
+  bool holds(int64_t version) const { return version >= 0 && version <= sched->round() && version > written - R; }
 
   void begin(int kind, double flops, double bytes) override {
     stats[kind].launches += 1;
@@ -455,7 +463,7 @@ struct RoundAhead {
   Scheduler::Saved saved;
 };
 // Waits for them and gives them to the scheduler; on failure the scheduler is back where it was when the round had been
-// launched, as if nothing had been done after it.
+// selected (abs_ctx::enqueued, written: what that leaves on the device).
 int collect(abs_ctx* ctx, RoundAhead& r) {
   r.live = false;
   const LossMailbox* const box = ctx->h_box + (r.t & 1);
@@ -465,9 +473,7 @@ int collect(abs_ctx* ctx, RoundAhead& r) {
     for (int a = 0; a < r.K; ++a) losses[a] = box->loss(r.pos_of[a]);
     rc = ctx->sched->set_losses(r.saved, r.K, losses, ctx->err);
   }
-  if (rc != ABS_OK) {
-    ctx->sched->restore(r.saved);
-  }
+  if (rc != ABS_OK) ctx->sched->restore(r.saved);
   return rc;
 }
 }  // namespace
@@ -506,35 +512,38 @@ int abs_round(abs_ctx* ctx, int32_t n_rounds) {
     fill_round_desc(ctx, sel, t, rd, pos_of);
     ctx->timing = cfg.profile == 1 || (cfg.profile > 1 && t % cfg.profile == 0);
     LossMailbox* const d_box = ctx->d_box + (t & 1);
-    hipError_t e;
-    if (cfg.model == ABS_MODEL_MLP) {
-      ctx->margs.mailbox = d_box;
-      e = launch_mlp_round(ctx->margs, rd, ctx->stream, ctx);
-    } else if (cfg.model == ABS_MODEL_CNN) {
-      ctx->cargs.mailbox = d_box;
-      e = launch_cnn_round(ctx->cargs, rd, ctx->stream, ctx);
-    } else {
-      RegressionArgs ra;
-      fill_regression_args(ctx, ra, d_box);
-      if (cfg.U > 1)
-        e = launch_regression_local_round(ra, rd, cfg.model == ABS_MODEL_SOFTMAX, ctx->stream, ctx);
-      else
-        e = cfg.model == ABS_MODEL_LINEAR ? launch_linreg_round(ra, rd, ctx->stream, ctx)
-                                          : launch_softmax_round(ra, rd, ctx->stream, ctx);
-    }
-    if (e != hipSuccess) {
-      if (prev.live) {
-        const int rc0 = collect(ctx, prev);
-        if (rc0 != ABS_OK) return rc0;
+    if (t >= ctx->enqueued) {
+      ctx->written = std::max(ctx->written, t + 1);
+      hipError_t e;
+      if (cfg.model == ABS_MODEL_MLP) {
+        ctx->margs.mailbox = d_box;
+        e = launch_mlp_round(ctx->margs, rd, ctx->stream, ctx);
+      } else if (cfg.model == ABS_MODEL_CNN) {
+        ctx->cargs.mailbox = d_box;
+        e = launch_cnn_round(ctx->cargs, rd, ctx->stream, ctx);
+      } else {
+        RegressionArgs ra;
+        fill_regression_args(ctx, ra, d_box);
+        if (cfg.U > 1)
+          e = launch_regression_local_round(ra, rd, cfg.model == ABS_MODEL_SOFTMAX, ctx->stream, ctx);
+        else
+          e = cfg.model == ABS_MODEL_LINEAR ? launch_linreg_round(ra, rd, ctx->stream, ctx)
+                                            : launch_softmax_round(ra, rd, ctx->stream, ctx);
       }
-      ctx->err = std::string("kernel launch: ") + hipGetErrorString(e);
-      return ABS_E_HIP;
+      if (e != hipSuccess) {
+        if (prev.live) {
+          const int rc0 = collect(ctx, prev);
+          if (rc0 != ABS_OK) return rc0;
+        }
+        ctx->err = std::string("kernel launch: ") + hipGetErrorString(e);
+        return ABS_E_HIP;
+      }
     }
-    ctx->lost = 0;
     if (ahead) {
+      ctx->enqueued = std::max(ctx->enqueued, t + 1);
       if (prev.live) {
         rc = collect(ctx, prev);
-        if (rc != ABS_OK) { ctx->lost = 1; return rc; }
+        if (rc != ABS_OK) return rc;
       }
       prev.live = true; prev.t = t; prev.K = K; prev.stamp = rd.stamp;
       std::copy(pos_of, pos_of + K, prev.pos_of);
@@ -560,12 +569,7 @@ int abs_round(abs_ctx* ctx, int32_t n_rounds) {
     rc = ctx->sched->complete(sel, losses, true, ctx->err);
     if (rc != ABS_OK) return rc;
   }
-  if (prev.live) {
-    const int rc = collect(ctx, prev);
-    if (rc != ABS_OK) ctx->lost = 0;     // nothing was started after it
-    return rc;
-  }
-  return ABS_OK;
+  return prev.live ? collect(ctx, prev) : ABS_OK;
 }
 
 // ---- batched simulations: S handles of one shape advance together, one set of launches per round
@@ -750,6 +754,10 @@ struct BatchRoundState {
     abort.store(true);
     return true;
   }
+  void wrote(int i) {                          // the round of simulation i that has been launched (its stamp is the version it writes)
+    int64_t& w = b->ctx[(size_t)i]->written;
+    w = std::max(w, (int64_t)stamp[(size_t)i]);
+  }
   void prepare(int k, int T) {                 // select the uploads, write the descriptors
     int km = 0;
     for (int i = lo + k; i < hi; i += T) {
@@ -780,6 +788,7 @@ struct BatchRoundState {
       }
       std::atomic_thread_fence(std::memory_order_acquire);
       abs_ctx* ctx = b->ctx[(size_t)i];
+      wrote(i);
       float losses[ABS_MAX_WORKERS];
       for (int a = 0; a < K; ++a) losses[a] = box->loss(a);
       const int r = ctx->sched->complete(sel[(size_t)i], losses, true, ctx->err);
@@ -843,16 +852,15 @@ static int batch_round_mlp(abs_batch* b, int32_t n_rounds) {
   return ABS_OK;
 }
 
-int abs_batch_round(abs_batch* b, int32_t n_rounds) {
-  if (!b || n_rounds < 0) return ABS_E_ARG;
-  const int S = (int)b->ctx.size();
+// Regression models: n_rounds rounds of simulations [first, last) in one set of launches each.
+static int batch_round_together(abs_batch* b, int first, int last, int32_t n_rounds) {
+  const int S = last - first;
   const abs_config& c0 = b->ctx[0]->cfg;
-  if (chain_model(c0.model)) return batch_round_mlp(b, n_rounds);
   BatchRoundState st;
   st.b = b;
   const size_t max_threads = 1 + (size_t)(b->pool ? b->pool->size() : 0);
-  st.sel.resize((size_t)S);
-  st.stamp.resize((size_t)S);
+  st.sel.resize(b->ctx.size());
+  st.stamp.resize(b->ctx.size());
   st.kmax.assign(max_threads, 0);
   st.rc.assign(max_threads, ABS_OK);
   st.bad_sim.assign(max_threads, -1);
@@ -872,7 +880,7 @@ int abs_batch_round(abs_batch* b, int32_t n_rounds) {
   int lo[kBatchGroups], hi[kBatchGroups];
   hipStream_t gstream[kBatchGroups];
   for (int g = 0; g < G; ++g) {
-    lo[g] = (int)((long)S * g / G); hi[g] = (int)((long)S * (g + 1) / G);
+    lo[g] = first + (int)((long)S * g / G); hi[g] = first + (int)((long)S * (g + 1) / G);
     gstream[g] = g == 0 ? b->stream : b->own[g - 1];
   }
   if (G > 1 && n_rounds > 0) {
@@ -883,7 +891,9 @@ int abs_batch_round(abs_batch* b, int32_t n_rounds) {
   bool inflight[kBatchGroups] = {};
   auto finish = [&](Team& team, int g) {
     inflight[g] = false;
-    return st.run(team, 1, lo[g], hi[g]);
+    const int r = st.run(team, 1, lo[g], hi[g]);
+    if (r != ABS_OK) for (int i = lo[g]; i < hi[g]; ++i) st.wrote(i);      // (a wait that was given up)
+    return r;
   };
   auto start = [&](Team& team, int g) {
     int r = st.run(team, 0, lo[g], hi[g]);
@@ -898,7 +908,11 @@ int abs_batch_round(abs_batch* b, int32_t n_rounds) {
     else if (e == hipSuccess)
       e = launch_regression_round_batch(b->d_args + lo[g], b->d_rds[st.buf] + off, b->rd_stride, (int)n, softmax,
                                         c0.dims[0], c0.dims[1], c0.B, Kmax, b->d_slots != nullptr, gstream[g]);
-    if (e != hipSuccess) { b->err = std::string("launch: ") + hipGetErrorString(e); return (int)ABS_E_HIP; }
+    if (e != hipSuccess) {
+      for (int i = lo[g]; i < hi[g]; ++i) st.wrote(i);
+      b->err = std::string("launch: ") + hipGetErrorString(e);
+      return (int)ABS_E_HIP;
+    }
     inflight[g] = true;
     return (int)ABS_OK;
   };
@@ -934,6 +948,31 @@ int abs_batch_round(abs_batch* b, int32_t n_rounds) {
   return rc;
 }
 
+int abs_batch_round(abs_batch* b, int32_t n_rounds) {
+  if (!b || n_rounds < 0) return ABS_E_ARG;
+  const int S = (int)b->ctx.size();
+  if (chain_model(b->ctx[0]->cfg.model)) return batch_round_mlp(b, n_rounds);
+  auto pending = [](const abs_ctx* c) { return c->pending(); };
+  if (std::none_of(b->ctx.begin(), b->ctx.end(), pending)) return batch_round_together(b, 0, S, n_rounds);
+  // Rounds that a failed abs_round left on the stream are finished by abs_round, round by round beside the others.
+  for (int32_t it = 0; it < n_rounds; ++it) {
+    for (int first = 0, last; first < S; first = last) {
+      abs_ctx* const c = b->ctx[(size_t)first];
+      int rc;
+      if (pending(c)) {
+        last = first + 1;
+        rc = abs_round(c, 1);
+        if (rc != ABS_OK) b->err = "simulation " + std::to_string(first) + ": " + c->err;
+      } else {
+        last = (int)(std::find_if(b->ctx.begin() + first, b->ctx.end(), pending) - b->ctx.begin());
+        rc = batch_round_together(b, first, last, 1);
+      }
+      if (rc != ABS_OK) return rc;
+    }
+  }
+  return ABS_OK;
+}
+
 const char* abs_batch_last_error(const abs_batch* b) { return b ? b->err.c_str() : g_batch_error.c_str(); }
 
 int abs_get_model(abs_ctx* ctx, int64_t version, float* h_out, size_t n_floats) {
@@ -942,9 +981,7 @@ int abs_get_model(abs_ctx* ctx, int64_t version, float* h_out, size_t n_floats) 
   if (n_floats != ctx->P) { ctx->err = "n_floats must equal the parameter count"; return ABS_E_ARG; }
   const int64_t t = ctx->sched->round();
   if (version < 0) version = t;
-  if (version > t || version < t - (ctx->R - 1) + 2 * ctx->lost || version < 0) {
-    ctx->err = "model version not in the ring"; return ABS_E_VERSION;
-  }
+  if (!ctx->holds(version)) { ctx->err = "model version not in the ring"; return ABS_E_VERSION; }
   const char* src = ctx->ws + ctx->off_ring + (size_t)(version % ctx->R) * ctx->slot_stride * sizeof(float);
   ABS_HIP(ctx, hipMemcpyAsync(h_out, src, n_floats * sizeof(float), hipMemcpyDeviceToHost, ctx->stream));
   ABS_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -960,9 +997,7 @@ static int enqueue_evaluation(abs_ctx* ctx, int64_t version, const void* d_X, co
   if (n_rows < 1 || n_rows > 0xFFFFFFFFll) { ctx->err = "n_rows must be in [1, 2^32)"; return ABS_E_ARG; }
   const int64_t t = ctx->sched->round();
   if (version < 0) version = t;
-  if (version > t || version < t - (ctx->R - 1) + 2 * ctx->lost || version < 0) {
-    ctx->err = "model version not in the ring"; return ABS_E_VERSION;
-  }
+  if (!ctx->holds(version)) { ctx->err = "model version not in the ring"; return ABS_E_VERSION; }
   const abs_config& cfg = ctx->cfg;
   const uint32_t slot = (uint32_t)(version % ctx->R);
   const bool mlp = cfg.model == ABS_MODEL_MLP, cnn = cfg.model == ABS_MODEL_CNN;
