@@ -177,3 +177,19 @@ def test_steps_taken_in_the_weight_gradients(dims, N, B, item):
     p = workloads.scaled_preset(3, M=max(512, 2 * N * B), dims=dims, n_classes=dims[-1], N=N, K0=N, B=B, n_slow=0, lr=1e-4)
     assert item in lib.abs_mlp_round_plan(lib.make_config(p), N).split()
     _check(run_pair(p, 3, checkpoints=(1,)))
+
+
+@pytest.mark.parametrize("h,C", [(512, 10), (512, 100), (768, 200)])          # one, two and four k-steps over the classes
+def test_input_gradient_of_the_output_layer_on_large_tiles(h, C):
+    import paper_2301_08895_amd as lib
+    p = workloads.scaled_preset(3, M=64 * 64, dims=[64, h, C], n_classes=C, N=64, K0=64, B=256, n_slow=0, lr=1e-4)
+    assert "dgrad:256x256/1" in lib.abs_mlp_round_plan(lib.make_config(p), 64).split()
+    _check(run_pair(p, 2, checkpoints=(1,)))
+    d = workloads.make_inputs(p)
+    runs = []
+    for _ in range(2):
+        sim = lib.Simulation(p, d)
+        sim.round(4)
+        runs.append(sim.model().copy())
+        sim.close()
+    assert np.array_equal(runs[0], runs[1])
