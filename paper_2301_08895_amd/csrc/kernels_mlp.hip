@@ -125,9 +125,12 @@ __global__ __launch_bounds__(256) void mlp_gather_t_kernel(const uint16_t* X, in
 // 768 blocks 205 / 201, 217 / 216, 238 / 238, 1536 blocks 307 / 323, 321 / 323, 357 / 362.  With a second hidden layer
 // the copy waits longer for its reader: 1000-1024-1024-10, 512 blocks 202 / 198, but 1000-2048-2048-10, 256 blocks 277 / 280,
 // 512-1920-1920-50, 512 blocks 75 / 82 (the copy, the output layer and the first weight gradient).
-// The 32-row form of that kernel leaves a CU room for more workgroups: there 768 ride (3072-512-10, 768 blocks, a round
-// 80 / 78.6 us, with split weight gradients 79 / 74; 3072-256-10, 384 blocks each way the same).
-constexpr int kGatherRide = 512, kGatherRideFew = 768;
+// The 32-row form of that kernel leaves a CU room for a second workgroup up to 96 classes (up to 80 KB; 91 and 101 KB beyond):
+// there 768 ride (3072-512-10, 768 blocks, a round 80 / 78.6 us, with split weight gradients 79 / 74; 3072-256-10, 384 blocks
+// each way the same; six simulations side by side, 10 classes 410 / 411, 96 classes 417 / 418).  Beyond 96 classes 512 as above
+// (3072-512-100, 768 blocks, 83.3 / 84.2, six side by side 451 / 483, 576 blocks 75.1 / 72.5 and 344 / 367; 3072-1024-100, 768
+// blocks 106.8 / 106.3 and 560 / 606).
+constexpr int kGatherRide = 512, kGatherRideFew = 768, kFewPairClasses = 96;
 constexpr int kGatherPitch = 256 + 2;      // the 8 blocks of 8 rows a wavefront reads start 8 banks apart
 struct GatherT {
   int blocks;                              // row blocks x column blocks that ride; 0: none
@@ -2724,16 +2727,24 @@ unsigned mlp_forward(const MlpArgs& a, const uint16_t* Xsrc, const RoundDesc& rd
 // long.  us of a round with 32 / 128 rows: 512-256-10, 16384 rows 65 / 70, 24576: 79.7 / 80.6, 32768: 103.9 / 103.5;
 // 512-2048-30, 16384: 205 / 208, 32768: 369 / 358; 512-256-100, 4096: 59.0 / 61.5, 6144: 68.1 / 66.6, 8192: 69.6 / 68.0;
 // 512-1536-100, 8192: 115.6 / 114.3; 512-2048-100, 8192: 133 / 138, 10240: 189 / 175.
-int ce_rows(const MlpPlan& p, int rows) {
-  const bool few = p.d[p.L] <= 32 ? rows <= 24576
-                 : p.dp[p.L] <= 128 && (rows <= 4096 || (rows <= 8192 && p.dp[p.L - 1] >= 2048));
+// Beyond 96 classes a CU holds one 32-row workgroup.  A short contraction, which gives the four wavefronts little to share, then
+// stays with 128 rows where blocks of the transposed minibatch ride (`gather` of them are there) and make it more than a workgroup
+// per CU, alone / six simulations side by side: 880-73-100, 2048 rows (192 workgroups) 35.8 / 37.8 and 88.0 / 88.6, 3072 (288)
+// 42.8 / 42.1 and 110 / 105, 4096 (384) 48.3 / 47.5 and 124 / 121; 2048-256-100, 3072 (480) 48.1 / 46.6 and 171 / 164; up to a
+// workgroup per CU, 512-200-100, 4096 (256) 42.9 / 45.3 and 132 / 126; long ones, 1000-300-100, 4096 (384) 49.3 / 50.1 and 188 / 178.
+int ce_rows(const MlpPlan& p, int rows, int gather) {
+  bool few = p.d[p.L] <= 32 ? rows <= 24576
+           : p.dp[p.L] <= 128 && (rows <= 4096 || (rows <= 8192 && p.dp[p.L - 1] >= 2048));
+  if (p.d[p.L] > kFewPairClasses && p.dp[p.L - 1] <= 256 && gather <= kGatherRide && rows / kCeFewRows + gather > 256) few = false;
   return few ? kCeFewRows : kCeRows;
 }
+// ... and how many blocks of the transposed minibatch ride in its launch.
+int gather_ride(const MlpPlan& p, int block_rows) { return block_rows == kCeFewRows && p.d[p.L] <= kFewPairClasses ? kGatherRideFew : kGatherRide; }
 
 // Output layer of a training pass: logits, loss sums per 128 rows, dZ_L in both orientations and its
 // column sums, in one kernel (mlp_logits_ce_kernel).
 void launch_logits_ce(const MlpArgs& a, const RoundDesc& rd, int rows, double arows, const float* wbase,
-                      const uint16_t* sbase, bool own, int gather_blocks, hipStream_t s, LaunchHook* hook) {
+                      const uint16_t* sbase, bool own, int block_rows, int gather_blocks, hipStream_t s, LaunchHook* hook) {
   const MlpPlan& p = a.plan;
   const int L = p.L;
   LogitsCeArgs c{};
@@ -2756,7 +2767,6 @@ void launch_logits_ce(const MlpArgs& a, const RoundDesc& rd, int rows, double ar
   c.dZT = at<uint16_t>(a, p.off_dzt[L]); c.lddzt = p.ldm;
   c.rowloss = at<float>(a, p.off_rowloss);
   c.colsum = at<float>(a, p.off_colsum[L]); c.ldcs = (size_t)p.dp[L];
-  const int block_rows = ce_rows(p, rows);
   kbegin(hook, KK_MLP_LOGITS_CE, 2.0 * arows * p.d[L - 1] * p.d[L] + arows * p.d[L] * 8.0,
               arows * (p.d[L - 1] * 2.0 + p.d[L] * 4.0 + (c.gt.blocks ? p.d[0] * 4.0 : 0.0)));
   plan_note("logits_ce", block_rows, p.dp[L], 1);
@@ -2927,9 +2937,10 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
     const int stile = local ? local_step_tiles(p, K) : step_tiles(p, rows);
     const bool sdirect = !local && stile && step_direct(p, rows);
     const int gather_blocks = (stile ? sdirect : wg0_direct) ? 0 : gather_t_blocks(p, rows);
-    const bool gather_rides = gather_blocks <= (ce_rows(p, rows) == kCeFewRows ? kGatherRideFew : kGatherRide);
-    launch_logits_ce(a, rd, rows, arows, wbase, sbase, own, gather_rides ? gather_blocks : 0, s, hook);
-    const int loss_blocks = p.Bp / ce_rows(p, rows);          // row blocks of the loss sums per upload
+    const int ce_block = ce_rows(p, rows, gather_blocks);
+    const bool gather_rides = gather_blocks <= gather_ride(p, ce_block);
+    launch_logits_ce(a, rd, rows, arows, wbase, sbase, own, ce_block, gather_rides ? gather_blocks : 0, s, hook);
+    const int loss_blocks = p.Bp / ce_block;               // row blocks of the loss sums per upload
 
     // ---- input gradients back through W_{L-1} .. W_1 (none is needed for the first layer)
     // (dZ_l likewise: read row-major only by the next product down; when writer and reader both run on
@@ -3002,7 +3013,7 @@ hipError_t launch_mlp_round(const MlpArgs& a, const RoundDesc& rd, hipStream_t s
       bias.col_begin[l] = bias_cols; bias_cols += p.d[l + 1];
       bias.colsum[l] = at<float>(a, p.off_colsum[l + 1]); bias.ldcs[l] = (size_t)p.dp[l + 1];
       bias.b_off[l] = p.b_off[l];
-      bias.prow[l] = (local ? p.Bp : rows) / (l == L - 1 ? ce_rows(p, rows) : 64);
+      bias.prow[l] = (local ? p.Bp : rows) / (l == L - 1 ? ce_block : 64);
     }
     bias.col_begin[L] = bias_cols;
     bias.w_cur = local ? wbase : ring + (size_t)rd.slot_cur * p.slot_stride;

@@ -41,3 +41,22 @@ def test_tiles_of_local_steps_follow_the_number_of_uploads():
     assert _items([512, 2048, 100], 4, 4096, 2, "wgrad", U=2)[:2] == ["wgrad_step_tile:64x64/2"] * 2
     assert _items([64, 2048, 100], 64, 128, 64, "wgrad", U=2)[:2] == ["wgrad_step_tile2:128x128/64"] * 2
     assert _items([512, 2048, 100], 4, 4096, 4, "wgrad", U=2)[1] == "wgrad_step_tile:128x128/4"      # 4 x 16 x 4 workgroups
+
+
+def test_rows_of_the_output_layer_beyond_96_classes():
+    """A CU holds one 32-row workgroup there: a short contraction takes 128 rows once they and the riding transposed minibatch are
+    more than a workgroup per CU, and fewer blocks of it ride."""
+    def ce(dims, K):
+        plan = _plan(dims, 32, 128, K)
+        at = [i for i, item in enumerate(plan) if item.startswith("logits_ce:")][0]
+        return plan[at].split("x")[0], "with_gather_t:64x256/1" in plan
+    for classes, dims in ((100, [880, 73]), (128, [880, 256])):
+        assert ce(dims + [classes], 21) == ("logits_ce:32", True)        # 84 + 168 workgroups
+        assert ce(dims + [classes], 22) == ("logits_ce:128", True)       # 88 + 176
+    assert ce([880, 73, 96], 32) == ("logits_ce:32", True)
+    assert ce([880, 300, 100], 32) == ("logits_ce:32", True)
+    assert ce([512, 200, 100], 32) == ("logits_ce:32", True)             # 128 + 128
+    assert ce([3072, 512, 100], 21) == ("logits_ce:32", True)            # 504 blocks ride
+    assert ce([3072, 512, 100], 22) == ("logits_ce:32", False)           # 528
+    assert ce([3072, 256, 100], 22) == ("logits_ce:32", False)
+    assert ce([3072, 512, 96], 32) == ("logits_ce:32", True)             # 768
