@@ -1143,13 +1143,18 @@ __global__ __launch_bounds__(512) void softmax_slice_kernel(RegressionArgs a, Ro
 }
 
 // Whether a round of K uploads of one simulation runs in slices: the model in registers in the other form (the orders match),
-// at least three tiles a step (a launch costs what two and a half tiles do there), rows that a workgroup's LDS holds, and
-// few enough uploads that eight workgroups each find a place at once.  us of a round, a workgroup per upload / slices, 784 x 10:
-// B = 64, U = 10: K = 4 128 / 90, 16 130 / 96, 32 132 / 122, 64 139 / 215; K = 16: B = 32, U = 10 73 / 81, B = 48, U = 2 33.8 / 30.4,
-// B = 128, U = 4 105 / 67, B = 250, U = 8 373 / 192.
+// at least three tiles a step, rows that a workgroup's LDS holds, and few enough uploads.  A launch costs what two and a half
+// tiles do there, and more the more rows all uploads ask for at once, so the more tiles the other form walks one after the other the
+// further uploads pay: three tiles up to 1400 rows, more up to 32 uploads, where eight workgroups each still find a place at
+// once.  us of a round, a workgroup per upload / slices, 784 x 10: B = 64, U = 10: K = 4 128 / 90, 16 130 / 96, 32 132 / 122,
+// 64 139 / 215; K = 16: B = 32, U = 10 73 / 81, B = 128, U = 4 105 / 67, B = 250, U = 8 373 / 192; U = 20, K = 24, 28, 30, 32:
+// B = 33 182 / 155, 160, 163, 166, B = 40 183 / 160, 166, 170, 176, B = 48 183 / 167, 177, 183, 190 (892 x 10: 209 / 187, 204, 211, 219;
+// 128 x 10: 161 / 153, 157, 160, 162); U = 6, K = 32: B = 49 82 / 70, B = 64 83 / 76.
+constexpr int kSliceThreeTileRows = 1400;
 static int fuse_form(int d, int C, int rows);
 bool softmax_local_sliced_ok(int d, int C, int B, int U, int K) {
-  return U > 1 && K <= kSliceMaxUploads && B >= kSliceMinB && B <= kSliceMaxB && softmax_local_fused_ok(B, U) && fuse_form(d, C, B * U) == kWreg;
+  return U > 1 && K <= kSliceMaxUploads && B >= kSliceMinB && B <= kSliceMaxB && (B > 48 || B * K <= kSliceThreeTileRows) &&
+         softmax_local_fused_ok(B, U) && fuse_form(d, C, B * U) == kWreg;
 }
 size_t softmax_local_slice_bytes(int d, int C, int B, int U, int N) {
   return softmax_local_sliced_ok(d, C, B, U, 1) ? (size_t)(N < kSliceMaxUploads ? N : kSliceMaxUploads) * slice_floats(B) * 4 : 0;

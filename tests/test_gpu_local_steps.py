@@ -124,26 +124,54 @@ def test_local_sgd_equals_the_hand_worked_run():
         assert np.int32(tr[t][10]).view(np.float32) == np.float32(l)
 
 
-@pytest.mark.parametrize("d,C,N,B,U,K", [
-    (4, 2, 3, 33, 2, 3),           # the shortest minibatch, a tile of one row; one block of features, in slice 0 alone
-    (784, 10, 6, 64, 3, 4),
-    (892, 16, 5, 50, 4, 5),        # the widest model
-    (128, 3, 4, 256, 8, 2),        # the most rows: two tiles per wavefront
-    (788, 7, 33, 40, 2, 32),       # the most uploads
-    (788, 7, 33, 40, 2, 33),       # ... one more: a workgroup per upload
+def _slice_scratch(sim, B, N):
+    """The part of a softmax handle's workspace that only the sliced steps write (behind everything but the evaluation's scratch)."""
+    up = lambda n: (n + 255) // 256 * 256
+    evaluation, slices = up(256 + 2 * up(16384 * 4)), up(min(N, 32) * (256 * B + 256 + 6 * B) * 4)
+    at = sim.ws_ptr - sim.d_ws.data_ptr() + sim.ws_bytes - evaluation - slices
+    return sim.d_ws[at:at + slices]
+
+
+@pytest.mark.parametrize("d,C,N,B,U,K,sliced", [
+    (4, 2, 3, 33, 2, 3, True),           # the shortest minibatch, a tile of one row; one block of features, in slice 0 alone
+    (784, 10, 6, 64, 3, 4, True),
+    (892, 16, 5, 50, 4, 5, True),        # the widest model
+    (128, 3, 4, 256, 8, 2, True),        # the most rows: two tiles per wavefront
+    (788, 7, 33, 40, 2, 32, True),       # the most uploads
+    (788, 7, 33, 40, 2, 33, False),      # ... one more: a workgroup per upload
+    (784, 10, 30, 48, 2, 29, True),      # three tiles: 1392 rows
+    (784, 10, 30, 48, 2, 30, False),     # ... and 1440
+    (60, 3, 32, 49, 2, 32, True),        # four tiles
 ])
-def test_sliced_softmax_steps_give_the_bits_of_the_batched_kernel(d, C, N, B, U, K):
+def test_sliced_softmax_steps_give_the_bits_of_the_batched_kernel(d, C, N, B, U, K, sliced):
     """One simulation's local steps run in slices of the features, a batch's in one workgroup per upload: the same sums in the same order."""
     import paper_2301_08895_amd as lib
     p = workloads.scaled_preset(2, M=max(600, 10 * N), dims=[d, C], n_classes=C, N=N, B=B, U=U, K0=K, k_mode=1, lr=0.5 / d)
     data = workloads.make_inputs(p)
     alone = lib.Simulation(p, data)
+    scratch = _slice_scratch(alone, B, N)
+    scratch.zero_()
     alone.round(5)
+    assert bool(scratch.any()) == sliced
     other = lib.Simulation(p, data)
+    scratch = _slice_scratch(other, B, N)
+    scratch.zero_()
     batch = lib.Batch([other])
     batch.round(5)
+    assert not bool(scratch.any())
     assert np.array_equal(alone.model(), other.model()) and np.array_equal(alone.trace(), other.trace())
     batch.close(); alone.close(); other.close()
+
+
+@pytest.mark.parametrize("B", [32, 257])
+def test_minibatches_that_never_run_in_slices_have_no_scratch_for_them(B):
+    import paper_2301_08895_amd as lib
+    size = lambda B, U: lib.abs_workspace_size(lib.make_config(workloads.scaled_preset(2, M=600, N=4, B=B, U=U, K0=2)))
+    slot, up = (784 * 10 + 10 + 63) // 64 * 64, lambda n: (n + 255) // 256 * 256
+    changes = up(4 * slot * 4) + up(4 * 4)               # the uploads' changes and losses
+    assert size(B, 2) - size(B, 1) == changes
+    inside = 33 if B == 32 else 256
+    assert size(inside, 2) - size(inside, 1) == changes + up(4 * (256 * inside + 256 + 6 * inside) * 4)
 
 
 @pytest.mark.parametrize("dims,N,B,U,item", [
