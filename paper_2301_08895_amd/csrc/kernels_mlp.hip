@@ -46,7 +46,8 @@ constexpr int kMaxSplit = 16;
 // with a pitch that is a multiple of 4 KB the same 128-byte column of every row of a tile maps
 // to one L2 channel, and all workgroups walk the k dimension in step.  The pad behind a row of a weight copy is
 // also read as data: gathered rows fetch the 64 elements behind the first row where a k-step reaches beyond d_0, so
-// it must be a k-step long and stays zero in every shadow slot (mlp_prepare clears them, nothing writes there).
+// it must be a k-step long and stays zero in every shadow slot (mlp_prepare clears them; mlp_step_kernel's tiles that are wider
+// than the class width store zeros there, nothing else writes to it).
 #ifndef ABS_PITCH_PAD
 #define ABS_PITCH_PAD 64
 #endif
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(256) void mlp_gather_t_kernel(const uint16_t* X, in
 }
 
 // The same by the last workgroups of the output-layer kernel's launch: it needs nothing but the drawn rows,
-// and that launch's own workgroups (one per 128 rows) leave most CUs idle.  Blocks of 64 rows x 256 columns,
+// and that launch's own workgroups (ce_rows()) leave CUs idle.  Blocks of 64 rows x 256 columns,
 // all of a thread's loads in flight together.  The kernel's LDS lets a CU hold one workgroup (98, 131 or 147 KB for
 // up to 64, 128 or 256 classes), so beyond kGatherRide blocks (two waves) the launch of its own is the faster one.
 // Sum of a round's kernels, us, own launch / riding, by blocks and classes: 1000-520-C, 64 blocks 46 / 42 (10), 52 / 47
@@ -267,7 +268,7 @@ enum { EPI_RELU = 0, EPI_LOGITS = 1, EPI_DGRAD = 2, EPI_WGRAD = 3 };
 
 // ------------------------------------------------------------------ bias update
 // b_j <- b_j - sum over the rows of dZ_l[.][j] (Eq. 2 / Eq. 3 for the biases).  The producers of
-// dZ_l leave the column sums of every block of 64 rows (128 for the output layer); 16 threads per entry
+// dZ_l leave the column sums of every block of 64 rows (the output layer: ce_rows()); 16 threads per entry
 // add them (partial row g, g + 16, ... each, then the 16 shares in order).  A block of 256 threads
 // takes 16 consecutive entries of the concatenated bias vectors.
 struct BiasCore {
@@ -1799,6 +1800,8 @@ __device__ __forceinline__ void step_tile(const StepArgs& g, const StepLayer& ly
 #pragma unroll
     for (int i = 0; i < TMx * TNx / 8 / NT; ++i) {
       const int q = t + NT * i, ml = q / (TNx / 8), ch = (q % (TNx / 8)) * 8;
+      // (a tile may be wider than dp_out, by up to half: zeros into the rows' pad)
+      static_assert(TNx - 64 <= kPitchPad, "the pad holds what a tile has beyond the narrowest layer");
       if (m0 + ml < ly.d_in) *(uint4*)(wr + (size_t)(m0 + ml) * ly.ldwn + n0 + ch) = *(const uint4*)&sN[ml * Cfg::kPitchN + ch];
     }
   }
@@ -2054,13 +2057,13 @@ __global__ __launch_bounds__(256, 1) void mlp_logits_ce_kernel(LogitsCeArgs a, R
   }
 }
 
-// The same for rounds of few rows (ce_rows), where the kernel above leaves most CUs idle and each busy one waits
-// for its own long stream of tiles (0.9 us a k-step of 64, bound by what one CU has in flight: some 32 KB): a workgroup owns 32 rows, its four wavefronts share the CONTRACTION (pairs of
-// 32-wide sub-steps p, p + 4, ...), and operands go from memory straight into registers, the next pair's on their
-// way under this one's products.  The
-// four partial logits meet in LDS, summed in wavefront order; then a wavefront has 8 whole rows, 16 lanes to a row.
+// The same for rounds of few rows (ce_rows), where the kernel above leaves most CUs idle and each busy one waits for its own
+// long stream of tiles (0.9 us a k-step of 64, bound by what one CU has in flight: some 32 KB).  A workgroup owns 32 rows,
+// its four wavefronts share the CONTRACTION (pairs of 32-wide sub-steps p, p + 4, ...), and operands go from memory straight
+// into registers, the next pair's on their way under this one's products.  The four partial logits meet in LDS, summed in
+// wavefront order; then a wavefront has 8 whole rows, 16 lanes to a row.
 // us, 128-row / 32-row workgroups: 1024 x 512, 10 classes 9.0 / 6.7, 4096 x 1024 12.9 / 7.8, 1152 x 300, 26 classes 8.2 / 6.5,
-// 8192 x 2048, 100 classes 33 / 28.  Eight wavefronts to the contraction: 7.3 instead of 7.8 for 4096 x 1024, but
+// 8192 x 2048, 100 classes 33 / 25.  Eight wavefronts to the contraction: 7.3 instead of 7.8 for 4096 x 1024, but
 // 46 instead of 28 with 100 classes (more lines asked for than the L1 can hold until their other half is).
 constexpr int kCeFewRows = 32;
 template <int CB>                        // blocks of 16 classes that are computed: 16 CB >= C, at most 8
@@ -2726,7 +2729,7 @@ unsigned mlp_forward(const MlpArgs& a, const uint16_t* Xsrc, const RoundDesc& rd
 // per CU, beyond (a workgroup's W_L^T is the larger operand) at half a one, or at one where the contraction is
 // long.  us of a round with 32 / 128 rows: 512-256-10, 16384 rows 65 / 70, 24576: 79.7 / 80.6, 32768: 103.9 / 103.5;
 // 512-2048-30, 16384: 205 / 208, 32768: 369 / 358; 512-256-100, 4096: 59.0 / 61.5, 6144: 68.1 / 66.6, 8192: 69.6 / 68.0;
-// 512-1536-100, 8192: 115.6 / 114.3; 512-2048-100, 8192: 133 / 138, 10240: 189 / 175.
+// 512-1536-100, 8192: 115.6 / 114.3; 512-2048-100, 8192: 133 / 138, 9216: 183 / 169; 512-4096-100, 8192: 230 / 240, 9216: 297 / 276.
 // Beyond 96 classes a CU holds one 32-row workgroup.  A short contraction, which gives the four wavefronts little to share, then
 // stays with 128 rows where blocks of the transposed minibatch ride (`gather` of them are there) and make it more than a workgroup
 // per CU, alone / six simulations side by side: 880-73-100, 2048 rows (192 workgroups) 35.8 / 37.8 and 88.0 / 88.6, 3072 (288)
@@ -2741,7 +2744,7 @@ int ce_rows(const MlpPlan& p, int rows, int gather) {
 // ... and how many blocks of the transposed minibatch ride in its launch.
 int gather_ride(const MlpPlan& p, int block_rows) { return block_rows == kCeFewRows && p.d[p.L] <= kFewPairClasses ? kGatherRideFew : kGatherRide; }
 
-// Output layer of a training pass: logits, loss sums per 128 rows, dZ_L in both orientations and its
+// Output layer of a training pass: logits, loss sums per `block_rows` rows (ce_rows()), dZ_L in both orientations and its
 // column sums, in one kernel (mlp_logits_ce_kernel).
 void launch_logits_ce(const MlpArgs& a, const RoundDesc& rd, int rows, double arows, const float* wbase,
                       const uint16_t* sbase, bool own, int block_rows, int gather_blocks, hipStream_t s, LaunchHook* hook) {
@@ -2789,8 +2792,11 @@ void launch_logits_ce(const MlpArgs& a, const RoundDesc& rd, int rows, double ar
 }
 
 // Whether a round of `rows` stacked rows at U = 1 takes its steps in mlp_step_kernel, and with which tiles (0: split
-// weight gradients, partials and updates).  Unsplit, the contraction may have at most 64 k-steps (at 96 3072-512-10
-// takes 110 us a round against 97), and with tiles of 128 x 128 there is a limit to the work too, beyond which the 256 x 256
+// weight gradients, partials and updates).  Unsplit, the contraction may have at most 64 k-steps: up to there it wins in every
+// shape measured that the limits below leave in, beyond it turns at another length for each (us of a round, split / unsplit with
+// the better tiles, at 64, 68, 72, 80 and 96 k-steps: 3072-512-10 82 / 75, 93 / 88, 86 / 89, 97 / 93, 93 / 101; 2048-1024-10 86 / 83,
+// 101 / 96, 102 / 98, 104 / 105, 109 / 117; 3072-2048-2048-100 361 / 339, 465 / 439, 461 / 452, 477 / 478, 497 / 520; 512-512-100
+// 54 / 45, 65 / 54, 61 / 54, 68 / 55, 72 / 59).  With tiles of 128 x 128 there is a limit to the work too, beyond which the 256 x 256
 // kernel's fewer bytes per flop win over its partials.  128 x 128 from 128 such tiles on, 64 x 64 below; where even these
 // are few, the split ones win earlier (us of a round, split / 64 x 64: 512-128-10, 18 tiles, 3072 rows 36.8 / 36.8, 4096: 37.4 / 40.7;
 // 880-73-100, 32 tiles, 3072: 44.9 / 44.6, 4096: 45.7 / 47.5; 1024-128-100, 36 tiles, 4096: 55.4 / 47.8).

@@ -929,13 +929,14 @@ __global__ __launch_bounds__(kFuseThreads, TR == 16 ? 2 : 4) void softmax_local_
 // upload has eight workgroups, slice s taking exactly the features that wavefront s has there (blocks s, s + 8, ... of 16),
 // and a step is cut where its only exchange is: launch u adds the eight slices' partial logits of step u - 1, forms dZ
 // (every slice for itself: B x 16 values), its features' gradient and model, and leaves its partial logits of step u.
-// The launch boundary is the barrier; U + 1 launches of 8 us, bound by chains of latencies: arguments and rows 1.6, the rows'
-// requests (64 of them all over the dataset) 1.4, softmax 1.0, gradient 1.0, logits 0.8, launch to launch 1.  All sums run in the order of the kernel above, operand by
-// operand, so the two give the same bits (a batch of simulations, which has uploads enough, keeps that one).
+// The launch boundary is the barrier; U + 1 launches of 8 us, bound by chains of latencies: arguments and rows 1.6, the
+// rows' requests (64 of them all over the dataset) 1.4, softmax 1.0, gradient 1.0, logits 0.8, launch to launch 1.  All sums
+// run in the order of the kernel above, operand by operand, so the two give the same bits (a batch of simulations, which has
+// uploads enough, keeps that one).
 constexpr int kSliceMaxUploads = 32, kSliceMinB = 33, kSliceMaxB = 256;
 constexpr int kSlices = kFuseWaves;
-// scratch per upload, floats: two sets of partial logits [slice][row][16], the running loss of [row % 16][class]
-// dataset rows and labels of three steps (launch u leaves those of step u + 1 while its own rows are on their way)
+// scratch per upload, in floats: two sets of partial logits [slice][row][16]; the running loss of [row % 16][class]; the dataset
+// rows and labels of three steps (launch u leaves those of step u + 1 while its own rows are on their way)
 __host__ __device__ inline size_t slice_floats(int B) { return (size_t)2 * kSlices * B * 16 + 256 + 6 * (size_t)B; }
 
 template <int C>
