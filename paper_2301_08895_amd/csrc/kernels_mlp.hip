@@ -2063,8 +2063,8 @@ __global__ __launch_bounds__(256, 1) void mlp_logits_ce_kernel(LogitsCeArgs a, R
 // into registers, the next pair's on their way under this one's products.  The four partial logits meet in LDS, summed in
 // wavefront order; then a wavefront has 8 whole rows, 16 lanes to a row.
 // us, 128-row / 32-row workgroups: 1024 x 512, 10 classes 9.0 / 6.7, 4096 x 1024 12.9 / 7.8, 1152 x 300, 26 classes 8.2 / 6.5,
-// 8192 x 2048, 100 classes 33 / 25.  Eight wavefronts to the contraction: 7.3 instead of 7.8 for 4096 x 1024, but
-// 46 instead of 28 with 100 classes (more lines asked for than the L1 can hold until their other half is).
+// 8192 x 2048, 100 classes 33 / 25.  Eight wavefronts to the contraction: 7.3 instead of 7.8 for 4096 x 1024, but 46
+// for the last one (more lines asked for than the L1 can hold until their other half is).
 constexpr int kCeFewRows = 32;
 template <int CB>                        // blocks of 16 classes that are computed: 16 CB >= C, at most 8
 __global__ __launch_bounds__(256, 1) void mlp_logits_ce_few_kernel(LogitsCeArgs a, RoundDesc rd) {
