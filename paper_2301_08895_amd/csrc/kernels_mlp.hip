@@ -1281,8 +1281,12 @@ __global__ __launch_bounds__(512, 1) void mlp_gemm256_kernel(GemmArgs g, RoundDe
     // halves, one half ahead of the MFMAs that use them (us, the loop below / both stages at once / this, 100 classes: 8192 x 2048
     // 21.1 / 19.7 / 18.8, 32768 x 2048 61.0 / 59.5 / 55.4; 64 classes, 16384 x 1024 16.4 / 15.6 / 14.5).
 #define ABS_DMA_STEP(j_, st_) { ABS_DMA_B(j_, st_, 0); ABS_DMA_A(j_, st_, 0); ABS_DMA_B(j_, st_, 1); ABS_DMA_A(j_, st_, 1); }
-#define ABS_SUB_A(set_, s_, h_) _Pragma("unroll") for (int i = 0; i < 4; ++i) sa[set_][i] = *(const bf16x8_t*)&stage[fa_row + ((s_) ? ch1 : ch0) + (h_) * kHalf3 + i * 16 * BK];
-#define ABS_SUB_B(set_) _Pragma("unroll") for (int i = 0; i < 4; ++i) sb[set_][i] = *(const bf16x8_t*)&stage[fb_row + ((set_) ? ch1 : ch0) + (i >> 1) * kHalf3 + (i & 1) * 16 * BK];
+#define ABS_SUB_A(set_, s_, h_)                                                                                       \
+  _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                                       \
+    sa[set_][i] = *(const bf16x8_t*)&stage[fa_row + ((s_) ? ch1 : ch0) + (h_) * kHalf3 + i * 16 * BK];
+#define ABS_SUB_B(set_)                                                                                               \
+  _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                                       \
+    sb[set_][i] = *(const bf16x8_t*)&stage[fb_row + ((set_) ? ch1 : ch0) + (i >> 1) * kHalf3 + (i & 1) * 16 * BK];
 #define ABS_SUB_MMA(h_, aset_, bset_)                                                                                 \
   _Pragma("unroll") for (int i = 0; i < 4; ++i) _Pragma("unroll") for (int b = 0; b < 4; ++b)                         \
     acc[(h_) * 4 + i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sa[aset_][i], sb[bset_][b], acc[(h_) * 4 + i][b], 0, 0, 0);
